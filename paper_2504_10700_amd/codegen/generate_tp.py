@@ -11,9 +11,9 @@ bilinear couplings through the same sparse tensors with a different free index:
   backward  q[l1]    = C . h_l2 . g_l3 ;  dR[p] = Y_l1 . q ;  dY_l1 += R[p] q
             s[l2]    = C . Y_l1 . g_l3 ;  dh_l2 += R[p] s      (the edge's share of its sender's dh)
 
-A third program, the second-order pass, is derived from the forward one (autodiff.py): the
-message's derivative along the cotangents (hy, hh, hr) of (dY, dh, dR) is added to ddA, and
-the reverse-mode derivative of sum(g * that derivative) gives d2Y, d2h and d2R.
+A third program, the second-order pass, adds the message's derivative along the cotangents
+(hy, hh, hr) of (dY, dh, dR) to ddA and writes the derivatives d2Y, d2h and d2R of
+sum(g * that derivative).  All programs go path by path.
 
 The sparse terms come from the library's host tables (tp_plan_terms on a host-only plan);
 every coupling tensor is divided by its most frequent |coefficient| (the factor is folded
@@ -30,7 +30,6 @@ from typing import Dict, List, Optional, Tuple
 
 import numpy as np
 
-from .autodiff import replay_with_tangent, reverse
 from .program import Program
 from .scheme import couple_into
 from .tables import HOST_LIB
@@ -38,11 +37,9 @@ from .tables import HOST_LIB
 _HERE = os.path.dirname(os.path.abspath(__file__))
 OUT_DIR = os.path.join(os.path.dirname(_HERE), "csrc", "generated")
 
-# tag -> (l_Y, l_h, L_max)
-SPECS = {
-    "y3h0o3": (3, 0, 3),
-    "y3h1o3": (3, 1, 3),
-}
+# tag -> (l_Y, l_h, L_max): the messages of a model whose atomic basis goes up to L_max = l_Y, for sender
+# features up to any order l_h <= L_max (0: the first layer; the outputs of the product basis afterwards)
+SPECS = {f"y{l}h{lh}o{l}": (l, lh, l) for l in (3, 2, 1) for lh in range(l + 1)}
 
 
 class _Config(C.Structure):
@@ -130,40 +127,77 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
     h = [Bq.inp(f"h[{b}]") for b in range(tab.n_h)]
     r = [Bq.inp(f"r[{p}]") for p in range(tab.P)]
     g = [Bq.inp(f"g[{c}]") for c in range(tab.n_out)]
+    # path by path, so that only the sums over the paths stay live from one path to the next
     dy: List[Optional[int]] = [None] * tab.n_Y
+    dh: List[Optional[int]] = [None] * tab.n_h   # the edge's share of its sender's gradient
     for p, (l1, l2, l3) in enumerate(tab.paths):
-        Cs, kappa = scaled[p]
-        q: List[Optional[int]] = [None] * (2 * l1 + 1)
-        couple_into(Bq, np.transpose(Cs, (1, 2, 0)), h[sl(l2)], g[sl(l3)], q)   # q[a] = sum C[a,b,c] h[b] g[c]
-        dot = None
-        for a, qa in zip(y[sl(l1)], q):
-            if qa is not None:
-                dot = Bq.fma(a, qa, dot)
-        Bq.out(f"dr[{p}]", None if dot is None else Bq.cmul(dot, kappa))
+        terms, kappa = scaled_terms(Bq, tab.C[p], g[sl(l3)])
         rk = Bq.cmul(r[p], kappa)
-        for i, qa in enumerate(q):
-            if qa is not None:
-                dy[l1 * l1 + i] = Bq.fma(rk, qa, dy[l1 * l1 + i])
+        s = couple_terms(Bq, terms, y[sl(l1)], "b", [None] * (2 * l2 + 1))      # s[b] = sum C[a,b,c] y[a] g[c]
+        u = [Bq.mul(rk, x) for x in h[sl(l2)]]
+        dy[sl(l1)] = couple_terms(Bq, terms, u, "a", dy[sl(l1)])                # dy[a] += sum C[a,b,c] u[b] g[c]
+        Bq.out(f"dr[{p}]", scaled_dot(Bq, h[sl(l2)], s, kappa))
+        add_scaled(Bq, rk, s, dh, l2)
+        Bq.fence(dy[sl(l1)] + dh[sl(l2)])
     for a in range(tab.n_Y):
         Bq.out(f"dy[{a}]", dy[a])
-    # the edge's share of its sender's gradient: dh[b] = sum_p r[p] sum C[a,b,c] y[a] g[c]
-    dh: List[Optional[int]] = [None] * tab.n_h
-    for p, (l1, l2, l3) in enumerate(tab.paths):
-        Cs, kappa = scaled[p]
-        s: List[Optional[int]] = [None] * (2 * l2 + 1)
-        couple_into(Bq, np.transpose(Cs, (0, 2, 1)), y[sl(l1)], g[sl(l3)], s)   # s[b] = sum C[a,b,c] y[a] g[c]
-        rk = Bq.cmul(r[p], kappa)
-        for i, sb in enumerate(s):
-            if sb is not None:
-                dh[l2 * l2 + i] = Bq.fma(rk, sb, dh[l2 * l2 + i])
     for b in range(tab.n_h):
         Bq.out(f"dh[{b}]", dh[b])
     return F, Bq
 
 
-def build_double_backward(tab: TPTables, F: Program) -> Program:
+def scaled_terms(P: Program, Cp: np.ndarray, g):
+    """The terms of a path as (a, b, sign, |C[a,b,c]| / kappa * g[c]): g scaled once per magnitude and
+    shared by every coupling that contracts with g."""
+    Cs, kappa = split_scale(Cp)
+    return [(int(a), int(b), Cs[a, b, c] > 0, P.cmul(g[c], round_unit(abs(float(Cs[a, b, c])))))
+            for a, b, c in zip(*np.nonzero(Cs))], kappa
+
+
+def round_unit(c: float) -> float:
+    return 1.0 if abs(c - 1.0) < 1e-13 else c
+
+
+def couple_terms(P: Program, terms, x, free: str, acc: List[Optional[int]]) -> List[Optional[int]]:
+    """acc[free index] += sum over the terms of sign * x[the other index] * scaled g."""
+    acc = list(acc)
+    for a, b, plus, gs in terms:
+        i, xi = (a, x[b]) if free == "a" else (b, x[a])
+        if acc[i] is None:
+            t = P.mul(xi, gs)
+            acc[i] = t if plus else P.cmul(t, -1.0)
+        else:
+            acc[i] = P.fma(xi, gs, acc[i]) if plus else P.fnma(xi, gs, acc[i])
+    return acc
+
+
+def scaled_dot(P: Program, x, v, kappa: float) -> Optional[int]:
+    """kappa * sum_i x[i] v[i]; entries of v that do not occur are None."""
+    dot = None
+    for xi, vi in zip(x, v):
+        if vi is not None:
+            dot = P.fma(xi, vi, dot)
+    return None if dot is None else P.cmul(dot, kappa)
+
+
+def add_scaled(P: Program, f: int, v, acc: List[Optional[int]], l: int) -> None:
+    """acc[components of order l] += f * v."""
+    for i, vi in enumerate(v):
+        if vi is not None:
+            acc[l * l + i] = P.fma(f, vi, acc[l * l + i])
+
+
+def build_double_backward(tab: TPTables) -> Program:
     """psi = sum_c g[c] * (derivative of the edge's message along (hy, hh, hr)):
-    dda += that derivative; d2y, d2h, d2r = d psi / d (y, h, r) (overwritten)."""
+    dda += that derivative; d2y, d2h, d2r = d psi / d (y, h, r) (overwritten).
+
+    The message is linear in each of y, h and r, so every path needs five couplings through its
+    tensor, and nothing of one path is needed by another (k = kappa):
+      u = k r h,  v = k (hr h + r hh)
+      dda += C.y.v + C.hy.u,   d2y += C.v.g
+      s = C.y.g,  s' = C.hy.g:   d2r = k (h.s' + hh.s),   d2h += k (hr s + r s')
+    (Differentiating the forward program mechanically gives the same sums in an order in which the
+    intermediates of all paths are live at once: 6 KB of scratch per lane for l_h = 2 in fp64.)"""
     P = Program()
     y = [P.inp(f"y[{a}]") for a in range(tab.n_Y)]
     hy = [P.inp(f"hy[{a}]") for a in range(tab.n_Y)]
@@ -172,28 +206,38 @@ def build_double_backward(tab: TPTables, F: Program) -> Program:
     r = [P.inp(f"r[{p}]") for p in range(tab.P)]
     hr = [P.inp(f"hr[{p}]") for p in range(tab.P)]
     g = [P.inp(f"g[{c}]") for c in range(tab.n_out)]
-    dda = [P.inp(f"dda[{c}]") for c in range(tab.n_out)]
-    unused = P.inp("T(0)")     # primal value of the forward accumulator: never live
-    inputs = {f"y[{a}]": (y[a], hy[a]) for a in range(tab.n_Y)}
-    inputs.update({f"h[{b}]": (h[b], hh[b]) for b in range(tab.n_h)})
-    inputs.update({f"r[{p}]": (r[p], hr[p]) for p in range(tab.P)})
-    inputs.update({f"acc[{c}]": (unused, None) for c in range(tab.n_out)})
-    outs = replay_with_tangent(F, P, inputs)
-    seeds: Dict[int, int] = {}
+    dda: List[Optional[int]] = [P.inp(f"dda[{c}]") for c in range(tab.n_out)]
+    d2y: List[Optional[int]] = [None] * tab.n_Y
+    d2h: List[Optional[int]] = [None] * tab.n_h
+    for p, (l1, l2, l3) in enumerate(tab.paths):
+        Cs, kappa = split_scale(tab.C[p])
+        rk, hrk = P.cmul(r[p], kappa), P.cmul(hr[p], kappa)
+        u = [P.mul(rk, x) for x in h[sl(l2)]]
+        v = [P.fma(hrk, x, P.mul(rk, hx)) for x, hx in zip(h[sl(l2)], hh[sl(l2)])]
+        part = dda[sl(l3)]
+        couple_into(P, stack_pairs(Cs), y[sl(l1)] + hy[sl(l1)], v + u, part)
+        dda[sl(l3)] = part
+        terms, _ = scaled_terms(P, tab.C[p], g[sl(l3)])
+        d2y[sl(l1)] = couple_terms(P, terms, v, "a", d2y[sl(l1)])
+        s = couple_terms(P, terms, y[sl(l1)], "b", [None] * (2 * l2 + 1))
+        sh = couple_terms(P, terms, hy[sl(l1)], "b", [None] * (2 * l2 + 1))
+        P.out(f"d2r[{p}]", scaled_dot(P, h[sl(l2)] + hh[sl(l2)], sh + s, kappa))
+        add_scaled(P, hrk, s, d2h, l2)
+        add_scaled(P, rk, sh, d2h, l2)
+        P.fence(dda[sl(l3)] + d2y[sl(l1)] + d2h[sl(l2)])
     for c in range(tab.n_out):
-        t = outs[f"acc[{c}]"][1]
-        if t is not None:
-            seeds[t] = P.add(seeds.get(t), g[c])
-    adj = reverse(P, seeds)
-    for c in range(tab.n_out):
-        P.out(f"dda[{c}]", P.add(dda[c], outs[f"acc[{c}]"][1]))
-    for p in range(tab.P):
-        P.out(f"d2r[{p}]", adj.get(r[p]))
+        P.out(f"dda[{c}]", dda[c])
     for a in range(tab.n_Y):
-        P.out(f"d2y[{a}]", adj.get(y[a]))
+        P.out(f"d2y[{a}]", d2y[a])
     for b in range(tab.n_h):
-        P.out(f"d2h[{b}]", adj.get(h[b]))
+        P.out(f"d2h[{b}]", d2h[b])
     return P
+
+
+def stack_pairs(C: np.ndarray) -> np.ndarray:
+    """The tensor of C.x.v + C.x'.v' as one coupling of (x, x') with (v, v')."""
+    Z = np.zeros_like(C)
+    return np.concatenate([np.concatenate([C, Z], 1), np.concatenate([Z, C], 1)], 0)
 
 
 def self_check_double(tab: TPTables, D: Program, dtype=np.float64) -> Dict[str, float]:
@@ -298,9 +342,9 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append("")
     L.append("  // g = dA of the receiver; overwritten: dr, dy (this channel's share of the edge's dY) and dh")
     L.append("  // (the edge's share of the gradient of its sender's features)")
-    L.append("  template <typename T>")
+    L.append("  template <typename T, typename TR>")
     L.append("  static __device__ __forceinline__ void backward(const T (&y)[kNY], const T (&h)[kNh], const T (&r)[kP],")
-    L.append("                                                  const T (&g)[kNout], T (&dr)[kP], T (&dy)[kNY], T (&dh)[kNh]) {")
+    L.append("                                                  const T (&g)[kNout], TR (&dr)[kP], T (&dy)[kNY], T (&dh)[kNh]) {")
     L.append(Bq.emit("T", "    "))
     L.append("  }")
     L.append("")
@@ -308,10 +352,10 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append("  // dda += derivative of the edge's message along (hy, hh, hr); with psi = sum(g * that derivative):")
     L.append("  // d2r = d psi / d r, d2y = this channel's share of d psi / d y, d2h = the edge's share of d psi / d h")
     L.append("  // (all three overwritten).")
-    L.append("  template <typename T>")
+    L.append("  template <typename T, typename TR>")
     L.append("  static __device__ __forceinline__ void double_backward(const T (&y)[kNY], const T (&hy)[kNY], const T (&h)[kNh],")
     L.append("                                                         const T (&hh)[kNh], const T (&r)[kP], const T (&hr)[kP],")
-    L.append("                                                         const T (&g)[kNout], T (&dda)[kNout], T (&d2r)[kP],")
+    L.append("                                                         const T (&g)[kNout], T (&dda)[kNout], TR (&d2r)[kP],")
     L.append("                                                         T (&d2y)[kNY], T (&d2h)[kNh]) {")
     L.append(D.emit("T", "    "))
     L.append("  }")
@@ -323,7 +367,7 @@ def generate(tag: str, lib_path: str = HOST_LIB, verbose: bool = True) -> str:
     spec = SPECS[tag]
     tab = TPTables(lib_path, *spec)
     F, Bq = build_programs(tab)
-    D = build_double_backward(tab, F)
+    D = build_double_backward(tab)
     e64 = self_check(tab, F, Bq, np.float64)
     assert max(e64.values()) < 1e-12, e64
     d64 = self_check_double(tab, D, np.float64)

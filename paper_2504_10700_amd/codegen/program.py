@@ -13,6 +13,7 @@ import numpy as np
 
 # op codes
 INP, MUL, ADD, SUB, FMA, FNMA, CMUL, CFMA = "inp", "mul", "add", "sub", "fma", "fnma", "cmul", "cfma"
+FENCE = "fence"   # no operation: the device compiler may not move instructions across it
 
 
 class Program:
@@ -82,6 +83,12 @@ class Program:
     def out(self, lvalue: str, x: Optional[int]) -> None:
         self.outputs.append((lvalue, x))
 
+    def fence(self, values: Sequence[Optional[int]] = ()) -> None:
+        """Ends a part of the program: `values` are computed before it, the outputs named so far are
+        printed before it, and the device compiler moves no instruction across it, so that one part's
+        intermediates and results die before the next part begins."""
+        self.ops.append((FENCE, (len(self.outputs), tuple(v for v in values if v is not None))))
+
     # ---- analysis
     def live_ops(self) -> List[bool]:
         live = [False] * len(self.ops)
@@ -100,7 +107,7 @@ class Program:
         live = self.live_ops()
         c: Dict[str, int] = {}
         for i, op in enumerate(self.ops):
-            if live[i] and op[0] != INP:
+            if live[i] and op[0] not in (INP, FENCE):
                 c[op[0]] = c.get(op[0], 0) + 1
         c["total"] = sum(c.values())
         return c
@@ -224,7 +231,16 @@ class Program:
 
         def lit(c):
             return f"{scalar}({repr(float(c))})"
+        printed = 0
+
+        def outputs(upto):
+            return [f"{indent}{lv} = {n(x) if x is not None else scalar + '(0)'};" for lv, x in self.outputs[printed:upto]]
         for i, op in enumerate(self.ops):
+            if op[0] == FENCE:
+                upto, values = op[1]
+                lines += outputs(upto) + [f"{indent}end_of_part({', '.join(n(v) for v in values)});"]
+                printed = upto
+                continue
             if not live[i] or op[0] == INP:
                 continue
             name[i] = f"t{i}"
@@ -244,9 +260,7 @@ class Program:
             elif k == CFMA:
                 e = f"sc_fma({n(op[1])}, {lit(op[2])}, {n(op[3])})"
             lines.append(f"{indent}const {scalar} t{i} = {e};")
-        for lv, x in self.outputs:
-            lines.append(f"{indent}{lv} = {n(x) if x is not None else scalar + '(0)'};")
-        return "\n".join(lines)
+        return "\n".join(lines + outputs(len(self.outputs)))
 
 
 def _fma(x, y, z, dtype):

@@ -1,0 +1,573 @@
+// Kernel templates of the channelwise tensor product around generated straight-line arithmetic (see
+// tp_spec.hip for the mapping): included by the files that instantiate them.
+//
+// T = type of the arithmetic, TS = type the tensors are stored in.  fp64 rows are computed in fp64.
+// fp32 rows are computed in fp32 for the shapes with l_Y = L_max = 3 and l_h <= 1 on full 64-channel
+// blocks, and in fp64 everywhere else, like the table-driven kernels: an fp64 instruction issues at
+// the rate of an unpacked fp32 one on this chip, and the kernels are bound by the bytes of R.
+// kFull: the channel count is a multiple of 64.  Otherwise the lanes past the last channel repeat it:
+// their loads are valid, their stores are masked and their share of dY is zero.
+#pragma once
+#include <type_traits>
+
+#include "tp_internal.h"
+#include "tp_spec.h"
+
+namespace tp {
+namespace {
+
+using sc::kLanes;
+
+__device__ __forceinline__ float sc_fma(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+__device__ __forceinline__ double sc_fma(double x, double y, double z) { return __builtin_fma(x, y, z); }
+
+// Between two parts of a generated program (one path and the next): the given sums are complete here,
+// and nothing moves across.  Left to itself the compiler interleaves the paths until every register is taken
+// (second-order pass with l_h = 2 in fp64: 512 registers and 5 KB of scratch per lane).
+template <typename T>
+__device__ __forceinline__ void is_computed(const T& v) {
+  asm volatile("" ::"v"(v));
+}
+template <typename... V>
+__device__ __forceinline__ void end_of_part(const V&... v) {
+  (is_computed(v), ...);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+constexpr int kWaves = 4;
+constexpr int kThreads = kWaves * kLanes;
+constexpr int kStageStride = kLanes + 1;  // LDS row stride of the dY transpose (odd: two-way conflicts at most)
+
+// A row of N elements at p: 16-byte accesses and a scalar tail.  p is aligned to 16 B if the row size is
+// a multiple of 16 B, else only to the element (16-byte accesses need no more on this chip).
+template <typename T, int N>
+struct Row {
+  static constexpr int V = 16 / sizeof(T);
+  typedef T Vec __attribute__((ext_vector_type(V), aligned((N * sizeof(T)) % 16 == 0 ? 16 : sizeof(T))));
+};
+
+template <typename T, int N>
+__device__ __forceinline__ void load_row(const T* __restrict__ p, T (&v)[N]) {
+  constexpr int V = Row<T, N>::V;
+#pragma unroll
+  for (int i = 0; i + V <= N; i += V) {
+    const typename Row<T, N>::Vec x = *reinterpret_cast<const typename Row<T, N>::Vec*>(p + i);
+#pragma unroll
+    for (int k = 0; k < V; ++k) v[i + k] = x[k];
+  }
+#pragma unroll
+  for (int i = N / V * V; i < N; ++i) v[i] = p[i];
+}
+
+template <typename TS, typename T, int N>
+__device__ __forceinline__ void store_row(TS* __restrict__ p, const T (&v)[N]) {
+  constexpr int V = Row<TS, N>::V;
+#pragma unroll
+  for (int i = 0; i + V <= N; i += V) {
+    typename Row<TS, N>::Vec x;
+#pragma unroll
+    for (int k = 0; k < V; ++k) x[k] = static_cast<TS>(v[i + k]);
+    // A row of one 16-byte piece makes the wave's store one contiguous KB: streamed past the
+    // cache (measured faster).  Longer rows are written by several instructions that each touch
+    // a part of every line: left to the L2 to merge (streaming them measured slower).
+    if constexpr (N * sizeof(TS) == 16) __builtin_nontemporal_store(x, reinterpret_cast<typename Row<TS, N>::Vec*>(p + i));
+    else *reinterpret_cast<typename Row<TS, N>::Vec*>(p + i) = x;
+  }
+#pragma unroll
+  for (int i = N / V * V; i < N; ++i) p[i] = static_cast<TS>(v[i]);
+}
+
+// Values as stored -> values of the arithmetic (nothing where the types are the same).  The rows that are
+// requested ahead stay in the storage type until they are used: without the empty statement the
+// compiler moves the conversions, and products of the values with constants, to the request of the row, and
+// carries twice the registers from there to the use.
+template <typename T, typename TS, int N>
+__device__ __forceinline__ void widen(const TS (&v)[N], T (&w)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    TS x = v[i];
+    asm volatile("" : "+v"(x));
+    w[i] = static_cast<T>(x);
+  }
+}
+
+// R[e][p][ch] for all paths of edge e.
+template <typename T, int P>
+__device__ __forceinline__ void load_weights(const T* __restrict__ R, int e, int K, int ch, T (&r)[P]) {
+  const T* base = R + static_cast<size_t>(e) * P * K + ch;
+#pragma unroll
+  for (int p = 0; p < P; ++p) r[p] = base[static_cast<size_t>(p) * K];
+}
+
+// dR[e][p][ch] for all paths of edge e (every row is written as whole lines: streamed past the cache).
+template <bool kFull, typename TS, int P>
+__device__ __forceinline__ void store_weights(TS* __restrict__ dR, int e, int K, int ch, bool live, const TS (&dr)[P]) {
+  TS* out = dR + static_cast<size_t>(e) * P * K + ch;
+  if (!kFull && !live) return;
+#pragma unroll
+  for (int p = 0; p < P; ++p) __builtin_nontemporal_store(dr[p], out + static_cast<size_t>(p) * K);
+}
+
+// Empty statements that pin where values are computed.  Before the arithmetic of an edge, on values that do
+// not change over the edges of an atom: what follows from them (the row dA times every magnitude of
+// the couplings: 130 values for l_h = 2) would otherwise be moved in front of the loop and held in registers.
+// After it, on the sums over the edges: their additions would otherwise be moved behind the stores
+// of the edge, with all their operands live until there.
+template <typename T, int N>
+__device__ __forceinline__ void pin_values(T (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+template <typename T, int N>
+__device__ __forceinline__ void mask_dead_lanes(T (&v)[N], bool live) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = live ? v[i] : T(0);
+}
+
+// A wave-uniform value in the type of the arithmetic.  The conversion runs on the vector unit; the result
+// goes back to scalar registers, from where every instruction can read it.
+template <typename T, typename TS>
+__device__ __forceinline__ T widen_uniform(TS v) {
+  if constexpr (std::is_same<T, TS>::value) {
+    return v;
+  } else {
+    const unsigned long long bits = __builtin_bit_cast(unsigned long long, static_cast<double>(v));
+    const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(bits));
+    const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(bits >> 32));
+    return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+  }
+}
+
+// Y[e][:], identical for all lanes (e is wave-uniform): scalar loads.
+template <typename T, typename TS, int N>
+__device__ __forceinline__ void load_uniform(const TS* __restrict__ Y, int e, T (&y)[N]) {
+  const TS* base = Y + static_cast<size_t>(e) * N;
+#pragma unroll
+  for (int a = 0; a < N; ++a) y[a] = widen_uniform<T>(base[a]);
+}
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// blockIdx -> logical block such that the blocks an XCD receives (round-robin by blockIdx) form
+// one contiguous range of atoms: the atoms of one structure, which share their senders' rows of
+// h, then meet in one XCD's L2.  gridDim.x is a multiple of kXcds.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int64_t xcd_contiguous_block() {
+  const int64_t per = gridDim.x / kXcds;
+  return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+}
+
+// Sum of dy[a] over the 64 lanes in a fixed order, written to out[a] (a < N): lane 4a+q adds the
+// sixteen lanes 16q..16q+15 of component a from an LDS transpose (stage: N * kStageStride
+// elements owned by this wave), then the four quarters are combined with two exchanges.
+template <typename T, typename TS, int N>
+__device__ __forceinline__ void lane_sum_store(T* stage, int lane, const T (&dy)[N], TS* __restrict__ out) {
+  static_assert(N <= 16, "one lane quartet per component");
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the previous edge's reads of the stage are done
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int a = 0; a < N; ++a) stage[a * kStageStride + lane] = dy[a];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int a = lane >> 2, q = lane & 3;
+  T s = T(0);
+  if (a < N) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += stage[a * kStageStride + q * 16 + i];
+  }
+  s += __shfl_xor(s, 1);
+  s += __shfl_xor(s, 2);
+  if (q == 0 && a < N) out[a] = static_cast<TS>(s);
+}
+
+// Store of a wave's rows (N elements per lane, lane rows N elements apart = one contiguous block
+// of 64*N elements) as whole lines: every lane's row goes through an LDS block of the same
+// layout and comes back so that store instruction k writes the k-th contiguous KB of the block
+// instead of 64 pieces of 16 bytes (partial lines, N*sizeof(T)/16 times the write requests);
+// streamed past the cache.  stage: 64*N elements of LDS owned by this wave; block: where lane
+// 0's row goes; live: lanes whose rows exist.  Rows that are no whole number of 16-byte pieces (9 values of
+// 4 bytes) are aligned to their elements only and go out one element per lane and instruction.
+template <typename TS, typename T, int N>
+__device__ __forceinline__ void store_rows_coalesced(TS* __restrict__ block, TS* stage, int lane, const T (&v)[N], int live) {
+  constexpr int V = (N * sizeof(TS)) % 16 == 0 ? 16 / sizeof(TS) : 1;
+  typedef TS Vec __attribute__((ext_vector_type(V)));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // earlier reads of the stage are done
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < N / V; ++j) {
+    Vec x;
+#pragma unroll
+    for (int k = 0; k < V; ++k) x[k] = static_cast<TS>(v[j * V + k]);
+    *reinterpret_cast<Vec*>(stage + lane * N + j * V) = x;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the other lanes' pieces are visible
+  __builtin_amdgcn_wave_barrier();
+  const int pieces = live * N / V;
+#pragma unroll
+  for (int q0 = 0; q0 < kLanes * N / V; q0 += kLanes) {
+    const int q = q0 + lane;
+    if (live == kLanes || q < pieces) {
+      const Vec x = *reinterpret_cast<const Vec*>(stage + q * V);
+      __builtin_nontemporal_store(x, reinterpret_cast<Vec*>(block + q * V));
+    }
+  }
+}
+
+// Channels of block cb: the lane's channel (dead lanes repeat the last one) and the number of live lanes.
+template <bool kFull>
+struct Channels {
+  int live, ch;
+  __device__ __forceinline__ Channels(int K, int cb, int lane) {
+    live = kFull ? kLanes : (K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes);
+    ch = cb * kLanes + (kFull || lane < live ? lane : live - 1);
+  }
+};
+
+template <typename T, typename TS, typename G, bool kFull>
+__global__ __launch_bounds__(kThreads) void forward_kernel(int K, int chblocks, int64_t n_units,
+                                                           const TS* __restrict__ Y, const TS* __restrict__ h,
+                                                           const TS* __restrict__ R,
+                                                           const EdgeList el, TS* __restrict__ A) {
+  __shared__ __attribute__((aligned(16))) TS out_stage[kWaves][kLanes * G::kNout];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = uniform(threadIdx.x / kLanes);
+  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
+  if (unit >= n_units) return;
+  const size_t node = unit / chblocks;
+  const int cb = static_cast<int>(unit % chblocks);
+  const Channels<kFull> chan(K, cb, lane);
+  const int ch = chan.ch;
+  const int e0 = uniform(el.first(node)), e1 = uniform(el.first(node + 1));
+  T acc[G::kNout];
+#pragma unroll
+  for (int c = 0; c < G::kNout; ++c) acc[c] = T(0);
+  if (e0 < e1) {
+    TS r0[G::kP], r1[G::kP], h0[G::kNh], h1[G::kNh];
+    auto add_edge = [&](int e, const TS (&h_row)[G::kNh], const TS (&r_row)[G::kP]) {
+      T y[G::kNY], hh[G::kNh], r[G::kP];
+      load_uniform<T, TS, G::kNY>(Y, e, y);
+      widen(h_row, hh);
+      widen(r_row, r);
+      G::forward(y, hh, r, acc);
+    };
+    load_weights<TS, G::kP>(R, e0, K, ch, r0);
+    load_row<TS, G::kNh>(h + (el.snd(e0) * K + ch) * G::kNh, h0);
+    int jn = (e0 + 1 < e1) ? el.raw(e0 + 1) : 0;  // sender of the next edge, read one step ahead
+    for (int e = e0; e < e1; e += 2) {
+      int jn2 = 0;
+      if (e + 1 < e1) {
+        load_weights<TS, G::kP>(R, e + 1, K, ch, r1);
+        load_row<TS, G::kNh>(h + (el.node(jn) * K + ch) * G::kNh, h1);
+        if (e + 2 < e1) jn2 = el.raw(e + 2);
+      }
+      add_edge(e, h0, r0);
+      if (e + 1 < e1) {
+        if (e + 2 < e1) {
+          load_weights<TS, G::kP>(R, e + 2, K, ch, r0);
+          load_row<TS, G::kNh>(h + (el.node(jn2) * K + ch) * G::kNh, h0);
+          if (e + 3 < e1) jn = el.raw(e + 3);
+        }
+        add_edge(e + 1, h1, r1);
+      }
+    }
+  }
+  store_rows_coalesced<TS, T, G::kNout>(A + (node * K + cb * kLanes) * G::kNout, out_stage[wave], lane, acc, chan.live);
+}
+
+// receiver[e] for every edge, from the receivers' offsets: one thread per receiving atom.
+__global__ __launch_bounds__(256) void edge_receiver_kernel(int64_t n_out_nodes, const EdgeList el,
+                                                            int32_t* __restrict__ receiver) {
+  const int64_t node = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  if (node >= n_out_nodes) return;
+  const int e0 = el.first(node), e1 = el.first(node + 1);
+  for (int e = e0; e < e1; ++e) receiver[e] = static_cast<int32_t>(node);
+}
+
+// The backward walks the edges grouped by SENDER: one wave = one (sending atom, 64-channel block).
+// It keeps the atom's h row and its dh sum in registers, walks the edges the atom sends
+// (send_edge order: the order of the sum) and gathers per edge the dA row of the receiver (rows of
+// one structure, met in the XCD's L2) next to the edge's own R rows; dR and the channel block's
+// partial of dY leave per edge, dh leaves once per atom: no per-edge shares
+// of dh go to memory and come back.  Atoms that send nothing get a zero row.  Every index is
+// clamped where it is used.
+template <typename T, typename TS, typename G, bool kFull>
+__global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
+    int K, int chblocks, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
+    const TS* __restrict__ h, const TS* __restrict__ R, const int32_t* __restrict__ send_ptr,
+    const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const TS* __restrict__ dA,
+    TS* __restrict__ dR, TS* __restrict__ dY_partial, TS* __restrict__ dh) {
+  __shared__ T stage_all[kWaves][G::kNY * kStageStride];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = uniform(threadIdx.x / kLanes);
+  T* stage = stage_all[wave];
+  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
+  if (unit >= n_units) return;
+  const size_t node = unit / chblocks;
+  const int cb = static_cast<int>(unit % chblocks);
+  const Channels<kFull> chan(K, cb, lane);
+  const int ch = chan.ch;
+  auto pos = [&](int v) { return v < 0 ? 0 : (v > n_edges ? n_edges : v); };
+  auto edge = [&](int q) {
+    const int e = send_edge[q];
+    return e < 0 ? 0 : (e >= n_edges ? n_edges - 1 : e);
+  };
+  auto atom = [&](int r) { return static_cast<size_t>(r < 0 ? 0 : (r >= n_out_nodes ? n_out_nodes - 1 : r)); };
+  const int q0 = uniform(pos(send_ptr[node])), q1 = uniform(pos(send_ptr[node + 1]));
+  T acc[G::kNh];
+#pragma unroll
+  for (int c = 0; c < G::kNh; ++c) acc[c] = T(0);
+  if (q0 < q1) {
+    T hh[G::kNh];
+    {
+      TS h_row[G::kNh];
+      load_row<TS, G::kNh>(h + (node * K + ch) * G::kNh, h_row);
+      widen(h_row, hh);
+    }
+    TS r0[G::kP], r1[G::kP], g0[G::kNout], g1[G::kNout];
+    int ea = uniform(edge(q0)), eb = 0;
+    load_weights<TS, G::kP>(R, ea, K, ch, r0);
+    load_row<TS, G::kNout>(dA + (atom(uniform(receiver[ea])) * K + ch) * G::kNout, g0);
+    // edge id and receiver of the edge after the current one, read one step ahead of its rows
+    int en = (q0 + 1 < q1) ? uniform(edge(q0 + 1)) : 0;
+    int rn = uniform(receiver[en]);
+
+    // One edge: arithmetic, dR row stores, dY summed over the 64 lanes in a fixed order, dh added up.
+    auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
+      T y[G::kNY], r[G::kP], g[G::kNout], dy[G::kNY], dhe[G::kNh];
+      TS dr[G::kP];
+      load_uniform<T, TS, G::kNY>(Y, e, y);
+      widen(r_row, r);
+      widen(g_row, g);
+      G::backward(y, hh, r, g, dr, dy, dhe);
+#pragma unroll
+      for (int c = 0; c < G::kNh; ++c) acc[c] += dhe[c];
+      pin_values(acc);
+      pin_values(dy);
+      pin_values(dr);
+      store_weights<kFull>(dR, e, K, ch, lane < chan.live, dr);
+      if constexpr (!kFull) mask_dead_lanes(dy, lane < chan.live);
+      lane_sum_store<T, TS, G::kNY>(stage, lane, dy, dY_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
+    };
+
+    for (int q = q0; q < q1; q += 2) {
+      if (q + 1 < q1) {
+        eb = en;
+        load_weights<TS, G::kP>(R, eb, K, ch, r1);
+        load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g1);
+        if (q + 2 < q1) {
+          en = uniform(edge(q + 2));
+          rn = uniform(receiver[en]);
+        }
+      }
+      finish_edge(ea, r0, g0);
+      if (q + 1 < q1) {
+        if (q + 2 < q1) {
+          ea = en;
+          load_weights<TS, G::kP>(R, ea, K, ch, r0);
+          load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
+          if (q + 3 < q1) {
+            en = uniform(edge(q + 3));
+            rn = uniform(receiver[en]);
+          }
+        }
+        finish_edge(eb, r1, g1);
+      }
+    }
+  }
+  if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(dh + (node * K + ch) * G::kNh, acc);
+}
+
+// Second-order pass: the backward's walk with the cotangents HR (per edge and path), Hh (at the
+// sender) and HY (wave-uniform) as additional inputs; ddA of the receiver is summed in registers
+// and stored once, d2R / d2Y partial / d2h share leave per edge like dR / dY / dh.
+template <typename T, typename TS, typename G, bool kFull>
+__global__ __launch_bounds__(kThreads) void double_backward_kernel(
+    int K, int chblocks, int64_t n_units, int64_t n_edges, const TS* __restrict__ Y, const TS* __restrict__ h,
+    const TS* __restrict__ R, const EdgeList el,
+    const TS* __restrict__ dA, const TS* __restrict__ HY, const TS* __restrict__ Hh, const TS* __restrict__ HR,
+    TS* __restrict__ ddA, TS* __restrict__ d2R, TS* __restrict__ d2Y_partial, TS* __restrict__ d2h_edge) {
+  __shared__ T stage_all[kWaves][G::kNY * kStageStride];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = uniform(threadIdx.x / kLanes);
+  T* stage = stage_all[wave];
+  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
+  if (unit >= n_units) return;
+  const size_t node = unit / chblocks;
+  const int cb = static_cast<int>(unit % chblocks);
+  const Channels<kFull> chan(K, cb, lane);
+  const int ch = chan.ch;
+  const int e0 = uniform(el.first(node)), e1 = uniform(el.first(node + 1));
+  T dda[G::kNout];
+#pragma unroll
+  for (int c = 0; c < G::kNout; ++c) dda[c] = T(0);
+  if (e0 < e1) {
+    T g[G::kNout];
+    {
+      TS g_row[G::kNout];
+      load_row<TS, G::kNout>(dA + (node * K + ch) * G::kNout, g_row);
+      widen(g_row, g);
+    }
+    // The rows of two edges in registers where they fit; fp64 arithmetic with 23 paths leaves room for one set,
+    // whose next rows are requested when the arithmetic has consumed it (two sets: 6 KB of scratch per lane).
+    constexpr bool kOneSet = sizeof(T) == 8 && G::kP > 17;
+    TS r0[G::kP], q0[G::kP], h0[G::kNh], x0[G::kNh];
+    auto load_edge = [&](int e, size_t j, TS (&r)[G::kP], TS (&q)[G::kP], TS (&h_row)[G::kNh], TS (&x_row)[G::kNh]) {
+      load_weights<TS, G::kP>(R, e, K, ch, r);
+      load_weights<TS, G::kP>(HR, e, K, ch, q);
+      load_row<TS, G::kNh>(h + (j * K + ch) * G::kNh, h_row);
+      load_row<TS, G::kNh>(Hh + (j * K + ch) * G::kNh, x_row);
+    };
+    load_edge(e0, el.snd(e0), r0, q0, h0, x0);
+    int jn = (e0 + 1 < e1) ? el.raw(e0 + 1) : 0;
+
+    auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&hr_row)[G::kP], const TS (&h_row)[G::kNh],
+                           const TS (&hx_row)[G::kNh]) {
+      T y[G::kNY], hy[G::kNY], r[G::kP], hr[G::kP], hh[G::kNh], hx[G::kNh], d2y[G::kNY], d2h[G::kNh];
+      TS d2r[G::kP];
+      pin_values(g);
+      load_uniform<T, TS, G::kNY>(Y, e, y);
+      load_uniform<T, TS, G::kNY>(HY, e, hy);
+      widen(r_row, r);
+      widen(hr_row, hr);
+      widen(h_row, hh);
+      widen(hx_row, hx);
+      G::double_backward(y, hy, hh, hx, r, hr, g, dda, d2r, d2y, d2h);
+      pin_values(dda);
+      pin_values(d2y);
+      pin_values(d2h);
+      pin_values(d2r);
+      store_weights<kFull>(d2R, e, K, ch, lane < chan.live, d2r);
+      if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(d2h_edge + (static_cast<size_t>(e) * K + ch) * G::kNh, d2h);
+      if constexpr (!kFull) mask_dead_lanes(d2y, lane < chan.live);
+      lane_sum_store<T, TS, G::kNY>(stage, lane, d2y, d2Y_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
+    };
+
+    if constexpr (kOneSet) {
+      for (int e = e0; e < e1; ++e) {
+        finish_edge(e, r0, q0, h0, x0);
+        if (e + 1 < e1) {
+          load_edge(e + 1, el.node(jn), r0, q0, h0, x0);
+          if (e + 2 < e1) jn = el.raw(e + 2);
+        }
+      }
+    } else {
+      TS r1[G::kP], q1[G::kP], h1[G::kNh], x1[G::kNh];
+      for (int e = e0; e < e1; e += 2) {
+        int jn2 = 0;
+        if (e + 1 < e1) {
+          load_edge(e + 1, el.node(jn), r1, q1, h1, x1);
+          if (e + 2 < e1) jn2 = el.raw(e + 2);
+        }
+        finish_edge(e, r0, q0, h0, x0);
+        if (e + 1 < e1) {
+          if (e + 2 < e1) {
+            load_edge(e + 2, el.node(jn2), r0, q0, h0, x0);
+            if (e + 3 < e1) jn = el.raw(e + 3);
+          }
+          finish_edge(e + 1, r1, q1, h1, x1);
+        }
+      }
+    }
+  }
+  if (kFull || lane < chan.live) store_row<TS, T, G::kNout>(ddA + (node * K + ch) * G::kNout, dda);
+}
+
+
+unsigned grid_for(int64_t n_units) {
+  const int64_t blocks = (n_units + kWaves - 1) / kWaves;
+  return static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds);
+}
+
+EdgeList edge_list(const FwdArgs& a) {
+  return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
+}
+EdgeList edge_list(const BwdArgs& a) {
+  return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
+}
+
+// Launches of one instance; chblocks = 64-channel blocks, the last one may be ragged (kFull = false).
+template <typename T, typename TS, typename G, bool kFull>
+struct Launch {
+  static hipError_t forward(const tp_plan* plan, const FwdArgs& a, hipStream_t stream) {
+    const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
+    const int64_t n_units = a.n_out_nodes * chblocks;
+    hipLaunchKernelGGL((forward_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K, chblocks,
+                       n_units, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R),
+                       edge_list(a), static_cast<TS*>(a.A));
+    return hipGetLastError();
+  }
+
+  static hipError_t backward(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
+    const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
+    int32_t* receiver = static_cast<int32_t*>(a.dh_edge);   // the shares' part of the workspace is free on this path
+    if (a.n_edges > 0 && a.n_out_nodes > 0) {
+      hipLaunchKernelGGL(edge_receiver_kernel, dim3(static_cast<unsigned>((a.n_out_nodes + 255) / 256)), dim3(256), 0,
+                         stream, a.n_out_nodes, edge_list(a), receiver);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    const int64_t n_units = a.n_in * chblocks;
+    // without receivers or edges no list is walked: every atom gets its zero row
+    hipLaunchKernelGGL((backward_by_sender_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K,
+                       chblocks, n_units, a.n_out_nodes, a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0,
+                       static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R), a.send_ptr,
+                       a.send_edge, receiver, static_cast<const TS*>(a.dA), static_cast<TS*>(a.dR),
+                       static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
+    return hipGetLastError();
+  }
+
+  static hipError_t double_backward(const tp_plan* plan, const DblArgs& d, hipStream_t stream) {
+    const BwdArgs& a = d.b;
+    const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
+    const int64_t n_units = a.n_out_nodes * chblocks;
+    hipLaunchKernelGGL((double_backward_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K,
+                       chblocks, n_units, a.n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
+                       static_cast<const TS*>(a.R), edge_list(a), static_cast<const TS*>(a.dA),
+                       static_cast<const TS*>(d.HY), static_cast<const TS*>(d.Hh), static_cast<const TS*>(d.HR),
+                       static_cast<TS*>(d.ddA), static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial),
+                       static_cast<TS*>(a.dh_edge));
+    return hipGetLastError();
+  }
+};
+
+// Calls fn.template operator()<Launch<...>>() for the instance that serves the plan.
+template <typename G, typename F>
+hipError_t with_instance(const tp_plan* plan, F&& fn) {
+  constexpr bool kSingle = G::kLY == 3 && G::kLout == 3 && G::kLh <= 1;   // fp32 arithmetic on full blocks (see the top)
+  typedef typename std::conditional<kSingle, float, double>::type F32Full;
+  const bool full = plan->cfg.num_channels % kLanes == 0;
+  if (plan->cfg.dtype == SC_F64)
+    return full ? fn.template operator()<Launch<double, double, G, true>>() : fn.template operator()<Launch<double, double, G, false>>();
+  return full ? fn.template operator()<Launch<F32Full, float, G, true>>() : fn.template operator()<Launch<double, float, G, false>>();
+}
+
+struct ForwardFn {
+  const tp_plan* plan; const FwdArgs& a; hipStream_t stream;
+  template <typename L> hipError_t operator()() const { return L::forward(plan, a, stream); }
+};
+struct BackwardFn {
+  const tp_plan* plan; const BwdArgs& a; hipStream_t stream;
+  template <typename L> hipError_t operator()() const { return L::backward(plan, a, stream); }
+};
+struct DoubleBackwardFn {
+  const tp_plan* plan; const DblArgs& a; hipStream_t stream;
+  template <typename L> hipError_t operator()() const { return L::double_backward(plan, a, stream); }
+};
+
+// What tp_spec.hip needs to know of one generated shape.
+template <typename G>
+struct GeneratedShape {
+  static hipError_t forward(const tp_plan* p, const FwdArgs& a, hipStream_t s) { return with_instance<G>(p, ForwardFn{p, a, s}); }
+  static hipError_t backward(const tp_plan* p, const BwdArgs& a, hipStream_t s) { return with_instance<G>(p, BackwardFn{p, a, s}); }
+  static hipError_t double_backward(const tp_plan* p, const DblArgs& a, hipStream_t s) {
+    return with_instance<G>(p, DoubleBackwardFn{p, a, s});
+  }
+  static SpecEntry entry() {
+    return SpecEntry{G::kLY, G::kLh, G::kLout, G::kP, {G::kOps[0], G::kOps[1], G::kOps[2]},
+                     {G::kFlops[0], G::kFlops[1], G::kFlops[2]}, &forward, &backward, &double_backward};
+  }
+};
+
+}  // namespace
+}  // namespace tp

@@ -154,6 +154,15 @@ def test_other_configurations(tp, l_Y, l_h, L_max):
     full_parity(tp, wl_of("other", 50, 5, 64, l_Y, l_h, L_max, "f64", 5200))
 
 
+@pytest.mark.parametrize("dtype,K", [("f32", 64), ("f32", 100), ("f64", 64), ("f64", 7)])
+@pytest.mark.parametrize("l,l_h", [(l, l_h) for l in (1, 2, 3) for l_h in range(l + 1)])
+def test_every_generated_shape(tp, l, l_h, dtype, K):
+    """Full and ragged channel blocks of every generated shape; receivers with 0, 1, 2 and more edges.  fp32 rows
+    of all but (3,0,3) and (3,1,3) on full blocks are computed in fp64 and rounded once."""
+    info = full_parity(tp, wl_of("generated", 30, 3, K, l, l_h, l, dtype, 5250 + 10 * l + l_h))
+    assert info.specialised == 1
+
+
 def test_degenerate_graphs(tp):
     # one node without edges; a star (every edge into node 0); a high-degree tail
     full_parity(tp, wl_of("one_node", 1, 3, 128, 3, 1, 3, "f32", 5301))
