@@ -99,8 +99,8 @@ typedef enum { SC_F32 = 0, SC_F64 = 1, SC_BF16 = 2 } sc_dtype;
 #define SC_COMPONENT_MAJOR 8u /* the per-node tensors (A, B, dB, dA, and H, ddB, dA2 of the second-order
                                  pass) are laid out [n_nodes][component][K] (channel fastest) instead
                                  of [n_nodes][K][component]; W and dW keep their layout.  Served for
-                                 plans with a generated kernel (sc_info.specialised) and fp32 or fp64
-                                 rows; otherwise the call fails with SC_ERR_UNSUPPORTED and launches
+                                 plans with a generated kernel (sc_info.specialised), l_max = 3 and
+                                 nu_max = 3 (or the tiny configuration) and fp32 or fp64 rows; otherwise the call fails with SC_ERR_UNSUPPORTED and launches
                                  nothing.  The per-node results are those of the default layout,
                                  bit for bit, transposed.                                         */
 

@@ -42,6 +42,17 @@ SPECS = {
     "l3n3_0e1o2e3o": (3, 3, ((0, 1), (1, -1), (2, 1), (3, -1))),
     "l1n2_0e": (1, 2, ((0, 1),)),
     "l3n3_0e": (3, 3, ((0, 1),)),      # scalar outputs only: the product of a model's last layer
+    # smaller models: features up to l = 2, products of two features
+    "l2n3_0e": (2, 3, ((0, 1),)),
+    "l2n3_0e1o": (2, 3, ((0, 1), (1, -1))),
+    "l2n3_0e1o2e": (2, 3, ((0, 1), (1, -1), (2, 1))),
+    "l2n2_0e": (2, 2, ((0, 1),)),
+    "l2n2_0e1o": (2, 2, ((0, 1), (1, -1))),
+    "l2n2_0e1o2e": (2, 2, ((0, 1), (1, -1), (2, 1))),
+    "l3n2_0e": (3, 2, ((0, 1),)),
+    "l3n2_0e1o": (3, 2, ((0, 1), (1, -1))),
+    "l3n2_0e1o2e": (3, 2, ((0, 1), (1, -1), (2, 1))),
+    "l3n2_0e1o2e3o": (3, 2, ((0, 1), (1, -1), (2, 1), (3, -1))),
 }
 
 
@@ -345,11 +356,11 @@ def emit_inc(tag: str, tab: Tables, basis, fold, fwd: Program, bwd: Program, dbl
     L.append(f"  static constexpr int kOps[3] = {{{fc['total']}, {bc['total']}, {dc['total']}}};")
     L.append(f"  static constexpr int kFlops[3] = {{{flops(fc)}, {flops(bc)}, {flops(dc)}}};")
     L.append("")
-    L.append("  // w'[s] = sum_p F[s,p] * W[z,p,k]; Wz points at W[z,0,k], consecutive paths are K apart.")
-    L.append("  template <typename T>")
-    L.append("  static __device__ __forceinline__ void fold(const T* __restrict__ Wz, int K, T (&w)[kS]) {")
+    L.append("  // w'[s] = sum_p F[s,p] * W[z,p,k]; Wz points at W[z,0,k] (stored as TW), consecutive paths are K apart.")
+    L.append("  template <typename T, typename TW>")
+    L.append("  static __device__ __forceinline__ void fold(const TW* __restrict__ Wz, int K, T (&w)[kS]) {")
     for s, lst in enumerate(fold):
-        terms = " + ".join(f"T({repr(c)}) * Wz[{p} * K]" for p, c in lst)
+        terms = " + ".join(f"T({repr(c)}) * T(Wz[{p} * K])" for p, c in lst)
         L.append(f"    w[{s}] = {terms};")
     L.append("  }")
     L.append("")

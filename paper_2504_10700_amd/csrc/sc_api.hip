@@ -32,7 +32,8 @@ __global__ void fill_zero_kernel(unsigned int* p, size_t n_words) {
     p[i] = 0u;
 }
 
-// bytes of one element of W / dW / the per-tile dW rows (fp32 also when the per-node rows are bfloat16)
+// bytes of one element of W and dW, and of the table-driven kernels' per-tile dW rows (fp32 also when the
+// per-node rows are bfloat16)
 size_t elem_size(const sc_plan* plan) { return plan->cfg.dtype == SC_F64 ? 8 : 4; }
 
 // Scratch of sc_forward_noalloc: the grouping of one call (what sc_forward keeps in the caller's
@@ -153,7 +154,7 @@ Workspace carve_workspace(const sc_plan* plan, int64_t n, const LaunchShape& sha
     w.wkey = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));
   }
   if (!forward_only)  // the weight-gradient rows of the backward passes
-    w.partial = take(elem_size(plan) * static_cast<size_t>(shape.max_tiles) * shape.chblocks * plan->S * kLanes);
+    w.partial = take((plan->specialised ? spec_value_bytes(plan) : elem_size(plan)) * static_cast<size_t>(shape.max_tiles) * shape.chblocks * plan->S * kLanes);
   w.max_tiles = shape.max_tiles;
   w.bytes = off;
   return w;
@@ -438,16 +439,19 @@ static sc_status check_layout_flag(const char* fn, const sc_plan* plan, uint32_t
   if (!(flags & SC_COMPONENT_MAJOR)) return SC_OK;
   if (!plan->specialised)
     return fail(SC_ERR_UNSUPPORTED, std::string(fn) + ": SC_COMPONENT_MAJOR needs a plan served by a generated kernel (sc_info.specialised)");
-  if (plan->cfg.dtype == SC_BF16)
-    return fail(SC_ERR_UNSUPPORTED, std::string(fn) + ": SC_COMPONENT_MAJOR is not served for bfloat16 rows");
+  if (!sc::spec_has_component_major(plan))
+    return fail(SC_ERR_UNSUPPORTED, std::string(fn) + (plan->cfg.dtype == SC_BF16
+                    ? ": SC_COMPONENT_MAJOR is not served for bfloat16 rows"
+                    : ": SC_COMPONENT_MAJOR is served for l_max = 3, nu_max = 3 and for the tiny configuration"));
   return SC_OK;
 }
 
 // Checks of the tensor arguments and the launches of the forward pass, shared by sc_forward and
-// sc_forward_noalloc; the plan's device is current.
+// sc_forward_noalloc; the plan's device is current.  direct (generated kernels, no grouping wanted):
+// one launch whose waves fold their weights themselves; ws is not used.
 static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z,
                                   const void* W, void* B, const sc::Workspace& ws, const sc::LaunchShape& shape,
-                                  uint32_t flags, hipStream_t stream) {
+                                  uint32_t flags, bool direct, hipStream_t stream) {
   if (!A || !z || !W || !B) return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": NULL tensor argument");
   if (misaligned(A, 16) || misaligned(W, 16) || misaligned(B, 16) || misaligned(z, 4))
     return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": tensor pointer not 16-byte aligned");
@@ -457,9 +461,11 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
   const bool group = !(flags & SC_REUSE_GROUPING);
   // the prepare launch also orders windows of the batch by element for the forward kernel (not for a
   // batch that is ordered already, nor for small ones, where that costs more than it saves)
-  const bool window_order = plan->specialised && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
+  const bool window_order = plan->specialised && !direct && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
                             (n_nodes >= SC_WINDOW_ORDER_MIN_NODES || (plan->cfg.flags & SC_PLAN_WINDOW_ORDER));
-  if (plan->specialised) {
+  if (plan->specialised && direct) {
+    // nothing to prepare
+  } else if (plan->specialised) {
     // the forward itself needs no grouping: the two halves of it ride in the prepare and the forward launch
     e = sc::launch_spec_prepare(plan, n_nodes, z, W, ws, shape, group, !(flags & SC_REUSE_WEIGHTS), window_order, stream);
     if (e != hipSuccess) return fail_hip(e, (std::string(fn) + ": prepare launch").c_str());
@@ -468,9 +474,9 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
     if (e != hipSuccess) return fail_hip(e, (std::string(fn) + ": grouping launch").c_str());
   }
   if (plan->profile) (void)hipEventRecord(plan->ev[0], stream);
-  e = plan->specialised ? sc::launch_spec_forward(plan, n_nodes, A, z, B, ws, shape,
+  e = plan->specialised ? sc::launch_spec_forward(plan, n_nodes, A, z, W, B, ws, shape,
                                                   !group ? 0 : (flags & SC_Z_GROUPED) ? 2 : 1, window_order,
-                                                  (flags & SC_COMPONENT_MAJOR) != 0, stream)
+                                                  (flags & SC_COMPONENT_MAJOR) != 0, direct, stream)
                         : sc::launch_generic_forward(plan, n_nodes, A, W, B, ws, shape, stream);
   if (e != hipSuccess) return fail_hip(e, (std::string(fn) + ": kernel launch").c_str());
   if (plan->profile) {
@@ -489,7 +495,7 @@ sc_status sc_forward(sc_plan* plan, int64_t n_nodes, const void* A, const int32_
   if (n_nodes == 0) return SC_OK;
   DeviceGuard guard(plan->cfg.device);
   if (!guard.ok) return fail(SC_ERR_HIP, "sc_forward: cannot make the plan's device current");
-  return forward_launches("sc_forward", plan, n_nodes, A, z, W, B, ws, shape, flags, static_cast<hipStream_t>(hip_stream));
+  return forward_launches("sc_forward", plan, n_nodes, A, z, W, B, ws, shape, flags, false, static_cast<hipStream_t>(hip_stream));
 }
 
 sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B,
@@ -502,7 +508,10 @@ sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, cons
                                       std::to_string(SC_NOALLOC_MAX_NODES) + "; use sc_forward with a workspace");
   const sc::LaunchShape shape = sc::launch_shape(plan, n_nodes);
   const size_t need = sc::carve_workspace(plan, n_nodes, shape, nullptr, true).bytes;
-  if (need > SC_NOALLOC_SCRATCH_BYTES)
+  // without room for the folded table the waves fold their weights themselves (plans for which the call
+  // has no such limit)
+  const bool direct = plan->specialised && need > SC_NOALLOC_SCRATCH_BYTES && sc::spec_scratch_optional(plan);
+  if (need > SC_NOALLOC_SCRATCH_BYTES && !direct)
     return fail(SC_ERR_WORKSPACE, "sc_forward_noalloc: this plan needs " + std::to_string(need) + " bytes of scratch for " +
                                       std::to_string(n_nodes) + " nodes, more than SC_NOALLOC_SCRATCH_BYTES = " +
                                       std::to_string(SC_NOALLOC_SCRATCH_BYTES) + "; use sc_forward with a workspace");
@@ -520,7 +529,7 @@ sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, cons
   // and there is no backward pass to leave one for.
   const sc::Workspace ws = sc::carve_workspace(plan, n_nodes, shape, base, true);
   return forward_launches("sc_forward_noalloc", plan, n_nodes, A, z, W, B, ws, shape,
-                          plan->specialised ? SC_REUSE_GROUPING : 0u, static_cast<hipStream_t>(hip_stream));
+                          plan->specialised ? SC_REUSE_GROUPING : 0u, direct, static_cast<hipStream_t>(hip_stream));
 }
 
 sc_status sc_backward(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, const void* dB,

@@ -4,6 +4,28 @@
 
 namespace sc {
 
+// One generated program and its launches.  wide: fp32 plans compute in fp64 (rows and weights stay
+// fp32); bfloat16 rows and the component-major layout are not served.
+struct SpecEntry {
+  int l_max, nu_max, num_out, out_l[SC_MAX_OUT], out_parity[SC_MAX_OUT];
+  int n_lm, P, S;
+  bool wide;
+  int32_t ops[3], flops[3];
+  hipError_t (*prepare)(const sc_plan*, int64_t n, const int32_t* z, const void* W, const Workspace&, const LaunchShape&,
+                        bool count, bool fold, bool window_order, hipStream_t);
+  hipError_t (*forward)(const sc_plan*, int64_t n, const void* A, const int32_t* z, const void* W, void* B, const Workspace&,
+                        const LaunchShape&, int group, bool window_order, bool component_major, bool direct, hipStream_t);
+  hipError_t (*backward)(const sc_plan*, int64_t n, const void* A, const void* dB, void* dA, const Workspace&,
+                         const LaunchShape&, bool component_major, hipStream_t);
+  hipError_t (*double_backward)(const sc_plan*, const void* A, const void* W, const void* dB, const void* H, void* ddB,
+                                void* dA2, const Workspace&, const LaunchShape&, bool component_major, hipStream_t);
+  hipError_t (*finalize)(const sc_plan*, void* dW, const Workspace&, const LaunchShape&, hipStream_t);
+};
+const SpecEntry* spec_entries_l2();
+int spec_entries_l2_count();
+const SpecEntry* spec_entries_l3n2();
+int spec_entries_l3n2_count();
+
 // Returns the id (> 0) of the generated kernel that serves this plan, 0 if none.
 int spec_lookup(const sc_plan* plan);
 // Size of the internal (reduced) path basis of a generated kernel.
@@ -12,6 +34,14 @@ int spec_basis_size(int id);
 void spec_op_counts(int id, int32_t ops[3], int32_t flops[3]);
 // Waves per workgroup (= per tile) of the generated kernels.
 int spec_waves_per_tile();
+
+// Does the plan's generated kernel serve SC_COMPONENT_MAJOR?
+bool spec_has_component_major(const sc_plan* plan);
+// Plans that the table-driven kernels served before: a forward whose scratch has no room for the folded
+// table runs with weights folded by the waves (launch_spec_forward, direct).
+bool spec_scratch_optional(const sc_plan* plan);
+// Bytes of a folded weight and of a per-tile dW value (the plan must have a generated kernel).
+size_t spec_value_bytes(const sc_plan* plan);
 
 // Bytes of the folded-weight table wf[element][channel][stride] of a generated kernel.
 size_t spec_folded_bytes(const sc_plan* plan);
@@ -26,14 +56,15 @@ hipError_t launch_spec_prepare(const sc_plan* plan, int64_t n, const int32_t* z,
 // table_only: offsets and tile table without the permutation (the batch is already grouped).
 hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z, const Workspace& ws,
                                const LaunchShape& shape, bool table_only, hipStream_t stream);
-// Forward over the nodes in natural order from ws.wfold; group: the second half of the grouping
+// Forward over the nodes in natural order from ws.wfold, or (direct) with weights that every wave
+// folds from W by itself; group: the second half of the grouping
 // rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only).
 // component_major: the per-node tensors are laid out [node][component][channel]
 // (SC_COMPONENT_MAJOR; plans whose rows are stored in the arithmetic type only).
 // window_order: the kernel follows ws.wnode / ws.wkey, written by the prepare launch of the same call.
-hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, void* B,
+hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                                const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
-                               bool component_major, hipStream_t stream);
+                               bool component_major, bool direct, hipStream_t stream);
 // The grouped passes read ws.perm (null: the batch is already grouped, identity) and ws.tiles; the backward reads ws.wfold, the second-order pass folds W itself.
 hipError_t launch_spec_backward(const sc_plan* plan, int64_t n, const void* A, const void* dB, void* dA,
                                 const Workspace& ws, const LaunchShape& shape, bool component_major,

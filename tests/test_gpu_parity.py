@@ -121,6 +121,65 @@ def test_outputs_up_to_L3(sc, dtype):
         full_parity(sc, wl_of("out_L3b", 700, 89, 96, 3, 3, outs, dtype, 2310))
 
 
+SMALLER = [(2, 3, O01[:1]), (2, 3, O01), (2, 3, O012), (2, 2, O01[:1]), (2, 2, O01), (2, 2, O012),
+           (3, 2, O01[:1]), (3, 2, O01), (3, 2, O012), (3, 2, O012 + ((3, -1),))]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("l_max,nu_max,outs", SMALLER)
+def test_generated_kernels_of_smaller_models(sc, l_max, nu_max, outs, dtype):
+    """l_max = 2 and nu_max = 2: the three passes and the call without a workspace against the oracle and,
+    since fp32 plans of these shapes compute in fp64, against the table-driven kernels (which do, too): both
+    round each row value once, so that they differ by at most two roundings (2^-23) of a value, plus what fp64
+    arithmetic leaves."""
+    import torch
+    name = f"small_l{l_max}n{nu_max}_{len(outs)}"
+    for N, K, Z in ((130, 72, 3), (257, 64, 89)):   # idle lanes; ragged tiles, elements with one node and with none
+        wl = wl_of(f"{name}_{N}", N, Z, K, l_max, nu_max, outs, dtype, 2500 + N, z_mode="uniform")
+        T = oracle_tables(wl)
+        inp = workloads.make_inputs(wl, T.paths)
+        runs = [GpuRun(sc, wl, inp, flags) for flags in (0, sc.SC_PLAN_FORCE_GENERIC)]
+        assert [sc.sc_plan_info(r.plan).specialised for r in runs] == [1, 0]
+        H = workloads.make_cotangent(wl)
+        got = [(r.forward(), *r.backward(sc.SC_REUSE_GROUPING | sc.SC_REUSE_WEIGHTS), *r.double_backward(H)[:3]) for r in runs]
+        A, z, W, dB = runs[0].inputs_as_computed()
+        Hc = torch.tensor(H, dtype=runs[0].tdt).double().numpy()
+        ref = (oracle_forward(osc, T, A, z, W), *oracle_backward(osc, T, A, z, W, dB),
+               *oracle_double_backward(osc, T, A, z, W, dB, Hc))
+        for what, g, t, r in zip(("B", "dA", "dW", "ddB", "dA2", "dW2"), *got, ref):
+            if what in ("dW", "dW2"):
+                check_dw(what, g, r, z, dtype, case=wl.name)
+                continue
+            check(what, g, r, dtype)
+            if dtype == "f32":
+                rms = np.sqrt((r ** 2).mean())
+                assert (np.abs(g.astype(np.float64) - t) <= 2.0 ** -23 * np.abs(r) + 1e-12 * rms).all(), what
+        B = torch.full_like(runs[0].B, float("nan"))
+        sc.sc_forward_noalloc(runs[0].plan, N, runs[0].A, runs[0].z, runs[0].W, B)
+        assert np.array_equal(B.cpu().numpy(), got[0][0])
+        with pytest.raises(sc.ScError) as e:   # as before there were generated kernels for these shapes
+            runs[0].forward(sc.SC_COMPONENT_MAJOR)
+        assert e.value.status == sc.SC_ERR_UNSUPPORTED
+        for r in runs:
+            r.close()
+    with pytest.raises(sc.ScError) as e:
+        sc.sc_plan_create(64, l_max, nu_max, 5, outs, sc.SC_BF16, 0)
+    assert e.value.status == sc.SC_ERR_UNSUPPORTED
+
+
+def test_smaller_models_without_room_for_folded_weights(sc):
+    # 512 elements x 256 channels x 27 rows of fp64 folded weights are 28 MB: the call without a workspace folds
+    # them inside the forward instead (the plan has always been served)
+    wl = wl_of("small_many_elements", 300, 512, 256, 2, 3, O012, "f64", 2590, z_mode="uniform")
+    T = oracle_tables(wl)
+    run = GpuRun(sc, wl, workloads.make_inputs(wl, T.paths))
+    want = run.forward()
+    run.B.fill_(float("nan"))
+    sc.sc_forward_noalloc(run.plan, run.N, run.A, run.z, run.W, run.B)
+    assert np.abs(run.B.cpu().numpy() - want).max() <= 1e-13 * np.sqrt((want ** 2).mean())
+    run.close()
+
+
 def test_degenerate_batches(sc):
     # one node; all nodes of one element; most elements absent.  With 1 or 2 of 89 elements present
     # the 87-88 zero rows shrink the whole-tensor rms 9.4x / 6.7x: the error of the present rows is
