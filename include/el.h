@@ -12,7 +12,7 @@
  * index l*l + l + m as in sc.h.  No bias and no normalisation factor inside the operation.
  * This is a dense contraction: the kernels run on the matrix cores (MFMA, fp32 or fp64
  * inputs and accumulation) when K_in and K_out are multiples of 64 (forward alone: K_in a
- * multiple of 16), and on plain vector kernels otherwise.
+ * multiple of 16), and in fp64 on the matrix cores otherwise.
  *
  * Conventions as in sc.h: device pointers, dense row-major, 16-byte aligned; calls enqueue on
  * the given HIP stream and never synchronise; outputs are overwritten; errors by return code

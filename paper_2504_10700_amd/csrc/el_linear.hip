@@ -20,7 +20,7 @@
 // lane.  The atoms are cut into ranges, every range writes a partial dW (mfma_dw_lds_kernel:
 // dY rows shared through LDS, two row tiles per wave; mfma_dw_kernel: every other shape), a
 // second kernel adds the partials in a fixed order (no atomics).
-// Channel counts outside the MFMA tilings run on plain vector kernels with fp64 accumulation.
+// Channel counts outside these tilings: split_forward_kernel and split_dw_kernel (fp64 products and sums).
 #include <algorithm>
 #include <atomic>
 #include <string>
@@ -362,45 +362,182 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(int64_t n_elems, int n_r
   if (q == 0 && i < n_elems) dW[i] = ((quarter[0][lane] + quarter[1][lane]) + quarter[2][lane]) + quarter[3][lane];
 }
 
-// ---- plain vector kernels for channel counts the MFMA tiling does not cover (fp64 accumulation)
-template <typename T, bool kTrans>
-__global__ void plain_forward_kernel(int64_t n_nodes, int k_red, int k_cols, int l_max, const T* __restrict__ X,
-                                     const T* __restrict__ W, T* __restrict__ Y) {
-  const int nc = (l_max + 1) * (l_max + 1);
-  const int64_t idx = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (idx >= n_nodes * k_cols) return;
-  const int64_t n = idx / k_cols;
-  const int j = static_cast<int>(idx % k_cols);
-  double y[16];
-  for (int c = 0; c < nc; ++c) y[c] = 0.0;
-  for (int k = 0; k < k_red; ++k) {
-    const T* x = X + (static_cast<size_t>(n) * k_red + k) * nc;
-    for (int c = 0; c < nc; ++c) {
-      const int l = order_of(c);
-      const T w = kTrans ? W[(static_cast<size_t>(l) * k_cols + j) * k_red + k]
-                         : W[(static_cast<size_t>(l) * k_red + k) * k_cols + j];
-      y[c] += static_cast<double>(x[c]) * static_cast<double>(w);
+// ---- the products cut along the reduction: any channel count, and batches of few row tiles (split_small)
+//
+// A workgroup owns 16 atoms x 16 columns with all components and its four waves take every fourth step of the
+// reduction; the four partial tiles meet in LDS (fixed order) and leave as whole lines.  TA = type of the products
+// and sums: double for channel counts that the kernels above do not tile (their rows may be fp32: the fp64 matrix
+// rate is half the fp32 one, and these shapes are far from it), the storage type where only the batch is small.
+// What bounds it: small batches the chain of one wave (load -> products -> LDS -> store), large ones the matrix
+// cores.  Against one thread per (atom, column) in fp64, us: forward 100 -> 128 channels 155 atoms 198 -> 10, 4000 508 -> 46.
+// k_red and k_cols are free: positions past the end supply zeros, columns past the end are not stored.
+template <typename TA>
+struct SplitRow {   // elements per row of a partial tile in LDS: the four rows that one instruction writes meet no bank twice
+  static constexpr int stride = sizeof(TA) == 4 ? 20 : 16;
+};
+
+// blockIdx -> logical block such that an XCD's blocks are one contiguous range (the column tiles of a row tile read
+// the same rows of X: they meet in one L2).  gridDim.x is a multiple of kXcds.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int64_t xcd_contiguous_block() {
+  const int64_t per = gridDim.x / kXcds;
+  return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+}
+unsigned xcd_grid(int64_t blocks) { return static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds); }
+
+// kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).
+template <typename TS, typename TA, int LMAX, bool kTrans>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void split_forward_kernel(
+    int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W, TS* __restrict__ Y) {
+  constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
+  constexpr int CG = NC < 4 ? NC : 4;                        // components per round through LDS
+  constexpr int RS = SplitRow<TA>::stride;
+  typedef typename Mma<TA>::acc_t acc_t;
+  __shared__ __attribute__((aligned(16))) TA red[kWaves][CG][16 * RS];
+  __shared__ __attribute__((aligned(16))) TS out[16][16 * NC];
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int kq = lane / 16, i16 = lane & 15;
+  const int col_tiles = (k_cols + 15) / 16;
+  const int64_t tile = xcd_contiguous_block();
+  if (tile >= (n_nodes + 15) / 16 * col_tiles) return;       // the same for the whole workgroup
+  const int64_t n0 = tile / col_tiles * 16;
+  const int j0 = static_cast<int>(tile % col_tiles) * 16;
+  const int64_t na = n0 + i16 < n_nodes ? n0 + i16 : n_nodes - 1;
+  const int j = j0 + i16 < k_cols ? j0 + i16 : k_cols - 1;
+  const int steps = (k_red + 3) / 4;
+  const TS* xrow = X + static_cast<size_t>(na) * k_red * NC;
+  acc_t acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = acc_t{0, 0, 0, 0};
+
+  auto load = [&](int s, TS (&a)[NC], TS (&b)[L]) {
+    const int k = s * 4 + kq, kc = k < k_red ? k : k_red - 1;
+    load_unaligned<TS, NC>(xrow + static_cast<size_t>(kc) * NC, a);
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+      b[l] = kTrans ? W[(static_cast<size_t>(l) * k_cols + j) * k_red + kc] : W[(static_cast<size_t>(l) * k_red + kc) * k_cols + j];
+  };
+  auto multiply = [&](int s, const TS (&a)[NC], const TS (&b)[L]) {
+    const bool live = s * 4 + kq < k_red;                    // both operands are zeroed: the row re-read may hold a NaN
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      acc[c] = Mma<TA>::mma(live ? static_cast<TA>(a[c]) : TA(0), live ? static_cast<TA>(b[order_of(c)]) : TA(0), acc[c]);
+  };
+  if (wave < steps) {
+    TS a[2][NC], b[2][L];
+    load(wave, a[0], b[0]);
+    for (int s = wave; s < steps; s += 2 * kWaves) {
+      const int s1 = s + kWaves, s2 = s + 2 * kWaves;
+      load(s1 < steps ? s1 : s, a[1], b[1]);
+      multiply(s, a[0], b[0]);
+      if (s1 < steps) {
+        load(s2 < steps ? s2 : s1, a[0], b[0]);
+        multiply(s1, a[1], b[1]);
+      }
     }
   }
-  for (int c = 0; c < nc; ++c) Y[idx * nc + c] = static_cast<T>(y[c]);
+  const int er = threadIdx.x / 16, ec = threadIdx.x % 16;    // the entry that this thread sums
+#pragma unroll
+  for (int c0 = 0; c0 < NC; c0 += CG) {
+    if (c0 > 0) __syncthreads();                             // the previous round has been read
+#pragma unroll
+    for (int c = c0; c < c0 + CG && c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][c - c0][Mma<TA>::row(lane, r) * RS + i16] = acc[c][r];
+    __syncthreads();
+#pragma unroll
+    for (int c = c0; c < c0 + CG && c < NC; ++c) {
+      TA y = red[0][c - c0][er * RS + ec];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) y += red[w][c - c0][er * RS + ec];
+      out[er][ec * NC + c] = static_cast<TS>(y);
+    }
+  }
+  __syncthreads();
+  constexpr int V = NC % 4 == 0 ? 16 / sizeof(TS) : 1;       // rows of X and Y are whole 16-byte pieces, or not
+  typedef TS Vec __attribute__((ext_vector_type(V)));
+  constexpr int kPieces = 16 * NC / V;                       // per atom
+  const int live = (k_cols - j0 < 16 ? k_cols - j0 : 16) * NC / V;
+  for (int q = threadIdx.x; q < 16 * kPieces; q += kThreads) {
+    const int r = q / kPieces, p = q % kPieces;
+    if (n0 + r < n_nodes && p < live)
+      *reinterpret_cast<Vec*>(Y + (static_cast<size_t>(n0 + r) * k_cols + j0) * NC + p * V) =
+          *reinterpret_cast<const Vec*>(&out[r][p * V]);
+  }
 }
 
-// one thread per (l, k, j): sums over all atoms in atom order
-template <typename T>
-__global__ void plain_dw_kernel(int64_t n_nodes, int k_in, int k_out, int l_max, const T* __restrict__ X,
-                                const T* __restrict__ dY, T* __restrict__ dW) {
-  const int nc = (l_max + 1) * (l_max + 1);
-  const int64_t idx = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (idx >= static_cast<int64_t>(l_max + 1) * k_in * k_out) return;
-  const int j = static_cast<int>(idx % k_out);
-  const int k = static_cast<int>((idx / k_out) % k_in);
-  const int l = static_cast<int>(idx / (static_cast<int64_t>(k_out) * k_in));
-  double s = 0.0;
-  for (int64_t n = 0; n < n_nodes; ++n)
-    for (int c = l * l; c < (l + 1) * (l + 1); ++c)
-      s += static_cast<double>(X[(static_cast<size_t>(n) * k_in + k) * nc + c]) *
-           static_cast<double>(dY[(static_cast<size_t>(n) * k_out + j) * nc + c]);
-  dW[idx] = static_cast<T>(s);
+// dW for any channel count: a workgroup owns 16 x 16 entries of one order, its sixteen waves take every sixteenth
+// reduction step (4 atoms); their sums meet in LDS and are added in wave order.  Products and sums in fp64; no
+// workspace.  The highest orders, which have the most components, come first in the grid.  Bound by the vector cache
+// (four SIMDs ask for 512 lines per 28 products of theirs).  Against one thread per entry, us: 100 -> 128 channels, 155
+// atoms 143 -> 7, 4000 3980 -> 120; 96 -> 96, 3000 atoms 2962 -> 75.
+constexpr int kDwWaves = 16;
+
+template <typename TS, int ORDER>
+__device__ __forceinline__ void split_dw_order(int64_t n_nodes, int nc, int k_in, int k_out, const TS* __restrict__ X,
+                                               const TS* __restrict__ dY, TS* __restrict__ dW, int k0, int j0,
+                                               double (*red)[256]) {
+  constexpr int M = 2 * ORDER + 1;
+  typedef Mma<double>::acc_t acc_t;
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int nq = lane / 16, i16 = lane & 15;
+  const int k = k0 + i16 < k_in ? k0 + i16 : k_in - 1, j = j0 + i16 < k_out ? j0 + i16 : k_out - 1;
+  const TS* xcol = X + static_cast<size_t>(k) * nc + ORDER * ORDER;
+  const TS* ycol = dY + static_cast<size_t>(j) * nc + ORDER * ORDER;
+  acc_t acc{0, 0, 0, 0};
+  const int64_t steps = (n_nodes + 3) / 4;
+  auto load = [&](int64_t s, TS (&a)[M], TS (&b)[M]) {
+    const int64_t n = s * 4 + nq;
+    const size_t nc_ = static_cast<size_t>(n < n_nodes ? n : n_nodes - 1);
+    load_unaligned<TS, M>(xcol + nc_ * k_in * nc, a);
+    load_unaligned<TS, M>(ycol + nc_ * k_out * nc, b);
+  };
+  auto multiply = [&](int64_t s, const TS (&a)[M], const TS (&b)[M]) {
+    const bool live = s * 4 + nq < n_nodes;                  // both operands are zeroed: the row re-read may hold a NaN
+#pragma unroll
+    for (int c = 0; c < M; ++c)
+      acc = Mma<double>::mma(live ? static_cast<double>(a[c]) : 0.0, live ? static_cast<double>(b[c]) : 0.0, acc);
+  };
+  if (wave < steps) {
+    TS a[2][M], b[2][M];
+    load(wave, a[0], b[0]);
+    for (int64_t s = wave; s < steps; s += 2 * kDwWaves) {
+      const int64_t s1 = s + kDwWaves, s2 = s + 2 * kDwWaves;
+      load(s1 < steps ? s1 : s, a[1], b[1]);
+      multiply(s, a[0], b[0]);
+      if (s1 < steps) {
+        load(s2 < steps ? s2 : s1, a[0], b[0]);
+        multiply(s1, a[1], b[1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][Mma<double>::row(lane, r) * 16 + i16] = acc[r];
+  __syncthreads();
+  const int e = threadIdx.x, ko = k0 + e / 16, jo = j0 + e % 16;
+  if (e >= 256 || ko >= k_in || jo >= k_out) return;
+  double y = red[0][e];
+#pragma unroll
+  for (int w = 1; w < kDwWaves; ++w) y += red[w][e];
+  dW[(static_cast<size_t>(ORDER) * k_in + ko) * k_out + jo] = static_cast<TS>(y);
+}
+
+template <typename TS>
+__global__ __launch_bounds__(kDwWaves * kLanes) void split_dw_kernel(int64_t n_nodes, int l_max, int k_in, int k_out,
+                                                                     const TS* __restrict__ X, const TS* __restrict__ dY,
+                                                                     TS* __restrict__ dW) {
+  __shared__ double red[kDwWaves][256];
+  const int jtiles = (k_out + 15) / 16, ktiles = (k_in + 15) / 16, nc = (l_max + 1) * (l_max + 1);
+  const unsigned tiles = static_cast<unsigned>(jtiles) * ktiles;
+  const int j0 = static_cast<int>(blockIdx.x % jtiles) * 16, k0 = static_cast<int>(blockIdx.x / jtiles % ktiles) * 16;
+  switch (l_max - static_cast<int>(blockIdx.x / tiles)) {
+    case 0: return split_dw_order<TS, 0>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    case 1: return split_dw_order<TS, 1>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    case 2: return split_dw_order<TS, 2>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    default: return split_dw_order<TS, 3>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+  }
 }
 
 __global__ void zero_kernel(unsigned int* p, size_t n_words) {
@@ -452,6 +589,23 @@ int compute_units() {
 bool mfma_forward_ok(int k_red, int k_cols) { return k_red % (4 * kDepth) == 0 && k_cols % 64 == 0; }
 bool mfma_dw_ok(const el_config* c) { return c->k_in % 64 == 0 && c->k_out % 64 == 0; }
 
+// Does split_forward_kernel take a product that the other kernels tile as well?  Up to about one round of its
+// resident workgroups (a workgroup per 16 atoms x 16 columns, four of them per CU in fp32), where the others leave
+// most of the chip idle and run the whole reduction in one wave.  Forward, us, 128 -> 128 channels, other / split: fp32
+// l_max = 3, 61 atoms 34.4 / 10.2, 1000 23.6 / 14.2, 2000 26.7 / 25.5, 4000 30.0 / 43.2; l_max = 2, 1000 atoms
+// 17.0 / 10.8, 2000 18.5 / 18.6; 256 -> 128, 2000 atoms 47.7 / 40.1, 4000 52.2 / 71.3; fp64 (whose other kernel has
+// one wave per SIMD) 61 atoms 77.7 / 16.2, 2000 85.8 / 48.7, 4000 91.9 / 84.7.  Columns that take the other kernel several
+// turns of 64 (192): backward of 192 -> 128, 2000 atoms 99.9 / 72.1, 4000 130 / 123.
+bool split_small(size_t elem, int64_t n, int k_cols) {
+  const bool long_other = elem == 8 || (k_cols > 64 && k_cols % 128 != 0);
+  return (n + 15) / 16 * (k_cols / 16) <= static_cast<int64_t>(long_other ? 8 : 4) * compute_units();
+}
+
+// Does dX read W as it is?  Its strided reads of W save the launch that transposes W and cost less than it as long
+// as there is no more than one workgroup per CU.  Backward, us, 128 -> 128 channels, W as it is / transposed: fp32 61 atoms
+// 27.9 / 29.2, 500 31.8 / 33.4, 1000 44.3 / 39.8, 2000 73.1 / 55.3; fp64 500 atoms 41.8 / 44.5, 2000 117 / 113.
+bool dx_reads_w_as_is(int64_t n, int k_cols) { return (n + 15) / 16 * (k_cols / 16) <= compute_units(); }
+
 // Is the LDS-staged dW kernel the one for this configuration?
 bool dw_lds_ok(const el_config* c) { return c->dtype == SC_F32 && c->l_max == 3 && c->k_in % 128 == 0 && c->k_out % 64 == 0; }
 
@@ -464,9 +618,19 @@ int nodes_per_range(const el_config* cfg, int64_t n) {
   return static_cast<int>(std::min<int64_t>(per, int64_t(1) << 20));
 }
 
+template <typename T, typename TA, int LMAX, bool kTrans>
+hipError_t launch_split(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
+  const int64_t blocks = (n + 15) / 16 * ((k_cols + 15) / 16);
+  hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans>), dim3(xcd_grid(blocks)), dim3(kThreads), 0, stream, n,
+                     k_red, k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
+  return hipGetLastError();
+}
+
 template <typename T, int LMAX, bool kTrans>
 hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
-  // The MFMA kernels read B operands along rows of W (the backward hands them W transposed).
+  if (mfma_forward_ok(k_red, k_cols) && (kTrans || split_small(sizeof(T), n, k_cols)))
+    return launch_split<T, T, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
+  // The kernels below read B operands along rows of W (the backward hands them W transposed).
   if constexpr (!kTrans) {
     if (mfma_forward_ok(k_red, k_cols)) {
       const int64_t tiles = (n + 15) / 16;
@@ -490,11 +654,7 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
       return hipGetLastError();
     }
   }
-  const int64_t total = n * k_cols;
-  hipLaunchKernelGGL((plain_forward_kernel<T, kTrans>), dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0,
-                     stream, n, k_red, k_cols, LMAX, static_cast<const T*>(X), static_cast<const T*>(W),
-                     static_cast<T*>(Y));
-  return hipGetLastError();
+  return launch_split<T, double, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
 }
 
 template <typename T, bool kTrans>
@@ -513,8 +673,9 @@ hipError_t dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, 
                 hipStream_t stream) {
   const int64_t elems = static_cast<int64_t>(LMAX + 1) * cfg->k_in * cfg->k_out;
   if (!mfma_dw_ok(cfg)) {
-    hipLaunchKernelGGL((plain_dw_kernel<T>), dim3(static_cast<unsigned>((elems + 255) / 256)), dim3(256), 0, stream, n,
-                       cfg->k_in, cfg->k_out, LMAX, static_cast<const T*>(X), static_cast<const T*>(dY),
+    const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
+    hipLaunchKernelGGL((split_dw_kernel<T>), dim3(static_cast<unsigned>(tiles * (LMAX + 1))), dim3(kDwWaves * kLanes), 0,
+                       stream, n, LMAX, cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY),
                        static_cast<T*>(dW));
     return hipGetLastError();
   }
@@ -553,7 +714,7 @@ hipError_t dw_t(const el_config* cfg, int64_t n, const void* X, const void* dY, 
 
 // Workspace: [ W transposed, rounded up to 256 bytes ][ partial dW per range of atoms ].
 size_t wt_bytes(const el_config* cfg) {
-  if (!mfma_forward_ok(cfg->k_out, cfg->k_in)) return 0;   // the plain dX kernel reads W as it is
+  if (!mfma_forward_ok(cfg->k_out, cfg->k_in)) return 0;   // split_forward_kernel reads W as it is
   const size_t bytes = static_cast<size_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out * elem_size(cfg);
   return (bytes + 255) / 256 * 256;
 }
@@ -624,10 +785,10 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
   if (!workspace || workspace_bytes_given < workspace_bytes(cfg, n_nodes))
     return set_error(SC_ERR_WORKSPACE, "el_backward: workspace missing or smaller than el_workspace_bytes()");
   if (misaligned(workspace, 256)) return set_error(SC_ERR_WORKSPACE, "el_backward: workspace not 256-byte aligned");
-  // dX = dY times W transposed: reduction over the output channels, columns = input channels.  The MFMA
-  // kernels take W transposed once into the workspace (strided B operands cost a third more time).
+  // dX = dY times W transposed: reduction over the output channels, columns = input channels.  Beyond the smallest
+  // batches the kernels take W transposed once into the workspace (strided B operands cost a third more time).
   hipError_t e;
-  if (mfma_forward_ok(cfg->k_out, cfg->k_in)) {
+  if (mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n_nodes, cfg->k_in)) {
     const int64_t elems = static_cast<int64_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out;
     const unsigned tgrid = static_cast<unsigned>((elems + 255) / 256);
     if (cfg->dtype == SC_F64)

@@ -50,6 +50,21 @@ __device__ __forceinline__ void load_row(const T* __restrict__ p, T (&v)[N]) {
   }
 }
 
+// The same from an address that is aligned to its elements only (16-byte accesses need no more on this chip).
+template <typename T, int N>
+__device__ __forceinline__ void load_unaligned(const T* __restrict__ p, T (&v)[N]) {
+  constexpr int V = 16 / sizeof(T);
+  typedef T Vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+#pragma unroll
+  for (int i = 0; i + V <= N; i += V) {
+    const Vec x = *reinterpret_cast<const Vec*>(p + i);
+#pragma unroll
+    for (int k = 0; k < V; ++k) v[i + k] = x[k];
+  }
+#pragma unroll
+  for (int i = N / V * V; i < N; ++i) v[i] = p[i];
+}
+
 template <typename T, int N>
 __device__ __forceinline__ void store_row(T* __restrict__ p, const T (&v)[N]) {
   constexpr int V = 16 / sizeof(T);

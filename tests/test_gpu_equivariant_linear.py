@@ -69,6 +69,19 @@ def test_plain_fallback(el, k_in, k_out):
     run_case(el, 33, k_in, k_out, 2, "f64", 8400 + k_out)
 
 
+# Products cut along the reduction.  Any channel count (fewer reduction steps than waves, a reduction
+# and columns that are no multiple of 4 and 16), atoms around a row tile; and the batch size up to which they serve
+# the tiled channel counts too (4 x 256 tiles of 16 atoms x 16 columns in fp32, 8 x 256 in fp64; dX reads W as it
+# is up to 256 tiles).
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype", [
+    (1, 3, 1, 3, "f32"), (15, 100, 128, 3, "f32"), (17, 1, 17, 2, "f64"), (65, 13, 33, 1, "f32"), (67, 33, 31, 0, "f64"),
+    (263, 100, 50, 2, "f32"), (259, 90, 70, 3, "f64"),
+    (512, 128, 128, 3, "f32"), (513, 128, 128, 3, "f32"), (2048, 64, 128, 3, "f32"), (2049, 64, 128, 3, "f32"), (4096, 16, 64, 1, "f32"), (4097, 16, 64, 1, "f32"),
+    (4096, 64, 128, 1, "f64"), (4097, 64, 128, 1, "f64")])
+def test_products_cut_along_the_reduction(el, N, k_in, k_out, l_max, dtype):
+    run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N)
+
+
 def test_degenerate_sizes_and_errors(el):
     import torch
     run_case(el, 1, 128, 128, 3, "f32", 8501)
