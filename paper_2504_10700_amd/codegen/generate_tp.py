@@ -109,15 +109,16 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
     F = Program()
     y = [F.inp(f"y[{a}]") for a in range(tab.n_Y)]
     h = [F.inp(f"h[{b}]") for b in range(tab.n_h)]
-    r = [F.inp(f"r[{p}]") for p in range(tab.P)]
     acc: List[Optional[int]] = [F.inp(f"acc[{c}]") for c in range(tab.n_out)]
     for p, (l1, l2, l3) in enumerate(tab.paths):
         Cs, kappa = scaled[p]
-        rk = F.cmul(r[p], kappa)
+        rk = F.cmul(F.load(f"r[{p}]"), kappa)
         u = [F.mul(rk, hb) for hb in h[sl(l2)]]
         part = acc[sl(l3)]
         couple_into(F, Cs, y[sl(l1)], u, part)
         acc[sl(l3)] = part
+        if tab.n_h >= 9:   # many paths: without a boundary all of r is converted to fp64 in front of them
+            F.fence(part)
     for c in range(tab.n_out):
         F.out(f"acc[{c}]", acc[c])
 
@@ -125,25 +126,31 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
     Bq = Program()
     y = [Bq.inp(f"y[{a}]") for a in range(tab.n_Y)]
     h = [Bq.inp(f"h[{b}]") for b in range(tab.n_h)]
-    r = [Bq.inp(f"r[{p}]") for p in range(tab.P)]
     g = [Bq.inp(f"g[{c}]") for c in range(tab.n_out)]
     # path by path, so that only the sums over the paths stay live from one path to the next
     dy: List[Optional[int]] = [None] * tab.n_Y
     dh: List[Optional[int]] = [None] * tab.n_h   # the edge's share of its sender's gradient
     for p, (l1, l2, l3) in enumerate(tab.paths):
         terms, kappa = scaled_terms(Bq, tab.C[p], g[sl(l3)])
-        rk = Bq.cmul(r[p], kappa)
+        rk = Bq.cmul(Bq.load(f"r[{p}]"), kappa)
         s = couple_terms(Bq, terms, y[sl(l1)], "b", [None] * (2 * l2 + 1))      # s[b] = sum C[a,b,c] y[a] g[c]
         u = [Bq.mul(rk, x) for x in h[sl(l2)]]
         dy[sl(l1)] = couple_terms(Bq, terms, u, "a", dy[sl(l1)])                # dy[a] += sum C[a,b,c] u[b] g[c]
         Bq.out(f"dr[{p}]", scaled_dot(Bq, h[sl(l2)], s, kappa))
         add_scaled(Bq, rk, s, dh, l2)
+        out_when_complete(Bq, "dy", dy, tab.paths, p)
         Bq.fence(dy[sl(l1)] + dh[sl(l2)])
-    for a in range(tab.n_Y):
-        Bq.out(f"dy[{a}]", dy[a])
     for b in range(tab.n_h):
         Bq.out(f"dh[{b}]", dh[b])
     return F, Bq
+
+
+def out_when_complete(P: Program, name: str, v, paths, p: int) -> None:
+    """The components of order l1 of `v` leave with the last path that has this l1 (paths are ordered by l1)."""
+    l1 = paths[p][0]
+    if p + 1 == len(paths) or paths[p + 1][0] != l1:
+        for a in range(l1 * l1, (l1 + 1) * (l1 + 1)):
+            P.out(f"{name}[{a}]", v[a])
 
 
 def scaled_terms(P: Program, Cp: np.ndarray, g):
@@ -203,15 +210,13 @@ def build_double_backward(tab: TPTables) -> Program:
     hy = [P.inp(f"hy[{a}]") for a in range(tab.n_Y)]
     h = [P.inp(f"h[{b}]") for b in range(tab.n_h)]
     hh = [P.inp(f"hh[{b}]") for b in range(tab.n_h)]
-    r = [P.inp(f"r[{p}]") for p in range(tab.P)]
-    hr = [P.inp(f"hr[{p}]") for p in range(tab.P)]
     g = [P.inp(f"g[{c}]") for c in range(tab.n_out)]
     dda: List[Optional[int]] = [P.inp(f"dda[{c}]") for c in range(tab.n_out)]
     d2y: List[Optional[int]] = [None] * tab.n_Y
     d2h: List[Optional[int]] = [None] * tab.n_h
     for p, (l1, l2, l3) in enumerate(tab.paths):
         Cs, kappa = split_scale(tab.C[p])
-        rk, hrk = P.cmul(r[p], kappa), P.cmul(hr[p], kappa)
+        rk, hrk = P.cmul(P.load(f"r[{p}]"), kappa), P.cmul(P.load(f"hr[{p}]"), kappa)
         u = [P.mul(rk, x) for x in h[sl(l2)]]
         v = [P.fma(hrk, x, P.mul(rk, hx)) for x, hx in zip(h[sl(l2)], hh[sl(l2)])]
         part = dda[sl(l3)]
@@ -224,11 +229,10 @@ def build_double_backward(tab: TPTables) -> Program:
         P.out(f"d2r[{p}]", scaled_dot(P, h[sl(l2)] + hh[sl(l2)], sh + s, kappa))
         add_scaled(P, hrk, s, d2h, l2)
         add_scaled(P, rk, sh, d2h, l2)
+        out_when_complete(P, "d2y", d2y, tab.paths, p)
         P.fence(dda[sl(l3)] + d2y[sl(l1)] + d2h[sl(l2)])
     for c in range(tab.n_out):
         P.out(f"dda[{c}]", dda[c])
-    for a in range(tab.n_Y):
-        P.out(f"d2y[{a}]", d2y[a])
     for b in range(tab.n_h):
         P.out(f"d2h[{b}]", d2h[b])
     return P
@@ -333,18 +337,18 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append("  static constexpr int kOps[3] = {" + ", ".join(str(c["total"]) for c in cs) + "};")
     L.append("  static constexpr int kFlops[3] = {" + ", ".join(str(flops(c)) for c in cs) + "};")
     L.append("")
+    L.append("  // R: r[p] as T.  DR, DY: element p or a is assigned once, where the last path that contributes ends.")
     L.append("  // acc += message of one edge")
-    L.append("  template <typename T>")
-    L.append("  static __device__ __forceinline__ void forward(const T (&y)[kNY], const T (&h)[kNh], const T (&r)[kP],")
-    L.append("                                                 T (&acc)[kNout]) {")
+    L.append("  template <typename T, typename R>")
+    L.append("  static __device__ __forceinline__ void forward(const T (&y)[kNY], const T (&h)[kNh], const R& r, T (&acc)[kNout]) {")
     L.append(F.emit("T", "    "))
     L.append("  }")
     L.append("")
     L.append("  // g = dA of the receiver; overwritten: dr, dy (this channel's share of the edge's dY) and dh")
     L.append("  // (the edge's share of the gradient of its sender's features)")
-    L.append("  template <typename T, typename TR>")
-    L.append("  static __device__ __forceinline__ void backward(const T (&y)[kNY], const T (&h)[kNh], const T (&r)[kP],")
-    L.append("                                                  const T (&g)[kNout], TR (&dr)[kP], T (&dy)[kNY], T (&dh)[kNh]) {")
+    L.append("  template <typename T, typename R, typename DR, typename DY>")
+    L.append("  static __device__ __forceinline__ void backward(const T (&y)[kNY], const T (&h)[kNh], const R& r,")
+    L.append("                                                  const T (&g)[kNout], DR& dr, DY& dy, T (&dh)[kNh]) {")
     L.append(Bq.emit("T", "    "))
     L.append("  }")
     L.append("")
@@ -352,11 +356,11 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append("  // dda += derivative of the edge's message along (hy, hh, hr); with psi = sum(g * that derivative):")
     L.append("  // d2r = d psi / d r, d2y = this channel's share of d psi / d y, d2h = the edge's share of d psi / d h")
     L.append("  // (all three overwritten).")
-    L.append("  template <typename T, typename TR>")
+    L.append("  template <typename T, typename R, typename DR, typename DY>")
     L.append("  static __device__ __forceinline__ void double_backward(const T (&y)[kNY], const T (&hy)[kNY], const T (&h)[kNh],")
-    L.append("                                                         const T (&hh)[kNh], const T (&r)[kP], const T (&hr)[kP],")
-    L.append("                                                         const T (&g)[kNout], T (&dda)[kNout], TR (&d2r)[kP],")
-    L.append("                                                         T (&d2y)[kNY], T (&d2h)[kNh]) {")
+    L.append("                                                         const T (&hh)[kNh], const R& r, const R& hr,")
+    L.append("                                                         const T (&g)[kNout], T (&dda)[kNout], DR& d2r, DY& d2y,")
+    L.append("                                                         T (&d2h)[kNh]) {")
     L.append(D.emit("T", "    "))
     L.append("  }")
     L.append("};")

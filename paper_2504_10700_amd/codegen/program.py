@@ -13,6 +13,7 @@ import numpy as np
 
 # op codes
 INP, MUL, ADD, SUB, FMA, FNMA, CMUL, CFMA = "inp", "mul", "add", "sub", "fma", "fnma", "cmul", "cfma"
+LOAD = "load"     # an input that is read where it stands (its expression may convert)
 FENCE = "fence"   # no operation: the device compiler may not move instructions across it
 
 
@@ -27,6 +28,11 @@ class Program:
     def inp(self, cexpr: str) -> int:
         self.ops.append((INP, cexpr))
         self.names[len(self.ops) - 1] = cexpr
+        return len(self.ops) - 1
+
+    def load(self, cexpr: str) -> int:
+        """An input whose expression is evaluated here, once, and not at every use."""
+        self.ops.append((LOAD, cexpr))
         return len(self.ops) - 1
 
     def _push(self, key: Tuple) -> int:
@@ -107,7 +113,7 @@ class Program:
         live = self.live_ops()
         c: Dict[str, int] = {}
         for i, op in enumerate(self.ops):
-            if live[i] and op[0] not in (INP, FENCE):
+            if live[i] and op[0] not in (INP, LOAD, FENCE):
                 c[op[0]] = c.get(op[0], 0) + 1
         c["total"] = sum(c.values())
         return c
@@ -197,7 +203,7 @@ class Program:
             if not live[i]:
                 continue
             k = op[0]
-            if k == INP:
+            if k in (INP, LOAD):
                 val[i] = inputs[op[1]].astype(dtype)
             elif k == MUL:
                 val[i] = val[op[1]] * val[op[2]]
@@ -245,7 +251,9 @@ class Program:
                 continue
             name[i] = f"t{i}"
             k = op[0]
-            if k == MUL:
+            if k == LOAD:
+                e = op[1]
+            elif k == MUL:
                 e = f"{n(op[1])} * {n(op[2])}"
             elif k == ADD:
                 e = f"{n(op[1])} + {n(op[2])}"

@@ -529,10 +529,9 @@ __global__ __launch_bounds__(kDwWaves * kLanes) void split_dw_kernel(int64_t n_n
                                                                      const TS* __restrict__ X, const TS* __restrict__ dY,
                                                                      TS* __restrict__ dW) {
   __shared__ double red[kDwWaves][256];
-  const int jtiles = (k_out + 15) / 16, ktiles = (k_in + 15) / 16, nc = (l_max + 1) * (l_max + 1);
-  const unsigned tiles = static_cast<unsigned>(jtiles) * ktiles;
-  const int j0 = static_cast<int>(blockIdx.x % jtiles) * 16, k0 = static_cast<int>(blockIdx.x / jtiles % ktiles) * 16;
-  switch (l_max - static_cast<int>(blockIdx.x / tiles)) {
+  const int jtiles = (k_out + 15) / 16, nc = (l_max + 1) * (l_max + 1);
+  const int j0 = static_cast<int>(blockIdx.x % jtiles) * 16, k0 = static_cast<int>(blockIdx.x / jtiles) * 16;
+  switch (l_max - static_cast<int>(blockIdx.y)) {
     case 0: return split_dw_order<TS, 0>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
     case 1: return split_dw_order<TS, 1>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
     case 2: return split_dw_order<TS, 2>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
@@ -674,7 +673,7 @@ hipError_t dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, 
   const int64_t elems = static_cast<int64_t>(LMAX + 1) * cfg->k_in * cfg->k_out;
   if (!mfma_dw_ok(cfg)) {
     const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
-    hipLaunchKernelGGL((split_dw_kernel<T>), dim3(static_cast<unsigned>(tiles * (LMAX + 1))), dim3(kDwWaves * kLanes), 0,
+    hipLaunchKernelGGL((split_dw_kernel<T>), dim3(static_cast<unsigned>(tiles), LMAX + 1), dim3(kDwWaves * kLanes), 0,
                        stream, n, LMAX, cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY),
                        static_cast<T*>(dW));
     return hipGetLastError();

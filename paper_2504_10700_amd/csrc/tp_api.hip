@@ -271,8 +271,9 @@ sc_status tp_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_out, in
   char* dh_edge = workspace ? static_cast<char*>(workspace) +
                                   align_up(static_cast<size_t>(chblocks_of(plan)) * n_edges * plan->n_Y * elem_size(plan), 256)
                             : nullptr;
-  const tp::BwdArgs a{n_nodes_in, n_nodes_out, n_edges, Y,  h,  R,         sender,
-                      row_ptr,    send_ptr,    send_edge, dA, dY, dh, dR, workspace, dh_edge};
+  const bool one_block = chblocks_of(plan) == 1;   // its share of dY is the result: no sum, no copy (5 us)
+  const tp::BwdArgs a{n_nodes_in, n_nodes_out, n_edges, Y,  h,  R,  sender,
+                      row_ptr,    send_ptr,    send_edge, dA, dY, dh, dR, one_block ? dY : workspace, dh_edge};
   hipError_t e = hipSuccess;
   if (plan->specialised) {
     // generated kernels: one pass over the edges grouped by sender writes dR, the dY partials and dh itself
@@ -288,7 +289,7 @@ sc_status tp_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_out, in
         plan->ev_used[2] = true;
       }
     }
-    if (n_nodes_out > 0 && n_edges > 0) {
+    if (n_nodes_out > 0 && n_edges > 0 && !one_block) {
       e = tp::launch_dY_sum(plan, a, stream);
       if (e != hipSuccess) return fail_hip(e, "tp_backward: dY sum launch");
     }
@@ -302,7 +303,7 @@ sc_status tp_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_out, in
       (void)hipEventRecord(plan->ev[3], stream);
       plan->ev_used[1] = true;
     }
-    e = tp::launch_dY_sum(plan, a, stream);
+    if (!one_block) e = tp::launch_dY_sum(plan, a, stream);
     if (e != hipSuccess) return fail_hip(e, "tp_backward: dY sum launch");
   }
   if (n_nodes_in > 0) {
@@ -349,8 +350,9 @@ sc_status tp_double_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_
   char* dh_edge = workspace ? static_cast<char*>(workspace) +
                                   align_up(static_cast<size_t>(chblocks_of(plan)) * n_edges * plan->n_Y * elem_size(plan), 256)
                             : nullptr;
+  const bool one_block = chblocks_of(plan) == 1;   // its share of d2Y is the result: no sum, no copy
   const tp::DblArgs a{{n_nodes_in, n_nodes_out, n_edges, Y, h, R, sender, row_ptr, send_ptr, send_edge, dA, d2Y, d2h,
-                       d2R, workspace, dh_edge},
+                       d2R, one_block ? d2Y : workspace, dh_edge},
                       HY, Hh, HR, ddA};
   hipError_t e = hipSuccess;
   if (n_nodes_out > 0) {  // also with no edges: ddA is zeroed
@@ -362,7 +364,7 @@ sc_status tp_double_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_
       (void)hipEventRecord(plan->ev[7], stream);
       plan->ev_used[3] = true;
     }
-    e = tp::launch_dY_sum(plan, a.b, stream);
+    if (!one_block) e = tp::launch_dY_sum(plan, a.b, stream);
     if (e != hipSuccess) return fail_hip(e, "tp_double_backward: d2Y sum launch");
   }
   if (n_nodes_in > 0) {

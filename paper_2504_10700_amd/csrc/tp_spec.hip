@@ -6,13 +6,14 @@
 // sums the edges of a receiver):
 //   lane      = channel (64 consecutive channels per wave): a path's weights R[e][p][:] are one
 //               contiguous 256 B row per wave, the sender's features h[j][k][:] 16 B per lane
-//   wave      = forward: one (receiving atom, 64-channel block); it walks the edges the atom
-//               receives and keeps the atom's sum in registers.  Backward: one (sending atom,
-//               64-channel block); it walks the edges the atom sends, keeps the atom's h row and
-//               its dh sum in registers and gathers the receivers' dA rows; per edge it writes dR
-//               and the channel block's partial of dY.  Either way: no atomics, a fixed summation
-//               order, one store per atom.  The second-order pass walks by receiver (ddA in
-//               registers) and writes every edge's share of d2h, which a small kernel sums per sender.
+//   workgroup = forward: one (receiving atom, 64-channel block); each of its four waves walks every
+//               fourth edge the atom receives and keeps its sum in registers.  Backward: one (sending
+//               atom, 64-channel block); a wave walks every fourth edge the atom sends, keeps the
+//               atom's h row and its dh sum in registers and gathers the receivers' dA rows; per edge
+//               it writes dR and the channel block's partial of dY.  Either way the waves' sums meet in
+//               LDS: no atomics, a fixed summation order, one store per atom.  The second-order pass
+//               walks by receiver (ddA in registers) and writes every edge's share of d2h, which a
+//               small kernel sums per sender.
 //   Y[e][:]   is the same for all lanes: it is read with scalar loads and enters the
 //               arithmetic as scalar operands
 // The next edge's rows are requested before the current edge is evaluated (two register sets

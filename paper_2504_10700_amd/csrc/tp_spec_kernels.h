@@ -99,14 +99,47 @@ __device__ __forceinline__ void load_weights(const T* __restrict__ R, int e, int
   for (int p = 0; p < P; ++p) r[p] = base[static_cast<size_t>(p) * K];
 }
 
-// dR[e][p][ch] for all paths of edge e (every row is written as whole lines: streamed past the cache).
-template <bool kFull, typename TS, int P>
-__device__ __forceinline__ void store_weights(TS* __restrict__ dR, int e, int K, int ch, bool live, const TS (&dr)[P]) {
-  TS* out = dR + static_cast<size_t>(e) * P * K + ch;
-  if (!kFull && !live) return;
-#pragma unroll
-  for (int p = 0; p < P; ++p) __builtin_nontemporal_store(dr[p], out + static_cast<size_t>(p) * K);
-}
+// r[p] of a row in registers, in the type of the arithmetic.  The conversion happens where the path reads it: done
+// for the whole row up front it holds twice the registers of the row through all paths.
+template <typename T, typename TS, int P>
+struct PathRow {
+  const TS (&v)[P];
+  __device__ __forceinline__ T operator[](int p) const {
+    TS x = v[p];
+    if constexpr (!std::is_same<T, TS>::value) asm volatile("" : "+v"(x));
+    return static_cast<T>(x);
+  }
+};
+
+// dR[e][p][ch]: every path's value goes out when it is assigned (every row is written as whole lines: streamed
+// past the cache).
+template <bool kFull, typename T, typename TS>
+struct PathStore {
+  TS* out;     // dR + (e * P * K + ch)
+  size_t K;
+  bool live;
+  struct Ref {
+    const PathStore& s;
+    int p;
+    __device__ __forceinline__ void operator=(T v) const {
+      if (kFull || s.live) __builtin_nontemporal_store(static_cast<TS>(v), s.out + p * s.K);
+    }
+  };
+  __device__ __forceinline__ Ref operator[](int p) const { return Ref{*this, p}; }
+};
+
+// This channel's share of dY[e][a], into the wave's transpose stage (see lane_sum_store) when it is assigned.
+template <bool kFull, typename T>
+struct StageStore {
+  T* lane_column;
+  bool live;
+  struct Ref {
+    const StageStore& s;
+    int a;
+    __device__ __forceinline__ void operator=(T v) const { s.lane_column[a * kStageStride] = kFull || s.live ? v : T(0); }
+  };
+  __device__ __forceinline__ Ref operator[](int a) const { return Ref{*this, a}; }
+};
 
 // Empty statements that pin where values are computed.  Before the arithmetic of an edge, on values that do
 // not change over the edges of an atom: what follows from them (the row dA times every magnitude of
@@ -117,12 +150,6 @@ template <typename T, int N>
 __device__ __forceinline__ void pin_values(T (&v)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
-}
-
-template <typename T, int N>
-__device__ __forceinline__ void mask_dead_lanes(T (&v)[N], bool live) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = live ? v[i] : T(0);
 }
 
 // A wave-uniform value in the type of the arithmetic.  The conversion runs on the vector unit; the result
@@ -158,16 +185,18 @@ __device__ __forceinline__ int64_t xcd_contiguous_block() {
   return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
 }
 
-// Sum of dy[a] over the 64 lanes in a fixed order, written to out[a] (a < N): lane 4a+q adds the
-// sixteen lanes 16q..16q+15 of component a from an LDS transpose (stage: N * kStageStride
-// elements owned by this wave), then the four quarters are combined with two exchanges.
-template <typename T, typename TS, int N>
-__device__ __forceinline__ void lane_sum_store(T* stage, int lane, const T (&dy)[N], TS* __restrict__ out) {
-  static_assert(N <= 16, "one lane quartet per component");
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the previous edge's reads of the stage are done
+// Before the first write of an edge's values to the stage: the previous edge's reads of it are done.
+__device__ __forceinline__ void stage_is_free() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int a = 0; a < N; ++a) stage[a * kStageStride + lane] = dy[a];
+}
+
+// Sum over the 64 lanes of the N values that every lane has put into the stage (N * kStageStride elements owned by
+// this wave, value a of lane i at [a * kStageStride + i]), in a fixed order, written to out[a]: lane 4a+q adds the
+// sixteen lanes 16q..16q+15 of component a, then the four quarters are combined with two exchanges.
+template <int N, typename T, typename TS>
+__device__ __forceinline__ void lane_sum_store(const T* stage, int lane, TS* __restrict__ out) {
+  static_assert(N <= 16, "one lane quartet per component");
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const int a = lane >> 2, q = lane & 3;
@@ -179,6 +208,25 @@ __device__ __forceinline__ void lane_sum_store(T* stage, int lane, const T (&dy)
   s += __shfl_xor(s, 1);
   s += __shfl_xor(s, 2);
   if (q == 0 && a < N) out[a] = static_cast<TS>(s);
+}
+
+// The sums of a workgroup's four waves, added in wave order by wave 0; true for that wave.  scratch: kStride >=
+// N * kLanes values per wave, which nobody else reads or writes any more.
+template <int kStride, typename T, int N>
+__device__ __forceinline__ bool add_waves(int wave, int lane, T (&acc)[N], T* scratch) {
+  static_assert(N * kLanes <= kStride, "the sums of a wave fit its scratch");
+  stage_is_free();
+  if (wave > 0) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) scratch[wave * kStride + c * kLanes + lane] = acc[c];
+  }
+  __syncthreads();
+  if (wave > 0) return false;
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+    for (int c = 0; c < N; ++c) acc[c] += scratch[w * kStride + c * kLanes + lane];
+  return true;
 }
 
 // Store of a wave's rows (N elements per lane, lane rows N elements apart = one contiguous block
@@ -224,55 +272,62 @@ struct Channels {
   }
 };
 
+// A workgroup = one (atom, 64-channel block); its four waves take every fourth edge and add their sums at the end.
+// A wave per (atom, block), four atoms a workgroup, is slower at every size: it walks 20 edges in series where the
+// chip has waves to spare, waits for the atom with the most edges where it has not, and its waves share no rows.
+// Forward / backward / second-order pass, us, 128 channels, l_h = 1, wave -> workgroup per (atom, block): 250 atoms
+// 21 -> 9 / 53 -> 24 / 78 -> 37, 2000 40 -> 37 / 100 -> 79 / 230 -> 193, 10 000 243 -> 225 / 500 -> 492 / 859 -> 817; l_h = 2
+// (fp64 arithmetic), 3001 atoms 180 -> 165 / 368 -> 361 / 888 -> 817.
 template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) void forward_kernel(int K, int chblocks, int64_t n_units,
+__global__ __launch_bounds__(kThreads) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
                                                            const TS* __restrict__ Y, const TS* __restrict__ h,
                                                            const TS* __restrict__ R,
                                                            const EdgeList el, TS* __restrict__ A) {
-  __shared__ __attribute__((aligned(16))) TS out_stage[kWaves][kLanes * G::kNout];
+  __shared__ __attribute__((aligned(16))) T out_stage[kWaves][kLanes * G::kNout];
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = uniform(threadIdx.x / kLanes);
-  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
-  if (unit >= n_units) return;
+  const int64_t unit = unit0 + xcd_contiguous_block();
+  if (unit >= n_units) return;   // the whole workgroup: its waves meet at the end
   const size_t node = unit / chblocks;
   const int cb = static_cast<int>(unit % chblocks);
   const Channels<kFull> chan(K, cb, lane);
   const int ch = chan.ch;
-  const int e0 = uniform(el.first(node)), e1 = uniform(el.first(node + 1));
+  const int e0 = uniform(el.first(node)) + wave, e1 = uniform(el.first(node + 1));
   T acc[G::kNout];
 #pragma unroll
   for (int c = 0; c < G::kNout; ++c) acc[c] = T(0);
   if (e0 < e1) {
     TS r0[G::kP], r1[G::kP], h0[G::kNh], h1[G::kNh];
     auto add_edge = [&](int e, const TS (&h_row)[G::kNh], const TS (&r_row)[G::kP]) {
-      T y[G::kNY], hh[G::kNh], r[G::kP];
+      T y[G::kNY], hh[G::kNh];
       load_uniform<T, TS, G::kNY>(Y, e, y);
       widen(h_row, hh);
-      widen(r_row, r);
-      G::forward(y, hh, r, acc);
+      G::forward(y, hh, PathRow<T, TS, G::kP>{r_row}, acc);
     };
     load_weights<TS, G::kP>(R, e0, K, ch, r0);
     load_row<TS, G::kNh>(h + (el.snd(e0) * K + ch) * G::kNh, h0);
-    int jn = (e0 + 1 < e1) ? el.raw(e0 + 1) : 0;  // sender of the next edge, read one step ahead
-    for (int e = e0; e < e1; e += 2) {
+    int jn = (e0 + kWaves < e1) ? el.raw(e0 + kWaves) : 0;  // sender of the next edge, read one step ahead
+    for (int e = e0; e < e1; e += 2 * kWaves) {
       int jn2 = 0;
-      if (e + 1 < e1) {
-        load_weights<TS, G::kP>(R, e + 1, K, ch, r1);
+      if (e + kWaves < e1) {
+        load_weights<TS, G::kP>(R, e + kWaves, K, ch, r1);
         load_row<TS, G::kNh>(h + (el.node(jn) * K + ch) * G::kNh, h1);
-        if (e + 2 < e1) jn2 = el.raw(e + 2);
+        if (e + 2 * kWaves < e1) jn2 = el.raw(e + 2 * kWaves);
       }
       add_edge(e, h0, r0);
-      if (e + 1 < e1) {
-        if (e + 2 < e1) {
-          load_weights<TS, G::kP>(R, e + 2, K, ch, r0);
+      if (e + kWaves < e1) {
+        if (e + 2 * kWaves < e1) {
+          load_weights<TS, G::kP>(R, e + 2 * kWaves, K, ch, r0);
           load_row<TS, G::kNh>(h + (el.node(jn2) * K + ch) * G::kNh, h0);
-          if (e + 3 < e1) jn = el.raw(e + 3);
+          if (e + 3 * kWaves < e1) jn = el.raw(e + 3 * kWaves);
         }
-        add_edge(e + 1, h1, r1);
+        add_edge(e + kWaves, h1, r1);
       }
     }
   }
-  store_rows_coalesced<TS, T, G::kNout>(A + (node * K + cb * kLanes) * G::kNout, out_stage[wave], lane, acc, chan.live);
+  if (!add_waves<kLanes * G::kNout>(wave, lane, acc, out_stage[0])) return;
+  store_rows_coalesced<TS, T, G::kNout>(A + (node * K + cb * kLanes) * G::kNout, reinterpret_cast<TS*>(out_stage[wave]),
+                                        lane, acc, chan.live);
 }
 
 // receiver[e] for every edge, from the receivers' offsets: one thread per receiving atom.
@@ -284,16 +339,25 @@ __global__ __launch_bounds__(256) void edge_receiver_kernel(int64_t n_out_nodes,
   for (int e = e0; e < e1; ++e) receiver[e] = static_cast<int32_t>(node);
 }
 
-// The backward walks the edges grouped by SENDER: one wave = one (sending atom, 64-channel block).
-// It keeps the atom's h row and its dh sum in registers, walks the edges the atom sends
-// (send_edge order: the order of the sum) and gathers per edge the dA row of the receiver (rows of
+// Waves per SIMD that the backward kernels are held to.  With fp64 arithmetic and 10 to 17 paths the compiler takes a
+// little over the 256 registers that leave room for two, and a second wave hides more than the registers do: with the
+// conversions of r and the stores of dR and dY where their path has them (they waited for the end of the program
+// before), l_h = 2 at 3001 atoms and 128 channels, backward 499 -> 361 us, second-order pass 1500 atoms 478 -> 410; 64
+// channels, l = 2, l_h = 2, 2500 atoms 556 -> 193.
+template <typename T, typename TS, typename G>
+constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
+
+// The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, 64-channel block).
+// Its waves keep the atom's h row and their dh sums in registers, walk the edges the atom sends
+// (every fourth in send_edge order: with the order of the waves, the order of the sum) and gather
+// per edge the dA row of the receiver (rows of
 // one structure, met in the XCD's L2) next to the edge's own R rows; dR and the channel block's
 // partial of dY leave per edge, dh leaves once per atom: no per-edge shares
 // of dh go to memory and come back.  Atoms that send nothing get a zero row.  Every index is
 // clamped where it is used.
 template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
-    int K, int chblocks, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void backward_by_sender_kernel(
+    int K, int chblocks, int64_t unit0, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
     const TS* __restrict__ h, const TS* __restrict__ R, const int32_t* __restrict__ send_ptr,
     const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const TS* __restrict__ dA,
     TS* __restrict__ dR, TS* __restrict__ dY_partial, TS* __restrict__ dh) {
@@ -301,8 +365,8 @@ __global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = uniform(threadIdx.x / kLanes);
   T* stage = stage_all[wave];
-  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
-  if (unit >= n_units) return;
+  const int64_t unit = unit0 + xcd_contiguous_block();
+  if (unit >= n_units) return;   // the whole workgroup: its waves meet at the end
   const size_t node = unit / chblocks;
   const int cb = static_cast<int>(unit % chblocks);
   const Channels<kFull> chan(K, cb, lane);
@@ -313,7 +377,7 @@ __global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
     return e < 0 ? 0 : (e >= n_edges ? n_edges - 1 : e);
   };
   auto atom = [&](int r) { return static_cast<size_t>(r < 0 ? 0 : (r >= n_out_nodes ? n_out_nodes - 1 : r)); };
-  const int q0 = uniform(pos(send_ptr[node])), q1 = uniform(pos(send_ptr[node + 1]));
+  const int q0 = uniform(pos(send_ptr[node])) + wave, q1 = uniform(pos(send_ptr[node + 1]));
   T acc[G::kNh];
 #pragma unroll
   for (int c = 0; c < G::kNh; ++c) acc[c] = T(0);
@@ -324,57 +388,74 @@ __global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
       load_row<TS, G::kNh>(h + (node * K + ch) * G::kNh, h_row);
       widen(h_row, hh);
     }
-    TS r0[G::kP], r1[G::kP], g0[G::kNout], g1[G::kNout];
-    int ea = uniform(edge(q0)), eb = 0;
+    // one set of rows in registers where two do not fit (see the second-order kernel)
+    constexpr bool kOneSet = sizeof(TS) == 8 && G::kP >= 17;
+    TS r0[G::kP], g0[G::kNout];
+    int ea = uniform(edge(q0));
     load_weights<TS, G::kP>(R, ea, K, ch, r0);
     load_row<TS, G::kNout>(dA + (atom(uniform(receiver[ea])) * K + ch) * G::kNout, g0);
     // edge id and receiver of the edge after the current one, read one step ahead of its rows
-    int en = (q0 + 1 < q1) ? uniform(edge(q0 + 1)) : 0;
+    int en = (q0 + kWaves < q1) ? uniform(edge(q0 + kWaves)) : 0;
     int rn = uniform(receiver[en]);
 
     // One edge: arithmetic, dR row stores, dY summed over the 64 lanes in a fixed order, dh added up.
     auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
-      T y[G::kNY], r[G::kP], g[G::kNout], dy[G::kNY], dhe[G::kNh];
-      TS dr[G::kP];
+      T y[G::kNY], g[G::kNout], dhe[G::kNh];
+      const PathStore<kFull, T, TS> dr{dR + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
+      const StageStore<kFull, T> dy{stage + lane, lane < chan.live};
       load_uniform<T, TS, G::kNY>(Y, e, y);
-      widen(r_row, r);
       widen(g_row, g);
-      G::backward(y, hh, r, g, dr, dy, dhe);
+      stage_is_free();
+      G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, dhe);
 #pragma unroll
       for (int c = 0; c < G::kNh; ++c) acc[c] += dhe[c];
       pin_values(acc);
-      pin_values(dy);
-      pin_values(dr);
-      store_weights<kFull>(dR, e, K, ch, lane < chan.live, dr);
-      if constexpr (!kFull) mask_dead_lanes(dy, lane < chan.live);
-      lane_sum_store<T, TS, G::kNY>(stage, lane, dy, dY_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
+      lane_sum_store<G::kNY>(stage, lane, dY_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
     };
 
-    for (int q = q0; q < q1; q += 2) {
-      if (q + 1 < q1) {
-        eb = en;
-        load_weights<TS, G::kP>(R, eb, K, ch, r1);
-        load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g1);
-        if (q + 2 < q1) {
-          en = uniform(edge(q + 2));
-          rn = uniform(receiver[en]);
-        }
-      }
-      finish_edge(ea, r0, g0);
-      if (q + 1 < q1) {
-        if (q + 2 < q1) {
+    if constexpr (kOneSet) {
+      for (int q = q0; q < q1; q += kWaves) {
+        finish_edge(ea, r0, g0);
+        if (q + kWaves < q1) {
           ea = en;
           load_weights<TS, G::kP>(R, ea, K, ch, r0);
           load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
-          if (q + 3 < q1) {
-            en = uniform(edge(q + 3));
+          if (q + 2 * kWaves < q1) {
+            en = uniform(edge(q + 2 * kWaves));
             rn = uniform(receiver[en]);
           }
         }
-        finish_edge(eb, r1, g1);
+      }
+    } else {
+      TS r1[G::kP], g1[G::kNout];
+      int eb = 0;
+      for (int q = q0; q < q1; q += 2 * kWaves) {
+        if (q + kWaves < q1) {
+          eb = en;
+          load_weights<TS, G::kP>(R, eb, K, ch, r1);
+          load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g1);
+          if (q + 2 * kWaves < q1) {
+            en = uniform(edge(q + 2 * kWaves));
+            rn = uniform(receiver[en]);
+          }
+        }
+        finish_edge(ea, r0, g0);
+        if (q + kWaves < q1) {
+          if (q + 2 * kWaves < q1) {
+            ea = en;
+            load_weights<TS, G::kP>(R, ea, K, ch, r0);
+            load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
+            if (q + 3 * kWaves < q1) {
+              en = uniform(edge(q + 3 * kWaves));
+              rn = uniform(receiver[en]);
+            }
+          }
+          finish_edge(eb, r1, g1);
+        }
       }
     }
   }
+  if (!add_waves<G::kNY * kStageStride>(wave, lane, acc, stage_all[0])) return;
   if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(dh + (node * K + ch) * G::kNh, acc);
 }
 
@@ -382,8 +463,8 @@ __global__ __launch_bounds__(kThreads) void backward_by_sender_kernel(
 // sender) and HY (wave-uniform) as additional inputs; ddA of the receiver is summed in registers
 // and stored once, d2R / d2Y partial / d2h share leave per edge like dR / dY / dh.
 template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) void double_backward_kernel(
-    int K, int chblocks, int64_t n_units, int64_t n_edges, const TS* __restrict__ Y, const TS* __restrict__ h,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void double_backward_kernel(
+    int K, int chblocks, int64_t unit0, int64_t n_units, int64_t n_edges, const TS* __restrict__ Y, const TS* __restrict__ h,
     const TS* __restrict__ R, const EdgeList el,
     const TS* __restrict__ dA, const TS* __restrict__ HY, const TS* __restrict__ Hh, const TS* __restrict__ HR,
     TS* __restrict__ ddA, TS* __restrict__ d2R, TS* __restrict__ d2Y_partial, TS* __restrict__ d2h_edge) {
@@ -391,13 +472,13 @@ __global__ __launch_bounds__(kThreads) void double_backward_kernel(
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = uniform(threadIdx.x / kLanes);
   T* stage = stage_all[wave];
-  const int64_t unit = xcd_contiguous_block() * kWaves + wave;
-  if (unit >= n_units) return;
+  const int64_t unit = unit0 + xcd_contiguous_block();
+  if (unit >= n_units) return;   // the whole workgroup: its waves meet at the end
   const size_t node = unit / chblocks;
   const int cb = static_cast<int>(unit % chblocks);
   const Channels<kFull> chan(K, cb, lane);
   const int ch = chan.ch;
-  const int e0 = uniform(el.first(node)), e1 = uniform(el.first(node + 1));
+  const int e0 = uniform(el.first(node)) + wave, e1 = uniform(el.first(node + 1));
   T dda[G::kNout];
 #pragma unroll
   for (int c = 0; c < G::kNout; ++c) dda[c] = T(0);
@@ -408,9 +489,9 @@ __global__ __launch_bounds__(kThreads) void double_backward_kernel(
       load_row<TS, G::kNout>(dA + (node * K + ch) * G::kNout, g_row);
       widen(g_row, g);
     }
-    // The rows of two edges in registers where they fit; fp64 arithmetic with 23 paths leaves room for one set,
-    // whose next rows are requested when the arithmetic has consumed it (two sets: 6 KB of scratch per lane).
-    constexpr bool kOneSet = sizeof(T) == 8 && G::kP > 17;
+    // The rows of two edges in registers where they fit; fp64 arithmetic with ten or more paths leaves room for one set,
+    // whose next rows are requested when the arithmetic has consumed it (two sets: one wave per SIMD, or scratch).
+    constexpr bool kOneSet = sizeof(T) == 8 && G::kP >= 10;
     TS r0[G::kP], q0[G::kP], h0[G::kNh], x0[G::kNh];
     auto load_edge = [&](int e, size_t j, TS (&r)[G::kP], TS (&q)[G::kP], TS (&h_row)[G::kNh], TS (&x_row)[G::kNh]) {
       load_weights<TS, G::kP>(R, e, K, ch, r);
@@ -419,64 +500,69 @@ __global__ __launch_bounds__(kThreads) void double_backward_kernel(
       load_row<TS, G::kNh>(Hh + (j * K + ch) * G::kNh, x_row);
     };
     load_edge(e0, el.snd(e0), r0, q0, h0, x0);
-    int jn = (e0 + 1 < e1) ? el.raw(e0 + 1) : 0;
+    int jn = (e0 + kWaves < e1) ? el.raw(e0 + kWaves) : 0;
 
     auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&hr_row)[G::kP], const TS (&h_row)[G::kNh],
                            const TS (&hx_row)[G::kNh]) {
-      T y[G::kNY], hy[G::kNY], r[G::kP], hr[G::kP], hh[G::kNh], hx[G::kNh], d2y[G::kNY], d2h[G::kNh];
-      TS d2r[G::kP];
+      T y[G::kNY], hy[G::kNY], hh[G::kNh], hx[G::kNh], d2h[G::kNh];
+      const PathStore<kFull, T, TS> d2r{d2R + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
+      const StageStore<kFull, T> d2y{stage + lane, lane < chan.live};
       pin_values(g);
       load_uniform<T, TS, G::kNY>(Y, e, y);
       load_uniform<T, TS, G::kNY>(HY, e, hy);
-      widen(r_row, r);
-      widen(hr_row, hr);
       widen(h_row, hh);
       widen(hx_row, hx);
-      G::double_backward(y, hy, hh, hx, r, hr, g, dda, d2r, d2y, d2h);
+      stage_is_free();
+      G::double_backward(y, hy, hh, hx, PathRow<T, TS, G::kP>{r_row}, PathRow<T, TS, G::kP>{hr_row}, g, dda, d2r, d2y, d2h);
       pin_values(dda);
-      pin_values(d2y);
       pin_values(d2h);
-      pin_values(d2r);
-      store_weights<kFull>(d2R, e, K, ch, lane < chan.live, d2r);
       if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(d2h_edge + (static_cast<size_t>(e) * K + ch) * G::kNh, d2h);
-      if constexpr (!kFull) mask_dead_lanes(d2y, lane < chan.live);
-      lane_sum_store<T, TS, G::kNY>(stage, lane, d2y, d2Y_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
+      lane_sum_store<G::kNY>(stage, lane, d2Y_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
     };
 
     if constexpr (kOneSet) {
-      for (int e = e0; e < e1; ++e) {
+      for (int e = e0; e < e1; e += kWaves) {
         finish_edge(e, r0, q0, h0, x0);
-        if (e + 1 < e1) {
-          load_edge(e + 1, el.node(jn), r0, q0, h0, x0);
-          if (e + 2 < e1) jn = el.raw(e + 2);
+        if (e + kWaves < e1) {
+          load_edge(e + kWaves, el.node(jn), r0, q0, h0, x0);
+          if (e + 2 * kWaves < e1) jn = el.raw(e + 2 * kWaves);
         }
       }
     } else {
       TS r1[G::kP], q1[G::kP], h1[G::kNh], x1[G::kNh];
-      for (int e = e0; e < e1; e += 2) {
+      for (int e = e0; e < e1; e += 2 * kWaves) {
         int jn2 = 0;
-        if (e + 1 < e1) {
-          load_edge(e + 1, el.node(jn), r1, q1, h1, x1);
-          if (e + 2 < e1) jn2 = el.raw(e + 2);
+        if (e + kWaves < e1) {
+          load_edge(e + kWaves, el.node(jn), r1, q1, h1, x1);
+          if (e + 2 * kWaves < e1) jn2 = el.raw(e + 2 * kWaves);
         }
         finish_edge(e, r0, q0, h0, x0);
-        if (e + 1 < e1) {
-          if (e + 2 < e1) {
-            load_edge(e + 2, el.node(jn2), r0, q0, h0, x0);
-            if (e + 3 < e1) jn = el.raw(e + 3);
+        if (e + kWaves < e1) {
+          if (e + 2 * kWaves < e1) {
+            load_edge(e + 2 * kWaves, el.node(jn2), r0, q0, h0, x0);
+            if (e + 3 * kWaves < e1) jn = el.raw(e + 3 * kWaves);
           }
-          finish_edge(e + 1, r1, q1, h1, x1);
+          finish_edge(e + kWaves, r1, q1, h1, x1);
         }
       }
     }
   }
+  if (!add_waves<G::kNY * kStageStride>(wave, lane, dda, stage_all[0])) return;
   if (kFull || lane < chan.live) store_row<TS, T, G::kNout>(ddA + (node * K + ch) * G::kNout, dda);
 }
 
 
-unsigned grid_for(int64_t n_units) {
-  const int64_t blocks = (n_units + kWaves - 1) / kWaves;
-  return static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds);
+// Calls launch(first unit, grid) until all units (a workgroup each) are served: a grid holds less than 2^32 threads.
+template <typename F>
+hipError_t for_all_units(int64_t n_units, F&& launch) {
+  constexpr int64_t kMost = int64_t(1) << 23;
+  for (int64_t unit0 = 0; unit0 < n_units; unit0 += kMost) {
+    const int64_t blocks = n_units - unit0 < kMost ? n_units - unit0 : kMost;
+    launch(unit0, dim3(static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds)));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 EdgeList edge_list(const FwdArgs& a) {
@@ -492,10 +578,11 @@ struct Launch {
   static hipError_t forward(const tp_plan* plan, const FwdArgs& a, hipStream_t stream) {
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int64_t n_units = a.n_out_nodes * chblocks;
-    hipLaunchKernelGGL((forward_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K, chblocks,
-                       n_units, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R),
-                       edge_list(a), static_cast<TS*>(a.A));
-    return hipGetLastError();
+    return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
+      hipLaunchKernelGGL((forward_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0, n_units,
+                         static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R),
+                         edge_list(a), static_cast<TS*>(a.A));
+    });
   }
 
   static hipError_t backward(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
@@ -509,25 +596,27 @@ struct Launch {
     }
     const int64_t n_units = a.n_in * chblocks;
     // without receivers or edges no list is walked: every atom gets its zero row
-    hipLaunchKernelGGL((backward_by_sender_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K,
-                       chblocks, n_units, a.n_out_nodes, a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0,
-                       static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R), a.send_ptr,
-                       a.send_edge, receiver, static_cast<const TS*>(a.dA), static_cast<TS*>(a.dR),
-                       static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
-    return hipGetLastError();
+    const int n_edges = a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0;
+    return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
+      hipLaunchKernelGGL((backward_by_sender_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0,
+                         n_units, a.n_out_nodes, n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
+                         static_cast<const TS*>(a.R), a.send_ptr, a.send_edge, receiver, static_cast<const TS*>(a.dA),
+                         static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
+    });
   }
 
   static hipError_t double_backward(const tp_plan* plan, const DblArgs& d, hipStream_t stream) {
     const BwdArgs& a = d.b;
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int64_t n_units = a.n_out_nodes * chblocks;
-    hipLaunchKernelGGL((double_backward_kernel<T, TS, G, kFull>), dim3(grid_for(n_units)), dim3(kThreads), 0, stream, K,
-                       chblocks, n_units, a.n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
-                       static_cast<const TS*>(a.R), edge_list(a), static_cast<const TS*>(a.dA),
-                       static_cast<const TS*>(d.HY), static_cast<const TS*>(d.Hh), static_cast<const TS*>(d.HR),
-                       static_cast<TS*>(d.ddA), static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial),
-                       static_cast<TS*>(a.dh_edge));
-    return hipGetLastError();
+    return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
+      hipLaunchKernelGGL((double_backward_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0,
+                         n_units, a.n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
+                         static_cast<const TS*>(a.R), edge_list(a), static_cast<const TS*>(a.dA),
+                         static_cast<const TS*>(d.HY), static_cast<const TS*>(d.Hh), static_cast<const TS*>(d.HR),
+                         static_cast<TS*>(d.ddA), static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial),
+                         static_cast<TS*>(a.dh_edge));
+    });
   }
 };
 
