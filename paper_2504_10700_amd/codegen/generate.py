@@ -360,8 +360,12 @@ def emit_inc(tag: str, tab: Tables, basis, fold, fwd: Program, bwd: Program, dbl
     L.append("  template <typename T, typename TW>")
     L.append("  static __device__ __forceinline__ void fold(const TW* __restrict__ Wz, int K, T (&w)[kS]) {")
     for s, lst in enumerate(fold):
-        terms = " + ".join(f"T({repr(c)}) * T(Wz[{p} * K])" for p, c in lst)
-        L.append(f"    w[{s}] = {terms};")
+        # fused in a stated order: written with + the compiler chooses per kernel which product it rounds
+        terms = [f"T({repr(c)}), T(Wz[{p} * K])" for p, c in lst]
+        value = terms[0].replace(", ", " * ", 1)
+        for t in terms[1:]:
+            value = f"sc_fma({t}, {value})"
+        L.append(f"    w[{s}] = {value};")
     L.append("  }")
     L.append("")
     L.append("  template <typename T>")

@@ -508,9 +508,13 @@ sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, cons
                                       std::to_string(SC_NOALLOC_MAX_NODES) + "; use sc_forward with a workspace");
   const sc::LaunchShape shape = sc::launch_shape(plan, n_nodes);
   const size_t need = sc::carve_workspace(plan, n_nodes, shape, nullptr, true).bytes;
-  // without room for the folded table the waves fold their weights themselves (plans for which the call
-  // has no such limit)
-  const bool direct = plan->specialised && need > SC_NOALLOC_SCRATCH_BYTES && sc::spec_scratch_optional(plan);
+  // The waves fold their weights themselves where the scratch has no room for the folded table (plans for which
+  // the call has no such limit), and for small batches, where the launch that writes the table costs more than every
+  // node's own fold (86 rows of W from L2 for 0e+1o).  us per call, table / direct, 89 elements: fp32, 128 channels, 61
+  // nodes 0e+1o 7.6 / 4.8, 2000 9.6 / 7.5, 3000 11.2 / 10.9; 0e+1o+2e 2000 13.8 / 12.9, 3000 16.4 / 17.0; bfloat16 rows, 256
+  // channels (four blocks), 2000 12.7 / 11.6, 3000 14.8 / 15.1; fp64, 2000 20.4 / 17.9, 3000 23.3 / 24.2.
+  const bool small = n_nodes <= 2048 && n_nodes * shape.chblocks <= 8192;
+  const bool direct = plan->specialised && (need > SC_NOALLOC_SCRATCH_BYTES ? sc::spec_scratch_optional(plan) : small);
   if (need > SC_NOALLOC_SCRATCH_BYTES && !direct)
     return fail(SC_ERR_WORKSPACE, "sc_forward_noalloc: this plan needs " + std::to_string(need) + " bytes of scratch for " +
                                       std::to_string(n_nodes) + " nodes, more than SC_NOALLOC_SCRATCH_BYTES = " +

@@ -381,6 +381,10 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupAr
 #pragma unroll
       for (int q = 0; q < G::kP; ++q) wz[q] = src[static_cast<size_t>(q) * K];
       G::fold(wz, 1, w);
+      // finished values here, as where they come from the table: left open, the compiler fuses the fold's last
+      // multiplications into the arithmetic of the node, and the bits differ from the table's
+#pragma unroll
+      for (int i = 0; i < G::kS; ++i) asm volatile("" : "+v"(w[i]));
     } else {
       load_folded<T, G>(wf, e, chblocks, cb, lane, w);
     }
@@ -813,12 +817,14 @@ hipError_t prepare_launch(const sc_plan* plan, int64_t n, const int32_t* z, cons
 // they end) and, with the window order making the runs long whatever the share, the small bases
 // do best with five nodes per wave: 200k nodes, 29-row basis, forward 373 us with 20 nodes per
 // workgroup against 376 (16), 381 (24), 387 (28), 391 (32); the 49-row basis shows no preference
-// between 20 and 48 (268 us at 50k nodes, 256 channels) and keeps the rule above.
+// between 20 and 48 (268 us at 50k nodes, 256 channels) and keeps the rule above.  Batches that fit one round
+// with a node per wave take four: such calls last as long as one wave (fp64, 500 nodes 13.8 -> 11.2 us a call).
 inline int forward_tile_nodes(int64_t n, int chblocks, int64_t resident_wgs, int most) {
   auto cost = [&](int t) {
     const int64_t wgs = (n + t - 1) / t * chblocks;
     return static_cast<double>((wgs + resident_wgs - 1) / resident_wgs) * (t / kSpecWaves);
   };
+  if ((n + 3) / 4 * chblocks <= resident_wgs) return 4;
   if (most <= 32 && (n + 19) / 20 * chblocks >= 8 * resident_wgs) return 20;
   double best = cost(8);
   for (int t = 12; t <= most; t += 4) best = cost(t) < best ? cost(t) : best;
