@@ -10,8 +10,10 @@
 // input channels, columns = 16 output channels, one accumulator block per component (l,m); the
 // 2l+1 components of an order share their B operand.  With the layout X[atom][channel][lm]
 // the A operands of all components of one (atom, channel) are 64 contiguous bytes, and a lane
-// ends up with whole 64-byte rows of the result.  Kernels: mfma_forward_lds_kernel (fp32,
-// l_max = 3: X staged through LDS once per workgroup, B through a buffer descriptor, result
+// ends up with whole 64-byte rows of the result.  Kernels: mfma_forward_bf16_kernel (fp32, l_max = 3,
+// reduction channels a multiple of 32: every value as the sum of three bfloat16 values),
+// mfma_forward_lds_kernel (fp32, l_max = 3, others:
+// X staged through LDS once per workgroup, B through a buffer descriptor, result
 // rows stored as whole lines through an LDS transpose; the product lives in el_tile.h and is
 // shared with the fused linear + contraction kernel) and mfma_forward_kernel (every other
 // shape: operands straight from global memory through a four-deep register pipeline).
@@ -152,6 +154,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                         k_cols, X, W, Y, xs);
   for (int64_t unit = blockIdx.x; unit < u.n_full; unit += gridDim.x)
     forward_lds_unit<2>(n_nodes, unit / groups * 16, static_cast<int>(unit % groups) * 2, k_red, k_cols, X, W, Y, xs);
+}
+
+// The same product on the bfloat16 matrix cores (split_tile_product), k_red % 32 == 0: a workgroup of eight waves per
+// unit of 16 atoms x 128 columns, 128 registers, two workgroups per CU.  The matrix work is 3/8 of the fp32 instruction's;
+// what bounds it: requests of X, splitting, reads of LDS and products of a workgroup mostly follow one another (20 000
+// atoms, 128 -> 128 channels: 50 us without the requests and splits, 109 with both; the bytes need 60).
+// Forward, us, mfma_forward_lds_kernel -> this kernel: 128 -> 128 channels, 4000 atoms 31.6 -> 26.9, 10 000 66.5 -> 56.0,
+// 20 000 133 -> 102; 256 -> 256, 4000 atoms 110 -> 69; 256 -> 128, 3000 atoms 71 -> 41; 512 -> 128, 4000 atoms 114 -> 77.  With
+// one workgroup of the same kind per CU that walks the units with two sets of planes: 59 us at 10 000 atoms; with four
+// waves of twice the columns each: 61 us.  Error against 64 bits (2-norm, relative), 128 / 256 / 512 channels summed: 1.5e-7,
+// 2.3e-7, 3.4e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7, 4.1e-7 (32 products per rounding of the sum, not four).
+__global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void mfma_forward_bf16_kernel(
+    int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W,
+    float* __restrict__ Y) {
+  __shared__ __attribute__((aligned(16))) unsigned planes[3 * kSplitPlane];
+  static_assert(kSplitWaves * kStoreStageFloats <= 3 * kSplitPlane, "the store stages reuse the planes");
+  const int lane = threadIdx.x & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int groups = k_cols / 128;
+  const int64_t n0 = blockIdx.x / groups * int64_t(16);
+  const int jc[1] = {static_cast<int>(blockIdx.x % groups) * 128 + wave * 16 + (lane & 15)};
+  Mma<float>::acc_t acc[16][1];
+  const bool finite = split_tile_product(n_nodes, n0, jc[0], k_red, k_cols, X, W, planes, acc);
+  // (also the barrier after which the planes are free)
+  if (__syncthreads_or(!finite)) plain_tile_product(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
+  store_tile_coalesced<1>(Y, n_nodes, n0, k_cols, jc, acc, reinterpret_cast<float*>(planes) + wave * kStoreStageFloats);
 }
 
 // Partial dW of a range of atoms: part[range][l][k][j] = sum_{n in range} sum_{m in l} X[n][k][c] dY[n][j][c].
@@ -638,6 +665,11 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
       if (sizeof(T) == 4 && LMAX == 3 && k_cols % 128 == 0 && static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26)) {
         if constexpr (sizeof(T) == 4 && LMAX == 3) {   // the LDS-staged variant: two workgroups fit a CU
           const int64_t units = tiles * (k_cols / 128);
+          if (k_red % kSplitChunk == 0) {
+            hipLaunchKernelGGL(mfma_forward_bf16_kernel, dim3(static_cast<unsigned>(units)), dim3(kSplitThreads), 0, stream, n,
+                               k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
+            return hipGetLastError();
+          }
           const unsigned grid2 = static_cast<unsigned>(std::min<int64_t>(units, 2 * compute_units()));
           hipLaunchKernelGGL(mfma_forward_lds_kernel, dim3(grid2), dim3(kThreads), 0, stream, n, k_red, k_cols,
                              static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));

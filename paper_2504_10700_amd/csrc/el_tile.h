@@ -190,6 +190,160 @@ __device__ __forceinline__ void lds_tile_product(int64_t n_nodes, int64_t n0, in
   }
 }
 
+// ---- the same product on the bfloat16 matrix cores
+//
+// An fp32 value is the exact sum of three bfloat16 values (rounded to nearest: h, then what is left: m, then l; 8 + 8 + 8
+// bits), |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.  The products h h, h m, m h, m m, h l and l h are summed in fp32 by the matrix
+// core, smallest first; the three that are left out are below 2^-26 of |x w|, under the rounding of an fp32 product.
+typedef __bf16 Bf8 __attribute__((ext_vector_type(8)));
+typedef unsigned U4 __attribute__((ext_vector_type(4)));
+
+struct SplitPair {   // two values, a 16-bit half each
+  unsigned h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  typedef float F2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 B2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(F2{x, y}, B2));
+}
+__device__ __forceinline__ float low_half(unsigned u) { return __builtin_bit_cast(float, u << 16); }
+__device__ __forceinline__ float high_half(unsigned u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
+__device__ __forceinline__ SplitPair split_pair(float x, float y) {
+  SplitPair s;
+  s.h = pack_bf16(x, y);
+  const float rx = x - low_half(s.h), ry = y - high_half(s.h);
+  s.m = pack_bf16(rx, ry);
+  s.l = pack_bf16(rx - low_half(s.m), ry - high_half(s.m));
+  return s;
+}
+
+// The accumulators of rows n0..n0+15 and of the wave's 16 columns (this lane's: jc).  k_red % 32 == 0.  The workgroup
+// (eight waves) splits X in chunks of 32 reduction channels into LDS (three planes of [component][atom][32], which are
+// the A operands as the instruction reads them; the next chunk's rows are requested a chunk ahead); a wave splits its
+// own columns of W order by order, requested an order ahead.  Returns whether the lane's results are finite: an infinity
+// or a value that h rounds to one (from 0x7f7f8000 on) leaves an infinity or a NaN in every result it enters, where
+// the product in fp32 may have another value.
+constexpr int kSplitWaves = 8;
+constexpr int kSplitThreads = kSplitWaves * kLanes;
+constexpr int kSplitChunk = 32;
+constexpr int kSplitPlane = 16 * 16 * kSplitChunk / 2;    // 32-bit words of a plane: two channels each
+
+__device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
+                                                    const float* __restrict__ X, const float* __restrict__ W,
+                                                    unsigned* planes /* 3 * kSplitPlane words */,
+                                                    typename Mma<float>::acc_t (&acc)[16][1]) {
+  constexpr int NC = 16, L = 4;
+  typedef Mma<float>::acc_t acc_t;
+  typedef float V4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int q = lane / 16, i16 = lane & 15;
+  const int chunks = k_red / kSplitChunk;
+  // splitting role of this thread: half of the components of one atom of the tile and two reduction channels
+  const int half = threadIdx.x / 256, sa = threadIdx.x / 16 % 16, sk = threadIdx.x % 16;
+  int64_t ns = n0 + sa;
+  if (ns >= n_nodes) ns = n_nodes - 1;       // rows past the end split a valid atom and are not stored
+  const float* xsrc = X + (static_cast<size_t>(ns) * k_red + 2 * sk) * NC + half * 8;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c][0] = acc_t{0, 0, 0, 0};
+
+  V4 xr[2][2];
+  auto gload = [&](int chunk) {
+    const float* p = xsrc + static_cast<size_t>(chunk) * kSplitChunk * NC;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xr[i / 2][i % 2] = *reinterpret_cast<const V4*>(p + i / 2 * NC + i % 2 * 4);
+  };
+  auto split_x = [&]() {
+    unsigned* dst = planes + half * 8 * 256 + sa * 16 + sk;
+#pragma unroll
+    for (int c = 0; c < NC / 2; ++c) {
+      const float x = xr[0][c / 4][c % 4], y = xr[1][c / 4][c % 4];
+      const SplitPair s = split_pair(x, y);
+      dst[c * 256] = s.h;
+      dst[c * 256 + kSplitPlane] = s.m;
+      dst[c * 256 + 2 * kSplitPlane] = s.l;
+    }
+  };
+  // this lane's column of W: eight channels 8 q .. 8 q + 7 of a chunk, as in lds_tile_product through a descriptor
+  const unsigned boff = static_cast<unsigned>(8 * q * k_cols + jc) * 4u;
+  const unsigned row_bytes = static_cast<unsigned>(k_cols) * 4u;
+  const unsigned lstride = static_cast<unsigned>(k_red) * row_bytes;
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, static_cast<int>(L * lstride), 0x00020000);
+  float wr[8];
+  auto bload = [&](int chunk, int l) {
+    const unsigned so = static_cast<unsigned>(l) * lstride + static_cast<unsigned>(chunk * kSplitChunk) * row_bytes;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      wr[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrs, static_cast<int>(boff),
+                                                                             static_cast<int>(so + i * row_bytes), 0));
+  };
+  gload(0);
+  bload(0, L - 1);
+  // The waves that multiply go first: the two workgroups of a CU drift apart, and one's products cover the other's
+  // requests and splitting (20 000 atoms: 112 -> 102 us).
+  for (int ch = 0; ch < chunks; ++ch) {
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();                         // the reads of the previous chunk are done
+    split_x();
+    // (no condition on the request: at its join the compiler would wait for every outstanding load)
+    gload(ch + 1 < chunks ? ch + 1 : ch);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+#pragma unroll
+    for (int l = L - 1; l >= 0; --l) {
+      U4 b[3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const SplitPair s = split_pair(wr[2 * i], wr[2 * i + 1]);
+        b[0][i] = s.h;
+        b[1][i] = s.m;
+        b[2][i] = s.l;
+      }
+      const int next = l > 0 ? ch : (ch + 1 < chunks ? ch + 1 : ch);   // past the end: a valid chunk again
+      bload(next, l > 0 ? l - 1 : L - 1);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int c = l * l; c < (l + 1) * (l + 1); ++c) {
+        U4 a[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          a[p] = *reinterpret_cast<const U4*>(planes + p * kSplitPlane + c * 256 + i16 * 16 + q * 4);
+        constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};   // smallest products first
+#pragma unroll
+        for (int p = 0; p < 6; ++p)
+          acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf8, a[kA[p]]),
+                                                              __builtin_bit_cast(Bf8, b[kB[p]]), acc[c][0], 0, 0, 0);
+      }
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+  bool finite = true;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) finite &= __builtin_isfinite(acc[c][0][r]);
+  return finite;
+}
+
+// The same accumulators on the fp32 matrix cores, operands straight from memory: tiles that the split does not serve.
+__device__ __forceinline__ void plain_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
+                                                   const float* __restrict__ X, const float* __restrict__ W,
+                                                   typename Mma<float>::acc_t (&acc)[16][1]) {
+  constexpr int NC = 16, L = 4;
+  const int lane = threadIdx.x & (kLanes - 1), q = lane / 16, i16 = lane & 15;
+  const int64_t na = n0 + i16 < n_nodes ? n0 + i16 : n_nodes - 1;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c][0] = Mma<float>::acc_t{0, 0, 0, 0};
+  for (int k = q; k < k_red; k += 4) {
+    float a[NC], b[L];
+    load_row<float, NC>(X + (static_cast<size_t>(na) * k_red + k) * NC, a);
+#pragma unroll
+    for (int l = 0; l < L; ++l) b[l] = W[(static_cast<size_t>(l) * k_red + k) * k_cols + jc];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c][0] = Mma<float>::mma(a[c], b[order_of(c)], acc[c][0]);
+  }
+}
+
 // Store of a wave's result tile Y[n0 + 4*(lane/16) + r][jc[t]][0..15].  A lane holds whole 64-byte
 // rows; stored directly, every instruction would write a quarter of each row (16-byte pieces 64
 // bytes apart: partial lines, four times the write requests).  Per (t, r) the 16 rows of a

@@ -82,6 +82,37 @@ def test_products_cut_along_the_reduction(el, N, k_in, k_out, l_max, dtype):
     run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N)
 
 
+# The products on the bfloat16 matrix cores: one chunk of the reduction and several, a ragged last row tile, two
+# groups of columns; and the kernel of reductions that are no multiple of 32.
+@pytest.mark.parametrize("N,k_in,k_out", [(2065, 32, 128), (2100, 96, 256), (2049, 160, 128), (2070, 48, 128)])
+def test_products_of_split_values(el, N, k_in, k_out):
+    run_case(el, N, k_in, k_out, 3, "f32", 8800 + k_in)
+
+
+def test_values_that_do_not_split(el):
+    """Infinities, NaN and values that round to a bfloat16 infinity: the results of the tiles they are in are those of the
+    products in fp32, the others are untouched."""
+    import torch
+    N, K = 2080, 128
+    X, W, _ = workloads.make_linear_inputs(N, K, K, 3, 8900)
+    W *= 1e-3
+    X[5, 7, 2], X[700, 3, 0], X[1300, 100, 12], X[2079, 127, 15] = np.inf, 3.4e38, np.nan, -3.4e38
+    Xd, Wd = (torch.tensor(x, dtype=torch.float32, device="cuda:0") for x in (X, W))
+    Y = torch.empty((N, K, 16), device="cuda:0")
+    el.el_forward(el.make_config(K, K, 3), N, Xd, Wd, Y)
+    torch.cuda.synchronize()
+    got = Y.double().cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = oel.forward(Xd.double().cpu().numpy(), Wd.double().cpu().numpy())
+    assert np.isposinf(ref).any() and np.isneginf(ref).any() and np.isnan(ref).any()
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    inf = np.isinf(ref)
+    assert (got[inf] == ref[inf]).all()
+    for where in (np.isfinite(ref) & (np.abs(ref) > 1e25), np.isfinite(ref) & (np.abs(ref) < 1e25)):
+        err = np.abs(got[where] - ref[where]).max() / np.sqrt((ref[where] ** 2).mean())
+        assert err <= 1e-5, err
+
+
 def test_degenerate_sizes_and_errors(el):
     import torch
     run_case(el, 1, 128, 128, 3, "f32", 8501)
