@@ -447,11 +447,12 @@ static sc_status check_layout_flag(const char* fn, const sc_plan* plan, uint32_t
 }
 
 // Checks of the tensor arguments and the launches of the forward pass, shared by sc_forward and
-// sc_forward_noalloc; the plan's device is current.  direct (generated kernels, no grouping wanted):
-// one launch whose waves fold their weights themselves; ws is not used.
+// sc_forward_noalloc; the plan's device is current.  direct (generated kernels):
+// one launch whose waves fold their weights themselves; without a grouping ws is not used.  fold_table: that launch also
+// writes the folded table and, if wanted, the grouping, for the backward of the step.
 static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z,
                                   const void* W, void* B, const sc::Workspace& ws, const sc::LaunchShape& shape,
-                                  uint32_t flags, bool direct, hipStream_t stream) {
+                                  uint32_t flags, bool direct, bool fold_table, hipStream_t stream) {
   if (!A || !z || !W || !B) return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": NULL tensor argument");
   if (misaligned(A, 16) || misaligned(W, 16) || misaligned(B, 16) || misaligned(z, 4))
     return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": tensor pointer not 16-byte aligned");
@@ -476,7 +477,7 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
   if (plan->profile) (void)hipEventRecord(plan->ev[0], stream);
   e = plan->specialised ? sc::launch_spec_forward(plan, n_nodes, A, z, W, B, ws, shape,
                                                   !group ? 0 : (flags & SC_Z_GROUPED) ? 2 : 1, window_order,
-                                                  (flags & SC_COMPONENT_MAJOR) != 0, direct, stream)
+                                                  (flags & SC_COMPONENT_MAJOR) != 0, direct, fold_table, stream)
                         : sc::launch_generic_forward(plan, n_nodes, A, W, B, ws, shape, stream);
   if (e != hipSuccess) return fail_hip(e, (std::string(fn) + ": kernel launch").c_str());
   if (plan->profile) {
@@ -495,7 +496,11 @@ sc_status sc_forward(sc_plan* plan, int64_t n_nodes, const void* A, const int32_
   if (n_nodes == 0) return SC_OK;
   DeviceGuard guard(plan->cfg.device);
   if (!guard.ok) return fail(SC_ERR_HIP, "sc_forward: cannot make the plan's device current");
-  return forward_launches("sc_forward", plan, n_nodes, A, z, W, B, ws, shape, flags, false, static_cast<hipStream_t>(hip_stream));
+  // small batches: one launch that folds, groups and evaluates
+  const bool direct = plan->specialised && !(flags & (SC_REUSE_GROUPING | SC_REUSE_WEIGHTS | SC_COMPONENT_MAJOR)) &&
+                      !(plan->cfg.flags & SC_PLAN_WINDOW_ORDER) && sc::spec_direct_pays(plan, n_nodes, shape, true);
+  return forward_launches("sc_forward", plan, n_nodes, A, z, W, B, ws, shape, flags, direct, true,
+                          static_cast<hipStream_t>(hip_stream));
 }
 
 sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B,
@@ -509,12 +514,9 @@ sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, cons
   const sc::LaunchShape shape = sc::launch_shape(plan, n_nodes);
   const size_t need = sc::carve_workspace(plan, n_nodes, shape, nullptr, true).bytes;
   // The waves fold their weights themselves where the scratch has no room for the folded table (plans for which
-  // the call has no such limit), and for small batches, where the launch that writes the table costs more than every
-  // node's own fold (86 rows of W from L2 for 0e+1o).  us per call, table / direct, 89 elements: fp32, 128 channels, 61
-  // nodes 0e+1o 7.6 / 4.8, 2000 9.6 / 7.5, 3000 11.2 / 10.9; 0e+1o+2e 2000 13.8 / 12.9, 3000 16.4 / 17.0; bfloat16 rows, 256
-  // channels (four blocks), 2000 12.7 / 11.6, 3000 14.8 / 15.1; fp64, 2000 20.4 / 17.9, 3000 23.3 / 24.2.
-  const bool small = n_nodes <= 2048 && n_nodes * shape.chblocks <= 8192;
-  const bool direct = plan->specialised && (need > SC_NOALLOC_SCRATCH_BYTES ? sc::spec_scratch_optional(plan) : small);
+  // the call has no such limit), and for small batches.
+  const bool direct = plan->specialised && (need > SC_NOALLOC_SCRATCH_BYTES ? sc::spec_scratch_optional(plan)
+                                                                            : sc::spec_direct_pays(plan, n_nodes, shape, false));
   if (need > SC_NOALLOC_SCRATCH_BYTES && !direct)
     return fail(SC_ERR_WORKSPACE, "sc_forward_noalloc: this plan needs " + std::to_string(need) + " bytes of scratch for " +
                                       std::to_string(n_nodes) + " nodes, more than SC_NOALLOC_SCRATCH_BYTES = " +
@@ -533,7 +535,7 @@ sc_status sc_forward_noalloc(sc_plan* plan, int64_t n_nodes, const void* A, cons
   // and there is no backward pass to leave one for.
   const sc::Workspace ws = sc::carve_workspace(plan, n_nodes, shape, base, true);
   return forward_launches("sc_forward_noalloc", plan, n_nodes, A, z, W, B, ws, shape,
-                          plan->specialised ? SC_REUSE_GROUPING : 0u, direct, static_cast<hipStream_t>(hip_stream));
+                          plan->specialised ? SC_REUSE_GROUPING : 0u, direct, false, static_cast<hipStream_t>(hip_stream));
 }
 
 sc_status sc_backward(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, const void* dB,

@@ -3,6 +3,8 @@
 //
 // The same stable counting sort as sc_group.hip, cut in two so that no launch of its own is
 // needed and no single workgroup sits on the critical path:
+// (Small batches, split_count_all: there is no count role, the scatter and table workgroups count the batch for themselves.)
+//
 //   count role    (hosted by the launch that prepares the folded weights) every wave counts the
 //                 elements of its contiguous slice of z and writes one row of the count
 //                 matrix counts[wave][element];
@@ -45,7 +47,7 @@ struct SplitGroupArgs {
 };
 
 // dynamic LDS (bytes) a hosting kernel must provide for the count, scatter and table roles
-inline size_t split_group_lds_bytes(int Z) { return sizeof(int32_t) * (static_cast<size_t>(kGroupWavesPerWG + 1) * Z + 4 + 256); }
+__host__ __device__ inline size_t split_group_lds_bytes(int Z) { return sizeof(int32_t) * (static_cast<size_t>(kGroupWavesPerWG + 1) * Z + 4 + 256); }
 
 // Stable scatter of one 64-node chunk: lane holds element e (valid or not); cursor[e] is this
 // wave's next free position of element e (LDS).  The lanes that hold the same element are found
@@ -240,6 +242,28 @@ __device__ __forceinline__ int split_column(const SplitGroupArgs& g, int e, int 
     }
   }
   return run;
+}
+
+// The whole count matrix, into the workgroup's LDS (W * Z ints): for batches so small that every scatter and table
+// workgroup counts for itself and no launch has to come before theirs.  Ends with a barrier.
+__device__ __forceinline__ void split_count_all(const SplitGroupArgs& g, int32_t* counts) {
+  constexpr int kBatch = 8;
+  for (int i = threadIdx.x; i < g.W * g.Z; i += kSplitThreads) counts[i] = 0;
+  __syncthreads();
+  for (int i0 = 0; i0 < g.n; i0 += kBatch * kSplitThreads) {
+    int zs[kBatch];
+#pragma unroll
+    for (int c = 0; c < kBatch; ++c) {
+      const int i = i0 + c * kSplitThreads + threadIdx.x;
+      zs[c] = i < g.n ? g.z[i] : -1;
+    }
+#pragma unroll
+    for (int c = 0; c < kBatch; ++c) {
+      const int w = (i0 + c * kSplitThreads + static_cast<int>(threadIdx.x)) / g.nodes_per_wave;
+      if (zs[c] >= 0 && zs[c] < g.Z) atomicAdd(&counts[w * g.Z + zs[c]], 1);
+    }
+  }
+  __syncthreads();
 }
 
 // Workgroup `wg` scatters the slices of its four waves.  lds: 5 * Z ints.

@@ -14,7 +14,7 @@ struct SpecEntry {
   hipError_t (*prepare)(const sc_plan*, int64_t n, const int32_t* z, const void* W, const Workspace&, const LaunchShape&,
                         bool count, bool fold, bool window_order, hipStream_t);
   hipError_t (*forward)(const sc_plan*, int64_t n, const void* A, const int32_t* z, const void* W, void* B, const Workspace&,
-                        const LaunchShape&, int group, bool window_order, bool component_major, bool direct, hipStream_t);
+                        const LaunchShape&, int group, bool window_order, bool component_major, bool direct, bool fold_table, hipStream_t);
   hipError_t (*backward)(const sc_plan*, int64_t n, const void* A, const void* dB, void* dA, const Workspace&,
                          const LaunchShape&, bool component_major, hipStream_t);
   hipError_t (*double_backward)(const sc_plan*, const void* A, const void* W, const void* dB, const void* H, void* ddB,
@@ -43,6 +43,14 @@ bool spec_scratch_optional(const sc_plan* plan);
 // Bytes of a folded weight and of a per-tile dW value (the plan must have a generated kernel).
 size_t spec_value_bytes(const sc_plan* plan);
 
+// Bytes of the count matrix that the grouping roles of a direct forward keep in LDS.
+inline size_t split_counts_bytes(const sc_plan* plan, const LaunchShape& shape) {
+  return sizeof(int32_t) * static_cast<size_t>(shape.split_waves) * plan->cfg.num_elements;
+}
+
+// Does a forward without a prepare launch (direct) cost less than one with it?  groups: its launch also groups.
+bool spec_direct_pays(const sc_plan* plan, int64_t n, const LaunchShape& shape, bool groups);
+
 // Bytes of the folded-weight table wf[element][channel][stride] of a generated kernel.
 size_t spec_folded_bytes(const sc_plan* plan);
 
@@ -58,13 +66,14 @@ hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z,
                                const LaunchShape& shape, bool table_only, hipStream_t stream);
 // Forward over the nodes in natural order from ws.wfold, or (direct) with weights that every wave
 // folds from W by itself; group: the second half of the grouping
-// rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only).
+// rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only); with direct its
+// roles need no prepare launch, and fold_table: the launch also writes ws.wfold.
 // component_major: the per-node tensors are laid out [node][component][channel]
 // (SC_COMPONENT_MAJOR; plans whose rows are stored in the arithmetic type only).
 // window_order: the kernel follows ws.wnode / ws.wkey, written by the prepare launch of the same call.
 hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                                const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
-                               bool component_major, bool direct, hipStream_t stream);
+                               bool component_major, bool direct, bool fold_table, hipStream_t stream);
 // The grouped passes read ws.perm (null: the batch is already grouped, identity) and ws.tiles; the backward reads ws.wfold, the second-order pass folds W itself.
 hipError_t launch_spec_backward(const sc_plan* plan, int64_t n, const void* A, const void* dB, void* dA,
                                 const Workspace& ws, const LaunchShape& shape, bool component_major,

@@ -87,6 +87,21 @@ size_t spec_folded_bytes(const sc_plan* plan) {
          spec_value_bytes(plan);
 }
 
+// What it costs: every wave reads the external weights of its nodes' elements (P rows per node and channel block, from
+// L2) instead of folded rows; what it saves: a launch and its fold of all elements.  With 89 elements, us per call:
+//  - evaluation alone (prepare + forward / direct): fp32, 128 channels, 0e+1o (P = 86) 61 nodes 7.6 / 4.8, 2000 9.6 / 7.5, 4000
+//    13.6 / 13.6; 0e+1o+2e (159) 2000 13.8 / 12.9, 3000 16.4 / 17.0; 0e (28) 10 000 21.0 / 16.6; fp64 0e+1o 2000 20.4 / 17.9, 3000
+//    23.3 / 24.2; bfloat16 rows, 256 channels, 2000 12.7 / 11.6, 3000 14.8 / 15.1.  Limit: 2.8e6 bytes of W per lane.
+//  - with the grouping, whose workgroups then count the whole batch each (forward + backward): 0e+1o 40 nodes 20.0 / 17.8, 1400
+//    26.8 / 23.6, 2731 30.9 / 30.9; 0e+1o+2e 700 34.7 / 31.1, 1400 37.3 / 37.2, 2000 40.6 / 42.3; fp64 0e+1o 700 32.6 / 29.9, 2000
+//    52.9 / 55.5; l_max = 2 fp64 (41) 1400 26.2 / 22.7, 2731 31.7 / 31.6; four outputs, 64 channels (231) 700 34.2 / 29.5,
+//    2000 43.5 / 47.8.  Limits: 1.4e6 bytes, 2048 nodes, and a count matrix that fits beside the roles' LDS.
+bool spec_direct_pays(const sc_plan* plan, int64_t n, const LaunchShape& shape, bool groups) {
+  const double bytes = static_cast<double>(n) * shape.chblocks * entry_of(plan->specialised)->P * (plan->cfg.dtype == SC_F64 ? 8 : 4);
+  if (groups) return n <= 2048 && bytes <= 1.4e6 && split_counts_bytes(plan, shape) <= 16 * 1024;
+  return n <= 10000 && bytes <= 2.8e6;
+}
+
 hipError_t launch_spec_prepare(const sc_plan* plan, int64_t n, const int32_t* z, const void* W, const Workspace& ws,
                                const LaunchShape& shape, bool count, bool fold, bool window_order, hipStream_t stream) {
   return entry_of(plan->specialised)->prepare(plan, n, z, W, ws, shape, count, fold, window_order, stream);
@@ -102,9 +117,9 @@ hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z,
 
 hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                                const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
-                               bool component_major, bool direct, hipStream_t stream) {
+                               bool component_major, bool direct, bool fold_table, hipStream_t stream) {
   return entry_of(plan->specialised)->forward(plan, n, A, z, W, B, ws, shape, group, window_order && ws.wnode && ws.wkey,
-                                              component_major, direct, stream);
+                                              component_major, direct, fold_table, stream);
 }
 
 hipError_t launch_spec_backward(const sc_plan* plan, int64_t n, const void* A, const void* dB, void* dA,

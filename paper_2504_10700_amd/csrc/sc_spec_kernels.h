@@ -240,24 +240,11 @@ __device__ __forceinline__ void load_folded(const T* __restrict__ wf, int z, int
   for (int s = 0; s < G::kS; ++s) w[s] = src[s * kLanes];
 }
 
-// Launch 1.  Workgroups [0, window_wgs): window role (order of the forward pass); the next
-// count_wgs: count role of the grouping.  The others: one wave per (element, 64 channels) folds
-// W[element, :, channel] into wf.
+// Workgroup `wg` of the fold role: one wave per (element, 64 channels) folds W[element, :, channel] into wf.
 template <typename T, typename G, typename TW>
-__global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(SplitGroupArgs ga, int count_wgs, int window_wgs, int K,
-                                                                    int chblocks, int n_pairs,
-                                                                    const TW* __restrict__ W, T* __restrict__ wf) {
-  extern __shared__ unsigned char lds_raw[];
-  if (static_cast<int>(blockIdx.x) < window_wgs) {   // the longest role first
-    split_window_role(ga, blockIdx.x, reinterpret_cast<int32_t*>(lds_raw));
-    return;
-  }
-  if (static_cast<int>(blockIdx.x) < window_wgs + count_wgs) {
-    split_count_role(ga, blockIdx.x - window_wgs, reinterpret_cast<int32_t*>(lds_raw));
-    return;
-  }
+__device__ __forceinline__ void fold_role(int wg, int K, int chblocks, int n_pairs, const TW* __restrict__ W, T* __restrict__ wf) {
   const int lane = threadIdx.x & (kLanes - 1);
-  const int pair = (static_cast<int>(blockIdx.x) - window_wgs - count_wgs) * kSpecWaves + wave_of_thread();
+  const int pair = wg * kSpecWaves + wave_of_thread();
   if (pair >= n_pairs) return;
   const int z = pair / chblocks, cb = pair % chblocks;
   const int live = K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes;
@@ -275,6 +262,24 @@ __global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(SplitGroupAr
   for (int s = 0; s < G::kS; ++s) dst[s * kLanes] = w[s];
 }
 
+// Launch 1.  Workgroups [0, window_wgs): window role (order of the forward pass); the next
+// count_wgs: count role of the grouping.  The others: fold role.
+template <typename T, typename G, typename TW>
+__global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(SplitGroupArgs ga, int count_wgs, int window_wgs, int K,
+                                                                    int chblocks, int n_pairs,
+                                                                    const TW* __restrict__ W, T* __restrict__ wf) {
+  extern __shared__ unsigned char lds_raw[];
+  if (static_cast<int>(blockIdx.x) < window_wgs) {   // the longest role first
+    split_window_role(ga, blockIdx.x, reinterpret_cast<int32_t*>(lds_raw));
+    return;
+  }
+  if (static_cast<int>(blockIdx.x) < window_wgs + count_wgs) {
+    split_count_role(ga, blockIdx.x - window_wgs, reinterpret_cast<int32_t*>(lds_raw));
+    return;
+  }
+  fold_role<T, G, TW>(static_cast<int>(blockIdx.x) - window_wgs - count_wgs, K, chblocks, n_pairs, W, wf);
+}
+
 // The grouping alone (a backward pass that cannot reuse a forward's grouping): scatter and table roles.
 __global__ __launch_bounds__(kSpecThreads) void spec_scatter_kernel(SplitGroupArgs ga, int scatter_wgs) {
   extern __shared__ unsigned char lds_raw[];
@@ -289,14 +294,23 @@ __global__ __launch_bounds__(kSpecThreads) void spec_scatter_kernel(SplitGroupAr
 // kDirect: the weights of a run are folded from W (external paths) by the wave itself instead of
 // being read from the folded table, so that no launch has to come before this one.
 template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDirect>
-__global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupArgs ga, int scatter_wgs, int table, int K,
-                                                                    int chblocks, int n, int Z, int tile,
-                                                                    const TS* __restrict__ A,
-                                                                    const int32_t* __restrict__ z,
-                                                                    const T* __restrict__ wf, const TW* __restrict__ W,
-                                                                    TS* __restrict__ B) {
+__global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupArgs ga, int scatter_wgs, int table,
+                                                                    int fold_wgs, int K, int chblocks, int n, int Z,
+                                                                    int tile, const TS* __restrict__ A,
+                                                                    const int32_t* __restrict__ z, const T* __restrict__ wf,
+                                                                    const TW* __restrict__ W, TS* __restrict__ B) {
   extern __shared__ unsigned char lds_raw[];
   int block = blockIdx.x;
+  if constexpr (kDirect) {   // no launch came before: the roles count for themselves, the fold role is here
+    if (block < scatter_wgs + table) {
+      int32_t* counts = reinterpret_cast<int32_t*>(lds_raw) + split_group_lds_bytes(Z) / sizeof(int32_t);
+      split_count_all(ga, counts);
+      ga.counts = counts;
+    } else if (block < scatter_wgs + table + fold_wgs) {
+      fold_role<T, G, TW>(block - scatter_wgs - table, K, chblocks, Z * chblocks, W, const_cast<T*>(wf));   // read by nobody in this launch
+      return;
+    }
+  }
   if (block < scatter_wgs) {
     split_scatter_role(ga, block, reinterpret_cast<int32_t*>(lds_raw));
     return;
@@ -305,7 +319,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupAr
     split_table_role(ga, reinterpret_cast<int32_t*>(lds_raw));
     return;
   }
-  block -= scatter_wgs + table;
+  block -= scatter_wgs + table + fold_wgs;
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = wave_of_thread();
   T* stage = reinterpret_cast<T*>(lds_raw) + wave * kLanes * G::kNLM;  // [64][kNLM] per wave (if used)
@@ -836,13 +850,18 @@ inline int forward_tile_nodes(int64_t n, int chblocks, int64_t resident_wgs, int
 
 template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDirect>
 hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
-                      const Workspace& ws, const LaunchShape& shape, int group, bool window_order, hipStream_t stream) {
+                      const Workspace& ws, const LaunchShape& shape, int group, bool window_order, bool fold_table,
+                      hipStream_t stream) {
   // group: 0 no grouping roles, 1 scatter + table, 2 table only (the batch is already grouped)
   const bool scatter = group == 1;
   const int table = group != 0;
   const int scatter_wgs = scatter ? shape.split_waves / kGroupWavesPerWG : 0;
   size_t lds = (G::kNLM * sizeof(TS) != 16) ? sizeof(T) * kSpecWaves * G::kNLM * kLanes : 0;
-  if (table && split_group_lds_bytes(plan->cfg.num_elements) > lds) lds = split_group_lds_bytes(plan->cfg.num_elements);
+  if (table) {
+    const size_t roles = split_group_lds_bytes(plan->cfg.num_elements) + (kDirect ? split_counts_bytes(plan, shape) : 0);
+    if (roles > lds) lds = roles;
+  }
+  const int fold_wgs = kDirect && fold_table ? (plan->cfg.num_elements * shape.chblocks + kSpecWaves - 1) / kSpecWaves : 0;
   static const int wgs_per_cu = [] {   // resident workgroups per compute unit of this instance
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, &spec_forward_kernel<T, G, TS, TW, kCM, kDirect>, kSpecThreads, 0) != hipSuccess || nb < 1)
@@ -853,10 +872,10 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
                                             : forward_tile_nodes(n, shape.chblocks, static_cast<int64_t>(wgs_per_cu) * plan->num_cus,
                                                                  G::kS > 32 ? 64 : 32);
   const int tiles = static_cast<int>((n + tile - 1) / tile);
-  const int grid = scatter_wgs + table + tiles * shape.chblocks;
+  const int grid = scatter_wgs + table + fold_wgs + tiles * shape.chblocks;
   hipLaunchKernelGGL((spec_forward_kernel<T, G, TS, TW, kCM, kDirect>), dim3(grid), dim3(kSpecThreads), lds, stream,
-                     group_args(plan, n, z, ws, shape, window_order), scatter_wgs, table, plan->cfg.num_channels, shape.chblocks,
-                     static_cast<int>(n), plan->cfg.num_elements, tile, static_cast<const TS*>(A), z,
+                     group_args(plan, n, z, ws, shape, window_order), scatter_wgs, table, fold_wgs, plan->cfg.num_channels,
+                     shape.chblocks, static_cast<int>(n), plan->cfg.num_elements, tile, static_cast<const TS*>(A), z,
                      static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B));
   return hipGetLastError();
 }
@@ -950,7 +969,7 @@ struct Entry {
   }
   static hipError_t forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                             const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
-                            bool component_major, bool direct, hipStream_t stream) {
+                            bool component_major, bool direct, bool fold_table, hipStream_t stream) {
     return by_type(plan, [&](auto t) {
       typedef decltype(t) Y;
       typedef typename Y::T T;
@@ -958,12 +977,12 @@ struct Entry {
       typedef typename Y::TW TW;
       if (component_major) {
         if constexpr (std::is_same<T, TS>::value && !kWide) {
-          if (!direct) return fwd_launch<T, G, TS, TW, true, false>(plan, n, A, z, W, B, ws, shape, group, window_order, stream);
+          if (!direct) return fwd_launch<T, G, TS, TW, true, false>(plan, n, A, z, W, B, ws, shape, group, window_order, false, stream);
         }
         return hipErrorInvalidValue;   // refused by the caller
       }
-      if (direct) return fwd_launch<T, G, TS, TW, false, true>(plan, n, A, z, W, B, ws, shape, group, window_order, stream);
-      return fwd_launch<T, G, TS, TW, false, false>(plan, n, A, z, W, B, ws, shape, group, window_order, stream);
+      if (direct) return fwd_launch<T, G, TS, TW, false, true>(plan, n, A, z, W, B, ws, shape, group, window_order, fold_table, stream);
+      return fwd_launch<T, G, TS, TW, false, false>(plan, n, A, z, W, B, ws, shape, group, window_order, false, stream);
     });
   }
   static hipError_t backward(const sc_plan* plan, int64_t n, const void* A, const void* dB, void* dA, const Workspace& ws,

@@ -263,6 +263,45 @@ def test_window_order_shapes_and_invalid_indices(sc):
     run.close()
 
 
+# Small batches: one launch folds, groups and evaluates.  Same bits, forward and backward on its table and grouping, as
+# with the prepare launch (which the window order takes); up to the largest batch of that way (2034 nodes of the first
+# shape) and one node more, with invalid element indices, on a batch in the order of the elements, with as many elements
+# as the count matrix has room for and more.
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("K,l_max,nu,outs,dtype,Z,sizes", [
+    (128, 3, 3, O01, "f32", 89, (1, 2, 255, 257, 1100, 2034, 2035)), (100, 3, 3, O01, "f64", 10, (5, 1017, 1018)),
+    (64, 3, 3, O01 + ((2, 1),), "bf16", 89, (63, 700)), (72, 2, 3, O01, "f32", 1024, (300, 1025)),
+    (64, 3, 2, O01, "f64", 7, (2048, 2049))])
+def test_one_launch_forward(sc, K, l_max, nu, outs, dtype, Z, sizes, grouped):
+    import torch
+    wl = workloads.Workload("one_launch", max(sizes), Z, K, l_max, nu, outs, dtype, 4711)
+    T = osc.build_tables(osc.OracleConfig(K, l_max, nu, Z, outs))
+    inp = workloads.make_inputs(wl, T.paths)
+    runs = [GpuRun(sc, wl, inp, flags) for flags in (0, sc.SC_PLAN_WINDOW_ORDER)]
+    for n in sizes:
+        print(f"one launch K={K} l_max={l_max} nu={nu} {dtype} Z={Z} n={n} grouped={grouped}", flush=True)
+        z = runs[0].z[:n].clone()
+        if grouped:
+            z = torch.sort(z).values
+        elif n > 2:
+            z[n // 2], z[-1] = -1, Z
+        out = []
+        for r in runs:
+            B, dA = torch.full_like(r.B[:n], 7.0), torch.full_like(r.A[:n], 7.0)
+            dW = torch.full_like(r.W, 7.0)
+            flags = sc.SC_Z_GROUPED if grouped else 0
+            r.ws.fill_(255)
+            sc.sc_forward(r.plan, n, r.A, z, r.W, B, r.ws, r.ws_bytes, flags)
+            flags |= sc.SC_REUSE_GROUPING | sc.SC_REUSE_WEIGHTS
+            sc.sc_backward(r.plan, n, r.A, z, r.W, r.dB, dA, dW, r.ws, r.ws_bytes, flags)
+            out.append((B, dA, dW))
+        for name, a, b in zip(("B", "dA", "dW"), *out):
+            assert torch.equal(a, b), f"{name}, n={n}: other bits than with a prepare launch"
+        assert torch.isfinite(out[0][2]).all()
+    for r in runs:
+        r.close()
+
+
 def test_empty_batch(sc):
     import torch
     wl = wl_of("empty", 0, 5, 128, 3, 3, O01, "f32", 2400)
