@@ -165,6 +165,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // one workgroup of the same kind per CU that walks the units with two sets of planes: 59 us at 10 000 atoms; with four
 // waves of twice the columns each: 61 us.  Error against 64 bits (2-norm, relative), 128 / 256 / 512 channels summed: 1.5e-7,
 // 2.3e-7, 3.4e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7, 4.1e-7 (32 products per rounding of the sum, not four).
+// kTrans: W is [L][k_cols][k_red], dX reads the weights of the forward as they are.
+template <bool kTrans>
 __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void mfma_forward_bf16_kernel(
     int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W,
     float* __restrict__ Y) {
@@ -175,9 +177,9 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4
   const int64_t n0 = blockIdx.x / groups * int64_t(16);
   const int jc[1] = {static_cast<int>(blockIdx.x % groups) * 128 + wave * 16 + (lane & 15)};
   Mma<float>::acc_t acc[16][1];
-  const bool finite = split_tile_product(n_nodes, n0, jc[0], k_red, k_cols, X, W, planes, acc);
+  const bool finite = split_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, planes, acc);
   // (also the barrier after which the planes are free)
-  if (__syncthreads_or(!finite)) plain_tile_product(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
+  if (__syncthreads_or(!finite)) plain_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
   store_tile_coalesced<1>(Y, n_nodes, n0, k_cols, jc, acc, reinterpret_cast<float*>(planes) + wave * kStoreStageFloats);
 }
 
@@ -632,6 +634,22 @@ bool split_small(size_t elem, int64_t n, int k_cols) {
 // 27.9 / 29.2, 500 31.8 / 33.4, 1000 44.3 / 39.8, 2000 73.1 / 55.3; fp64 500 atoms 41.8 / 44.5, 2000 117 / 113.
 bool dx_reads_w_as_is(int64_t n, int k_cols) { return (n + 15) / 16 * (k_cols / 16) <= compute_units(); }
 
+// Is the product served by mfma_forward_bf16_kernel, beyond the batches of split_forward_kernel?  (Its 31-bit offsets into W
+// go through a buffer descriptor.)
+bool bf16_parts_ok(size_t elem, int l_max, int64_t n, int k_red, int k_cols) {
+  return elem == 4 && l_max == 3 && k_cols % 128 == 0 && k_red % kSplitChunk == 0 && mfma_forward_ok(k_red, k_cols) &&
+         static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26) && !split_small(elem, n, k_cols);
+}
+
+// ... whose dX reads W as it is: a lane's channels are contiguous there, the launch that transposes W is saved.  Its 16-byte requests
+// use half a line each and cost more than the rows of a transposed W, so only up to twelve chunks of a workgroup's
+// reduction per CU.  Backward, us, W transposed / as it is: 128 -> 128 channels, 2500 atoms 59.9 / 56.5, 4000 61.9 / 58.8,
+// 10 000 (10 chunks per CU) 123.3 / 122.4, 20 000 205 / 208; 256 -> 128, 1500 atoms 62.9 / 59.2; 128 -> 256, 3000 84.8 / 82.5.
+bool dx_parts_read_w_as_is(const el_config* c, int64_t n) {
+  return bf16_parts_ok(elem_size(c), c->l_max, n, c->k_out, c->k_in) &&
+         (n + 15) / 16 * (c->k_in / 128) * (c->k_out / kSplitChunk) <= static_cast<int64_t>(12) * compute_units();
+}
+
 // Is the LDS-staged dW kernel the one for this configuration?
 bool dw_lds_ok(const el_config* c) { return c->dtype == SC_F32 && c->l_max == 3 && c->k_in % 128 == 0 && c->k_out % 64 == 0; }
 
@@ -654,9 +672,17 @@ hipError_t launch_split(int64_t n, int k_red, int k_cols, const void* X, const v
 
 template <typename T, int LMAX, bool kTrans>
 hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
+  if constexpr (sizeof(T) == 4 && LMAX == 3) {
+    if (bf16_parts_ok(sizeof(T), LMAX, n, k_red, k_cols)) {
+      const int64_t units = (n + 15) / 16 * (k_cols / 128);
+      hipLaunchKernelGGL((mfma_forward_bf16_kernel<kTrans>), dim3(static_cast<unsigned>(units)), dim3(kSplitThreads), 0, stream,
+                         n, k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
+      return hipGetLastError();
+    }
+  }
   if (mfma_forward_ok(k_red, k_cols) && (kTrans || split_small(sizeof(T), n, k_cols)))
     return launch_split<T, T, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
-  // The kernels below read B operands along rows of W (the backward hands them W transposed).
+  // The tiled kernels below read B operands along rows of W (the backward hands them W transposed).
   if constexpr (!kTrans) {
     if (mfma_forward_ok(k_red, k_cols)) {
       const int64_t tiles = (n + 15) / 16;
@@ -665,11 +691,6 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
       if (sizeof(T) == 4 && LMAX == 3 && k_cols % 128 == 0 && static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26)) {
         if constexpr (sizeof(T) == 4 && LMAX == 3) {   // the LDS-staged variant: two workgroups fit a CU
           const int64_t units = tiles * (k_cols / 128);
-          if (k_red % kSplitChunk == 0) {
-            hipLaunchKernelGGL(mfma_forward_bf16_kernel, dim3(static_cast<unsigned>(units)), dim3(kSplitThreads), 0, stream, n,
-                               k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
-            return hipGetLastError();
-          }
           const unsigned grid2 = static_cast<unsigned>(std::min<int64_t>(units, 2 * compute_units()));
           hipLaunchKernelGGL(mfma_forward_lds_kernel, dim3(grid2), dim3(kThreads), 0, stream, n, k_red, k_cols,
                              static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
@@ -817,9 +838,11 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
     return set_error(SC_ERR_WORKSPACE, "el_backward: workspace missing or smaller than el_workspace_bytes()");
   if (misaligned(workspace, 256)) return set_error(SC_ERR_WORKSPACE, "el_backward: workspace not 256-byte aligned");
   // dX = dY times W transposed: reduction over the output channels, columns = input channels.  Beyond the smallest
-  // batches the kernels take W transposed once into the workspace (strided B operands cost a third more time).
+  // batches the kernels take W transposed once into the workspace (strided B operands cost a third more time for the fp32
+  // and fp64 instructions; the kernel of the bfloat16 parts reads W as it is for longer).
   hipError_t e;
-  if (mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n_nodes, cfg->k_in)) {
+  if (mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n_nodes, cfg->k_in) &&
+      !dx_parts_read_w_as_is(cfg, n_nodes)) {
     const int64_t elems = static_cast<int64_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out;
     const unsigned tgrid = static_cast<unsigned>((elems + 255) / 256);
     if (cfg->dtype == SC_F64)

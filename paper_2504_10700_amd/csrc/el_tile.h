@@ -222,12 +222,14 @@ __device__ __forceinline__ SplitPair split_pair(float x, float y) {
 // the A operands as the instruction reads them; the next chunk's rows are requested a chunk ahead); a wave splits its
 // own columns of W order by order, requested an order ahead.  Returns whether the lane's results are finite: an infinity
 // or a value that h rounds to one (from 0x7f7f8000 on) leaves an infinity or a NaN in every result it enters, where
-// the product in fp32 may have another value.
+// the product in fp32 may have another value.  kTrans: W is [order][column][reduction channel], a lane's eight channels are
+// contiguous (two 16-byte requests; the sixteen columns of a wave read whole 128-byte lines).
 constexpr int kSplitWaves = 8;
 constexpr int kSplitThreads = kSplitWaves * kLanes;
 constexpr int kSplitChunk = 32;
 constexpr int kSplitPlane = 16 * 16 * kSplitChunk / 2;    // 32-bit words of a plane: two channels each
 
+template <bool kTrans>
 __device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
                                                     const float* __restrict__ X, const float* __restrict__ W,
                                                     unsigned* planes /* 3 * kSplitPlane words */,
@@ -264,14 +266,24 @@ __device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, 
     }
   };
   // this lane's column of W: eight channels 8 q .. 8 q + 7 of a chunk, as in lds_tile_product through a descriptor
-  const unsigned boff = static_cast<unsigned>(8 * q * k_cols + jc) * 4u;
-  const unsigned row_bytes = static_cast<unsigned>(k_cols) * 4u;
-  const unsigned lstride = static_cast<unsigned>(k_red) * row_bytes;
+  const unsigned boff = static_cast<unsigned>(kTrans ? jc * k_red + 8 * q : 8 * q * k_cols + jc) * 4u;
+  const unsigned row_bytes = kTrans ? 4u : static_cast<unsigned>(k_cols) * 4u;   // from a reduction channel to the next
+  const unsigned lstride = static_cast<unsigned>(k_red) * static_cast<unsigned>(k_cols) * 4u;
   const __amdgpu_buffer_rsrc_t wrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, static_cast<int>(L * lstride), 0x00020000);
   float wr[8];
   auto bload = [&](int chunk, int l) {
     const unsigned so = static_cast<unsigned>(l) * lstride + static_cast<unsigned>(chunk * kSplitChunk) * row_bytes;
+    if constexpr (kTrans) {
+#pragma unroll
+      for (int i = 0; i < 8; i += 4) {
+        const V4 v = __builtin_bit_cast(V4, __builtin_amdgcn_raw_buffer_load_b128(wrs, static_cast<int>(boff),
+                                                                                  static_cast<int>(so + i * 4), 0));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) wr[i + k] = v[k];
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       wr[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrs, static_cast<int>(boff),
@@ -326,6 +338,7 @@ __device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, 
 }
 
 // The same accumulators on the fp32 matrix cores, operands straight from memory: tiles that the split does not serve.
+template <bool kTrans>
 __device__ __forceinline__ void plain_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
                                                    const float* __restrict__ X, const float* __restrict__ W,
                                                    typename Mma<float>::acc_t (&acc)[16][1]) {
@@ -338,7 +351,8 @@ __device__ __forceinline__ void plain_tile_product(int64_t n_nodes, int64_t n0, 
     float a[NC], b[L];
     load_row<float, NC>(X + (static_cast<size_t>(na) * k_red + k) * NC, a);
 #pragma unroll
-    for (int l = 0; l < L; ++l) b[l] = W[(static_cast<size_t>(l) * k_red + k) * k_cols + jc];
+    for (int l = 0; l < L; ++l)
+      b[l] = W[kTrans ? (static_cast<size_t>(l) * k_cols + jc) * k_red + k : (static_cast<size_t>(l) * k_red + k) * k_cols + jc];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c][0] = Mma<float>::mma(a[c], b[order_of(c)], acc[c][0]);
   }

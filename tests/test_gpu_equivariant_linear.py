@@ -89,6 +89,25 @@ def test_products_of_split_values(el, N, k_in, k_out):
     run_case(el, N, k_in, k_out, 3, "f32", 8800 + k_in)
 
 
+# dX of these products reads W as it is: the same sums in the same order as el_forward on W transposed, also in tiles
+# that are computed again.  One chunk of the reduction and several, two groups of columns, a reduction that is no multiple of
+# 32; and the last and the first batch on the two sides of the rule (12 x 256 chunks of 16 atoms x 128 columns x 32 channels).
+@pytest.mark.parametrize("N,k_in,k_out", [(2065, 128, 32), (2049, 128, 160), (1100, 256, 96), (2070, 128, 48),
+                                          (3072, 128, 512), (3073, 128, 512)])
+def test_dx_is_the_product_with_w_transposed(el, N, k_in, k_out):
+    import torch
+    X, W, dY = (torch.tensor(x, dtype=torch.float32, device="cuda:0") for x in workloads.make_linear_inputs(N, k_in, k_out, 3, 8960))
+    dY[5, 7, 2], dY[700, 3, 0], dY[1000, 1, 12], dY[N - 1, k_out - 1, 15] = np.inf, 3.4e38, np.nan, -3.4e38
+    cfg = el.make_config(k_in, k_out, 3)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    dX, ref, dW = torch.empty_like(X), torch.empty_like(X), torch.empty_like(W)
+    el.el_backward(cfg, N, X, W, dY, dX, dW, torch.empty(nbytes, dtype=torch.uint8, device="cuda:0"), nbytes)
+    el.el_forward(el.make_config(k_out, k_in, 3), N, dY, W.transpose(1, 2).contiguous(), ref)
+    torch.cuda.synchronize()
+    assert ref.isnan().any() and torch.equal(dX.isnan(), ref.isnan())
+    assert torch.equal(dX.nan_to_num(nan=0.0), ref.nan_to_num(nan=0.0))
+
+
 def test_values_that_do_not_split(el):
     """Infinities, NaN and values that round to a bfloat16 infinity: the results of the tiles they are in are those of the
     products in fp32, the others are untouched."""
