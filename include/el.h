@@ -10,9 +10,15 @@
  *
  * one K_in x K_out matrix per order l, shared by the 2l+1 components of that order; component
  * index l*l + l + m as in sc.h.  No bias and no normalisation factor inside the operation.
- * This is a dense contraction: the kernels run on the matrix cores (MFMA, fp32 or fp64
- * inputs and accumulation) when K_in and K_out are multiples of 64 (forward alone: K_in a
- * multiple of 16), and in fp64 on the matrix cores otherwise.
+ * This is a dense contraction on the matrix cores.  fp64: fp64 products and sums.  fp32: fp32
+ * products and sums when K_in and K_out are multiples of 64 (forward alone: K_in a multiple of
+ * 16), fp64 products and sums otherwise.  Batches of some thousand atoms with l_max = 3, columns
+ * a multiple of 128 and the channels that are summed a multiple of 32 take the bfloat16 matrix
+ * cores: every fp32 value as the exact sum of three bfloat16 values (rows that hold a value for
+ * which there is no such sum, below 2^-110 or beyond the largest bfloat16, are computed with fp32
+ * products), products down to 2^-34 of the value, sums in fp32.  Its error against 64 bits is
+ * that of fp32 products (one term: at most 1.006 of half an ulp; two: 1.2 times the 2-norm of
+ * theirs) or smaller (from 32 channels on less than half).
  *
  * Conventions as in sc.h: device pointers, dense row-major, 16-byte aligned; calls enqueue on
  * the given HIP stream and never synchronise; outputs are overwritten; errors by return code

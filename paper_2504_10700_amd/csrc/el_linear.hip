@@ -11,7 +11,7 @@
 // 2l+1 components of an order share their B operand.  With the layout X[atom][channel][lm]
 // the A operands of all components of one (atom, channel) are 64 contiguous bytes, and a lane
 // ends up with whole 64-byte rows of the result.  Kernels: mfma_forward_bf16_kernel (fp32, l_max = 3,
-// reduction channels a multiple of 32: every value as the sum of three bfloat16 values),
+// reduction channels a multiple of 32: every value as the exact sum of three bfloat16 values),
 // mfma_forward_lds_kernel (fp32, l_max = 3, others:
 // X staged through LDS once per workgroup, B through a buffer descriptor, result
 // rows stored as whole lines through an LDS transpose; the product lives in el_tile.h and is
@@ -157,14 +157,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // The same product on the bfloat16 matrix cores (split_tile_product), k_red % 32 == 0: a workgroup of eight waves per
-// unit of 16 atoms x 128 columns, 128 registers, two workgroups per CU.  The matrix work is 3/8 of the fp32 instruction's;
-// what bounds it: requests of X, splitting, reads of LDS and products of a workgroup mostly follow one another (20 000
-// atoms, 128 -> 128 channels: 50 us without the requests and splits, 109 with both; the bytes need 60).
-// Forward, us, mfma_forward_lds_kernel -> this kernel: 128 -> 128 channels, 4000 atoms 31.6 -> 26.9, 10 000 66.5 -> 56.0,
-// 20 000 133 -> 102; 256 -> 256, 4000 atoms 110 -> 69; 256 -> 128, 3000 atoms 71 -> 41; 512 -> 128, 4000 atoms 114 -> 77.  With
-// one workgroup of the same kind per CU that walks the units with two sets of planes: 59 us at 10 000 atoms; with four
-// waves of twice the columns each: 61 us.  Error against 64 bits (2-norm, relative), 128 / 256 / 512 channels summed: 1.5e-7,
-// 2.3e-7, 3.4e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7, 4.1e-7 (32 products per rounding of the sum, not four).
+// unit of 16 atoms x 128 columns, 128 registers, two workgroups per CU.  The matrix work is half of the fp32 instruction's;
+// what bounds it: requests of X, splitting, reads of LDS and products of a workgroup mostly follow one another, and units are
+// large (bf16_parts_ok).  Forward on inputs from memory, us, mfma_forward_lds_kernel -> this kernel: 128 -> 128 channels, 4096 atoms
+// 37.9 -> 27.8, 8192 60.0 -> 46.0, 16 384 101 -> 88, 24 000 141 -> 127; 256 -> 256, 4096 atoms 108 -> 70; 256 -> 128, 3000 atoms
+// 69 -> 45; 512 -> 128, 4096 atoms 140 -> 84.  Error against 64 bits (2-norm, relative), 128 / 256 / 512 channels summed: 0.73e-7,
+// 1.0e-7, 1.5e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7, 4.0e-7 (32 products per rounding of the sum, not four); of one nonzero
+// weight per column, largest: 5.99e-8 and 5.96e-8; of two, 2-norm: 3.7e-8 and 3.1e-8.
 // kTrans: W is [L][k_cols][k_red], dX reads the weights of the forward as they are.
 template <bool kTrans>
 __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void mfma_forward_bf16_kernel(
@@ -172,14 +171,16 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4
     float* __restrict__ Y) {
   __shared__ __attribute__((aligned(16))) unsigned planes[3 * kSplitPlane];
   static_assert(kSplitWaves * kStoreStageFloats <= 3 * kSplitPlane, "the store stages reuse the planes");
-  const int lane = threadIdx.x & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
   const int groups = k_cols / 128;
   const int64_t n0 = blockIdx.x / groups * int64_t(16);
-  const int jc[1] = {static_cast<int>(blockIdx.x % groups) * 128 + wave * 16 + (lane & 15)};
+  const int j0 = static_cast<int>(blockIdx.x % groups) * 128;
   Mma<float>::acc_t acc[16][1];
-  const bool finite = split_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, planes, acc);
+  bool x_served;
+  const bool served = split_tile_product<kTrans>(n_nodes, n0, j0, k_red, k_cols, X, W, planes, acc, x_served);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int jc[1] = {j0 + wave * 16 + static_cast<int>(threadIdx.x % 16)};
   // (also the barrier after which the planes are free)
-  if (__syncthreads_or(!finite)) plain_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
+  if (__syncthreads_or(!x_served) || !served) plain_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
   store_tile_coalesced<1>(Y, n_nodes, n0, k_cols, jc, acc, reinterpret_cast<float*>(planes) + wave * kStoreStageFloats);
 }
 
@@ -635,19 +636,24 @@ bool split_small(size_t elem, int64_t n, int k_cols) {
 bool dx_reads_w_as_is(int64_t n, int k_cols) { return (n + 15) / 16 * (k_cols / 16) <= compute_units(); }
 
 // Is the product served by mfma_forward_bf16_kernel, beyond the batches of split_forward_kernel?  (Its 31-bit offsets into W
-// go through a buffer descriptor.)
+// go through a buffer descriptor.)  With up to 128 channels summed it gains least per unit and needs the units even over the CUs:
+// between two and five units per CU not where less than half of the CUs get one more (forward, 128 -> 128 channels, us,
+// mfma_forward_lds_kernel / this kernel: 2.03 units per CU 60 / 64, 2.44 62 / 65, 2.69 76 / 68, 3.42 78 / 83, 4.0 101 / 88, 4.39
+// 103 / 106, 5.03 119 / 119, 5.9 141 / 127); with 32 channels, not beyond two units per CU (4.9: 45 / 47).
 bool bf16_parts_ok(size_t elem, int l_max, int64_t n, int k_red, int k_cols) {
-  return elem == 4 && l_max == 3 && k_cols % 128 == 0 && k_red % kSplitChunk == 0 && mfma_forward_ok(k_red, k_cols) &&
-         static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26) && !split_small(elem, n, k_cols);
+  if (!(elem == 4 && l_max == 3 && k_cols % 128 == 0 && k_red % kSplitChunk == 0 && mfma_forward_ok(k_red, k_cols) &&
+        static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26) && !split_small(elem, n, k_cols)))
+    return false;
+  const int64_t cus = compute_units(), units = (n + 15) / 16 * (k_cols / 128), more = units % cus;
+  if (units <= 2 * cus) return true;
+  return k_red >= 64 && (k_red > 128 || units > 5 * cus || more == 0 || more > cus / 2);
 }
 
-// ... whose dX reads W as it is: a lane's channels are contiguous there, the launch that transposes W is saved.  Its 16-byte requests
-// use half a line each and cost more than the rows of a transposed W, so only up to twelve chunks of a workgroup's
-// reduction per CU.  Backward, us, W transposed / as it is: 128 -> 128 channels, 2500 atoms 59.9 / 56.5, 4000 61.9 / 58.8,
-// 10 000 (10 chunks per CU) 123.3 / 122.4, 20 000 205 / 208; 256 -> 128, 1500 atoms 62.9 / 59.2; 128 -> 256, 3000 84.8 / 82.5.
+// ... whose dX reads W as it is: a lane's channels are contiguous there and the launch that transposes W is saved.  Backward, us, W
+// transposed / as it is: 128 -> 128 channels, 2100 atoms 60.8 / 57.8, 8192 108 / 100, 20 480 237 / 226; 256 -> 128, 3000 atoms 87.4 /
+// 83.5, 20 000 429 / 407; 256 -> 256, 20 000 atoms 716 / 714.
 bool dx_parts_read_w_as_is(const el_config* c, int64_t n) {
-  return bf16_parts_ok(elem_size(c), c->l_max, n, c->k_out, c->k_in) &&
-         (n + 15) / 16 * (c->k_in / 128) * (c->k_out / kSplitChunk) <= static_cast<int64_t>(12) * compute_units();
+  return bf16_parts_ok(elem_size(c), c->l_max, n, c->k_out, c->k_in);
 }
 
 // Is the LDS-staged dW kernel the one for this configuration?
@@ -839,7 +845,7 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
   if (misaligned(workspace, 256)) return set_error(SC_ERR_WORKSPACE, "el_backward: workspace not 256-byte aligned");
   // dX = dY times W transposed: reduction over the output channels, columns = input channels.  Beyond the smallest
   // batches the kernels take W transposed once into the workspace (strided B operands cost a third more time for the fp32
-  // and fp64 instructions; the kernel of the bfloat16 parts reads W as it is for longer).
+  // and fp64 instructions; the kernel of the bfloat16 parts reads W as it is).
   hipError_t e;
   if (mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n_nodes, cfg->k_in) &&
       !dx_parts_read_w_as_is(cfg, n_nodes)) {

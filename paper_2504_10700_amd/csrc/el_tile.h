@@ -192,9 +192,12 @@ __device__ __forceinline__ void lds_tile_product(int64_t n_nodes, int64_t n0, in
 
 // ---- the same product on the bfloat16 matrix cores
 //
-// An fp32 value is the exact sum of three bfloat16 values (rounded to nearest: h, then what is left: m, then l; 8 + 8 + 8
-// bits), |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.  The products h h, h m, m h, m m, h l and l h are summed in fp32 by the matrix
-// core, smallest first; the three that are left out are below 2^-26 of |x w|, under the rounding of an fp32 product.
+// An fp32 value of magnitude 2^-110 or more is the exact sum of three bfloat16 values (rounded to nearest: h, then what
+// is left: m, then l; 8 + 8 + 8 bits), |m| <= 2^-8 |x|, |l| <= 2^-17 |x|.  Below, its last bits may be under 2^-133, the last
+// bit that a bfloat16 has, and the sum is another value: split_pair notes it.  (The matrix core takes subnormal parts as they are.)
+// Of the nine products of the parts, l l (at most 2^-34 of |x w|) is left out.  An instruction sums its products and the accumulator
+// in fp32 and cuts smaller products off at the last bit of the largest; the seven products with an m or an l are therefore
+// summed by themselves, which costs 2^-8 of that error, and join the sum of the h h once per 32 channels.
 typedef __bf16 Bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned U4 __attribute__((ext_vector_type(4)));
 
@@ -208,62 +211,77 @@ __device__ __forceinline__ unsigned pack_bf16(float x, float y) {
 }
 __device__ __forceinline__ float low_half(unsigned u) { return __builtin_bit_cast(float, u << 16); }
 __device__ __forceinline__ float high_half(unsigned u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
-__device__ __forceinline__ SplitPair split_pair(float x, float y) {
+// left: collects what l stands for; its low 16 bits stay zero as long as every value is the sum of its parts.
+__device__ __forceinline__ SplitPair split_pair(float x, float y, unsigned& left) {
   SplitPair s;
   s.h = pack_bf16(x, y);
   const float rx = x - low_half(s.h), ry = y - high_half(s.h);
   s.m = pack_bf16(rx, ry);
-  s.l = pack_bf16(rx - low_half(s.m), ry - high_half(s.m));
+  const float tx = rx - low_half(s.m), ty = ry - high_half(s.m);
+  s.l = pack_bf16(tx, ty);
+  left |= __builtin_bit_cast(unsigned, tx) | __builtin_bit_cast(unsigned, ty);
+  asm volatile("" : "+v"(left));             // collected here: put off, the compiler holds two registers of every pair
   return s;
 }
 
-// The accumulators of rows n0..n0+15 and of the wave's 16 columns (this lane's: jc).  k_red % 32 == 0.  The workgroup
+// The accumulators of rows n0..n0+15 and of the wave's 16 of the 128 columns from j0 on.  k_red % 32 == 0.  The workgroup
 // (eight waves) splits X in chunks of 32 reduction channels into LDS (three planes of [component][atom][32], which are
 // the A operands as the instruction reads them; the next chunk's rows are requested a chunk ahead); a wave splits its
-// own columns of W order by order, requested an order ahead.  Returns whether the lane's results are finite: an infinity
-// or a value that h rounds to one (from 0x7f7f8000 on) leaves an infinity or a NaN in every result it enters, where
-// the product in fp32 may have another value.  kTrans: W is [order][column][reduction channel], a lane's eight channels are
-// contiguous (two 16-byte requests; the sixteen columns of a wave read whole 128-byte lines).
+// own columns of W order by order, requested an order ahead.  x_served: the values of X that the wave has split
+// are the sums of their parts (for other waves' columns as well).  Returns whether the wave's values of W are, and its results are
+// finite (an infinity, or a value that h rounds to one, from 0x7f7f8000 on, leaves an infinity or a NaN in every result it
+// enters, where the product in fp32 may have another value).  kTrans: W is [order][column][reduction channel], a lane's eight channels are contiguous (two 16-byte requests; the
+// sixteen columns of a wave read whole 128-byte lines).
 constexpr int kSplitWaves = 8;
 constexpr int kSplitThreads = kSplitWaves * kLanes;
 constexpr int kSplitChunk = 32;
 constexpr int kSplitPlane = 16 * 16 * kSplitChunk / 2;    // 32-bit words of a plane: two channels each
 
 template <bool kTrans>
-__device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
+__device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, int j0, int k_red, int k_cols,
                                                     const float* __restrict__ X, const float* __restrict__ W,
                                                     unsigned* planes /* 3 * kSplitPlane words */,
-                                                    typename Mma<float>::acc_t (&acc)[16][1]) {
+                                                    typename Mma<float>::acc_t (&acc)[16][1], bool& x_served) {
   constexpr int NC = 16, L = 4;
   typedef Mma<float>::acc_t acc_t;
   typedef float V4 __attribute__((ext_vector_type(4)));
-  const int lane = threadIdx.x & (kLanes - 1);
-  const int q = lane / 16, i16 = lane & 15;
+  // The thread's number as a value of its own: what is derived from it here ends with the loop, and what the
+  // caller derives from it is not held in registers through the loop.
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int q = tid / 16 % 4, i16 = tid % 16, jc = j0 + tid / kLanes * 16 + i16;
   const int chunks = k_red / kSplitChunk;
   // splitting role of this thread: half of the components of one atom of the tile and two reduction channels
-  const int half = threadIdx.x / 256, sa = threadIdx.x / 16 % 16, sk = threadIdx.x % 16;
+  const int half = tid / 256, sa = tid / 16 % 16, sk = tid % 16;
   int64_t ns = n0 + sa;
   if (ns >= n_nodes) ns = n_nodes - 1;       // rows past the end split a valid atom and are not stored
-  const float* xsrc = X + (static_cast<size_t>(ns) * k_red + 2 * sk) * NC + half * 8;
+  // (through a descriptor of the tile's rows, like W: the lane's part is one 32-bit offset)
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(X + static_cast<size_t>(n0) * k_red * NC), 0, 16 * k_red * NC * 4, 0x00020000);
+  const unsigned xoff = ((static_cast<unsigned>(ns - n0) * k_red + 2 * sk) * NC + half * 8) * 4u;
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c][0] = acc_t{0, 0, 0, 0};
 
+  unsigned long long x_inexact = 0, w_inexact = 0;   // lanes that have split a value into parts of another sum
   V4 xr[2][2];
   auto gload = [&](int chunk) {
-    const float* p = xsrc + static_cast<size_t>(chunk) * kSplitChunk * NC;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) xr[i / 2][i % 2] = *reinterpret_cast<const V4*>(p + i / 2 * NC + i % 2 * 4);
+    for (int i = 0; i < 4; ++i)
+      xr[i / 2][i % 2] = __builtin_bit_cast(V4, __builtin_amdgcn_raw_buffer_load_b128(
+          xrs, static_cast<int>(xoff), (chunk * kSplitChunk * NC + i / 2 * NC + i % 2 * 4) * 4, 0));
   };
   auto split_x = [&]() {
+    unsigned left = 0;
     unsigned* dst = planes + half * 8 * 256 + sa * 16 + sk;
 #pragma unroll
     for (int c = 0; c < NC / 2; ++c) {
       const float x = xr[0][c / 4][c % 4], y = xr[1][c / 4][c % 4];
-      const SplitPair s = split_pair(x, y);
+      const SplitPair s = split_pair(x, y, left);
       dst[c * 256] = s.h;
       dst[c * 256 + kSplitPlane] = s.m;
       dst[c * 256 + 2 * kSplitPlane] = s.l;
     }
+    x_inexact |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
   };
   // this lane's column of W: eight channels 8 q .. 8 q + 7 of a chunk, as in lds_tile_product through a descriptor
   const unsigned boff = static_cast<unsigned>(kTrans ? jc * k_red + 8 * q : 8 * q * k_cols + jc) * 4u;
@@ -289,42 +307,60 @@ __device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, 
       wr[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrs, static_cast<int>(boff),
                                                                              static_cast<int>(so + i * row_bytes), 0));
   };
+  auto read_a = [&](int part, int c) {
+    return *reinterpret_cast<const U4*>(planes + part * kSplitPlane + c * 256 + i16 * 16 + q * 4);
+  };
   gload(0);
   bload(0, L - 1);
   // The waves that multiply go first: the two workgroups of a CU drift apart, and one's products cover the other's
-  // requests and splitting (20 000 atoms: 112 -> 102 us).
+  // requests and splitting (20 000 atoms: 112 -> 102 us, with six products).
   for (int ch = 0; ch < chunks; ++ch) {
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();                         // the reads of the previous chunk are done
     split_x();
+    __builtin_amdgcn_sched_barrier(0);       // (what is split is out of the registers before the next rows come in)
     // (no condition on the request: at its join the compiler would wait for every outstanding load)
     gload(ch + 1 < chunks ? ch + 1 : ch);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
+    U4 a[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) a[p] = read_a(p, (L - 1) * (L - 1));
 #pragma unroll
     for (int l = L - 1; l >= 0; --l) {
       U4 b[3];
+      unsigned left = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const SplitPair s = split_pair(wr[2 * i], wr[2 * i + 1]);
+        const SplitPair s = split_pair(wr[2 * i], wr[2 * i + 1], left);
         b[0][i] = s.h;
         b[1][i] = s.m;
         b[2][i] = s.l;
       }
+      w_inexact |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
+      __builtin_amdgcn_sched_barrier(0);
       const int next = l > 0 ? ch : (ch + 1 < chunks ? ch + 1 : ch);   // past the end: a valid chunk again
       bload(next, l > 0 ? l - 1 : L - 1);
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int c = l * l; c < (l + 1) * (l + 1); ++c) {
-        U4 a[3];
+        // The parts of X in turn, l first; where one has been used for the last time, the next component's is requested
+        // (4000 atoms, 256 -> 256 channels: 76 -> 71 us).
+        const int next_c = c + 1 < (l + 1) * (l + 1) ? c + 1 : (l > 0 ? (l - 1) * (l - 1) : -1);
+        acc_t small{0, 0, 0, 0};
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-          a[p] = *reinterpret_cast<const U4*>(planes + p * kSplitPlane + c * 256 + i16 * 16 + q * 4);
-        constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};   // smallest products first
+        for (int p = 2; p >= 0; --p) {
 #pragma unroll
-        for (int p = 0; p < 6; ++p)
-          acc[c][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf8, a[kA[p]]),
-                                                              __builtin_bit_cast(Bf8, b[kB[p]]), acc[c][0], 0, 0, 0);
+          for (int w = 2; w >= 0; --w) {
+            if (p + w == 4) continue;        // l l
+            acc_t& sum = p + w == 0 ? acc[c][0] : small;
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf8, a[p]), __builtin_bit_cast(Bf8, b[w]), sum, 0, 0, 0);
+          }
+          if (next_c >= 0) a[p] = read_a(p, next_c);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[c][0][r] += small[r];
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -334,10 +370,13 @@ __device__ __forceinline__ bool split_tile_product(int64_t n_nodes, int64_t n0, 
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int r = 0; r < 4; ++r) finite &= __builtin_isfinite(acc[c][0][r]);
-  return finite;
+  x_served = x_inexact == 0;
+  return w_inexact == 0 && __builtin_amdgcn_ballot_w64(!finite) == 0;
 }
 
-// The same accumulators on the fp32 matrix cores, operands straight from memory: tiles that the split does not serve.
+// The same accumulators on the fp32 matrix cores, operands straight from memory: what the parts do not serve.  (Requests a
+// step ahead do not fit the registers.)  Forward of 4096 atoms, us, with no such value / one weight / one value of X in a tenth of the
+// tiles / all of X (mfma_forward_lds_kernel): 128 -> 128 channels 28 / 52 / 59 / 64 (38), 256 -> 256 69 / 124 / 136 / 188 (107).
 template <bool kTrans>
 __device__ __forceinline__ void plain_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
                                                    const float* __restrict__ X, const float* __restrict__ W,

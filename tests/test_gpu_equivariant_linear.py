@@ -89,9 +89,30 @@ def test_products_of_split_values(el, N, k_in, k_out):
     run_case(el, N, k_in, k_out, 3, "f32", 8800 + k_in)
 
 
+# ... and the sides of the rule that takes units of 16 atoms x 128 columns to them (512, 640 and 1280 units with 64 channels
+# summed, 512 with 32), against torch in fp64: forward and, with the channel counts exchanged, dX.
+@pytest.mark.parametrize("N,k_red", [(8192, 64), (8193, 64), (10240, 64), (10241, 64), (20480, 64), (20481, 64), (8193, 32)])
+def test_batches_on_both_sides_of_the_rule(el, N, k_red):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(8850)
+    X = torch.randn((N, k_red, 16), generator=gen, device="cuda")
+    W = torch.randn((4, k_red, 128), generator=gen, device="cuda") / k_red ** 0.5
+    Y, dX, dW = torch.empty((N, 128, 16), device="cuda"), torch.empty((N, 128, 16), device="cuda"), torch.empty((4, 128, k_red), device="cuda")
+    el.el_forward(el.make_config(k_red, 128, 3), N, X, W, Y)
+    cfg = el.make_config(128, k_red, 3)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    el.el_backward(cfg, N, torch.zeros_like(dX), W.transpose(1, 2).contiguous(), X, dX, dW,
+                   torch.empty(nbytes, dtype=torch.uint8, device="cuda"), nbytes)
+    for c in range(16):
+        ref = X[:, :, c].double() @ W[int(c ** 0.5)].double()
+        for what, got in (("Y", Y), ("dX", dX)):
+            err = ((got[:, :, c].double() - ref).abs().max() / ref.square().mean().sqrt()).item()
+            assert err <= 1e-5, (what, c, err)
+
+
 # dX of these products reads W as it is: the same sums in the same order as el_forward on W transposed, also in tiles
 # that are computed again.  One chunk of the reduction and several, two groups of columns, a reduction that is no multiple of
-# 32; and the last and the first batch on the two sides of the rule (12 x 256 chunks of 16 atoms x 128 columns x 32 channels).
+# 32, a ragged last row tile and none.
 @pytest.mark.parametrize("N,k_in,k_out", [(2065, 128, 32), (2049, 128, 160), (1100, 256, 96), (2070, 128, 48),
                                           (3072, 128, 512), (3073, 128, 512)])
 def test_dx_is_the_product_with_w_transposed(el, N, k_in, k_out):
@@ -130,6 +151,59 @@ def test_values_that_do_not_split(el):
     for where in (np.isfinite(ref) & (np.abs(ref) > 1e25), np.isfinite(ref) & (np.abs(ref) < 1e25)):
         err = np.abs(got[where] - ref[where]).max() / np.sqrt((ref[where] ** 2).mean())
         assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("x_scale,w_scale", [(s, 1.0) for s in (1e-30, 1e-34, 1e-36, 1e-38)] +
+                         [(1.0, s) for s in (1e-30, 1e-34, 1e-36, 1e-38)] + [(1e-17, 1e-17), (1e-19, 1e-18), (1e36, 1e-36)])
+def test_small_values(el, x_scale, w_scale):
+    """Products of values whose last bits no bfloat16 part holds (below 2^-110, 8e-34), or whose products are near the
+    smallest fp32 value: forward and dX keep the bound of all others."""
+    import torch
+    N, K = 2065, 128
+    X, W, _ = workloads.make_linear_inputs(N, K, K, 3, 8970)
+    X, W = (torch.tensor(v * s, dtype=torch.float32) for v, s in ((X, x_scale), (W, w_scale)))
+    ref = oel.forward(X.double().numpy(), W.double().numpy())
+    Xd, Wd = X.cuda(), W.cuda()
+    Y, dX, dW = torch.empty_like(Xd), torch.empty_like(Xd), torch.empty_like(Wd)
+    cfg = el.make_config(K, K, 3)
+    el.el_forward(cfg, N, Xd, Wd, Y)
+    nbytes = el.el_workspace_bytes(cfg, N)   # dX of (Wt, dY = X) is the forward of (X, W)
+    el.el_backward(cfg, N, torch.zeros_like(Xd), Wd.transpose(1, 2).contiguous(), Xd, dX, dW,
+                   torch.empty(nbytes, dtype=torch.uint8, device="cuda:0"), nbytes)
+    for what, got in (("Y", Y), ("dX", dX)):
+        err = np.abs(got.double().cpu().numpy() - ref).max() / np.sqrt((ref ** 2).mean())
+        print(f"  X {x_scale:g} W {w_scale:g} {what}: {err:.2e}", flush=True)
+        assert err <= 1e-5, (what, err)
+
+
+def test_values_of_every_exponent_keep_their_bits(el):
+    """W a permutation of the channels: the result is the permuted input, bit for bit, whatever the exponent: a row tile of
+    16 atoms per exponent from the smallest subnormal value to the largest finite one, and one with all of them."""
+    import torch
+    K, tiles = 128, 278
+    rng = np.random.default_rng(8980)
+    e = np.repeat(np.arange(-149, 129), 16)[:, None, None] * np.ones((1, K, 16))
+    e[-16:] = rng.integers(-149, 128, (16, K, 16))
+    with np.errstate(over="ignore"):
+        X = np.ldexp(rng.choice([-1.0, 1.0], e.shape) * rng.uniform(1, 2, e.shape), e.astype(np.int64)).astype(np.float32)
+    X = np.clip(X, -np.finfo(np.float32).max, np.finfo(np.float32).max)
+    N = 16 * tiles
+    W = np.zeros((4, K, K), dtype=np.float32)
+    want = np.empty_like(X)
+    for l in range(4):
+        perm = rng.permutation(K)
+        W[l, perm, np.arange(K)] = 1.0
+        want[:, :, l * l:(l + 1) ** 2] = X[:, perm, l * l:(l + 1) ** 2]
+    Xd, Wd, want = (torch.tensor(v, device="cuda:0") for v in (X, W, want))
+    Y, dX, dW = torch.empty_like(Xd), torch.empty_like(Xd), torch.empty_like(Wd)
+    cfg = el.make_config(K, K, 3)
+    el.el_forward(cfg, N, Xd, Wd, Y)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    el.el_backward(cfg, N, torch.zeros_like(Xd), Wd.transpose(1, 2).contiguous(), Xd, dX, dW,
+                   torch.empty(nbytes, dtype=torch.uint8, device="cuda:0"), nbytes)
+    for what, got in (("Y", Y), ("dX", dX)):
+        wrong = (got != want).flatten(1).any(1).nonzero().flatten()
+        assert wrong.numel() == 0, (what, wrong[:20].tolist())
 
 
 def test_degenerate_sizes_and_errors(el):
