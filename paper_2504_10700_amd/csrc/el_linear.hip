@@ -413,12 +413,26 @@ __device__ __forceinline__ int64_t xcd_contiguous_block() {
   const int64_t per = gridDim.x / kXcds;
   return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
 }
-unsigned xcd_grid(int64_t blocks) { return static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds); }
+
+// Calls launch(first tile, workgroups) until all tiles (a workgroup of so many threads each) are served: a grid holds
+// less than 2^32 threads.  A grid is a multiple of kXcds.
+template <typename F>
+hipError_t for_all_tiles(int64_t n_tiles, int threads, F&& launch) {
+  const int64_t most = (int64_t(1) << 31) / threads;
+  for (int64_t tile0 = 0; tile0 < n_tiles; tile0 += most) {
+    const int64_t blocks = std::min(n_tiles - tile0, most);
+    launch(tile0, static_cast<unsigned>((blocks + kXcds - 1) / kXcds * kXcds));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 // kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).
 template <typename TS, typename TA, int LMAX, bool kTrans>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void split_forward_kernel(
-    int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W, TS* __restrict__ Y) {
+    int64_t tile0, int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W,
+    TS* __restrict__ Y) {
   constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
   constexpr int CG = NC < 4 ? NC : 4;                        // components per round through LDS
   constexpr int RS = SplitRow<TA>::stride;
@@ -429,7 +443,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
   const int kq = lane / 16, i16 = lane & 15;
   const int col_tiles = (k_cols + 15) / 16;
-  const int64_t tile = xcd_contiguous_block();
+  const int64_t tile = tile0 + xcd_contiguous_block();
   if (tile >= (n_nodes + 15) / 16 * col_tiles) return;       // the same for the whole workgroup
   const int64_t n0 = tile / col_tiles * 16;
   const int j0 = static_cast<int>(tile % col_tiles) * 16;
@@ -555,12 +569,14 @@ __device__ __forceinline__ void split_dw_order(int64_t n_nodes, int nc, int k_in
 }
 
 template <typename TS>
-__global__ __launch_bounds__(kDwWaves * kLanes) void split_dw_kernel(int64_t n_nodes, int l_max, int k_in, int k_out,
-                                                                     const TS* __restrict__ X, const TS* __restrict__ dY,
+__global__ __launch_bounds__(kDwWaves * kLanes) void split_dw_kernel(int64_t tile0, int64_t n_nodes, int l_max, int k_in,
+                                                                     int k_out, const TS* __restrict__ X, const TS* __restrict__ dY,
                                                                      TS* __restrict__ dW) {
   __shared__ double red[kDwWaves][256];
   const int jtiles = (k_out + 15) / 16, nc = (l_max + 1) * (l_max + 1);
-  const int j0 = static_cast<int>(blockIdx.x % jtiles) * 16, k0 = static_cast<int>(blockIdx.x / jtiles) * 16;
+  const int64_t tile = tile0 + blockIdx.x;
+  if (tile >= static_cast<int64_t>((k_in + 15) / 16) * jtiles) return;   // the grid is rounded up; the whole workgroup
+  const int j0 = static_cast<int>(tile % jtiles) * 16, k0 = static_cast<int>(tile / jtiles) * 16;
   switch (l_max - static_cast<int>(blockIdx.y)) {
     case 0: return split_dw_order<TS, 0>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
     case 1: return split_dw_order<TS, 1>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
@@ -670,10 +686,10 @@ int nodes_per_range(const el_config* cfg, int64_t n) {
 
 template <typename T, typename TA, int LMAX, bool kTrans>
 hipError_t launch_split(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
-  const int64_t blocks = (n + 15) / 16 * ((k_cols + 15) / 16);
-  hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans>), dim3(xcd_grid(blocks)), dim3(kThreads), 0, stream, n,
-                     k_red, k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
-  return hipGetLastError();
+  return for_all_tiles((n + 15) / 16 * ((k_cols + 15) / 16), kThreads, [&](int64_t tile0, unsigned grid) {
+    hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans>), dim3(grid), dim3(kThreads), 0, stream, tile0, n, k_red,
+                       k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
+  });
 }
 
 template <typename T, int LMAX, bool kTrans>
@@ -732,10 +748,10 @@ hipError_t dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, 
   const int64_t elems = static_cast<int64_t>(LMAX + 1) * cfg->k_in * cfg->k_out;
   if (!mfma_dw_ok(cfg)) {
     const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
-    hipLaunchKernelGGL((split_dw_kernel<T>), dim3(static_cast<unsigned>(tiles), LMAX + 1), dim3(kDwWaves * kLanes), 0,
-                       stream, n, LMAX, cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY),
-                       static_cast<T*>(dW));
-    return hipGetLastError();
+    return for_all_tiles(tiles, kDwWaves * kLanes, [&](int64_t tile0, unsigned grid) {
+      hipLaunchKernelGGL((split_dw_kernel<T>), dim3(grid, LMAX + 1), dim3(kDwWaves * kLanes), 0, stream, tile0, n, LMAX,
+                         cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY), static_cast<T*>(dW));
+    });
   }
   const int per = nodes_per_range(cfg, n);
   const int ranges = static_cast<int>((n + per - 1) / per);

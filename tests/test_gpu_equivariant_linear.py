@@ -82,6 +82,30 @@ def test_products_cut_along_the_reduction(el, N, k_in, k_out, l_max, dtype):
     run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N)
 
 
+def test_more_tiles_than_a_grid_holds(el):
+    """2^28 atoms with one channel (2^24 tiles of 16 atoms), and one atom with 32 770 channels (2049^2 tiles of dW): more
+    threads than the 2^32 of a grid.  One term per result: a product rounded once."""
+    import torch
+    n = 2 ** 28 + 17
+    X = torch.randn((n, 1, 1), device="cuda")
+    W = torch.full((1, 1, 1), 1.7, device="cuda")
+    Y = torch.full_like(X, float("nan"))
+    el.el_forward(el.make_config(1, 1, 0), n, X, W, Y)
+    assert torch.equal(Y, X * W)
+    del X, Y
+    k = 32770
+    X, dY, dX = torch.randn((1, k, 1), device="cuda"), torch.randn((1, k, 1), device="cuda"), torch.full((1, k, 1), float("nan"), device="cuda")
+    W, dW = torch.ones((1, k, k), device="cuda"), torch.full((1, k, k), float("nan"), device="cuda")
+    cfg = el.make_config(k, k, 0)
+    nbytes = el.el_workspace_bytes(cfg, 1)
+    el.el_backward(cfg, 1, X, W, dY, dX, dW, torch.empty(nbytes, dtype=torch.uint8, device="cuda"), nbytes)
+    assert torch.equal(dW[0], X[0] * dY[0].T)
+    want = dY.double().sum().item()
+    assert abs(dX.double() - want).max().item() <= 2.0 ** -23 * abs(want) + 1e-9 * k ** 0.5
+    del X, dY, dX, W, dW
+    torch.cuda.empty_cache()
+
+
 # The products on the bfloat16 matrix cores: one chunk of the reduction and several, a ragged last row tile, two
 # groups of columns; and the kernel of reductions that are no multiple of 32.
 @pytest.mark.parametrize("N,k_in,k_out", [(2065, 32, 128), (2100, 96, 256), (2049, 160, 128), (2070, 48, 128)])
