@@ -511,6 +511,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
+// The same product where the tiles would be mostly padding (few_channels): one thread per (atom, column), fp64 products
+// and sums.  Bound by the bytes of X and Y (l_max = 3, one channel, 200 000 atoms: 8 us for 26 MB).
+template <typename TS, int LMAX, bool kTrans>
+__global__ __launch_bounds__(kThreads) void few_channels_kernel(int64_t block0, int64_t n_nodes, int k_red, int k_cols,
+                                                                const TS* __restrict__ X, const TS* __restrict__ W,
+                                                                TS* __restrict__ Y) {
+  constexpr int NC = (LMAX + 1) * (LMAX + 1);
+  const int64_t i = (block0 + blockIdx.x) * kThreads + threadIdx.x;
+  if (i >= n_nodes * k_cols) return;
+  const int64_t n = i / k_cols;
+  const int j = static_cast<int>(i % k_cols);
+  double y[NC] = {};
+  for (int k = 0; k < k_red; ++k) {
+    TS x[NC];
+    load_unaligned<TS, NC>(X + (static_cast<size_t>(n) * k_red + k) * NC, x);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int l = order_of(c);
+      y[c] += static_cast<double>(x[c]) *
+              static_cast<double>(kTrans ? W[(static_cast<size_t>(l) * k_cols + j) * k_red + k] : W[(static_cast<size_t>(l) * k_red + k) * k_cols + j]);
+    }
+  }
+  TS out[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) out[c] = static_cast<TS>(y[c]);
+  store_row<TS, NC>(Y + static_cast<size_t>(i) * NC, out);
+}
+
 // dW for any channel count: a workgroup owns 16 x 16 entries of one order, its sixteen waves take every sixteenth
 // reduction step (4 atoms); their sums meet in LDS and are added in wave order.  Products and sums in fp64; no
 // workspace.  The highest orders, which have the most components, come first in the grid.  Bound by the vector cache
@@ -646,6 +674,13 @@ bool split_small(size_t elem, int64_t n, int k_cols) {
   return (n + 15) / 16 * (k_cols / 16) <= static_cast<int64_t>(long_other ? 8 : 4) * compute_units();
 }
 
+// Does few_channels_kernel take a product of untiled channel counts?  A tile pads them to 4 x 16.  Forward of 200 000 atoms, us,
+// split_forward_kernel / few_channels_kernel: l_max = 3, 1 -> 1 channels 93 / 8, 3 -> 2 97 / 18; l_max = 2, 2 -> 8 63 / 19; l_max = 1,
+// 3 -> 8 22 / 9, 1 -> 128 196 / 91; l_max = 0, 5 -> 8 10.5 / 6.  Up to 20 000 atoms the calls take what a launch takes, 4 to 9 us, either way.
+bool few_channels(int l_max, int k_red, int k_cols) {
+  return (k_red <= 5 && k_cols <= 8 && k_red * k_cols * (l_max + 1) <= 64) || (l_max == 1 && k_red <= 2);
+}
+
 // Does dX read W as it is?  Its strided reads of W save the launch that transposes W and cost less than it as long
 // as there is no more than one workgroup per CU.  Backward, us, 128 -> 128 channels, W as it is / transposed: fp32 61 atoms
 // 27.9 / 29.2, 500 31.8 / 33.4, 1000 44.3 / 39.8, 2000 73.1 / 55.3; fp64 500 atoms 41.8 / 44.5, 2000 117 / 113.
@@ -728,6 +763,11 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
       return hipGetLastError();
     }
   }
+  if (few_channels(LMAX, k_red, k_cols))
+    return for_all_tiles((n * k_cols + kThreads - 1) / kThreads, kThreads, [&](int64_t block0, unsigned grid) {
+      hipLaunchKernelGGL((few_channels_kernel<T, LMAX, kTrans>), dim3(grid), dim3(kThreads), 0, stream, block0, n, k_red,
+                         k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
+    });
   return launch_split<T, double, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
 }
 

@@ -82,17 +82,29 @@ def test_products_cut_along_the_reduction(el, N, k_in, k_out, l_max, dtype):
     run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N)
 
 
+# Channel counts for which a tile would be mostly padding (a thread per result) and their neighbours on the other side of
+# the rule; dX takes it with the counts exchanged.
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype", [
+    (300, 5, 8, 0, "f32"), (300, 6, 8, 0, "f32"), (257, 4, 8, 1, "f64"), (257, 2, 33, 1, "f32"), (255, 2, 8, 2, "f32"),
+    (256, 3, 8, 2, "f64"), (300, 1, 1, 3, "f32"), (100, 4, 4, 3, "f64"), (100, 5, 4, 3, "f32")])
+def test_few_channels(el, N, k_in, k_out, l_max, dtype):
+    run_case(el, N, k_in, k_out, l_max, dtype, 8750 + N)
+
+
 def test_more_tiles_than_a_grid_holds(el):
-    """2^28 atoms with one channel (2^24 tiles of 16 atoms), and one atom with 32 770 channels (2049^2 tiles of dW): more
-    threads than the 2^32 of a grid.  One term per result: a product rounded once."""
+    """2^28 atoms with one channel in and one or nine out (2^24 tiles of 16 atoms), and one atom with 32 770 channels (2049^2
+    tiles of dW): more threads than the 2^32 of a grid.  One term per result: a product rounded once."""
     import torch
     n = 2 ** 28 + 17
     X = torch.randn((n, 1, 1), device="cuda")
-    W = torch.full((1, 1, 1), 1.7, device="cuda")
-    Y = torch.full_like(X, float("nan"))
-    el.el_forward(el.make_config(1, 1, 0), n, X, W, Y)
-    assert torch.equal(Y, X * W)
-    del X, Y
+    for k_out in (1, 9):
+        W = torch.randn((1, 1, k_out), device="cuda")
+        Y = torch.full((n, k_out, 1), float("nan"), device="cuda")
+        el.el_forward(el.make_config(1, k_out, 0), n, X, W, Y)
+        for j in range(k_out):
+            assert torch.equal(Y[:, j], X[:, 0] * W[0, 0, j]), (k_out, j)
+        del Y
+    del X
     k = 32770
     X, dY, dX = torch.randn((1, k, 1), device="cuda"), torch.randn((1, k, 1), device="cuda"), torch.full((1, k, 1), float("nan"), device="cuda")
     W, dW = torch.ones((1, k, k), device="cuda"), torch.full((1, k, k), float("nan"), device="cuda")
