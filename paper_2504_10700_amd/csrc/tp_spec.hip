@@ -6,8 +6,8 @@
 // sums the edges of a receiver):
 //   lane      = channel (64 consecutive channels per wave): a path's weights R[e][p][:] are one
 //               contiguous 256 B row per wave, the sender's features h[j][k][:] 16 B per lane
-//   workgroup = forward: one (receiving atom, 64-channel block); each of its four waves walks every
-//               fourth edge the atom receives and keeps its sum in registers.  Backward: one (sending
+//   workgroup = forward: one (receiving atom, 64-channel block); each of its four waves (two,
+//               waves_per_unit) walks every fourth edge the atom receives and keeps its sum in registers.  Backward: one (sending
 //               atom, 64-channel block); a wave walks every fourth edge the atom sends, keeps the
 //               atom's h row and its dh sum in registers and gathers the receivers' dA rows; per edge
 //               it writes dR and the channel block's partial of dY.  Either way the waves' sums meet in

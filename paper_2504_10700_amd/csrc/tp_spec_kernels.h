@@ -34,8 +34,6 @@ __device__ __forceinline__ void end_of_part(const V&... v) {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-constexpr int kWaves = 4;
-constexpr int kThreads = kWaves * kLanes;
 constexpr int kStageStride = kLanes + 1;  // LDS row stride of the dY transpose (odd: two-way conflicts at most)
 
 // A row of N elements at p: 16-byte accesses and a scalar tail.  p is aligned to 16 B if the row size is
@@ -210,9 +208,9 @@ __device__ __forceinline__ void lane_sum_store(const T* stage, int lane, TS* __r
   if (q == 0 && a < N) out[a] = static_cast<TS>(s);
 }
 
-// The sums of a workgroup's four waves, added in wave order by wave 0; true for that wave.  scratch: kStride >=
+// The sums of a workgroup's waves, added in wave order by wave 0; true for that wave.  scratch: kStride >=
 // N * kLanes values per wave, which nobody else reads or writes any more.
-template <int kStride, typename T, int N>
+template <int kWaves, int kStride, typename T, int N>
 __device__ __forceinline__ bool add_waves(int wave, int lane, T (&acc)[N], T* scratch) {
   static_assert(N * kLanes <= kStride, "the sums of a wave fit its scratch");
   stage_is_free();
@@ -272,14 +270,14 @@ struct Channels {
   }
 };
 
-// A workgroup = one (atom, 64-channel block); its four waves take every fourth edge and add their sums at the end.
-// A wave per (atom, block), four atoms a workgroup, is slower at every size: it walks 20 edges in series where the
-// chip has waves to spare, waits for the atom with the most edges where it has not, and its waves share no rows.
+// A workgroup = one (atom, 64-channel block); its kWaves waves take every kWaves-th edge and add their sums at the end.
+// With twenty edges an atom a wave per (atom, block), four atoms a workgroup, is slower at every size: it walks them in series where
+// the chip has waves to spare, waits for the atom with the most edges where it has not, and its waves share no rows.
 // Forward / backward / second-order pass, us, 128 channels, l_h = 1, wave -> workgroup per (atom, block): 250 atoms
 // 21 -> 9 / 53 -> 24 / 78 -> 37, 2000 40 -> 37 / 100 -> 79 / 230 -> 193, 10 000 243 -> 225 / 500 -> 492 / 859 -> 817; l_h = 2
 // (fp64 arithmetic), 3001 atoms 180 -> 165 / 368 -> 361 / 888 -> 817.
-template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
+template <typename T, typename TS, typename G, bool kFull, int kWaves>
+__global__ __launch_bounds__(kWaves * kLanes) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
                                                            const TS* __restrict__ Y, const TS* __restrict__ h,
                                                            const TS* __restrict__ R,
                                                            const EdgeList el, TS* __restrict__ A) {
@@ -325,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void forward_kernel(int K, int chblocks, 
       }
     }
   }
-  if (!add_waves<kLanes * G::kNout>(wave, lane, acc, out_stage[0])) return;
+  if (!add_waves<kWaves, kLanes * G::kNout>(wave, lane, acc, out_stage[0])) return;
   store_rows_coalesced<TS, T, G::kNout>(A + (node * K + cb * kLanes) * G::kNout, reinterpret_cast<TS*>(out_stage[wave]),
                                         lane, acc, chan.live);
 }
@@ -349,14 +347,14 @@ constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
 
 // The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, 64-channel block).
 // Its waves keep the atom's h row and their dh sums in registers, walk the edges the atom sends
-// (every fourth in send_edge order: with the order of the waves, the order of the sum) and gather
+// (every kWaves-th in send_edge order: with the order of the waves, the order of the sum) and gather
 // per edge the dA row of the receiver (rows of
 // one structure, met in the XCD's L2) next to the edge's own R rows; dR and the channel block's
 // partial of dY leave per edge, dh leaves once per atom: no per-edge shares
 // of dh go to memory and come back.  Atoms that send nothing get a zero row.  Every index is
 // clamped where it is used.
-template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void backward_by_sender_kernel(
+template <typename T, typename TS, typename G, bool kFull, int kWaves>
+__global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void backward_by_sender_kernel(
     int K, int chblocks, int64_t unit0, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
     const TS* __restrict__ h, const TS* __restrict__ R, const int32_t* __restrict__ send_ptr,
     const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const TS* __restrict__ dA,
@@ -455,15 +453,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
       }
     }
   }
-  if (!add_waves<G::kNY * kStageStride>(wave, lane, acc, stage_all[0])) return;
+  if (!add_waves<kWaves, G::kNY * kStageStride>(wave, lane, acc, stage_all[0])) return;
   if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(dh + (node * K + ch) * G::kNh, acc);
 }
 
 // Second-order pass: the backward's walk with the cotangents HR (per edge and path), Hh (at the
 // sender) and HY (wave-uniform) as additional inputs; ddA of the receiver is summed in registers
 // and stored once, d2R / d2Y partial / d2h share leave per edge like dR / dY / dh.
-template <typename T, typename TS, typename G, bool kFull>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void double_backward_kernel(
+template <typename T, typename TS, typename G, bool kFull, int kWaves>
+__global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void double_backward_kernel(
     int K, int chblocks, int64_t unit0, int64_t n_units, int64_t n_edges, const TS* __restrict__ Y, const TS* __restrict__ h,
     const TS* __restrict__ R, const EdgeList el,
     const TS* __restrict__ dA, const TS* __restrict__ HY, const TS* __restrict__ Hh, const TS* __restrict__ HR,
@@ -547,7 +545,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
       }
     }
   }
-  if (!add_waves<G::kNY * kStageStride>(wave, lane, dda, stage_all[0])) return;
+  if (!add_waves<kWaves, G::kNY * kStageStride>(wave, lane, dda, stage_all[0])) return;
   if (kFull || lane < chan.live) store_row<TS, T, G::kNout>(ddA + (node * K + ch) * G::kNout, dda);
 }
 
@@ -565,6 +563,14 @@ hipError_t for_all_units(int64_t n_units, F&& launch) {
   return hipSuccess;
 }
 
+// Waves that share the edges of an atom: four, or two where most atoms have fewer edges than four waves and there are
+// atoms enough to fill the chip with the waves that have one.  Two / four, 128 channels, l_h = 0 and 1, forward, backward, second-order
+// pass: 10 000 atoms with one edge each 0.91, 0.76, 0.78 of the time, with three 0.97, 0.91, 0.87; 30 000 with three 0.96, 0.86, 0.87,
+// with four, l_h = 1, 1.03, 0.93, 0.92, with twenty (10 000, 64 channels) 1.05, 1.2, 1.02; 3000 atoms with two 0.92, 1.1, 0.92.
+int waves_per_unit(int64_t n_edges, int64_t n_atoms, int64_t n_units) {
+  return n_edges <= 3 * n_atoms && n_units >= 8192 ? 2 : 4;
+}
+
 EdgeList edge_list(const FwdArgs& a) {
   return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
 }
@@ -578,8 +584,10 @@ struct Launch {
   static hipError_t forward(const tp_plan* plan, const FwdArgs& a, hipStream_t stream) {
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int64_t n_units = a.n_out_nodes * chblocks;
+    const int waves = waves_per_unit(a.n_edges, a.n_out_nodes, n_units);
+    const auto kernel = waves == 4 ? &forward_kernel<T, TS, G, kFull, 4> : &forward_kernel<T, TS, G, kFull, 2>;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
-      hipLaunchKernelGGL((forward_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0, n_units,
+      hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, chblocks, unit0, n_units,
                          static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R),
                          edge_list(a), static_cast<TS*>(a.A));
     });
@@ -595,10 +603,12 @@ struct Launch {
       if (e != hipSuccess) return e;
     }
     const int64_t n_units = a.n_in * chblocks;
+    const int waves = waves_per_unit(a.n_edges, a.n_in, n_units);
+    const auto kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4> : &backward_by_sender_kernel<T, TS, G, kFull, 2>;
     // without receivers or edges no list is walked: every atom gets its zero row
     const int n_edges = a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
-      hipLaunchKernelGGL((backward_by_sender_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0,
+      hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, chblocks, unit0,
                          n_units, a.n_out_nodes, n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
                          static_cast<const TS*>(a.R), a.send_ptr, a.send_edge, receiver, static_cast<const TS*>(a.dA),
                          static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
@@ -609,8 +619,10 @@ struct Launch {
     const BwdArgs& a = d.b;
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int64_t n_units = a.n_out_nodes * chblocks;
+    const int waves = waves_per_unit(a.n_edges, a.n_out_nodes, n_units);
+    const auto kernel = waves == 4 ? &double_backward_kernel<T, TS, G, kFull, 4> : &double_backward_kernel<T, TS, G, kFull, 2>;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
-      hipLaunchKernelGGL((double_backward_kernel<T, TS, G, kFull>), grid, dim3(kThreads), 0, stream, K, chblocks, unit0,
+      hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, chblocks, unit0,
                          n_units, a.n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
                          static_cast<const TS*>(a.R), edge_list(a), static_cast<const TS*>(a.dA),
                          static_cast<const TS*>(d.HY), static_cast<const TS*>(d.Hh), static_cast<const TS*>(d.HR),

@@ -363,6 +363,14 @@ def test_edges_shared_by_the_waves(tp, mean_degree, K, l, l_h, dtype):
     full_parity(tp, wl_of("shared_edges", 37, mean_degree, K, l, l_h, l, dtype, 5400 + mean_degree))
 
 
+# Two waves an atom: few edges an atom, and 8192 units of an atom and 64 channels or more; the last case has a unit less.
+@pytest.mark.parametrize("N,mean_degree,K,l,l_h,dtype", [
+    (8192, 2, 8, 3, 1, "f32"), (4100, 1, 72, 3, 0, "f32"), (4096, 2, 128, 3, 1, "f32"), (8192, 2, 8, 2, 2, "f32"),
+    (8200, 1, 4, 3, 2, "f64"), (8191, 2, 8, 3, 1, "f32")])
+def test_edges_shared_by_two_waves(tp, N, mean_degree, K, l, l_h, dtype):
+    full_parity(tp, wl_of("two_waves", N, mean_degree, K, l, l_h, l, dtype, 5450 + mean_degree))
+
+
 @pytest.mark.parametrize("flags", [0, 2])
 def test_wrong_index_arrays_stay_inside_the_buffers(tp, flags):
     """The index arrays are not validated, but every index is clamped where it is read: a list with
