@@ -53,23 +53,28 @@ def test_matches_sc_forward_on_calls_in_a_row_with_shrinking_inputs(sc, flags):
     run.close()
 
 
-# Up to 2048 nodes (and 8192 pairs of node and channel block) the waves fold their own weights: the same bits as from
-# the table, on both sides of the limits and around the four nodes of the smallest workgroup.
-@pytest.mark.parametrize("K,l_max,nu,outputs,dtype", [(128, 3, 3, O01, "f32"), (100, 3, 3, O01 + ((2, 1),), "f32"),
-                                                      (64, 3, 3, O01 + ((2, 1), (3, -1)), "bf16"), (72, 3, 3, O01, "f64"),
-                                                      (320, 2, 3, O01, "f32")])
-def test_small_batches(sc, K, l_max, nu, outputs, dtype):
+# In small batches the waves fold their own weights: up to 10 000 nodes and 2.8e6 bytes of W per lane (nodes x 64-channel
+# blocks x paths x bytes of a weight).  The same bits as from the folded table, which a plan with SC_PLAN_WINDOW_ORDER
+# always takes: at the last size of the rule, one node more, and around the four nodes of the smallest workgroup.
+@pytest.mark.parametrize("K,l_max,nu,outputs,dtype,last", [
+    (128, 3, 3, O01, "f32", 4069), (100, 3, 3, O01 + ((2, 1),), "f32", 2201), (64, 3, 3, O01 + ((2, 1), (3, -1)), "bf16", 3030),
+    (72, 3, 3, O01, "f64", 2034), (320, 2, 3, O01, "f32", 3414), (64, 3, 3, O01[:1], "f32", 10_000)])
+def test_small_batches(sc, K, l_max, nu, outputs, dtype, last):
     import torch
-    wl = workloads.Workload("noalloc_small", 2049, 11, K, l_max, nu, outputs, dtype, 5102)
+    wl = workloads.Workload("noalloc_small", last + 1, 11, K, l_max, nu, outputs, dtype, 5102)
     T = osc.build_tables(osc.OracleConfig(wl.num_channels, wl.l_max, wl.nu_max, wl.num_elements, wl.out_irreps))
-    run = GpuRun(sc, wl, workloads.make_inputs(wl, T.paths))
-    for n in (2049, 2048, 1639, 1638, 9, 5, 4, 3, 1):   # 1638 nodes x 5 channel blocks <= 8192
+    per_node = (K + 63) // 64 * len(T.paths) * (8 if dtype == "f64" else 4)
+    assert last == min(10_000, int(2.8e6 // per_node)), "the rule's limit for this plan"
+    inp = workloads.make_inputs(wl, T.paths)
+    run, table = (GpuRun(sc, wl, inp, flags) for flags in (0, sc.SC_PLAN_WINDOW_ORDER))
+    for n in (last + 1, last, 9, 5, 4, 3, 1):
         print(f"sc_forward_noalloc K={K} l_max={l_max} {dtype} n={n}", flush=True)
         B_ws, B_na = (torch.full((n, K, wl.n_LM), float("nan"), dtype=run.tdt, device=run.dev) for _ in range(2))
-        sc.sc_forward(run.plan, n, run.A, run.z, run.W, B_ws, run.ws, run.ws_bytes)
+        sc.sc_forward(table.plan, n, run.A, run.z, run.W, B_ws, table.ws, table.ws_bytes)
         sc.sc_forward_noalloc(run.plan, n, run.A, run.z, run.W, B_na)
-        assert torch.isfinite(B_ws).all() and torch.equal(B_ws, B_na), f"n={n}: results differ from sc_forward"
+        assert torch.isfinite(B_ws).all() and torch.equal(B_ws, B_na), f"n={n}: results differ from those of the table"
     run.close()
+    table.close()
 
 
 def test_fp64_tiny_configuration(sc):
