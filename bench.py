@@ -561,10 +561,11 @@ def measure_linear(n_nodes=10_000, k_in=128, k_out=128, l_max=3, steps=50, warmu
     return {"metric": "atoms/sec per-order channel-mixing linear fwd+bwd", "value": n_nodes / (dt / steps),
             "unit": "nodes/s", "steps": steps, "warmup": warmup, "ms_per_step": dt / steps * 1e3, "dtype": "f32",
             "config": {"workload": f"{n_nodes} nodes, {k_in} -> {k_out} channels, l_max={l_max}, forward+backward",
-                       "kernel": "MFMA 16x16x4 f32"},
+                       "kernel": "MFMA: 16x16x4 f32, or 16x16x32 bf16 on three exact parts of every value, by the size of the product"},
             "roofline": {"bound": "mfma", "kernel": "forward (Y = X W per order)", "achieved": tf,
                          "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / FP32_PEAK_TFLOPS, "traffic": None,
                          "kernel_ms": f_ms, "flops_per_launch": gemm_flops,
+                         "note": "peak of the fp32 instruction, also where the bfloat16 parts are taken",
                          "backward": {"ms": b_ms, "flops": 2 * gemm_flops,
                                       "achieved": 2 * gemm_flops / (b_ms * 1e-3) / 1e12}}}
 
