@@ -156,32 +156,40 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     forward_lds_unit<2>(n_nodes, unit / groups * 16, static_cast<int>(unit % groups) * 2, k_red, k_cols, X, W, Y, xs);
 }
 
-// The same product on the bfloat16 matrix cores (split_tile_product), k_red % 32 == 0: a workgroup of eight waves per
-// unit of 16 atoms x 128 columns, 128 registers, two workgroups per CU.  The matrix work is half of the fp32 instruction's;
-// what bounds it: requests of X, splitting, reads of LDS and products of a workgroup mostly follow one another, and units are
-// large (bf16_parts_ok).  Forward on inputs from memory, us, mfma_forward_lds_kernel -> this kernel: 128 -> 128 channels, 4096 atoms
-// 37.9 -> 27.8, 8192 60.0 -> 46.0, 16 384 101 -> 88, 24 000 141 -> 127; 256 -> 256, 4096 atoms 108 -> 70; 256 -> 128, 3000 atoms
-// 69 -> 45; 512 -> 128, 4096 atoms 140 -> 84.  Error against 64 bits (2-norm, relative), 128 / 256 / 512 channels summed: 0.73e-7,
-// 1.0e-7, 1.5e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7, 4.0e-7 (32 products per rounding of the sum, not four); of one nonzero
-// weight per column, largest: 5.99e-8 and 5.96e-8; of two, 2-norm: 3.7e-8 and 3.1e-8.
+// The same product on the bfloat16 matrix cores (SplitPass), k_red % 32 == 0: one workgroup of eight waves per CU (256 registers), which
+// walks its share of the row tiles of its 128 columns, two tiles a pass.  What bounds it at 8192 atoms and 128 -> 128 channels (two tiles per
+// CU, 41 us): 29 us for the rows at the rate of a large copy, 15 us of products, 8 us of stores at the end of the pass with nothing left to
+// overlap them.  Forward on inputs from memory, us, before (two workgroups per CU, each with one tile and its own split of
+// W; at 10 000 and 12 288 atoms mfma_forward_lds_kernel) -> this: 128 -> 128 channels, 4096 atoms 26.9 -> 23.1, 5000 33.0 -> 33.7, 8192
+// 42.3 -> 40.6, 10 000 60.8 -> 55.5, 12 288 65.0 -> 58.3, 24 000 119 -> 113; 256 -> 256, 6000 atoms 99.9 -> 95.4; 256 -> 128, 4096 atoms
+// 47.2 -> 37.7; 512 -> 128, 3000 atoms 75 -> 58.  The pairs of X split in the first half of a step, right behind their requests: 4096
+// atoms 24.2, 10 000 56.6.  One tile a pass with requests two steps ahead: 24.2 and 55.3, 256 -> 256 6000 atoms 96.6.  Error against 64 bits
+// (2-norm, relative), 128 / 256 / 512 channels summed: 0.73e-7, 1.0e-7, 1.5e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7,
+// 4.0e-7 (32 products per rounding of the sum, not four); of one nonzero weight per column, largest: 5.99e-8 and 5.96e-8; of
+// two, 2-norm: 3.7e-8 and 3.1e-8.
 // kTrans: W is [L][k_cols][k_red], dX reads the weights of the forward as they are.
+template <bool kTrans, int G>
+__device__ __forceinline__ void split_passes(const SplitArgs& p, int64_t t0, int64_t t1, int j0, unsigned* lds, int* x_bad) {
+  int64_t t = t0;
+  for (; t + kSplitRows <= t1; t += kSplitRows) SplitPass<kSplitRows, kTrans, G>::run(p, t * 16, j0, lds, x_bad);
+  if (t < t1) SplitPass<1, kTrans, G>::run(p, t * 16, j0, lds, x_bad);
+}
+
 template <bool kTrans>
-__global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void mfma_forward_bf16_kernel(
+__global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_forward_bf16_kernel(
     int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W,
     float* __restrict__ Y) {
-  __shared__ __attribute__((aligned(16))) unsigned planes[3 * kSplitPlane];
-  static_assert(kSplitWaves * kStoreStageFloats <= 3 * kSplitPlane, "the store stages reuse the planes");
-  const int groups = k_cols / 128;
-  const int64_t n0 = blockIdx.x / groups * int64_t(16);
-  const int j0 = static_cast<int>(blockIdx.x % groups) * 128;
-  Mma<float>::acc_t acc[16][1];
-  bool x_served;
-  const bool served = split_tile_product<kTrans>(n_nodes, n0, j0, k_red, k_cols, X, W, planes, acc, x_served);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-  const int jc[1] = {j0 + wave * 16 + static_cast<int>(threadIdx.x % 16)};
-  // (also the barrier after which the planes are free)
-  if (__syncthreads_or(!x_served) || !served) plain_tile_product<kTrans>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
-  store_tile_coalesced<1>(Y, n_nodes, n0, k_cols, jc, acc, reinterpret_cast<float*>(planes) + wave * kStoreStageFloats);
+  __shared__ __attribute__((aligned(16))) unsigned lds[2 * kSplitSlot];
+  __shared__ int x_bad;
+  const int groups = k_cols / 128, ranges = gridDim.x / groups;
+  const int j0 = static_cast<int>(blockIdx.x % groups) * 128, range = blockIdx.x / groups;
+  const int64_t tiles = (n_nodes + 15) / 16;
+  const int64_t t0 = tiles * range / ranges, t1 = tiles * (range + 1) / ranges;
+  const SplitArgs p{n_nodes, k_red, k_cols, X, W, Y};
+  if (__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) < kSplitThreads / 2)
+    split_passes<kTrans, 0>(p, t0, t1, j0, lds, &x_bad);
+  else
+    split_passes<kTrans, 1>(p, t0, t1, j0, lds, &x_bad);
 }
 
 // Partial dW of a range of atoms: part[range][l][k][j] = sum_{n in range} sum_{m in l} X[n][k][c] dY[n][j][c].
@@ -687,22 +695,21 @@ bool few_channels(int l_max, int k_red, int k_cols) {
 bool dx_reads_w_as_is(int64_t n, int k_cols) { return (n + 15) / 16 * (k_cols / 16) <= compute_units(); }
 
 // Is the product served by mfma_forward_bf16_kernel, beyond the batches of split_forward_kernel?  (Its 31-bit offsets into W
-// go through a buffer descriptor.)  With up to 128 channels summed it gains least per unit and needs the units even over the CUs:
-// between two and five units per CU not where less than half of the CUs get one more (forward, 128 -> 128 channels, us,
-// mfma_forward_lds_kernel / this kernel: 2.03 units per CU 60 / 64, 2.44 62 / 65, 2.69 76 / 68, 3.42 78 / 83, 4.0 101 / 88, 4.39
-// 103 / 106, 5.03 119 / 119, 5.9 141 / 127); with 32 channels, not beyond two units per CU (4.9: 45 / 47).
+// go through a buffer descriptor.)  With up to 64 channels summed a pass is mostly the split of its W and its stores: beyond two row tiles
+// per CU not with 32 channels, and with 64 not where less than half of the CUs get one more of two to five (forward, 32 -> 128 channels, us,
+// mfma_forward_lds_kernel / this kernel: 10 000 atoms 27.7 / 31.1, 48 000 104 / 114; 64 -> 128, 10 000 atoms 38.5 / 40.3, 20 000 70 / 69).
 bool bf16_parts_ok(size_t elem, int l_max, int64_t n, int k_red, int k_cols) {
   if (!(elem == 4 && l_max == 3 && k_cols % 128 == 0 && k_red % kSplitChunk == 0 && mfma_forward_ok(k_red, k_cols) &&
         static_cast<int64_t>(k_red) * k_cols < (int64_t(1) << 26) && !split_small(elem, n, k_cols)))
     return false;
   const int64_t cus = compute_units(), units = (n + 15) / 16 * (k_cols / 128), more = units % cus;
-  if (units <= 2 * cus) return true;
-  return k_red >= 64 && (k_red > 128 || units > 5 * cus || more == 0 || more > cus / 2);
+  if (units <= 2 * cus || k_red > 64) return true;
+  return k_red == 64 && (units > 5 * cus || more == 0 || more > cus / 2);
 }
 
-// ... whose dX reads W as it is: a lane's channels are contiguous there and the launch that transposes W is saved.  Backward, us, W
-// transposed / as it is: 128 -> 128 channels, 2100 atoms 60.8 / 57.8, 8192 108 / 100, 20 480 237 / 226; 256 -> 128, 3000 atoms 87.4 /
-// 83.5, 20 000 429 / 407; 256 -> 256, 20 000 atoms 716 / 714.
+// ... whose dX reads W as it is: a lane's channels are contiguous there and the launch that transposes W is saved.  (Backward, us, with
+// the kernel of two workgroups per CU, W transposed / as it is: 128 -> 128 channels, 2100 atoms 60.8 / 57.8, 8192 108 / 100, 20 480
+// 237 / 226; 256 -> 128, 3000 atoms 87.4 / 83.5, 20 000 429 / 407; 256 -> 256, 20 000 atoms 716 / 714.)
 bool dx_parts_read_w_as_is(const el_config* c, int64_t n) {
   return bf16_parts_ok(elem_size(c), c->l_max, n, c->k_out, c->k_in);
 }
@@ -731,8 +738,9 @@ template <typename T, int LMAX, bool kTrans>
 hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
   if constexpr (sizeof(T) == 4 && LMAX == 3) {
     if (bf16_parts_ok(sizeof(T), LMAX, n, k_red, k_cols)) {
-      const int64_t units = (n + 15) / 16 * (k_cols / 128);
-      hipLaunchKernelGGL((mfma_forward_bf16_kernel<kTrans>), dim3(static_cast<unsigned>(units)), dim3(kSplitThreads), 0, stream,
+      const int groups = k_cols / 128;
+      const int64_t ranges = std::min<int64_t>((n + 15) / 16, std::max(1, compute_units() / groups));
+      hipLaunchKernelGGL((mfma_forward_bf16_kernel<kTrans>), dim3(static_cast<unsigned>(ranges * groups)), dim3(kSplitThreads), 0, stream,
                          n, k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
       return hipGetLastError();
     }
