@@ -20,7 +20,7 @@
 // dW: rows = 16 input channels, columns = 16 output channels, reduction = atoms (four per
 // MFMA) and the components of the order; A and B operands are again 64 contiguous bytes per
 // lane.  The atoms are cut into ranges, every range writes a partial dW (mfma_dw_lds_kernel:
-// dY rows shared through LDS, two row tiles per wave; mfma_dw_kernel: every other shape), a
+// both operands through a ring in LDS; mfma_dw_kernel: every other shape), a
 // second kernel adds the partials in a fixed order (no atomics).
 // Channel counts outside these tilings: split_forward_kernel and split_dw_kernel (fp64 products and sums).
 #include <algorithm>
@@ -245,123 +245,125 @@ __global__ __launch_bounds__(kThreads) void mfma_dw_kernel(int64_t n_nodes, int 
         out[(static_cast<size_t>(l) * k_in + kt + Mma<T>::row(lane, r)) * k_out + j0 + t * 16] = acc[l][t][r];
 }
 
-// The same partial dW for fp32, l_max = 3 and k_in a multiple of 128, with more reuse per loaded
-// byte: the workgroup owns 128 input channels x 64 output channels (wave w: two row tiles, 32
-// input channels, against all four column tiles: 32 accumulator blocks), the dY rows of a
-// reduction step (4 atoms x 64 channels x 64 B = 16 KB) are loaded once per workgroup and shared
-// through LDS (two buffers, rows padded to 80 B against bank conflicts), X rows come straight from
-// global memory; both are requested one step ahead.  Per MFMA a wave reads 96 B instead of 320 B.
-// One workgroup per CU (the accumulators and two operand sets fill the register file).
-constexpr int kDwRow = 20;   // floats per (atom, output channel) row of dY in LDS
+// The same partial dW for fp32, l_max = 3 and k_in a multiple of 128.  A workgroup of eight waves owns 128 input x 64 output channels, a
+// wave 32 x 32 of them with all orders (64 accumulator registers; the 32x32x2 instruction: lane L supplies row L % 32 and atom
+// L / 32).  X and dY reach the matrix cores through LDS, written there by the memory path itself (loads straight to LDS, no
+// registers) in a ring of chunks of four atoms, two of them under way; the operands of two atoms are read before the products of
+// the two before them.  One workgroup per CU.
+// What bounds it at 10 000 atoms, 128 -> 128 channels (62 us): 34 us of products at 2.4 GHz, which these products do not hold (54 us where
+// all values are zero), 5 us for the partial results, 6 us until the first rows are there.  Four waves with X straight in registers and dY
+// through them to LDS needed the range in steps of 16 atoms: backward, us, that -> this: 40 atoms 28.0 -> 26.7, 2100 53.8 -> 47.0,
+// 10 000 121.1 -> 120.3; 256 -> 128, 2100 atoms 81.2 -> 74.0, 24 000 456 -> 458.
+constexpr int kDwRingWaves = 8;
+constexpr int kDwRingThreads = kDwRingWaves * kLanes;
+constexpr int kDwSlots = 3, kDwChunk = 4;                     // chunks of the ring, atoms of a chunk
+constexpr int kDwIn = 128, kDwOut = 64;                       // channels of a workgroup
+constexpr int kDwAtom = (kDwIn + kDwOut) * 16;                // floats of an atom in LDS: rows of X, then of dY
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void mfma_dw_lds_kernel(
+__global__ __launch_bounds__(kDwRingThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_dw_lds_kernel(
     int64_t n_nodes, int nodes_per_range, int k_in, int k_out, const float* __restrict__ X,
     const float* __restrict__ dY, float* __restrict__ part) {
-  constexpr int NC = 16, L = 4, NT = 4, NU = 2;
-  typedef Mma<float>::acc_t acc_t;
   typedef float V4 __attribute__((ext_vector_type(4)));
-  __shared__ __attribute__((aligned(16))) float ys[2][4 * 64 * kDwRow];
-  const int lane = threadIdx.x & (kLanes - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-  const int jgroups = k_out / 64, kgroups = k_in / 128;
-  const int jg = blockIdx.x % jgroups;
-  const int kg = (blockIdx.x / jgroups) % kgroups;
-  const int64_t range = blockIdx.x / (jgroups * kgroups);
+  typedef float V16 __attribute__((ext_vector_type(16)));
+  constexpr int L = 4;
+  __shared__ __attribute__((aligned(16))) float ring[kDwSlots * kDwChunk * kDwAtom];
+  const int lane = threadIdx.x % kLanes;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
+  const int jgroups = k_out / kDwOut, kgroups = k_in / kDwIn;
+  // (the workgroups of a range, which read the same rows, on one XCD: they meet in its L2)
+  const int own = static_cast<int>(gridDim.x), at = static_cast<int>(blockIdx.x);
+  const int per_xcd = own / 8, extra = own % 8, xcd = at % 8;
+  const int block = xcd * per_xcd + (xcd < extra ? xcd : extra) + at / 8;
+  const int j0 = block % jgroups * kDwOut;
+  const int k0 = block / jgroups % kgroups * kDwIn;
+  const int64_t range = block / (jgroups * kgroups);
   const int64_t r0 = range * nodes_per_range;
   const int64_t r1 = (r0 + nodes_per_range < n_nodes) ? r0 + nodes_per_range : n_nodes;
-  const int steps = static_cast<int>((r1 - r0 + 3) / 4);
-  const int kt = kg * 128 + wave * 32;                       // first input channel of this wave
-  const int j0 = jg * 64;                                    // first output channel of the workgroup
-  const int la = lane / 16;                                  // this lane's atom within a reduction step
-  // staging role of this thread: atom tid/64 of the step, output channel tid%64 of the group
-  const int sa = threadIdx.x / 64, sj = threadIdx.x % 64;
-  float* const swr = &ys[0][(sa * 64 + sj) * kDwRow];
-  const float* const brd = &ys[0][(la * 64 + (lane & 15)) * kDwRow];   // column tile 0, this lane's row
+  const int chunks = static_cast<int>((r1 - r0 + kDwChunk - 1) / kDwChunk);   // at least one
 
-  acc_t acc[L][NU][NT];
+  // A chunk: per wave half an atom, four KB of X (16 channels each) and two of dY.  The four 16-byte pieces of a row are permuted
+  // by its channel so that the operand reads meet no bank twice.
+  const int piece = (lane / 4) * 64 + ((lane % 4) ^ (lane / 16)) * 16;
+  auto request = [&](int chunk, int slot) {                    // (past the end: the last chunk again)
+    int64_t n = r0 + kDwChunk * static_cast<int64_t>(chunk < chunks ? chunk : chunks - 1) + wave / 2;
+    if (n >= r1) n = r1 - 1;                                   // an atom past the end is a copy that is zeroed when it is read
+    float* const to = ring + (slot * kDwChunk + wave / 2) * kDwAtom;
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(X + (static_cast<size_t>(n) * k_in + k0) * 16), 0, kDwIn * 64, 0x00020000);
+    const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(dY + (static_cast<size_t>(n) * k_out + j0) * 16), 0, kDwOut * 64, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int block = wave % 2 * 4 + i;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (__attribute__((address_space(3))) void*)(to + block * 256), 16, piece, block * 1024, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int block = wave % 2 * 2 + i;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(yrs, (__attribute__((address_space(3))) void*)(to + kDwIn * 16 + block * 256), 16, piece,
+                                               block * 1024, 0, 0);
+    }
+  };
+  constexpr int kRequests = 6;
+
+  const int i32 = lane % 32, h = lane / 32, wi = wave / 2, wj = wave % 2;
+  struct Operands {
+    V4 a[4], b[4];
+  };
+  int aoff[4];                                                 // floats; the columns of the wave lie at a constant distance
+#pragma unroll
+  for (int p = 0; p < 4; ++p) aoff[p] = h * kDwAtom + i32 * 16 + (p ^ (i32 / 4 % 4)) * 4;
+  auto read = [&](int slot, int chunk, int half, Operands& o) {
+    const float* const s = ring + (slot * kDwChunk + half * 2) * kDwAtom;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      o.a[p] = *reinterpret_cast<const V4*>(s + wi * 512 + aoff[p]);
+      o.b[p] = *reinterpret_cast<const V4*>(s + (kDwIn / 32 + wj) * 512 + aoff[p]);
+    }
+    const int64_t n = r0 + kDwChunk * static_cast<int64_t>(chunk) + half * 2;
+    if (n + 1 >= r1 && n + h >= r1) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o.a[p] = o.b[p] = V4{0, 0, 0, 0};
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  V16 acc[L];
 #pragma unroll
   for (int l = 0; l < L; ++l)
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
+    for (int r = 0; r < 16; ++r) acc[l][r] = 0;
+  auto multiply = [&](const Operands& o) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[l][u][t] = acc_t{0, 0, 0, 0};
+    for (int c = 0; c < 16; ++c)
+      acc[order_of(c)] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[c / 4][c % 4], o.b[c / 4][c % 4], acc[order_of(c)], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // All but the requests of one chunk of this wave are served, its reads are done, and every wave is here.
+  auto meet = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kRequests) : "memory"); };
 
-  // rows past the end of the range: a valid atom's address, A operands zeroed
-  auto aload = [&](int step, V4 (&a)[NU][4]) {
-    const int64_t n = r0 + step * 4 + la;
-    const int64_t nc = n < r1 ? n : r1 - 1;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const V4* p = reinterpret_cast<const V4*>(X + (static_cast<size_t>(nc) * k_in + kt + u * 16 + (lane & 15)) * NC);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[u][i] = n < r1 ? p[i] : V4{0, 0, 0, 0};
-    }
-  };
-  auto yload = [&](int step, V4 (&y)[4]) {
-    const int64_t n = r0 + step * 4 + sa;
-    const int64_t nc = n < r1 ? n : r1 - 1;
-    const V4* p = reinterpret_cast<const V4*>(dY + (static_cast<size_t>(nc) * k_out + j0 + sj) * NC);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = p[i];
-  };
-  auto ystage = [&](int buf, const V4 (&y)[4]) {
-    V4* p = reinterpret_cast<V4*>(swr + buf * 4 * 64 * kDwRow);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = y[i];
-  };
-  auto multiply = [&](int buf, const V4 (&a)[NU][4]) {
-    const float* bb = brd + buf * 4 * 64 * kDwRow;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {             // a quarter of the components at a time
-      V4 b[NT];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) b[t] = *reinterpret_cast<const V4*>(bb + t * 16 * kDwRow + q * 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)             // component c = 4 q + i; consecutive MFMAs use different accumulators
-#pragma unroll
-        for (int u = 0; u < NU; ++u)
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-            acc[order_of(4 * q + i)][u][t] = Mma<float>::mma(a[u][q][i], b[t][i], acc[order_of(4 * q + i)][u][t]);
-    }
-  };
-
-  // Operands are requested TWO steps before their use (a step is ~2 us of matrix work, about the
-  // memory latency under load; one step of lead left ~1.5 us of stall per step).  Four A sets and
-  // two dY register sets rotate with period four: the loop is unrolled by four and has no branch
-  // inside (past the end of the range the A operands are zero and the addresses clamped, so the
-  // padding steps add nothing), which keeps the compiler's wait counts exact.
-  if (steps > 0) {
-    const int padded = (steps + 3) / 4 * 4;
-    V4 a[4][NU][4], yr[2][4];
-    aload(0, a[0]);
-    yload(0, yr[0]);
-    aload(1, a[1]);
-    yload(1, yr[1]);
-    ystage(0, yr[0]);
-    __syncthreads();
-    for (int s = 0; s < padded; s += 4) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        aload(s + i + 2, a[(i + 2) & 3]);
-        yload(s + i + 2, yr[i & 1]);              // (the set that held step s+i, staged a step ago)
-        multiply(i & 1, a[i]);
-        ystage((i + 1) & 1, yr[(i + 1) & 1]);     // step s+i+1, requested a step ago
-        __syncthreads();
-      }
-    }
+  Operands o0, o1;
+  request(0, 0);
+  request(1, 1);
+  meet();
+  request(2, 2);
+  read(0, 0, 0, o0);
+  int slot = 0;
+  for (int c = 0; c < chunks; ++c) {
+    read(slot, c, 1, o1);
+    multiply(o0);
+    meet();                                                    // chunk c + 1 is here, chunk c has been read by all
+    request(c + kDwSlots, slot);
+    slot = slot == kDwSlots - 1 ? 0 : slot + 1;
+    read(slot, c + 1, 0, o0);
+    multiply(o1);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // no request may reach LDS after the workgroup has given it back
   float* out = part + static_cast<size_t>(range) * L * k_in * k_out;
 #pragma unroll
   for (int l = 0; l < L; ++l)
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          out[(static_cast<size_t>(l) * k_in + kt + u * 16 + Mma<float>::row(lane, r)) * k_out + j0 + t * 16 + (lane & 15)] =
-              acc[l][u][t][r];
+    for (int r = 0; r < 16; ++r)                               // rows 8 (r / 4) + 4 (lane / 32) + r % 4 of the 32 x 32 result
+      out[(static_cast<size_t>(l) * k_in + k0 + wi * 32 + r / 4 * 8 + h * 4 + r % 4) * k_out + j0 + wj * 32 + i32] = acc[l][r];
 }
 
 // dW[i] = sum of part[r][i] over the ranges r.  A workgroup of four waves owns 64 elements; wave
@@ -805,8 +807,8 @@ hipError_t dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, 
   const int ranges = static_cast<int>((n + per - 1) / per);
   if constexpr (sizeof(T) == 4 && LMAX == 3) {
     if (dw_lds_ok(cfg)) {
-      const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(ranges) * (cfg->k_in / 128) * (cfg->k_out / 64));
-      hipLaunchKernelGGL(mfma_dw_lds_kernel, dim3(grid), dim3(kThreads), 0, stream, n, per, cfg->k_in, cfg->k_out,
+      const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(ranges) * (cfg->k_in / kDwIn) * (cfg->k_out / kDwOut));
+      hipLaunchKernelGGL(mfma_dw_lds_kernel, dim3(grid), dim3(kDwRingThreads), 0, stream, n, per, cfg->k_in, cfg->k_out,
                          static_cast<const float*>(X), static_cast<const float*>(dY), static_cast<float*>(ws));
       hipLaunchKernelGGL((dw_reduce_kernel<T>), dim3(static_cast<unsigned>((elems + 63) / 64)), dim3(256), 0, stream,
                          elems, ranges, static_cast<const T*>(ws), static_cast<T*>(dW));
