@@ -26,6 +26,8 @@
 #include <algorithm>
 #include <atomic>
 #include <string>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/el.h"
 #include "el_tile.h"
@@ -37,6 +39,91 @@ namespace {
 using sc::DeviceGuard;
 using sc::misaligned;
 using sc::set_error;
+
+// ---- work that rides in another launch of the backward (a launch of its own costs 5 to 9 us): W transposed in the dW
+// launch, for the dX that follows it; the sum of the partial dW in the dX launch.
+
+// Wt[l][j][k] = W[l][k][j]: the dX product then reads its B operands along rows like the forward.
+template <typename T>
+struct Transpose {
+  const T* W;
+  T* Wt;
+  int n_l, k_in, k_out;
+  int blocks;                                  // workgroups that do it, before those of the launch itself: a multiple of 8 (XCDs), 0: none
+};
+
+template <typename T>
+__device__ __forceinline__ void transpose_role(const Transpose<T>& t, int block) {
+  const int64_t n = static_cast<int64_t>(t.n_l) * t.k_in * t.k_out;
+  for (int64_t i = block * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n; i += static_cast<int64_t>(t.blocks) * blockDim.x) {
+    const int k = static_cast<int>(i % t.k_in), j = static_cast<int>(i / t.k_in % t.k_out);
+    const int l = static_cast<int>(i / (static_cast<int64_t>(t.k_in) * t.k_out));
+    t.Wt[i] = t.W[(static_cast<size_t>(l) * t.k_in + k) * t.k_out + j];
+  }
+}
+
+// dW[i] = sum of part[r][i] over the ranges r, a slice of 64 lanes x 16 bytes at a time.  Four waves share a slice; wave
+// q adds the q-th quarter of the ranges (eight sums in turn, sixteen requests in flight, combined in a fixed tree), the four quarter
+// sums are added in wave order: a fixed order altogether, so the result is bitwise reproducible.
+template <typename T>
+struct RangeSum {
+  const T* part;
+  T* dW;
+  int64_t elems;                               // a multiple of kSlice
+  int ranges;                                  // 0: nothing to add
+  static constexpr int V = 16 / sizeof(T), kSlice = 64 * V;
+};
+
+// The slices first, first + stride, ...; quarter: 4 x kSlice elements of LDS per four waves.  Called by all waves of the workgroup.
+template <typename T>
+__device__ __forceinline__ void add_ranges(const RangeSum<T>& s, int64_t first, int64_t stride, T* quarter) {
+  constexpr int V = RangeSum<T>::V, kSlice = RangeSum<T>::kSlice, U = 8;
+  typedef T Vec __attribute__((ext_vector_type(V)));
+  const int lane = threadIdx.x % kLanes, q = threadIdx.x / kLanes % 4, team = threadIdx.x / 256, teams = blockDim.x / 256;
+  const int ra = s.ranges * q / 4, rb = s.ranges * (q + 1) / 4;
+  T* const mine = quarter + team * 4 * kSlice;
+  for (int64_t s0 = first * teams; s0 * kSlice < s.elems; s0 += stride * teams) {
+    const int64_t i = (s0 + team) * kSlice + lane * V;
+    const bool live = i < s.elems;
+    Vec a[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int v = 0; v < V; ++v) a[k][v] = T(0);
+    if (live) {
+      const T* src = s.part + i;
+      int r = ra;
+      for (; r + 2 * U <= rb; r += 2 * U) {
+        Vec x[2 * U];
+#pragma unroll
+        for (int k = 0; k < 2 * U; ++k) x[k] = *reinterpret_cast<const Vec*>(src + static_cast<size_t>(r + k) * s.elems);
+#pragma unroll
+        for (int k = 0; k < 2 * U; ++k) a[k % U] += x[k];
+      }
+      for (; r + U <= rb; r += U) {
+        Vec x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) x[k] = *reinterpret_cast<const Vec*>(src + static_cast<size_t>(r + k) * s.elems);
+#pragma unroll
+        for (int k = 0; k < U; ++k) a[k] += x[k];
+      }
+      for (; r < rb; ++r) a[0] += *reinterpret_cast<const Vec*>(src + static_cast<size_t>(r) * s.elems);
+    }
+#pragma unroll
+    for (int w = U / 2; w >= 1; w /= 2)
+#pragma unroll
+      for (int k = 0; k < w; ++k) a[k] += a[k + w];
+    *reinterpret_cast<Vec*>(mine + q * kSlice + lane * V) = a[0];
+    __syncthreads();
+    if (q == 0 && live) {
+      Vec y = a[0];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) y += *reinterpret_cast<const Vec*>(mine + w * kSlice + lane * V);
+      *reinterpret_cast<Vec*>(s.dW + i) = y;
+    }
+    __syncthreads();
+  }
+}
 
 // Y[n][j][c] = sum_k X[n][k][c] * W[l(c)][k][j], W is [L][k_red][k_cols] (the dX product of the
 // backward passes W transposed, so that both read their B operands along rows of W).
@@ -175,21 +262,32 @@ __device__ __forceinline__ void split_passes(const SplitArgs& p, int64_t t0, int
   if (t < t1) SplitPass<1, kTrans, G>::run(p, t * 16, j0, lds, x_bad);
 }
 
+// sum: partial dW to add up, after the row tiles: by the workgroups that have one tile less than others and would wait for them (16 us
+// at 128 channels, more than their share of the sum takes), if they are a quarter of all or more, and by all otherwise.
 template <bool kTrans>
 __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_forward_bf16_kernel(
     int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W,
-    float* __restrict__ Y) {
+    float* __restrict__ Y, RangeSum<float> sum) {
   __shared__ __attribute__((aligned(16))) unsigned lds[2 * kSplitSlot];
   __shared__ int x_bad;
   const int groups = k_cols / 128, ranges = gridDim.x / groups;
-  const int j0 = static_cast<int>(blockIdx.x % groups) * 128, range = blockIdx.x / groups;
+  const int group = blockIdx.x % groups, range = blockIdx.x / groups;
   const int64_t tiles = (n_nodes + 15) / 16;
   const int64_t t0 = tiles * range / ranges, t1 = tiles * (range + 1) / ranges;
   const SplitArgs p{n_nodes, k_red, k_cols, X, W, Y};
   if (__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) < kSplitThreads / 2)
-    split_passes<kTrans, 0>(p, t0, t1, j0, lds, &x_bad);
+    split_passes<kTrans, 0>(p, t0, t1, group * 128, lds, &x_bad);
   else
-    split_passes<kTrans, 1>(p, t0, t1, j0, lds, &x_bad);
+    split_passes<kTrans, 1>(p, t0, t1, group * 128, lds, &x_bad);
+  if constexpr (kTrans) {
+    if (sum.ranges == 0) return;
+    const int64_t few = tiles / ranges;
+    const int less = static_cast<int>(ranges - tiles % ranges);              // ranges with `few` tiles (all, if they divide evenly)
+    static_assert(8 * RangeSum<float>::kSlice <= 2 * kSplitSlot, "the quarter sums reuse the planes");
+    float* const quarter = reinterpret_cast<float*>(lds);
+    if (4 * less < ranges) add_ranges(sum, blockIdx.x, gridDim.x, quarter);
+    else if (t1 - t0 == few) add_ranges(sum, (range - (t0 - range * few)) * groups + group, static_cast<int64_t>(less) * groups, quarter);
+  }
 }
 
 // Partial dW of a range of atoms: part[range][l][k][j] = sum_{n in range} sum_{m in l} X[n][k][c] dY[n][j][c].
@@ -198,15 +296,17 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2
 template <typename T, int LMAX, int NT>
 __global__ __launch_bounds__(kThreads) void mfma_dw_kernel(int64_t n_nodes, int nodes_per_range, int k_in, int k_out,
                                                            const T* __restrict__ X, const T* __restrict__ dY,
-                                                           T* __restrict__ part) {
+                                                           T* __restrict__ part, Transpose<T> tr) {
   constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
   typedef typename Mma<T>::acc_t acc_t;
+  if (static_cast<int>(blockIdx.x) < tr.blocks) return transpose_role(tr, static_cast<int>(blockIdx.x));
+  const int block = static_cast<int>(blockIdx.x) - tr.blocks;
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
   const int jgroups = k_out / (16 * NT), kgroups = k_in / 64;
-  const int jg = blockIdx.x % jgroups;
-  const int kg = (blockIdx.x / jgroups) % kgroups;
-  const int64_t range = blockIdx.x / (jgroups * kgroups);
+  const int jg = block % jgroups;
+  const int kg = (block / jgroups) % kgroups;
+  const int64_t range = block / (jgroups * kgroups);
   const int64_t r0 = range * nodes_per_range;
   const int64_t r1 = (r0 + nodes_per_range < n_nodes) ? r0 + nodes_per_range : n_nodes;
   const int k = (kg * kWaves + wave) * 16 + (lane & 15);   // row (input channel) of this lane's A operands
@@ -262,7 +362,7 @@ constexpr int kDwAtom = (kDwIn + kDwOut) * 16;                // floats of an at
 
 __global__ __launch_bounds__(kDwRingThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_dw_lds_kernel(
     int64_t n_nodes, int nodes_per_range, int k_in, int k_out, const float* __restrict__ X,
-    const float* __restrict__ dY, float* __restrict__ part) {
+    const float* __restrict__ dY, float* __restrict__ part, Transpose<float> tr) {
   typedef float V4 __attribute__((ext_vector_type(4)));
   typedef float V16 __attribute__((ext_vector_type(16)));
   constexpr int L = 4;
@@ -271,7 +371,8 @@ __global__ __launch_bounds__(kDwRingThreads) __attribute__((amdgpu_waves_per_eu(
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
   const int jgroups = k_out / kDwOut, kgroups = k_in / kDwIn;
   // (the workgroups of a range, which read the same rows, on one XCD: they meet in its L2)
-  const int own = static_cast<int>(gridDim.x), at = static_cast<int>(blockIdx.x);
+  if (static_cast<int>(blockIdx.x) < tr.blocks) return transpose_role(tr, static_cast<int>(blockIdx.x));
+  const int own = static_cast<int>(gridDim.x) - tr.blocks, at = static_cast<int>(blockIdx.x) - tr.blocks;
   const int per_xcd = own / 8, extra = own % 8, xcd = at % 8;
   const int block = xcd * per_xcd + (xcd < extra ? xcd : extra) + at / 8;
   const int j0 = block % jgroups * kDwOut;
@@ -366,40 +467,11 @@ __global__ __launch_bounds__(kDwRingThreads) __attribute__((amdgpu_waves_per_eu(
       out[(static_cast<size_t>(l) * k_in + k0 + wi * 32 + r / 4 * 8 + h * 4 + r % 4) * k_out + j0 + wj * 32 + i32] = acc[l][r];
 }
 
-// dW[i] = sum of part[r][i] over the ranges r.  A workgroup of four waves owns 64 elements; wave
-// q adds the q-th quarter of the ranges (eight independent loads in flight, partial sums
-// combined in a fixed tree), the four quarter sums are added in wave order: a fixed order
-// altogether, so the result is bitwise reproducible.
+// The sum of the partial dW as a launch of its own.
 template <typename T>
-__global__ __launch_bounds__(256) void dw_reduce_kernel(int64_t n_elems, int n_ranges, const T* __restrict__ part,
-                                                        T* __restrict__ dW) {
-  __shared__ T quarter[4][64];
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int64_t i = blockIdx.x * int64_t(64) + lane;
-  const int ra = n_ranges * q / 4, rb = n_ranges * (q + 1) / 4;
-  constexpr int U = 8;
-  T a[U];
-#pragma unroll
-  for (int k = 0; k < U; ++k) a[k] = T(0);
-  if (i < n_elems) {
-    const T* src = part + i;
-    int r = ra;
-    for (; r + U <= rb; r += U) {
-      T v[U];
-#pragma unroll
-      for (int k = 0; k < U; ++k) v[k] = src[static_cast<size_t>(r + k) * n_elems];
-#pragma unroll
-      for (int k = 0; k < U; ++k) a[k] += v[k];
-    }
-    for (; r < rb; ++r) a[0] += src[static_cast<size_t>(r) * n_elems];
-  }
-#pragma unroll
-  for (int w = U / 2; w >= 1; w /= 2)
-#pragma unroll
-    for (int k = 0; k < w; ++k) a[k] += a[k + w];
-  quarter[q][lane] = a[0];
-  __syncthreads();
-  if (q == 0 && i < n_elems) dW[i] = ((quarter[0][lane] + quarter[1][lane]) + quarter[2][lane]) + quarter[3][lane];
+__global__ __launch_bounds__(256) void dw_reduce_kernel(RangeSum<T> sum) {
+  __shared__ __attribute__((aligned(16))) T quarter[4 * RangeSum<T>::kSlice];
+  add_ranges(sum, blockIdx.x, gridDim.x, quarter);
 }
 
 // ---- the products cut along the reduction: any channel count, and batches of few row tiles (split_small)
@@ -417,10 +489,10 @@ struct SplitRow {   // elements per row of a partial tile in LDS: the four rows 
 };
 
 // blockIdx -> logical block such that an XCD's blocks are one contiguous range (the column tiles of a row tile read
-// the same rows of X: they meet in one L2).  gridDim.x is a multiple of kXcds.
+// the same rows of X: they meet in one L2).  blocks is a multiple of kXcds.
 constexpr int kXcds = 8;
-__device__ __forceinline__ int64_t xcd_contiguous_block() {
-  const int64_t per = gridDim.x / kXcds;
+__device__ __forceinline__ int64_t xcd_contiguous_block(unsigned blocks) {
+  const int64_t per = blocks / kXcds;
   return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
 }
 
@@ -438,11 +510,12 @@ hipError_t for_all_tiles(int64_t n_tiles, int threads, F&& launch) {
   return hipSuccess;
 }
 
-// kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).
-template <typename TS, typename TA, int LMAX, bool kTrans>
+// kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).  kSum: workgroups from `blocks` on add
+// partial dW.
+template <typename TS, typename TA, int LMAX, bool kTrans, bool kSum>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void split_forward_kernel(
-    int64_t tile0, int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W,
-    TS* __restrict__ Y) {
+    int64_t tile0, unsigned blocks, int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W,
+    TS* __restrict__ Y, RangeSum<TS> sum) {
   constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
   constexpr int CG = NC < 4 ? NC : 4;                        // components per round through LDS
   constexpr int RS = SplitRow<TA>::stride;
@@ -453,7 +526,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
   const int kq = lane / 16, i16 = lane & 15;
   const int col_tiles = (k_cols + 15) / 16;
-  const int64_t tile = tile0 + xcd_contiguous_block();
+  if constexpr (kSum) {
+    if (blockIdx.x >= blocks) {
+      static_assert(sizeof(red) >= 4 * RangeSum<TS>::kSlice * sizeof(TS), "the quarter sums reuse the partial tiles");
+      return add_ranges(sum, blockIdx.x - blocks, gridDim.x - blocks, reinterpret_cast<TS*>(red));
+    }
+  }
+  const int64_t tile = tile0 + xcd_contiguous_block(blocks);
   if (tile >= (n_nodes + 15) / 16 * col_tiles) return;       // the same for the whole workgroup
   const int64_t n0 = tile / col_tiles * 16;
   const int j0 = static_cast<int>(tile % col_tiles) * 16;
@@ -629,15 +708,9 @@ __global__ void zero_kernel(unsigned int* p, size_t n_words) {
     p[i] = 0u;
 }
 
-// Wt[l][j][k] = W[l][k][j]: the dX product then reads its B operands along rows like the forward.
 template <typename T>
-__global__ void transpose_w_kernel(int n_l, int k_in, int k_out, const T* __restrict__ W, T* __restrict__ Wt) {
-  const int64_t idx = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (idx >= static_cast<int64_t>(n_l) * k_in * k_out) return;
-  const int k = static_cast<int>(idx % k_in);
-  const int j = static_cast<int>((idx / k_in) % k_out);
-  const int l = static_cast<int>(idx / (static_cast<int64_t>(k_in) * k_out));
-  Wt[idx] = W[(static_cast<size_t>(l) * k_in + k) * k_out + j];
+__global__ void transpose_w_kernel(Transpose<T> t) {
+  transpose_role(t, static_cast<int>(blockIdx.x));
 }
 
 // ---- host side
@@ -728,27 +801,41 @@ int nodes_per_range(const el_config* cfg, int64_t n) {
   return static_cast<int>(std::min<int64_t>(per, int64_t(1) << 20));
 }
 
+// ride: partial dW that the launch may add up (it then sets ride->ranges to 0); NULL: none.
 template <typename T, typename TA, int LMAX, bool kTrans>
-hipError_t launch_split(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
+hipError_t launch_split(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, RangeSum<T>* ride, hipStream_t stream) {
   return for_all_tiles((n + 15) / 16 * ((k_cols + 15) / 16), kThreads, [&](int64_t tile0, unsigned grid) {
-    hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans>), dim3(grid), dim3(kThreads), 0, stream, tile0, n, k_red,
-                       k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
+    const T *x = static_cast<const T*>(X), *w = static_cast<const T*>(W);
+    T* y = static_cast<T*>(Y);
+    if constexpr (sizeof(T) == sizeof(TA)) {
+      if (ride && ride->ranges > 0) {
+        const unsigned more = static_cast<unsigned>(std::min<int64_t>((ride->elems + ride->kSlice - 1) / ride->kSlice, compute_units()));
+        hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans, true>), dim3(grid + more), dim3(kThreads), 0, stream, tile0, grid,
+                           n, k_red, k_cols, x, w, y, *ride);
+        ride->ranges = 0;
+        return;
+      }
+    }
+    hipLaunchKernelGGL((split_forward_kernel<T, TA, LMAX, kTrans, false>), dim3(grid), dim3(kThreads), 0, stream, tile0, grid, n, k_red,
+                       k_cols, x, w, y, RangeSum<T>{});
   });
 }
 
 template <typename T, int LMAX, bool kTrans>
-hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, hipStream_t stream) {
+hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, RangeSum<T>* ride, hipStream_t stream) {
   if constexpr (sizeof(T) == 4 && LMAX == 3) {
     if (bf16_parts_ok(sizeof(T), LMAX, n, k_red, k_cols)) {
       const int groups = k_cols / 128;
       const int64_t ranges = std::min<int64_t>((n + 15) / 16, std::max(1, compute_units() / groups));
+      RangeSum<float> sum{};
+      if (kTrans && ride) std::swap(sum, *ride);
       hipLaunchKernelGGL((mfma_forward_bf16_kernel<kTrans>), dim3(static_cast<unsigned>(ranges * groups)), dim3(kSplitThreads), 0, stream,
-                         n, k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
+                         n, k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y), sum);
       return hipGetLastError();
     }
   }
   if (mfma_forward_ok(k_red, k_cols) && (kTrans || split_small(sizeof(T), n, k_cols)))
-    return launch_split<T, T, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
+    return launch_split<T, T, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, ride, stream);
   // The tiled kernels below read B operands along rows of W (the backward hands them W transposed).
   if constexpr (!kTrans) {
     if (mfma_forward_ok(k_red, k_cols)) {
@@ -778,61 +865,51 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
       hipLaunchKernelGGL((few_channels_kernel<T, LMAX, kTrans>), dim3(grid), dim3(kThreads), 0, stream, block0, n, k_red,
                          k_cols, static_cast<const T*>(X), static_cast<const T*>(W), static_cast<T*>(Y));
     });
-  return launch_split<T, double, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, stream);
+  return launch_split<T, double, LMAX, kTrans>(n, k_red, k_cols, X, W, Y, nullptr, stream);
 }
 
 template <typename T, bool kTrans>
-hipError_t forward_t(int l_max, int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y,
+hipError_t forward_t(int l_max, int64_t n, int k_red, int k_cols, const void* X, const void* W, void* Y, RangeSum<T>* ride,
                      hipStream_t stream) {
   switch (l_max) {
-    case 0: return forward_l<T, 0, kTrans>(n, k_red, k_cols, X, W, Y, stream);
-    case 1: return forward_l<T, 1, kTrans>(n, k_red, k_cols, X, W, Y, stream);
-    case 2: return forward_l<T, 2, kTrans>(n, k_red, k_cols, X, W, Y, stream);
-    default: return forward_l<T, 3, kTrans>(n, k_red, k_cols, X, W, Y, stream);
+    case 0: return forward_l<T, 0, kTrans>(n, k_red, k_cols, X, W, Y, ride, stream);
+    case 1: return forward_l<T, 1, kTrans>(n, k_red, k_cols, X, W, Y, ride, stream);
+    case 2: return forward_l<T, 2, kTrans>(n, k_red, k_cols, X, W, Y, ride, stream);
+    default: return forward_l<T, 3, kTrans>(n, k_red, k_cols, X, W, Y, ride, stream);
   }
 }
 
+// The partial dW of the tiled kernels; returns in *sum what is left to add.
 template <typename T, int LMAX>
-hipError_t dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, void* dW, void* ws,
-                hipStream_t stream) {
-  const int64_t elems = static_cast<int64_t>(LMAX + 1) * cfg->k_in * cfg->k_out;
-  if (!mfma_dw_ok(cfg)) {
-    const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
-    return for_all_tiles(tiles, kDwWaves * kLanes, [&](int64_t tile0, unsigned grid) {
-      hipLaunchKernelGGL((split_dw_kernel<T>), dim3(grid, LMAX + 1), dim3(kDwWaves * kLanes), 0, stream, tile0, n, LMAX,
-                         cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY), static_cast<T*>(dW));
-    });
-  }
+hipError_t partial_dw_l(const el_config* cfg, int64_t n, const void* X, const void* dY, void* dW, void* ws, const Transpose<T>& tr,
+                        RangeSum<T>* sum, hipStream_t stream) {
   const int per = nodes_per_range(cfg, n);
   const int ranges = static_cast<int>((n + per - 1) / per);
+  *sum = RangeSum<T>{static_cast<const T*>(ws), static_cast<T*>(dW), static_cast<int64_t>(LMAX + 1) * cfg->k_in * cfg->k_out, ranges};
   if constexpr (sizeof(T) == 4 && LMAX == 3) {
     if (dw_lds_ok(cfg)) {
       const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(ranges) * (cfg->k_in / kDwIn) * (cfg->k_out / kDwOut));
-      hipLaunchKernelGGL(mfma_dw_lds_kernel, dim3(grid), dim3(kDwRingThreads), 0, stream, n, per, cfg->k_in, cfg->k_out,
-                         static_cast<const float*>(X), static_cast<const float*>(dY), static_cast<float*>(ws));
-      hipLaunchKernelGGL((dw_reduce_kernel<T>), dim3(static_cast<unsigned>((elems + 63) / 64)), dim3(256), 0, stream,
-                         elems, ranges, static_cast<const T*>(ws), static_cast<T*>(dW));
+      hipLaunchKernelGGL(mfma_dw_lds_kernel, dim3(grid + tr.blocks), dim3(kDwRingThreads), 0, stream, n, per, cfg->k_in, cfg->k_out,
+                         static_cast<const float*>(X), static_cast<const float*>(dY), static_cast<float*>(ws), tr);
       return hipGetLastError();
     }
   }
   // column tiles per workgroup: the accumulators (orders x tiles x 4 values) must fit the registers
   constexpr int NT = sizeof(T) == 4 ? 4 : 2;
   const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(ranges) * (cfg->k_in / 64) * (cfg->k_out / (16 * NT)));
-  hipLaunchKernelGGL((mfma_dw_kernel<T, LMAX, NT>), dim3(grid), dim3(kThreads), 0, stream, n, per, cfg->k_in,
-                     cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY), static_cast<T*>(ws));
-  hipLaunchKernelGGL((dw_reduce_kernel<T>), dim3(static_cast<unsigned>((elems + 63) / 64)), dim3(256), 0, stream, elems,
-                     ranges, static_cast<const T*>(ws), static_cast<T*>(dW));
+  hipLaunchKernelGGL((mfma_dw_kernel<T, LMAX, NT>), dim3(grid + tr.blocks), dim3(kThreads), 0, stream, n, per, cfg->k_in,
+                     cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY), static_cast<T*>(ws), tr);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t dw_t(const el_config* cfg, int64_t n, const void* X, const void* dY, void* dW, void* ws,
-                hipStream_t stream) {
+hipError_t partial_dw(const el_config* cfg, int64_t n, const void* X, const void* dY, void* dW, void* ws, const Transpose<T>& tr,
+                      RangeSum<T>* sum, hipStream_t stream) {
   switch (cfg->l_max) {
-    case 0: return dw_l<T, 0>(cfg, n, X, dY, dW, ws, stream);
-    case 1: return dw_l<T, 1>(cfg, n, X, dY, dW, ws, stream);
-    case 2: return dw_l<T, 2>(cfg, n, X, dY, dW, ws, stream);
-    default: return dw_l<T, 3>(cfg, n, X, dY, dW, ws, stream);
+    case 0: return partial_dw_l<T, 0>(cfg, n, X, dY, dW, ws, tr, sum, stream);
+    case 1: return partial_dw_l<T, 1>(cfg, n, X, dY, dW, ws, tr, sum, stream);
+    case 2: return partial_dw_l<T, 2>(cfg, n, X, dY, dW, ws, tr, sum, stream);
+    default: return partial_dw_l<T, 3>(cfg, n, X, dY, dW, ws, tr, sum, stream);
   }
 }
 
@@ -854,6 +931,49 @@ size_t workspace_bytes(const el_config* cfg, int64_t n) {
   return (bytes + 255) / 256 * 256 + 256;
 }
 
+// dX = dY times W transposed: reduction over the output channels, columns = input channels.  Beyond the smallest
+// batches the kernels take W transposed once into the workspace (strided B operands cost a third more time for the fp32
+// and fp64 instructions; the kernel of the bfloat16 parts reads W as it is).  With the tiled dW two launches: the partial dW
+// and W transposed, then dX and the sum of the partial dW.  Backward, us, with a launch for each -> with two: 128 -> 128 channels, 40
+// atoms 26.8 -> 25.1, 1000 41.3 -> 33.3, 10 000 120.3 -> 115.8, 16 384 170.8 -> 170.2; 64 -> 64, 1500 atoms 30.6 -> 24.5; l_max = 1,
+// 256 -> 128, 300 atoms 17.4 -> 11.6; fp64 128 -> 128, 4000 atoms 206 -> 192.
+template <typename T>
+hipError_t backward_t(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, void* dX, void* dW, void* ws,
+                      hipStream_t stream) {
+  const bool transposed = mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n, cfg->k_in) && !dx_parts_read_w_as_is(cfg, n);
+  Transpose<T> tr{static_cast<const T*>(W), static_cast<T*>(ws), cfg->l_max + 1, cfg->k_in, cfg->k_out, 0};
+  if (transposed) {                            // about a thousand elements a workgroup
+    const int64_t elems = static_cast<int64_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out;
+    tr.blocks = static_cast<int>(std::min<int64_t>((elems + 8191) / 8192 * 8, 2048));
+  }
+  auto dx = [&](RangeSum<T>* ride) {
+    return transposed ? forward_t<T, false>(cfg->l_max, n, cfg->k_out, cfg->k_in, dY, ws, dX, ride, stream)
+                      : forward_t<T, true>(cfg->l_max, n, cfg->k_out, cfg->k_in, dY, W, dX, ride, stream);
+  };
+  if (mfma_dw_ok(cfg)) {
+    RangeSum<T> sum{};
+    hipError_t e = partial_dw<T>(cfg, n, X, dY, dW, static_cast<char*>(ws) + wt_bytes(cfg), tr, &sum, stream);
+    if (e != hipSuccess) return e;
+    e = dx(&sum);
+    if (e != hipSuccess || sum.ranges == 0) return e;
+    hipLaunchKernelGGL((dw_reduce_kernel<T>), dim3(static_cast<unsigned>(std::min<int64_t>((sum.elems + sum.kSlice - 1) / sum.kSlice, 1 << 16))),
+                       dim3(256), 0, stream, sum);
+    return hipGetLastError();
+  }
+  if (transposed) {
+    hipLaunchKernelGGL((transpose_w_kernel<T>), dim3(tr.blocks), dim3(256), 0, stream, tr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  const hipError_t e = dx(nullptr);
+  if (e != hipSuccess) return e;
+  const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
+  return for_all_tiles(tiles, kDwWaves * kLanes, [&](int64_t tile0, unsigned grid) {
+    hipLaunchKernelGGL((split_dw_kernel<T>), dim3(grid, cfg->l_max + 1), dim3(kDwWaves * kLanes), 0, stream, tile0, n, cfg->l_max,
+                       cfg->k_in, cfg->k_out, static_cast<const T*>(X), static_cast<const T*>(dY), static_cast<T*>(dW));
+  });
+}
+
 }  // namespace
 }  // namespace el
 
@@ -871,8 +991,8 @@ sc_status el_forward(const el_config* cfg, int64_t n_nodes, const void* X, const
   if (!guard.ok) return set_error(SC_ERR_HIP, "el_forward: cannot make cfg->device current");
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const hipError_t e = cfg->dtype == SC_F64
-                           ? forward_t<double, false>(cfg->l_max, n_nodes, cfg->k_in, cfg->k_out, X, W, Y, stream)
-                           : forward_t<float, false>(cfg->l_max, n_nodes, cfg->k_in, cfg->k_out, X, W, Y, stream);
+                           ? forward_t<double, false>(cfg->l_max, n_nodes, cfg->k_in, cfg->k_out, X, W, Y, nullptr, stream)
+                           : forward_t<float, false>(cfg->l_max, n_nodes, cfg->k_in, cfg->k_out, X, W, Y, nullptr, stream);
   if (e != hipSuccess) return set_error(SC_ERR_HIP, std::string("el_forward: kernel launch: ") + hipGetErrorString(e));
   return SC_OK;
 }
@@ -909,35 +1029,9 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
   if (!workspace || workspace_bytes_given < workspace_bytes(cfg, n_nodes))
     return set_error(SC_ERR_WORKSPACE, "el_backward: workspace missing or smaller than el_workspace_bytes()");
   if (misaligned(workspace, 256)) return set_error(SC_ERR_WORKSPACE, "el_backward: workspace not 256-byte aligned");
-  // dX = dY times W transposed: reduction over the output channels, columns = input channels.  Beyond the smallest
-  // batches the kernels take W transposed once into the workspace (strided B operands cost a third more time for the fp32
-  // and fp64 instructions; the kernel of the bfloat16 parts reads W as it is).
-  hipError_t e;
-  if (mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n_nodes, cfg->k_in) &&
-      !dx_parts_read_w_as_is(cfg, n_nodes)) {
-    const int64_t elems = static_cast<int64_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out;
-    const unsigned tgrid = static_cast<unsigned>((elems + 255) / 256);
-    if (cfg->dtype == SC_F64)
-      hipLaunchKernelGGL((transpose_w_kernel<double>), dim3(tgrid), dim3(256), 0, stream, cfg->l_max + 1, cfg->k_in,
-                         cfg->k_out, static_cast<const double*>(W), static_cast<double*>(workspace));
-    else
-      hipLaunchKernelGGL((transpose_w_kernel<float>), dim3(tgrid), dim3(256), 0, stream, cfg->l_max + 1, cfg->k_in,
-                         cfg->k_out, static_cast<const float*>(W), static_cast<float*>(workspace));
-    e = hipGetLastError();
-    if (e != hipSuccess) return set_error(SC_ERR_HIP, std::string("el_backward: transpose launch: ") + hipGetErrorString(e));
-    e = cfg->dtype == SC_F64
-            ? forward_t<double, false>(cfg->l_max, n_nodes, cfg->k_out, cfg->k_in, dY, workspace, dX, stream)
-            : forward_t<float, false>(cfg->l_max, n_nodes, cfg->k_out, cfg->k_in, dY, workspace, dX, stream);
-  } else {
-    e = cfg->dtype == SC_F64
-            ? forward_t<double, true>(cfg->l_max, n_nodes, cfg->k_out, cfg->k_in, dY, W, dX, stream)
-            : forward_t<float, true>(cfg->l_max, n_nodes, cfg->k_out, cfg->k_in, dY, W, dX, stream);
-  }
-  if (e != hipSuccess) return set_error(SC_ERR_HIP, std::string("el_backward: dX launch: ") + hipGetErrorString(e));
-  void* partials = static_cast<char*>(workspace) + wt_bytes(cfg);
-  e = cfg->dtype == SC_F64 ? dw_t<double>(cfg, n_nodes, X, dY, dW, partials, stream)
-                           : dw_t<float>(cfg, n_nodes, X, dY, dW, partials, stream);
-  if (e != hipSuccess) return set_error(SC_ERR_HIP, std::string("el_backward: dW launch: ") + hipGetErrorString(e));
+  const hipError_t e = cfg->dtype == SC_F64 ? backward_t<double>(cfg, n_nodes, X, W, dY, dX, dW, workspace, stream)
+                                            : backward_t<float>(cfg, n_nodes, X, W, dY, dX, dW, workspace, stream);
+  if (e != hipSuccess) return set_error(SC_ERR_HIP, std::string("el_backward: kernel launch: ") + hipGetErrorString(e));
   return SC_OK;
 }
 

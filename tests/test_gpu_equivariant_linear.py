@@ -242,6 +242,33 @@ def test_values_of_every_exponent_keep_their_bits(el):
         assert wrong.numel() == 0, (what, wrong[:20].tolist())
 
 
+# dW: ranges of atoms that end inside a chunk of four (the copies that fill it count nothing), and every launch that adds the ranges up: the
+# product that reads W as it is and the one that reads it transposed, the workgroups of the products of split values that have
+# a tile less than others (282 tiles on 256), all of them (257 and 511 on 256 within one tile of even), and a launch of its own.
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype", [
+    (2, 128, 64, 3, "f32"), (17, 128, 128, 3, "f32"), (19, 256, 64, 3, "f32"), (1000, 128, 128, 3, "f32"), (1001, 64, 64, 2, "f64"),
+    (4097, 128, 128, 3, "f32"), (4499, 128, 128, 3, "f32"), (8171, 128, 128, 3, "f32"), (2070, 64, 64, 1, "f32"), (1030, 192, 64, 0, "f64")])
+def test_ranges_of_dw(el, N, k_in, k_out, l_max, dtype):
+    run_case(el, N, k_in, k_out, l_max, dtype, 8990 + N)
+
+
+def test_infinite_row_at_the_end_of_a_range(el):
+    import torch
+    N, K = 5, 128
+    X, _, dY = workloads.make_linear_inputs(N, K, K, 3, 8995)
+    dY[N - 1, 3, 2], X[N - 1, 9, 5] = np.inf, -np.inf
+    Xd, dYd = (torch.tensor(x, dtype=torch.float32, device="cuda:0") for x in (X, dY))
+    Wd, dX, dW = torch.zeros((4, K, K), device="cuda:0"), torch.empty_like(Xd), torch.empty((4, K, K), device="cuda:0")
+    cfg = el.make_config(K, K, 3)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    el.el_backward(cfg, N, Xd, Wd, dYd, dX, dW, torch.empty(nbytes, dtype=torch.uint8, device="cuda:0"), nbytes)
+    got = dW.double().cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = oel.backward(Xd.double().cpu().numpy(), Wd.double().cpu().numpy(), dYd.double().cpu().numpy())[1]
+    assert np.isinf(ref).any() and not np.isnan(ref).any()
+    assert (np.isinf(got) == np.isinf(ref)).all() and (got[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+
+
 def test_degenerate_sizes_and_errors(el):
     import torch
     run_case(el, 1, 128, 128, 3, "f32", 8501)
