@@ -33,6 +33,12 @@
 //   4 finalize  per (element, channel block): sum of the per-tile dW' rows in a fixed order
 //               (fp64) and the map to the external paths
 //
+// Arguments.  The first 14 words of a kernel's arguments (scalars and pointers, up to the first structure) come with the wave in
+// scalar registers (-amdgpu-kernarg-preload-count); the rest it loads, which is one memory latency at the head of every launch.
+// So what the head of a kernel needs stands first: sizes, the tile table, the order of the nodes.  Before / with, us a step,
+// 128 channels, 0e+1o: 3072 atoms 32.4 / 31.0, 10 000 74.7 / 72.8 (bfloat16 rows 56.4 / 55.2), 2731 atoms of l_max = 2 in
+// fp64 31.7 / 30.6; from 50 000 atoms on no difference.
+//
 // Included by the files that hold the generated programs; each makes table entries of them (Entry below).
 #pragma once
 #include <type_traits>
@@ -265,10 +271,13 @@ __device__ __forceinline__ void fold_role(int wg, int K, int chblocks, int n_pai
 // Launch 1.  Workgroups [0, window_wgs): window role (order of the forward pass); the next
 // count_wgs: count role of the grouping.  The others: fold role.
 template <typename T, typename G, typename TW>
-__global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(SplitGroupArgs ga, int count_wgs, int window_wgs, int K,
-                                                                    int chblocks, int n_pairs,
-                                                                    const TW* __restrict__ W, T* __restrict__ wf) {
+__global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(const int32_t* __restrict__ z, int n, int Z, int window_wgs,
+                                                                    int count_wgs, const TW* __restrict__ W, T* __restrict__ wf,
+                                                                    int K, int chblocks, int n_pairs, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
+  ga.z = z;
+  ga.n = n;
+  ga.Z = Z;
   if (static_cast<int>(blockIdx.x) < window_wgs) {   // the longest role first
     split_window_role(ga, blockIdx.x, reinterpret_cast<int32_t*>(lds_raw));
     return;
@@ -294,11 +303,12 @@ __global__ __launch_bounds__(kSpecThreads) void spec_scatter_kernel(SplitGroupAr
 // kDirect: the weights of a run are folded from W (external paths) by the wave itself instead of
 // being read from the folded table, so that no launch has to come before this one.
 template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDirect>
-__global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupArgs ga, int scatter_wgs, int table,
-                                                                    int fold_wgs, int K, int chblocks, int n, int Z,
-                                                                    int tile, const TS* __restrict__ A,
-                                                                    const int32_t* __restrict__ z, const T* __restrict__ wf,
-                                                                    const TW* __restrict__ W, TS* __restrict__ B) {
+__global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_t* __restrict__ wnode,
+                                                                    const int32_t* __restrict__ elements, int scatter_wgs,
+                                                                    int table, int chblocks, int tile, int n, int Z, int K,
+                                                                    int fold_wgs, const TS* __restrict__ A,
+                                                                    const T* __restrict__ wf, const TW* __restrict__ W,
+                                                                    TS* __restrict__ B, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
   int block = blockIdx.x;
   if constexpr (kDirect) {   // no launch came before: the roles count for themselves, the fold role is here
@@ -348,13 +358,10 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupAr
   const int cnt = j1 - j0;
   int key = Z, mine = j0 + lane;   // the lane's node and its element index
   if (lane < cnt) {
-    int e;
-    if (ga.wnode) {   // positions follow the window order written by the count role (uniform)
-      mine = ga.wnode[j0 + lane];
+    const int e = elements[j0 + lane];
+    if (wnode) {   // positions follow the window order written by the count role (uniform)
+      mine = wnode[j0 + lane];
       mine = mine < 0 ? 0 : (mine >= n ? n - 1 : mine);
-      e = ga.wkey[j0 + lane];
-    } else {
-      e = z[j0 + lane];
     }
     key = (e >= 0 && e < Z) ? e : Z;
   }
@@ -463,13 +470,9 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(SplitGroupAr
 // handling, 295 (one wave per SIMD, 736 instead of 496 us at 50k nodes / 256 channels) with it.
 template <typename T, typename G, int kOcc = 0, bool kStreamDA = false, bool kFull = false, typename TS = T, bool kCM = false>
 __global__ __launch_bounds__(kSpecThreads) __attribute__((amdgpu_waves_per_eu(kOcc == 0 ? 1 : kOcc, 8)))
-void spec_backward_kernel(int K, int chblocks, int n_blocks,
-                                                                     const TS* __restrict__ A,
-                                                                     const T* __restrict__ wf,
-                                                                     const TS* __restrict__ dB, TS* __restrict__ dA,
-                                                                     T* __restrict__ partial,
-                                                                     const TileDesc* __restrict__ tiles,
-                                                                     const int32_t* __restrict__ perm) {
+void spec_backward_kernel(const TileDesc* __restrict__ tiles, int n_blocks, int chblocks, const int32_t* __restrict__ perm, int K,
+                          const T* __restrict__ wf, const TS* __restrict__ A, const TS* __restrict__ dB, TS* __restrict__ dA,
+                          T* __restrict__ partial) {
   extern __shared__ unsigned char lds_raw[];
   T* red = reinterpret_cast<T*>(lds_raw);  // [kSpecWaves][kS][64]
   T* stage = red + kSpecWaves * G::kS * kLanes + wave_of_thread() * kLanes * G::kNlm;  // [64][kNlm] per wave
@@ -588,9 +591,9 @@ struct NodeRows2 {
 
 template <typename T, typename G, bool kFull, typename TS, typename TW, bool kCM>
 __global__ __launch_bounds__(kSpecThreads) void spec_double_backward_kernel(
-    int K, int chblocks, int n_blocks, const TS* __restrict__ A, const TW* __restrict__ W, const TS* __restrict__ dB,
-    const TS* __restrict__ H, TS* __restrict__ ddB, TS* __restrict__ dA2, T* __restrict__ partial,
-    const TileDesc* __restrict__ tiles, const int32_t* __restrict__ perm) {
+    const TileDesc* __restrict__ tiles, int n_blocks, int chblocks, const int32_t* __restrict__ perm, int K,
+    const TW* __restrict__ W, const TS* __restrict__ A, const TS* __restrict__ H, const TS* __restrict__ dB,
+    TS* __restrict__ ddB, TS* __restrict__ dA2, T* __restrict__ partial) {
   extern __shared__ unsigned char lds_raw[];
   T* red = reinterpret_cast<T*>(lds_raw);  // [kSpecWaves][kS][64]
   T* stage = red + kSpecWaves * G::kS * kLanes + wave_of_thread() * kLanes * G::kNlm;  // [64][kNlm] per wave
@@ -642,9 +645,9 @@ __global__ __launch_bounds__(kSpecThreads) void spec_double_backward_kernel(
 // See above.  LDS: w' [kSpecWaves][kS][64] | sums [kSpecWaves][kS][64] | stage [kSpecWaves][64][kNlm].
 template <typename T, typename G, bool kFull, typename TS, typename TW, bool kCM>
 __global__ __launch_bounds__(kSpecThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_double_backward_lds_kernel(
-    int K, int chblocks, int n_blocks, const TS* __restrict__ A, const TW* __restrict__ W, const TS* __restrict__ dB,
-    const TS* __restrict__ H, TS* __restrict__ ddB, TS* __restrict__ dA2, T* __restrict__ partial,
-    const TileDesc* __restrict__ tiles, const int32_t* __restrict__ perm) {
+    const TileDesc* __restrict__ tiles, int n_blocks, int chblocks, const int32_t* __restrict__ perm, int K,
+    const TW* __restrict__ W, const TS* __restrict__ A, const TS* __restrict__ H, const TS* __restrict__ dB,
+    TS* __restrict__ ddB, TS* __restrict__ dA2, T* __restrict__ partial) {
   extern __shared__ unsigned char lds_raw[];
   T* red = reinterpret_cast<T*>(lds_raw);  // [kSpecWaves][kS][64]: every wave's w' columns
   T* acc_all = red + kSpecWaves * G::kS * kLanes;                         // [kSpecWaves][kS][64] dW2' sums
@@ -820,8 +823,9 @@ hipError_t prepare_launch(const sc_plan* plan, int64_t n, const int32_t* z, cons
   const size_t lds = window ? split_window_lds_bytes(plan->cfg.num_elements)
                             : count ? split_group_lds_bytes(plan->cfg.num_elements) : 0;
   hipLaunchKernelGGL((spec_prepare_kernel<T, G, TW>), dim3(grid), dim3(kSpecThreads), lds, stream,
-                     group_args(plan, n, z, ws, shape, window), count_wgs, window_wgs, plan->cfg.num_channels, shape.chblocks, n_pairs,
-                     static_cast<const TW*>(W), static_cast<T*>(ws.wfold));
+                     z, static_cast<int>(n), plan->cfg.num_elements, window_wgs, count_wgs, static_cast<const TW*>(W),
+                     static_cast<T*>(ws.wfold), plan->cfg.num_channels, shape.chblocks, n_pairs,
+                     group_args(plan, n, z, ws, shape, window));
   return hipGetLastError();
 }
 
@@ -879,9 +883,10 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
   const int tiles = static_cast<int>((n + tile - 1) / tile);
   const int grid = scatter_wgs + table + fold_wgs + tiles * shape.chblocks;
   hipLaunchKernelGGL((spec_forward_kernel<T, G, TS, TW, kCM, kDirect>), dim3(grid), dim3(kSpecThreads), lds, stream,
-                     group_args(plan, n, z, ws, shape, window_order), scatter_wgs, table, fold_wgs, plan->cfg.num_channels,
-                     shape.chblocks, static_cast<int>(n), plan->cfg.num_elements, tile, static_cast<const TS*>(A), z,
-                     static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B));
+                     window_order ? ws.wnode : nullptr, window_order ? ws.wkey : z, scatter_wgs, table, shape.chblocks, tile,
+                     static_cast<int>(n), plan->cfg.num_elements, plan->cfg.num_channels, fold_wgs, static_cast<const TS*>(A),
+                     static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B),
+                     group_args(plan, n, z, ws, shape, window_order));
   return hipGetLastError();
 }
 
@@ -899,9 +904,9 @@ hipError_t bwd_launch(const sc_plan* plan, int64_t n, const void* A, const void*
   }
   const hipError_t e = raise_lds_limit(kernel, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpecThreads), lds, stream, plan->cfg.num_channels, shape.chblocks,
-                     n_blocks, static_cast<const TS*>(A), static_cast<const T*>(ws.wfold), static_cast<const TS*>(dB),
-                     static_cast<TS*>(dA), static_cast<T*>(ws.partial), ws.tiles, ws.perm);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpecThreads), lds, stream, ws.tiles, n_blocks, shape.chblocks, ws.perm,
+                     plan->cfg.num_channels, static_cast<const T*>(ws.wfold), static_cast<const TS*>(A),
+                     static_cast<const TS*>(dB), static_cast<TS*>(dA), static_cast<T*>(ws.partial));
   return hipGetLastError();
 }
 
@@ -917,10 +922,9 @@ hipError_t dbl_launch(const sc_plan* plan, const void* A, const void* W, const v
   if constexpr (kLds) kernel = full ? &spec_double_backward_lds_kernel<T, G, true, TS, TW, kCM> : &spec_double_backward_lds_kernel<T, G, false, TS, TW, kCM>;
   const hipError_t e = raise_lds_limit(kernel, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpecThreads), lds, stream, plan->cfg.num_channels, shape.chblocks,
-                     n_blocks, static_cast<const TS*>(A), static_cast<const TW*>(W), static_cast<const TS*>(dB),
-                     static_cast<const TS*>(H), static_cast<TS*>(ddB), static_cast<TS*>(dA2),
-                     static_cast<T*>(ws.partial), ws.tiles, ws.perm);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpecThreads), lds, stream, ws.tiles, n_blocks, shape.chblocks, ws.perm,
+                     plan->cfg.num_channels, static_cast<const TW*>(W), static_cast<const TS*>(A), static_cast<const TS*>(H),
+                     static_cast<const TS*>(dB), static_cast<TS*>(ddB), static_cast<TS*>(dA2), static_cast<T*>(ws.partial));
   return hipGetLastError();
 }
 
