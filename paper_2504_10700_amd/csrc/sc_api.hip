@@ -78,22 +78,33 @@ LaunchShape launch_shape(const sc_plan* plan, int64_t n) {
   int64_t t;
   if (plan->specialised) {
     // Generated kernels: the grouped sequence is cut every t positions and at element boundaries, and the
-    // pieces are processed largest first (see split_table_role).  t: a whole number of nodes per wave such
-    // that the whole pieces make about one and a half workgroups per compute unit (the shorter pieces next
-    // to element boundaries fill the rest), at least two and at most 24 nodes per wave.  Measured on
-    // MI355X, 128 channels, 89 elements of skewed frequency, us per step against t: 3072 nodes 8 -> 37.8,
-    // 16 -> 34.2, 24 -> 35.8; 5000 nodes 12 -> 53.1, 24 -> 50.1, 40 -> 52.4; 10000 nodes 24 -> 83.0, 40 -> 81.9,
-    // 56 -> 80.8, 80 -> 86.2; 15000 nodes 24 -> 107.5, 80 -> 106.1, 128 -> 117.4; 40000 nodes 32 -> 250.6,
-    // 96 -> 246.0, 128 -> 258.1; 200000 nodes 64 -> 1160, 96 -> 1151, 128 -> 1155.
-    const int64_t target = static_cast<int64_t>(plan->num_cus) * 3 / 2;
-    t = (work + target - 1) / target;
-    t = (t + waves_per_tile - 1) / waves_per_tile * waves_per_tile;
-    const int64_t lo = 2 * waves_per_tile, hi = 24 * waves_per_tile;
-    if (t < lo) t = lo;
-    if (t > hi) t = hi;
-    if (plan->cfg.tile_nodes > 0) t = plan->cfg.tile_nodes;
-    s.tile_nodes = static_cast<int>(t);
+    // pieces are processed largest first (see split_table_role).  The chip holds two workgroups per compute unit of the
+    // kernels that matter here, and a compute unit with two whole pieces ends when it has done both, so a whole piece
+    // should be hardly more than the even share of a slot (work / slots nodes per wave): one round of whole pieces, which
+    // the shorter ones next to element boundaries fill up.  One node per wave on top of the share leaves the pieces that
+    // much fewer, so that the short ones find free slots.  Shares above 24 nodes per wave are cut into equal rounds.  (A list
+    // schedule of the pieces on 2 x 256 slots that share the issue of their compute unit reproduces the times below.)
+    // Measured, us, 128 channels, 89 elements of skewed frequency, against t: step, 3500 nodes 16 -> 35.5, 20 -> 33.8,
+    // 24 -> 34.7; 10000 nodes 32 -> 75.8, 40 -> 71.8, 44 -> 70.4, 56 -> 73.4; 15000 nodes 64 -> 101.2, 80 -> 105.1; 40000
+    // nodes 84 -> 230.3, 96 -> 233.6; step with the second-order pass, 6000 nodes 24 -> 104.9, 28 -> 101.6, 32 -> 102.7;
+    // 10000 nodes 32 -> 154.9, 44 -> 141.6, 48 -> 146.6, 56 -> 151.4; 15000 nodes 64 -> 197.8, 80 -> 210.4.
+    const int64_t slots = static_cast<int64_t>(plan->num_cus) * 2 * waves_per_tile;
+    const int64_t rounds = work > 0 ? (work + 24 * slots - 1) / (24 * slots) : 1;
+    t = ((work + rounds * slots - 1) / (rounds * slots) + 1) * waves_per_tile;
+    if (t < 2 * waves_per_tile) t = 2 * waves_per_tile;
+    const bool chosen = plan->cfg.tile_nodes > 0;
+    s.tile_nodes = chosen ? plan->cfg.tile_nodes : static_cast<int>(t);
     s.max_tiles = static_cast<int>(n / s.tile_nodes) + 1 + plan->cfg.num_elements;
+    // t grows in steps, so a smaller batch may have more tiles: a workspace serves all batches up to its own.  n / t is at
+    // most n / 8 and, with t / 4 above work / (rounds * slots), below rounds * slots / (4 * chblocks); both grow with n.
+    int64_t cuts = n / (2 * waves_per_tile);
+    const int64_t full = rounds * slots / (waves_per_tile * s.chblocks);
+    if (full < cuts) cuts = full;
+    s.tiles_room = chosen ? s.max_tiles : static_cast<int>(cuts) + 1 + plan->cfg.num_elements;
+    int64_t u = (work + plan->num_cus * 3 / 2 - 1) / (plan->num_cus * 3 / 2);
+    u = (u + waves_per_tile - 1) / waves_per_tile * waves_per_tile;
+    u = u < 2 * waves_per_tile ? 2 * waves_per_tile : u > 24 * waves_per_tile ? 24 * waves_per_tile : u;
+    s.scratch_room = chosen ? s.max_tiles : static_cast<int>(n / u) + 1 + plan->cfg.num_elements;
   } else {
     // Table-driven kernels: every element's nodes split evenly into tiles of at most t nodes, about eight
     // (tile x channel block) workgroups per compute unit on small batches, bounded for large ones (the
@@ -106,6 +117,7 @@ LaunchShape launch_shape(const sc_plan* plan, int64_t n) {
     if (plan->cfg.tile_nodes > 0) t = plan->cfg.tile_nodes;
     s.tile_nodes = static_cast<int>(t);
     s.max_tiles = static_cast<int>(n / s.tile_nodes) + plan->cfg.num_elements;
+    s.tiles_room = s.scratch_room = s.max_tiles;
   }
   // Grouping: one single-workgroup launch for small batches (group_waves = 0), else three
   // launches with about four 64-node chunks per wave, at most kMaxGroupWaves waves.
@@ -147,14 +159,14 @@ Workspace carve_workspace(const sc_plan* plan, int64_t n, const LaunchShape& sha
   w.tile_off = static_cast<int32_t*>(take(sizeof(int32_t) * (Z + 1)));
   w.counts = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(kMaxGroupWaves) * Z));
   w.perm = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));
-  w.tiles = static_cast<TileDesc*>(take(sizeof(TileDesc) * static_cast<size_t>(shape.max_tiles)));
+  w.tiles = static_cast<TileDesc*>(take(sizeof(TileDesc) * static_cast<size_t>(forward_only ? shape.scratch_room : shape.tiles_room)));
   if (plan->specialised) w.wfold = take(spec_folded_bytes(plan));
   if (plan->specialised) {
     w.wnode = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));
     w.wkey = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));
   }
   if (!forward_only)  // the weight-gradient rows of the backward passes
-    w.partial = take((plan->specialised ? spec_value_bytes(plan) : elem_size(plan)) * static_cast<size_t>(shape.max_tiles) * shape.chblocks * plan->S * kLanes);
+    w.partial = take((plan->specialised ? spec_value_bytes(plan) : elem_size(plan)) * static_cast<size_t>(shape.tiles_room) * shape.chblocks * plan->S * kLanes);
   w.max_tiles = shape.max_tiles;
   w.bytes = off;
   return w;

@@ -32,11 +32,11 @@ struct Workspace {
   int32_t* tile_off;   // [Z+1] first tile of each element
   int32_t* counts;     // [kMaxGroupWaves][Z] scratch of the counting sort
   int32_t* perm;       // [N] node indices grouped by element (stable)
-  TileDesc* tiles;     // [max_tiles]
+  TileDesc* tiles;     // [tiles_room]
   void* wfold;         // generated kernels: weights folded into the internal basis, [Z][K][stride]
   int32_t* wnode;      // generated kernels: [N] window order of the forward pass (node per position) ...
   int32_t* wkey;       // ... and [N] its element index (Z: outside the range)
-  void* partial;       // [max_tiles][chblocks][S][64] per-tile dW contributions
+  void* partial;       // [tiles_room][chblocks][S][64] per-tile dW contributions
   int32_t max_tiles;
   size_t bytes;
 };
@@ -54,6 +54,8 @@ struct GenericTables {
 struct LaunchShape {
   int tile_nodes;   // nodes per tile (per workgroup)
   int max_tiles;    // upper bound of the tile count = grid size / chblocks
+  int tiles_room;   // tiles that the workspace has room for: max_tiles of this and of every smaller batch
+  int scratch_room; // ... in the scratch of a forward without a workspace (part of that call's documented limit)
   int chblocks;     // ceil(K / 64)
   int group_waves;  // rows used of the count matrix (0: single-launch grouping)
   int nodes_per_group_wave;

@@ -128,3 +128,18 @@ def test_workspace_size_follows_the_batch():
     # never less than the per-node arrays (permutation, window order) and the folded weights
     assert all(b >= 12 * n + 89 * 2 * 29 * 256 for b, n in zip(sizes, (1, 100, 3072, 10_000, 200_000)))
     sc.sc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("channels,l_max,nu,dtype", [(64, 3, 3, "f32"), (128, 3, 3, "f64"), (320, 2, 3, "f32"), (100, 3, 2, "f64")])
+def test_workspace_serves_every_smaller_batch(channels, l_max, nu, dtype):
+    # the tile length grows in steps with the batch (one more node per wave of a tile, or one more round of tiles), so the
+    # number of tiles falls there; the size of the workspace does not
+    plan = host_plan(channels, l_max, nu, 89, O01, {"f32": sc.SC_F32, "f64": sc.SC_F64}[dtype])
+    blocks = -(-channels // 64)
+    step = 2048 // blocks                       # nodes that fill 256 units x 2 workgroups x 4 waves once
+    at = {1, 7, 8, 9, 300_000}
+    for k in range(1, 60):
+        at |= {max(1, k * step + d) for d in (-1, 0, 1, step // 2)}
+    sizes = [sc.sc_workspace_bytes(plan, n) for n in sorted(at)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    sc.sc_plan_destroy(plan)
