@@ -150,27 +150,38 @@ __device__ __forceinline__ void pin_values(T (&v)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
 }
 
-// A wave-uniform value in the type of the arithmetic.  The conversion runs on the vector unit; the result
-// goes back to scalar registers, from where every instruction can read it.
-template <typename T, typename TS>
-__device__ __forceinline__ T widen_uniform(TS v) {
-  if constexpr (std::is_same<T, TS>::value) {
-    return v;
-  } else {
-    const unsigned long long bits = __builtin_bit_cast(unsigned long long, static_cast<double>(v));
-    const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(bits));
-    const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(bits >> 32));
-    return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
-  }
-}
-
-// Y[e][:], identical for all lanes (e is wave-uniform): scalar loads.
+// Y[e][:], identical for all lanes (e is wave-uniform).  Rows in the type of the arithmetic: scalar loads where the edge is
+// evaluated.  fp64 arithmetic on fp32 rows: value a in lane a of one register, requested with the other rows of the edge,
+// widened by one instruction and read back to scalar registers, which have no room for a second set of them; as
+// scalar loads every edge waits for memory there, its other rows long in registers, and every value is widened by itself.
+// (Bound by latency at two to four waves per SIMD.  With the forward's requests out of their conditions, below: forward and
+// backward, l_h = 2, 3001 atoms, 128 channels, 475 -> 457 us; l_h = 1, fp32 arithmetic, 10 000 atoms, 687 -> 679.)
 template <typename T, typename TS, int N>
-__device__ __forceinline__ void load_uniform(const TS* __restrict__ Y, int e, T (&y)[N]) {
-  const TS* base = Y + static_cast<size_t>(e) * N;
+struct UniformRow {
+  static constexpr bool kAhead = !std::is_same<T, TS>::value;
+  static_assert(N <= kLanes, "a lane per value");
+  TS mine;
+  __device__ __forceinline__ void request(const TS* __restrict__ Y, int e, int lane) {
+    if constexpr (kAhead) mine = Y[static_cast<size_t>(e) * N + (lane < N ? lane : N - 1)];
+  }
+  __device__ __forceinline__ void use(const TS* __restrict__ Y, int e, T (&y)[N]) const {
+    if constexpr (kAhead) {
+      TS x = mine;
+      asm volatile("" : "+v"(x));   // widened here and not at the request
+      const unsigned long long bits = __builtin_bit_cast(unsigned long long, static_cast<double>(x));
 #pragma unroll
-  for (int a = 0; a < N; ++a) y[a] = widen_uniform<T>(base[a]);
-}
+      for (int a = 0; a < N; ++a) {
+        const unsigned lo = __builtin_amdgcn_readlane(static_cast<unsigned>(bits), a);
+        const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(bits >> 32), a);
+        y[a] = __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+      }
+    } else {
+      const TS* base = Y + static_cast<size_t>(e) * N;
+#pragma unroll
+      for (int a = 0; a < N; ++a) y[a] = base[a];
+    }
+  }
+};
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -276,8 +287,13 @@ struct Channels {
 // Forward / backward / second-order pass, us, 128 channels, l_h = 1, wave -> workgroup per (atom, block): 250 atoms
 // 21 -> 9 / 53 -> 24 / 78 -> 37, 2000 40 -> 37 / 100 -> 79 / 230 -> 193, 10 000 243 -> 225 / 500 -> 492 / 859 -> 817; l_h = 2
 // (fp64 arithmetic), 3001 atoms 180 -> 165 / 368 -> 361 / 888 -> 817.
+// Waves per SIMD that the forward is held to: with fp64 arithmetic on fp32 rows and 10 to 17 paths it wants 129 registers if
+// left alone, one over the limit for four.
+template <typename T, typename TS, typename G>
+constexpr int kForwardWaves = sizeof(T) == 8 && sizeof(TS) == 4 && G::kP >= 10 && G::kP <= 17 ? 4 : 1;
+
 template <typename T, typename TS, typename G, bool kFull, int kWaves>
-__global__ __launch_bounds__(kWaves * kLanes) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
+__global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kForwardWaves<T, TS, G>))) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
                                                            const TS* __restrict__ Y, const TS* __restrict__ h,
                                                            const TS* __restrict__ R,
                                                            const EdgeList el, TS* __restrict__ A) {
@@ -296,32 +312,36 @@ __global__ __launch_bounds__(kWaves * kLanes) void forward_kernel(int K, int chb
   for (int c = 0; c < G::kNout; ++c) acc[c] = T(0);
   if (e0 < e1) {
     TS r0[G::kP], r1[G::kP], h0[G::kNh], h1[G::kNh];
-    auto add_edge = [&](int e, const TS (&h_row)[G::kNh], const TS (&r_row)[G::kP]) {
+    UniformRow<T, TS, G::kNY> y0, y1;
+    auto add_edge = [&](int e, const UniformRow<T, TS, G::kNY>& y_row, const TS (&h_row)[G::kNh], const TS (&r_row)[G::kP]) {
       T y[G::kNY], hh[G::kNh];
-      load_uniform<T, TS, G::kNY>(Y, e, y);
+      y_row.use(Y, e, y);
       widen(h_row, hh);
       G::forward(y, hh, PathRow<T, TS, G::kP>{r_row}, acc);
     };
-    load_weights<TS, G::kP>(R, e0, K, ch, r0);
-    load_row<TS, G::kNh>(h + (el.snd(e0) * K + ch) * G::kNh, h0);
-    int jn = (e0 + kWaves < e1) ? el.raw(e0 + kWaves) : 0;  // sender of the next edge, read one step ahead
-    for (int e = e0; e < e1; e += 2 * kWaves) {
-      int jn2 = 0;
-      if (e + kWaves < e1) {
-        load_weights<TS, G::kP>(R, e + kWaves, K, ch, r1);
-        load_row<TS, G::kNh>(h + (el.node(jn) * K + ch) * G::kNh, h1);
-        if (e + 2 * kWaves < e1) jn2 = el.raw(e + 2 * kWaves);
-      }
-      add_edge(e, h0, r0);
-      if (e + kWaves < e1) {
-        if (e + 2 * kWaves < e1) {
-          load_weights<TS, G::kP>(R, e + 2 * kWaves, K, ch, r0);
-          load_row<TS, G::kNh>(h + (el.node(jn2) * K + ch) * G::kNh, h0);
-          if (e + 3 * kWaves < e1) jn = el.raw(e + 3 * kWaves);
-        }
-        add_edge(e + kWaves, h1, r1);
-      }
+    // No request stands under a condition: behind one the compiler waits for all of them, the one just made included, before
+    // the arithmetic that is meant to overlap it.  Past the last edge a request repeats its last one, all lanes the same line.
+    auto load_edge = [&](int e, int j, bool next, UniformRow<T, TS, G::kNY>& y_row, TS (&h_row)[G::kNh], TS (&r_row)[G::kP]) {
+      const int c = next ? ch : cb * kLanes;
+      y_row.request(Y, e, lane);
+      load_weights<TS, G::kP>(R, e, K, c, r_row);
+      load_row<TS, G::kNh>(h + (el.node(j) * K + c) * G::kNh, h_row);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_edge(e0, el.raw(e0), true, y0, h0, r0);
+    int jn = el.raw(e0 + kWaves < e1 ? e0 + kWaves : e0);  // sender of the next edge, read one step ahead
+    int e = e0;
+    for (; e + kWaves < e1; e += 2 * kWaves) {
+      const bool third = e + 2 * kWaves < e1;
+      const int eb = e + kWaves, ec = third ? e + 2 * kWaves : eb;
+      const int jn2 = el.raw(ec);
+      load_edge(eb, jn, true, y1, h1, r1);
+      add_edge(e, y0, h0, r0);
+      jn = el.raw(e + 3 * kWaves < e1 ? e + 3 * kWaves : ec);
+      load_edge(ec, jn2, third, y0, h0, r0);
+      add_edge(eb, y1, h1, r1);
     }
+    if (e < e1) add_edge(e, y0, h0, r0);
   }
   if (!add_waves<kWaves, kLanes * G::kNout>(wave, lane, acc, out_stage[0])) return;
   store_rows_coalesced<TS, T, G::kNout>(A + (node * K + cb * kLanes) * G::kNout, reinterpret_cast<TS*>(out_stage[wave]),
@@ -389,7 +409,9 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
     // one set of rows in registers where two do not fit (see the second-order kernel)
     constexpr bool kOneSet = sizeof(TS) == 8 && G::kP >= 17;
     TS r0[G::kP], g0[G::kNout];
+    UniformRow<T, TS, G::kNY> y0;
     int ea = uniform(edge(q0));
+    y0.request(Y, ea, lane);
     load_weights<TS, G::kP>(R, ea, K, ch, r0);
     load_row<TS, G::kNout>(dA + (atom(uniform(receiver[ea])) * K + ch) * G::kNout, g0);
     // edge id and receiver of the edge after the current one, read one step ahead of its rows
@@ -397,11 +419,11 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
     int rn = uniform(receiver[en]);
 
     // One edge: arithmetic, dR row stores, dY summed over the 64 lanes in a fixed order, dh added up.
-    auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
+    auto finish_edge = [&](int e, const UniformRow<T, TS, G::kNY>& y_row, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
       T y[G::kNY], g[G::kNout], dhe[G::kNh];
       const PathStore<kFull, T, TS> dr{dR + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
       const StageStore<kFull, T> dy{stage + lane, lane < chan.live};
-      load_uniform<T, TS, G::kNY>(Y, e, y);
+      y_row.use(Y, e, y);
       widen(g_row, g);
       stage_is_free();
       G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, dhe);
@@ -413,9 +435,10 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
 
     if constexpr (kOneSet) {
       for (int q = q0; q < q1; q += kWaves) {
-        finish_edge(ea, r0, g0);
+        finish_edge(ea, y0, r0, g0);
         if (q + kWaves < q1) {
           ea = en;
+          y0.request(Y, ea, lane);
           load_weights<TS, G::kP>(R, ea, K, ch, r0);
           load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
           if (q + 2 * kWaves < q1) {
@@ -426,10 +449,12 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       }
     } else {
       TS r1[G::kP], g1[G::kNout];
+      UniformRow<T, TS, G::kNY> y1;
       int eb = 0;
       for (int q = q0; q < q1; q += 2 * kWaves) {
         if (q + kWaves < q1) {
           eb = en;
+          y1.request(Y, eb, lane);
           load_weights<TS, G::kP>(R, eb, K, ch, r1);
           load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g1);
           if (q + 2 * kWaves < q1) {
@@ -437,10 +462,11 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
             rn = uniform(receiver[en]);
           }
         }
-        finish_edge(ea, r0, g0);
+        finish_edge(ea, y0, r0, g0);
         if (q + kWaves < q1) {
           if (q + 2 * kWaves < q1) {
             ea = en;
+            y0.request(Y, ea, lane);
             load_weights<TS, G::kP>(R, ea, K, ch, r0);
             load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
             if (q + 3 * kWaves < q1) {
@@ -448,7 +474,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
               rn = uniform(receiver[en]);
             }
           }
-          finish_edge(eb, r1, g1);
+          finish_edge(eb, y1, r1, g1);
         }
       }
     }
@@ -491,23 +517,28 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
     // whose next rows are requested when the arithmetic has consumed it (two sets: one wave per SIMD, or scratch).
     constexpr bool kOneSet = sizeof(T) == 8 && G::kP >= 10;
     TS r0[G::kP], q0[G::kP], h0[G::kNh], x0[G::kNh];
-    auto load_edge = [&](int e, size_t j, TS (&r)[G::kP], TS (&q)[G::kP], TS (&h_row)[G::kNh], TS (&x_row)[G::kNh]) {
+    UniformRow<T, TS, G::kNY> y0, hy0;
+    auto load_edge = [&](int e, size_t j, TS (&r)[G::kP], TS (&q)[G::kP], TS (&h_row)[G::kNh], TS (&x_row)[G::kNh],
+                         UniformRow<T, TS, G::kNY>& y_row, UniformRow<T, TS, G::kNY>& hy_row) {
+      y_row.request(Y, e, lane);
+      hy_row.request(HY, e, lane);
       load_weights<TS, G::kP>(R, e, K, ch, r);
       load_weights<TS, G::kP>(HR, e, K, ch, q);
       load_row<TS, G::kNh>(h + (j * K + ch) * G::kNh, h_row);
       load_row<TS, G::kNh>(Hh + (j * K + ch) * G::kNh, x_row);
     };
-    load_edge(e0, el.snd(e0), r0, q0, h0, x0);
+    load_edge(e0, el.snd(e0), r0, q0, h0, x0, y0, hy0);
     int jn = (e0 + kWaves < e1) ? el.raw(e0 + kWaves) : 0;
 
     auto finish_edge = [&](int e, const TS (&r_row)[G::kP], const TS (&hr_row)[G::kP], const TS (&h_row)[G::kNh],
-                           const TS (&hx_row)[G::kNh]) {
+                           const TS (&hx_row)[G::kNh], const UniformRow<T, TS, G::kNY>& y_row,
+                           const UniformRow<T, TS, G::kNY>& hy_row) {
       T y[G::kNY], hy[G::kNY], hh[G::kNh], hx[G::kNh], d2h[G::kNh];
       const PathStore<kFull, T, TS> d2r{d2R + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
       const StageStore<kFull, T> d2y{stage + lane, lane < chan.live};
       pin_values(g);
-      load_uniform<T, TS, G::kNY>(Y, e, y);
-      load_uniform<T, TS, G::kNY>(HY, e, hy);
+      y_row.use(Y, e, y);
+      hy_row.use(HY, e, hy);
       widen(h_row, hh);
       widen(hx_row, hx);
       stage_is_free();
@@ -520,27 +551,28 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
 
     if constexpr (kOneSet) {
       for (int e = e0; e < e1; e += kWaves) {
-        finish_edge(e, r0, q0, h0, x0);
+        finish_edge(e, r0, q0, h0, x0, y0, hy0);
         if (e + kWaves < e1) {
-          load_edge(e + kWaves, el.node(jn), r0, q0, h0, x0);
+          load_edge(e + kWaves, el.node(jn), r0, q0, h0, x0, y0, hy0);
           if (e + 2 * kWaves < e1) jn = el.raw(e + 2 * kWaves);
         }
       }
     } else {
       TS r1[G::kP], q1[G::kP], h1[G::kNh], x1[G::kNh];
+      UniformRow<T, TS, G::kNY> y1, hy1;
       for (int e = e0; e < e1; e += 2 * kWaves) {
         int jn2 = 0;
         if (e + kWaves < e1) {
-          load_edge(e + kWaves, el.node(jn), r1, q1, h1, x1);
+          load_edge(e + kWaves, el.node(jn), r1, q1, h1, x1, y1, hy1);
           if (e + 2 * kWaves < e1) jn2 = el.raw(e + 2 * kWaves);
         }
-        finish_edge(e, r0, q0, h0, x0);
+        finish_edge(e, r0, q0, h0, x0, y0, hy0);
         if (e + kWaves < e1) {
           if (e + 2 * kWaves < e1) {
-            load_edge(e + 2 * kWaves, el.node(jn2), r0, q0, h0, x0);
+            load_edge(e + 2 * kWaves, el.node(jn2), r0, q0, h0, x0, y0, hy0);
             if (e + 3 * kWaves < e1) jn = el.raw(e + 3 * kWaves);
           }
-          finish_edge(e + kWaves, r1, q1, h1, x1);
+          finish_edge(e + kWaves, r1, q1, h1, x1, y1, hy1);
         }
       }
     }
