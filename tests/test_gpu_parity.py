@@ -302,6 +302,42 @@ def test_one_launch_forward(sc, K, l_max, nu, outs, dtype, Z, sizes, grouped):
         r.close()
 
 
+# The tile length of the grouped passes follows the batch (nodes per wave and slot, rounds above 24): at the batches where it
+# steps, all in the workspace of the largest, against tiles of 16 nodes.  The rows of a node do not depend on the cut; dW adds
+# the same products in fp32 over the at most 25 nodes of a wave and over 4 waves (28 sums, each off by at most 2^-24 of itself,
+# and the partial sums of independent terms are no larger than the result, in the 2-norm), then the tiles in fp64: two
+# such results differ by at most 2 * 28 * 2^-24 = 3.4e-6.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tile_length_follows_the_batch(sc, dtype):
+    import torch
+    wl = workloads.Workload("tile_length", 24577, 5, 128, 3, 3, O01, dtype, 4712)
+    T = osc.build_tables(osc.OracleConfig(128, 3, 3, 5, O01))
+    gen = torch.Generator(device="cuda:0").manual_seed(4712)
+    rows, n_max = (torch.float32 if dtype == "f32" else torch.bfloat16), wl.num_nodes
+    rand = lambda *shape: torch.randn(*shape, generator=gen, device="cuda:0")
+    A, dB = rand(n_max, 128, 16).to(rows), rand(n_max, 128, 4).to(rows)
+    W = rand(5, len(T.paths), 128) / len(T.paths) ** 0.5
+    z = torch.randint(0, 4, (n_max,), generator=gen, device="cuda:0", dtype=torch.int32)   # the last element is absent
+    kind = sc.SC_F32 if dtype == "f32" else sc.SC_BF16
+    plans = [sc.sc_plan_create(128, 3, 3, 5, O01, kind, 0, 0, t) for t in (0, 16)]
+    sizes = [sc.sc_workspace_bytes(p, n_max) for p in plans]
+    work = [torch.empty(b, dtype=torch.uint8, device="cuda:0") for b in sizes]
+    for n in (1, 1023, 1024, 1025, 2048, 2049, 24576, 24577):
+        print(f"tile length {dtype} n={n}", flush=True)
+        out = []
+        for plan, ws, b in zip(plans, work, sizes):
+            ws.fill_(255)
+            B, dA, dW = torch.full_like(dB[:n], 7.0), torch.full_like(A[:n], 7.0), torch.full_like(W, 7.0)
+            sc.sc_forward(plan, n, A, z, W, B, ws, b)
+            sc.sc_backward(plan, n, A, z, W, dB, dA, dW, ws, b, sc.SC_REUSE_GROUPING | sc.SC_REUSE_WEIGHTS)
+            out.append((B, dA, dW))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+        a, b = out[0][2].double(), out[1][2].double()
+        assert not a[4].any() and float((a - b).norm()) <= 3.4e-6 * float(b.norm())
+    for plan in plans:
+        sc.sc_plan_destroy(plan)
+
+
 def test_empty_batch(sc):
     import torch
     wl = wl_of("empty", 0, 5, 128, 3, 3, O01, "f32", 2400)
