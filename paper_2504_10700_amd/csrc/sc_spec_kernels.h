@@ -716,9 +716,8 @@ constexpr bool kUseLdsState = sizeof(T) == 4 && G::kS <= 32;
 // matrix F (dW[p] = sum_s F[s,p] r[s]) falls into small independent blocks of one to three
 // internal rows s and the external paths p that depend on them (generated descriptors), so one
 // wave per (element, channel block, block of F) can do both steps without waiting for anyone:
-// it adds the block's rows over the element's tiles in tile order, in fp64, with the rows of up
-// to 32 tiles requested together (16 for two-row blocks), and writes the block's external paths.  Elements without nodes
-// own no tiles and get zeros.  Every sum has a fixed order: results are bitwise reproducible.
+// it adds the block's rows over the element's tiles in tile order, in fp64, and writes the block's
+// external paths.  Elements without nodes own no tiles and get zeros.  Every sum has a fixed order: results are bitwise reproducible.
 // What was measured on the way here (10k / 200k nodes): a sum kernel followed by an unfold kernel
 // 11.2 / 15.6 us; one workgroup per (element, channel block) for all rows 13.5 / 31 us (the twelve
 // workgroups of the six frequent elements own 60% of the bytes); four waves per block, a quarter
