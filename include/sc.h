@@ -165,7 +165,7 @@ sc_status sc_coupling_tensor(int32_t l1, int32_t l2, int32_t l3, double* out);
 
 /* Bytes of device workspace sc_forward / sc_backward need for a call with exactly
  * n_nodes nodes (a caller that sizes one buffer for several batch sizes takes the
- * maximum over them). */
+ * maximum over them; with a generated kernel that is the size for the largest). */
 sc_status sc_workspace_bytes(const sc_plan* plan, int64_t n_nodes, size_t* bytes);
 
 /* Forward of Algorithm 2.

@@ -101,10 +101,6 @@ LaunchShape launch_shape(const sc_plan* plan, int64_t n) {
     const int64_t full = rounds * slots / (waves_per_tile * s.chblocks);
     if (full < cuts) cuts = full;
     s.tiles_room = chosen ? s.max_tiles : static_cast<int>(cuts) + 1 + plan->cfg.num_elements;
-    int64_t u = (work + plan->num_cus * 3 / 2 - 1) / (plan->num_cus * 3 / 2);
-    u = (u + waves_per_tile - 1) / waves_per_tile * waves_per_tile;
-    u = u < 2 * waves_per_tile ? 2 * waves_per_tile : u > 24 * waves_per_tile ? 24 * waves_per_tile : u;
-    s.scratch_room = chosen ? s.max_tiles : static_cast<int>(n / u) + 1 + plan->cfg.num_elements;
   } else {
     // Table-driven kernels: every element's nodes split evenly into tiles of at most t nodes, about eight
     // (tile x channel block) workgroups per compute unit on small batches, bounded for large ones (the
@@ -117,7 +113,7 @@ LaunchShape launch_shape(const sc_plan* plan, int64_t n) {
     if (plan->cfg.tile_nodes > 0) t = plan->cfg.tile_nodes;
     s.tile_nodes = static_cast<int>(t);
     s.max_tiles = static_cast<int>(n / s.tile_nodes) + plan->cfg.num_elements;
-    s.tiles_room = s.scratch_room = s.max_tiles;
+    s.tiles_room = s.max_tiles;
   }
   // Grouping: one single-workgroup launch for small batches (group_waves = 0), else three
   // launches with about four 64-node chunks per wave, at most kMaxGroupWaves waves.
@@ -159,7 +155,7 @@ Workspace carve_workspace(const sc_plan* plan, int64_t n, const LaunchShape& sha
   w.tile_off = static_cast<int32_t*>(take(sizeof(int32_t) * (Z + 1)));
   w.counts = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(kMaxGroupWaves) * Z));
   w.perm = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));
-  w.tiles = static_cast<TileDesc*>(take(sizeof(TileDesc) * static_cast<size_t>(forward_only ? shape.scratch_room : shape.tiles_room)));
+  if (!(forward_only && plan->specialised)) w.tiles = static_cast<TileDesc*>(take(sizeof(TileDesc) * static_cast<size_t>(shape.tiles_room)));
   if (plan->specialised) w.wfold = take(spec_folded_bytes(plan));
   if (plan->specialised) {
     w.wnode = static_cast<int32_t*>(take(sizeof(int32_t) * static_cast<size_t>(n)));

@@ -32,7 +32,7 @@ struct Workspace {
   int32_t* tile_off;   // [Z+1] first tile of each element
   int32_t* counts;     // [kMaxGroupWaves][Z] scratch of the counting sort
   int32_t* perm;       // [N] node indices grouped by element (stable)
-  TileDesc* tiles;     // [tiles_room]
+  TileDesc* tiles;     // [tiles_room]; NULL where nothing may group (forward-only scratch of the generated kernels)
   void* wfold;         // generated kernels: weights folded into the internal basis, [Z][K][stride]
   int32_t* wnode;      // generated kernels: [N] window order of the forward pass (node per position) ...
   int32_t* wkey;       // ... and [N] its element index (Z: outside the range)
@@ -55,7 +55,6 @@ struct LaunchShape {
   int tile_nodes;   // nodes per tile (per workgroup)
   int max_tiles;    // upper bound of the tile count = grid size / chblocks
   int tiles_room;   // tiles that the workspace has room for: max_tiles of this and of every smaller batch
-  int scratch_room; // ... in the scratch of a forward without a workspace (part of that call's documented limit)
   int chblocks;     // ceil(K / 64)
   int group_waves;  // rows used of the count matrix (0: single-launch grouping)
   int nodes_per_group_wave;
@@ -108,7 +107,8 @@ inline bool misaligned(const void* p, size_t a) { return reinterpret_cast<uintpt
 sc_status set_error(sc_status code, const std::string& msg);
 
 LaunchShape launch_shape(const sc_plan* plan, int64_t n_nodes);
-// forward_only: the part the forward pass uses (the grouping), without the weight-gradient rows.
+// forward_only: the part the forward pass alone uses: no weight-gradient rows and, for the generated kernels, whose forward
+// needs no grouping, no tiles.
 Workspace carve_workspace(const sc_plan* plan, int64_t n_nodes, const LaunchShape& shape, void* base,
                           bool forward_only = false);
 

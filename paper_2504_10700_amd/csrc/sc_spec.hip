@@ -109,6 +109,7 @@ hipError_t launch_spec_prepare(const sc_plan* plan, int64_t n, const int32_t* z,
 
 hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z, const Workspace& ws,
                                const LaunchShape& shape, bool table_only, hipStream_t stream) {
+  if (!ws.tiles) return hipErrorInvalidValue;   // a workspace without room for tiles is never grouped
   const int scatter_wgs = table_only ? 0 : shape.split_waves / kGroupWavesPerWG;
   hipLaunchKernelGGL(spec_scatter_kernel, dim3(scatter_wgs + 1), dim3(kSpecThreads),
                      split_group_lds_bytes(plan->cfg.num_elements), stream, group_args(plan, n, z, ws, shape), scatter_wgs);
@@ -118,6 +119,7 @@ hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z,
 hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                                const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
                                bool component_major, bool direct, bool fold_table, hipStream_t stream) {
+  if (group != 0 && !ws.tiles) return hipErrorInvalidValue;
   return entry_of(plan->specialised)->forward(plan, n, A, z, W, B, ws, shape, group, window_order && ws.wnode && ws.wkey,
                                               component_major, direct, fold_table, stream);
 }

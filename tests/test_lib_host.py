@@ -5,6 +5,8 @@ import itertools
 import math
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -143,3 +145,19 @@ def test_workspace_serves_every_smaller_batch(channels, l_max, nu, dtype):
     sizes = [sc.sc_workspace_bytes(plan, n) for n in sorted(at)]
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
     sc.sc_plan_destroy(plan)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"), reason="needs g++ and the ROCm headers")
+def test_every_array_of_a_workspace_has_its_room(tmp_path):
+    # tests/workspace_layout_driver.cpp: the layouts of both kinds of workspace against the bounds that the launches use
+    exe = str(tmp_path / "layout")
+    lib = sc.LIB_PATH
+    build = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                            os.path.join(ROOT, "tests", "workspace_layout_driver.cpp"), lib, "-Wl,-rpath," + os.path.dirname(lib),
+                            "-Wl,-rpath-link,/opt/rocm/lib", "-Wl,--unresolved-symbols=ignore-in-shared-libs", "-o", exe],
+                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert build.returncode == 0, build.stdout
+    env = dict(os.environ, LD_LIBRARY_PATH="/opt/rocm/lib:" + os.environ.get("LD_LIBRARY_PATH", ""))
+    run = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, env=env, timeout=120)
+    assert run.returncode == 0, run.stdout
+    assert "workspace layouts checked" in run.stdout
