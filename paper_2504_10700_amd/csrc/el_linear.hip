@@ -269,16 +269,16 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2
     int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W,
     float* __restrict__ Y, RangeSum<float> sum) {
   __shared__ __attribute__((aligned(16))) unsigned lds[2 * kSplitSlot];
-  __shared__ int x_bad;
+  __shared__ int x_bad[kSplitRows];
   const int groups = k_cols / 128, ranges = gridDim.x / groups;
   const int group = blockIdx.x % groups, range = blockIdx.x / groups;
   const int64_t tiles = (n_nodes + 15) / 16;
   const int64_t t0 = tiles * range / ranges, t1 = tiles * (range + 1) / ranges;
   const SplitArgs p{n_nodes, k_red, k_cols, X, W, Y};
   if (__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) < kSplitThreads / 2)
-    split_passes<kTrans, 0>(p, t0, t1, group * 128, lds, &x_bad);
+    split_passes<kTrans, 0>(p, t0, t1, group * 128, lds, x_bad);
   else
-    split_passes<kTrans, 1>(p, t0, t1, group * 128, lds, &x_bad);
+    split_passes<kTrans, 1>(p, t0, t1, group * 128, lds, x_bad);
   if constexpr (kTrans) {
     if (sum.ranges == 0) return;
     const int64_t few = tiles / ranges;

@@ -270,7 +270,10 @@ struct SplitPass {
   typedef float V2 __attribute__((ext_vector_type(2)));
   static constexpr int NC = 16;
 
-  // The fp32 products of the same results, operands straight from memory: what the parts do not serve.
+  // The fp32 products of the same results, operands straight from memory: what the parts do not serve, a row tile (X) or a wave's
+  // columns (W) at a time.  Forward, us, with no such value / one weight / one value of X / one in a tenth of the tiles / one in each atom:
+  // 128 -> 128 channels, 4096 atoms 23 / 43 / 53 / 54 / 56, 10 000 56 / 109 / 72 / 89 / 146 (mfma_forward_lds_kernel 61), 256 -> 256, 4096
+  // 64 / 133 / 131 / 129 / 187.  With both tiles of a pass computed again for a value in one: 10 000 atoms 99 for one value of X, 117 in a tenth.
   static __device__ __forceinline__ void plain(const SplitArgs& p, int64_t n0, int jc, int q, int i16, acc_t (&acc)[8][2]) {
     const int64_t na = n0 + i16 < p.n_nodes ? n0 + i16 : p.n_nodes - 1;
 #pragma unroll
@@ -295,7 +298,7 @@ struct SplitPass {
     }
   }
 
-  // lds: two slots; x_bad: a word of LDS.  Called by all waves of the workgroup, those of both groups with the same n0 and j0.
+  // lds: two slots; x_bad: a word of LDS per row tile.  Called by all waves of the workgroup, those of both groups with the same n0 and j0.
   static __device__ __forceinline__ void run(const SplitArgs& p, int64_t n0, int j0, unsigned* lds, int* x_bad) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));              // what is derived from it here is not held in registers from pass to pass
@@ -310,7 +313,7 @@ struct SplitPass {
       for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int u = 0; u < 2; ++u) acc[t][i][u] = acc_t{0, 0, 0, 0};
-    if (tid == 0) *x_bad = 0;                  // (read last before the barriers of the previous pass's stores)
+    if (tid < R) x_bad[tid] = 0;               // (read last before the barriers of the previous pass's stores)
 
     // rows of X.  This thread: quarter xp of the rows of reduction channels 2 xk, 2 xk + 1 of atoms wave and wave + 8 of
     // the tile: four lanes read a row, and an instruction whole lines between them.
@@ -332,11 +335,10 @@ struct SplitPass {
           xr[e][j] = __builtin_bit_cast(V4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane + j * NC * 4, so, 0));
       }
     };
-    unsigned long long w_inexact = 0;          // lanes that have split a value into parts of another sum
-    unsigned x_left = 0;
-    auto split_x = [&](int slot, int i) {      // the i-th of this thread's eight pairs of the step
+    unsigned long long w_inexact = 0, x_inexact[R] = {};   // lanes that have split a value into parts of another sum
+    auto split_x = [&](int slot, int i, unsigned& left) {   // the i-th of this thread's eight pairs of the step
       unsigned* const dst = lds + slot * kSplitSlot + (4 * xp + i % 4) * kSplitComp + xk / 4 * kSplitEight + (wave + i / 4 * 8) * 4 + xk % 4;
-      const SplitPair s = split_pair(xr[i / 4][0][i % 4], xr[i / 4][1][i % 4], x_left);
+      const SplitPair s = split_pair(xr[i / 4][0][i % 4], xr[i / 4][1][i % 4], left);
       dst[0] = s.h;
       dst[kSplitPlane] = s.m;
       dst[2 * kSplitPlane] = s.l;
@@ -383,18 +385,19 @@ struct SplitPass {
       w_inexact |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
     };
 
-    // The products of a step.  The parts of X in turn, l first; where one has been used for the last time, the next
-    // component's is requested.  last: the chunk's last step, after which the next chunk's W takes the registers.
-    auto multiply = [&](int slot, acc_t (&sum)[8][2], bool last, int ch, int ahead) {
+    // The products of a step, and the split of the next one (inexact: of its tile).  The parts of X in turn, l
+    // first; where one has been used for the last time, the next component's is requested.  last: the chunk's last step, after which the next chunk's W takes the registers.
+    auto multiply = [&](int slot, acc_t (&sum)[8][2], unsigned long long& inexact, bool last, int ch, int ahead) {
       const unsigned* const src = lds + slot * kSplitSlot + q * kSplitEight + i16 * 4;
+      unsigned left = 0;
       U4 a[3];
 #pragma unroll
       for (int part = 0; part < 3; ++part) a[part] = *reinterpret_cast<const U4*>(src + part * kSplitPlane + O::component(0) * kSplitComp);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         if (i >= 4) {                          // (late: their requests have had half a step)
-          split_x(slot ^ 1, 2 * i - 8);
-          split_x(slot ^ 1, 2 * i - 7);
+          split_x(slot ^ 1, 2 * i - 8, left);
+          split_x(slot ^ 1, 2 * i - 7, left);
         }
         const int o = i < O::n_lo ? 0 : 1;
         acc_t small[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
@@ -423,6 +426,7 @@ struct SplitPass {
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      inexact |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
       __builtin_amdgcn_sched_barrier(0);       // (what is split is out of the registers before the next rows come in)
       gload(ahead);
       if (last) {
@@ -438,8 +442,10 @@ struct SplitPass {
     split_w(0);
     wload(1, 0);
     __builtin_amdgcn_sched_barrier(0);
+    unsigned first = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) split_x(0, i);
+    for (int i = 0; i < 8; ++i) split_x(0, i, first);
+    x_inexact[0] = __builtin_amdgcn_ballot_w64((first & 0xffffu) != 0);
     gload(1);
     split_w(1);
     wload(0, 1);
@@ -448,12 +454,13 @@ struct SplitPass {
       for (int t = 0; t < R; ++t) {
         const int slot = R == 2 ? t : ch & 1;
         __syncthreads();                       // this step's planes are written, those of the other slot have been read
-        multiply(slot, acc[t], t == R - 1, ch, ch * R + t + 2);
+        multiply(slot, acc[t], x_inexact[(t + 1) % R], t == R - 1, ch, ch * R + t + 2);
       }
     }
-    if ((x_left & 0xffffu) != 0) *x_bad = 1;
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+      if (x_inexact[t] != 0) x_bad[t] = 1;
     __syncthreads();                           // also: the planes have been read, the stages may take their place
-    const bool redo = *x_bad != 0 || w_inexact != 0;
     float* const stages = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int t = 0; t < R; ++t) {
@@ -466,7 +473,7 @@ struct SplitPass {
         for (int u = 0; u < 2; ++u)
 #pragma unroll
           for (int r = 0; r < 4; ++r) bad = __builtin_fmaf(acc[t][i][u][r], 0.0f, bad);
-      if (redo || __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0) plain(p, n0 + t * 16, jc, q, i16, acc[t]);
+      if (x_bad[t] != 0 || w_inexact != 0 || __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0) plain(p, n0 + t * 16, jc, q, i16, acc[t]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float* const stage = stages + (r & 1) * kSplitStage;

@@ -242,6 +242,58 @@ def test_values_of_every_exponent_keep_their_bits(el):
         assert wrong.numel() == 0, (what, wrong[:20].tolist())
 
 
+# Such values where a workgroup makes several passes over its row tiles (625 tiles on a workgroup per CU: passes of two and of one), in the
+# first tile of a pair, the second, the single one behind them and the last, ragged one: the rows of those tiles are the products in
+# fp32, and those of every other tile, the other one of the pair included, keep their bits.  Columns 64 to 127 of W have one nonzero value, 1:
+# there a small value comes back as it is.
+@pytest.mark.parametrize("value", [1.2345e-36, float("inf"), 3.4e38])
+def test_values_that_do_not_split_in_several_passes(el, value):
+    import torch
+    N, K = 9990, 128
+    cus, tiles = torch.cuda.get_device_properties(0).multi_processor_count, -(-N // 16)
+    starts = [tiles * r // cus for r in range(cus + 1)]
+    threes = [a for a, b in zip(starts, starts[1:]) if b - a == 3]
+    bad = [threes[0], threes[len(threes) // 3] + 1, threes[len(threes) // 2] + 2, tiles - 1]
+    gen = torch.Generator(device="cuda").manual_seed(8910)
+    X0 = torch.randn((N, K, 16), generator=gen, device="cuda")
+    W = torch.randn((4, K, K), generator=gen, device="cuda") / K ** 0.5
+    W[:, :, 64:] = 0
+    for l in range(4):
+        W[l, torch.randperm(K, generator=gen, device="cuda")[:64], torch.arange(64, 128, device="cuda")] = 1
+    X = X0.clone()
+    for t in bad:
+        X[16 * t + 3, 7, 2] = value
+    cfg = el.make_config(K, K, 3)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    ws, dW, Wt = torch.empty(nbytes, dtype=torch.uint8, device="cuda"), torch.empty_like(W), W.transpose(1, 2).contiguous()
+
+    def forward(x):
+        Y = torch.empty_like(x)
+        el.el_forward(cfg, N, x, W, Y)
+        return Y
+
+    def dx(x):                                   # dX of (Wt, dY = x) is the forward of (x, W)
+        dX = torch.empty_like(x)
+        el.el_backward(cfg, N, torch.zeros_like(x), Wt, x, dX, dW, ws, nbytes)
+        return dX
+
+    touched = torch.zeros(N, dtype=torch.bool, device="cuda")
+    for t in bad:
+        touched[16 * t:16 * t + 16] = True
+    order = torch.tensor([int(c ** 0.5) for c in range(16)], device="cuda")
+    rows = X[touched].double()
+    ref = torch.stack([rows[:, :, c] @ W[order[c]].double() for c in range(16)], dim=2)
+    for run in (forward, dx):
+        clean, got = run(X0), run(X)
+        assert torch.equal(got[~touched], clean[~touched]), run.__name__
+        g = got[touched].double()
+        assert torch.equal(g.isnan(), ref.isnan()) and torch.equal(g.isinf(), ref.isinf()), run.__name__
+        fine = ref.isfinite() & (ref.abs() < 1e25)
+        assert ((g - ref)[fine].abs().max() / ref[fine].square().mean().sqrt()).item() <= 1e-5
+        if value < 1:
+            assert torch.equal(g[:, 64:], ref[:, 64:]), run.__name__
+
+
 # dW: ranges of atoms that end inside a chunk of four (the copies that fill it count nothing), and every launch that adds the ranges up: the
 # product that reads W as it is and the one that reads it transposed, the workgroups of the products of split values that have
 # a tile less than others (282 tiles on 256), all of them (257 and 511 on 256 within one tile of even), and a launch of its own.
