@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // walks its share of the row tiles of its 128 columns, two tiles a pass.  What bounds it at 8192 atoms and 128 -> 128 channels (two tiles per
 // CU, 41 us): 29 us for the rows at the rate of a large copy, 15 us of products, 8 us of stores at the end of the pass with nothing left to
 // overlap them.  Forward on inputs from memory, us, before (two workgroups per CU, each with one tile and its own split of
-// W; at 10 000 and 12 288 atoms mfma_forward_lds_kernel) -> this: 128 -> 128 channels, 4096 atoms 26.9 -> 23.1, 5000 33.0 -> 33.7, 8192
+// W; at 10 000 and 12 288 atoms mfma_forward_lds_kernel) -> this: 128 -> 128 channels, 4096 atoms 26.9 -> 23.1, 8192
 // 42.3 -> 40.6, 10 000 60.8 -> 55.5, 12 288 65.0 -> 58.3, 24 000 119 -> 113; 256 -> 256, 6000 atoms 99.9 -> 95.4; 256 -> 128, 4096 atoms
 // 47.2 -> 37.7; 512 -> 128, 3000 atoms 75 -> 58.  The pairs of X split in the first half of a step, right behind their requests: 4096
 // atoms 24.2, 10 000 56.6.  One tile a pass with requests two steps ahead: 24.2 and 55.3, 256 -> 256 6000 atoms 96.6.  Error against 64 bits
@@ -288,6 +288,32 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2
     if (4 * less < ranges) add_ranges(sum, blockIdx.x, gridDim.x, quarter);
     else if (t1 - t0 == few) add_ranges(sum, (range - (t0 - range * few)) * groups + group, static_cast<int64_t>(less) * groups, quarter);
   }
+}
+
+// The same products with a workgroup per row tile and two of them on a CU (128 registers), each with its own split of W: where hardly more
+// tiles than CUs would leave most workgroups of the kernel above with one tile and let all wait for those with two (pair_pays).
+__global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void mfma_forward_bf16_pair_kernel(
+    int64_t n_nodes, int k_red, int k_cols, const float* __restrict__ X, const float* __restrict__ W, float* __restrict__ Y) {
+  __shared__ __attribute__((aligned(16))) unsigned planes[3 * kPairPlane];
+  static_assert(kSplitWaves * kStoreStageFloats <= 3 * kPairPlane, "the store stages reuse the planes");
+  const int groups = k_cols / 128;
+  const int64_t n0 = blockIdx.x / groups * int64_t(16);
+  const int j0 = static_cast<int>(blockIdx.x % groups) * 128;
+  // What is computed again is what a pass computes again (32 columns and two orders, or all for a value of X), so that a result does not
+  // depend on which of the kernels it is from.
+  __shared__ int bad[4][2];
+  if (threadIdx.x < 8) (&bad[0][0])[threadIdx.x] = 0;         // (the product begins with a barrier)
+  Mma<float>::acc_t acc[16][1];
+  bool x_served, redo[2];
+  split_tile_product(n_nodes, n0, j0, k_red, k_cols, X, W, planes, acc, x_served, redo);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+  const int jc[1] = {j0 + wave * 16 + static_cast<int>(threadIdx.x % 16)};
+  if (redo[0]) bad[wave / 2][0] = 1;
+  if (redo[1]) bad[wave / 2][1] = 1;
+  const bool all = __syncthreads_or(!x_served);               // (also the barrier after which the planes are free)
+  if (all || bad[wave / 2][0] != 0) plain_tile_product<0>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
+  if (all || bad[wave / 2][1] != 0) plain_tile_product<1>(n_nodes, n0, jc[0], k_red, k_cols, X, W, acc);
+  store_tile_coalesced<1>(Y, n_nodes, n0, k_cols, jc, acc, reinterpret_cast<float*>(planes) + wave * kStoreStageFloats);
 }
 
 // Partial dW of a range of atoms: part[range][l][k][j] = sum_{n in range} sum_{m in l} X[n][k][c] dY[n][j][c].
@@ -796,6 +822,19 @@ bool bf16_parts_ok(size_t elem, int l_max, int64_t n, int k_red, int k_cols) {
   return k_red == 64 && (units > 5 * cus || more == 0 || more > cus / 2);
 }
 
+// ... and with W read along its rows (not dX, whose launch also adds the partial dW) by the kernel with two workgroups on a CU?  Up to a quarter
+// more row tiles than CUs, with fewer channels summed up to five eighths more and twice as many, because the second tile of a pass costs more of it
+// there; 64 channels also beyond five tiles per CU, where a pass is mostly its stores.  Forward, us, one / two workgroups on a CU: 128 -> 128
+// channels, 4097 atoms 33.3 / 28.6, 4448 34.5 / 31.5, 5000 34.4 / 32.1, 6000 34.4 / 35.2; 256 -> 128, 4100 54.8 / 50.4; 256 -> 256, 2100 55.9 / 53.5, 3000 55.2 /
+// 56.2; 96 -> 128, 4100 27.5 / 23.9, 6400 29.4 / 27.8; 64 -> 128, 4100 22.8 / 19.2, 6400 23.9 / 23.2, 20 640 75.9 / 70.1, 40 000 123 / 119; 32 -> 128, 2100
+// 10.8 / 9.8, 5000 18.5 / 14.9, 8192 21.7 / 21.2.
+bool pair_pays(int64_t n, int k_red, int k_cols) {
+  const int64_t cus = compute_units(), units = (n + 15) / 16 * (k_cols / 128);
+  if (k_red <= 32) return true;                // (up to two per CU: bf16_parts_ok)
+  if (k_red == 64 && units > 5 * cus && units < (int64_t(1) << 22)) return true;   // (a workgroup each: the grid's limit)
+  return units > cus && units <= cus + (k_red <= 96 ? cus * 5 / 8 : cus / 4);
+}
+
 // ... whose dX reads W as it is: a lane's channels are contiguous there and the launch that transposes W is saved.  (Backward, us, with
 // the kernel of two workgroups per CU, W transposed / as it is: 128 -> 128 channels, 2100 atoms 60.8 / 57.8, 8192 108 / 100, 20 480
 // 237 / 226; 256 -> 128, 3000 atoms 87.4 / 83.5, 20 000 429 / 407; 256 -> 256, 20 000 atoms 716 / 714.)
@@ -840,6 +879,13 @@ hipError_t forward_l(int64_t n, int k_red, int k_cols, const void* X, const void
   if constexpr (sizeof(T) == 4 && LMAX == 3) {
     if (bf16_parts_ok(sizeof(T), LMAX, n, k_red, k_cols)) {
       const int groups = k_cols / 128;
+      if constexpr (!kTrans) {
+        if (pair_pays(n, k_red, k_cols)) {
+          hipLaunchKernelGGL(mfma_forward_bf16_pair_kernel, dim3(static_cast<unsigned>((n + 15) / 16 * groups)), dim3(kSplitThreads), 0, stream,
+                             n, k_red, k_cols, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<float*>(Y));
+          return hipGetLastError();
+        }
+      }
       const int64_t ranges = std::min<int64_t>((n + 15) / 16, std::max(1, compute_units() / groups));
       RangeSum<float> sum{};
       if (kTrans && ride) std::swap(sum, *ride);

@@ -507,6 +507,162 @@ struct SplitPass {
   }
 };
 
+// The accumulators of rows n0..n0+15 and of the wave's 16 of the 128 columns from j0 on, in half the registers of a pass: a workgroup with
+// one tile each for two workgroups on a CU (mfma_forward_bf16_pair_kernel).  The workgroup (eight waves) splits X in chunks of 32 reduction
+// channels into LDS (three planes of [component][atom][32]; the next chunk's rows are requested a chunk ahead); a wave splits its own
+// columns of W order by order, requested an order ahead.  x_served: the values of X that the wave has split are the sums of their parts (for other
+// waves' columns as well).  redo[G]: not so for the wave's values of W, or results that are not finite, in the orders of wave group G of a pass.
+constexpr int kPairPlane = 16 * 16 * kSplitChunk / 2;     // 32-bit words of a plane: two channels each
+
+__device__ __forceinline__ void split_tile_product(int64_t n_nodes, int64_t n0, int j0, int k_red, int k_cols,
+                                                   const float* __restrict__ X, const float* __restrict__ W,
+                                                   unsigned* planes /* 3 * kPairPlane words */,
+                                                   typename Mma<float>::acc_t (&acc)[16][1], bool& x_served, bool (&redo)[2]) {
+  constexpr int NC = 16, L = 4;
+  typedef Mma<float>::acc_t acc_t;
+  typedef float V4 __attribute__((ext_vector_type(4)));
+  // The thread's number as a value of its own: what is derived from it here ends with the loop, and what the
+  // caller derives from it is not held in registers through the loop.
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int q = tid / 16 % 4, i16 = tid % 16, jc = j0 + tid / kLanes * 16 + i16;
+  const int chunks = k_red / kSplitChunk;
+  // splitting role of this thread: half of the components of one atom of the tile and two reduction channels
+  const int half = tid / 256, sa = tid / 16 % 16, sk = tid % 16;
+  int64_t ns = n0 + sa;
+  if (ns >= n_nodes) ns = n_nodes - 1;       // rows past the end split a valid atom and are not stored
+  // (through a descriptor of the tile's rows, like W: the lane's part is one 32-bit offset)
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(X + static_cast<size_t>(n0) * k_red * NC), 0, 16 * k_red * NC * 4, 0x00020000);
+  const unsigned xoff = ((static_cast<unsigned>(ns - n0) * k_red + 2 * sk) * NC + half * 8) * 4u;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c][0] = acc_t{0, 0, 0, 0};
+
+  unsigned long long x_inexact = 0, w_inexact[2] = {};   // lanes that have split a value into parts of another sum
+  V4 xr[2][2];
+  auto gload = [&](int chunk) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      xr[i / 2][i % 2] = __builtin_bit_cast(V4, __builtin_amdgcn_raw_buffer_load_b128(
+          xrs, static_cast<int>(xoff), (chunk * kSplitChunk * NC + i / 2 * NC + i % 2 * 4) * 4, 0));
+  };
+  auto split_x = [&]() {
+    unsigned left = 0;
+    unsigned* dst = planes + half * 8 * 256 + sa * 16 + sk;
+#pragma unroll
+    for (int c = 0; c < NC / 2; ++c) {
+      const float x = xr[0][c / 4][c % 4], y = xr[1][c / 4][c % 4];
+      const SplitPair s = split_pair(x, y, left);
+      dst[c * 256] = s.h;
+      dst[c * 256 + kPairPlane] = s.m;
+      dst[c * 256 + 2 * kPairPlane] = s.l;
+    }
+    x_inexact |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
+  };
+  // this lane's column of W: eight channels 8 q .. 8 q + 7 of a chunk, as in lds_tile_product through a descriptor
+  const unsigned boff = static_cast<unsigned>(8 * q * k_cols + jc) * 4u;
+  const unsigned row_bytes = static_cast<unsigned>(k_cols) * 4u;   // from a reduction channel to the next
+  const unsigned lstride = static_cast<unsigned>(k_red) * static_cast<unsigned>(k_cols) * 4u;
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W), 0, static_cast<int>(L * lstride), 0x00020000);
+  float wr[8];
+  auto bload = [&](int chunk, int l) {
+    const unsigned so = static_cast<unsigned>(l) * lstride + static_cast<unsigned>(chunk * kSplitChunk) * row_bytes;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      wr[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrs, static_cast<int>(boff),
+                                                                             static_cast<int>(so + i * row_bytes), 0));
+  };
+  auto read_a = [&](int part, int c) {
+    return *reinterpret_cast<const U4*>(planes + part * kPairPlane + c * 256 + i16 * 16 + q * 4);
+  };
+  gload(0);
+  bload(0, L - 1);
+  // The waves that multiply go first: the two workgroups of a CU drift apart, and one's products cover the other's
+  // requests and splitting (20 000 atoms: 112 -> 102 us, with six products).
+  for (int ch = 0; ch < chunks; ++ch) {
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();                         // the reads of the previous chunk are done
+    split_x();
+    __builtin_amdgcn_sched_barrier(0);       // (what is split is out of the registers before the next rows come in)
+    // (no condition on the request: at its join the compiler would wait for every outstanding load)
+    gload(ch + 1 < chunks ? ch + 1 : ch);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    U4 a[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) a[p] = read_a(p, (L - 1) * (L - 1));
+#pragma unroll
+    for (int l = L - 1; l >= 0; --l) {
+      U4 b[3];
+      unsigned left = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const SplitPair s = split_pair(wr[2 * i], wr[2 * i + 1], left);
+        b[0][i] = s.h;
+        b[1][i] = s.m;
+        b[2][i] = s.l;
+      }
+      w_inexact[l % 3 == 0 ? 0 : 1] |= __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const int next = l > 0 ? ch : (ch + 1 < chunks ? ch + 1 : ch);   // past the end: a valid chunk again
+      bload(next, l > 0 ? l - 1 : L - 1);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int c = l * l; c < (l + 1) * (l + 1); ++c) {
+        // The parts of X in turn, l first; where one has been used for the last time, the next component's is requested
+        // (4000 atoms, 256 -> 256 channels: 76 -> 71 us).
+        const int next_c = c + 1 < (l + 1) * (l + 1) ? c + 1 : (l > 0 ? (l - 1) * (l - 1) : -1);
+        acc_t small{0, 0, 0, 0};
+#pragma unroll
+        for (int p = 2; p >= 0; --p) {
+#pragma unroll
+          for (int w = 2; w >= 0; --w) {
+            if (p + w == 4) continue;        // l l
+            acc_t& sum = p + w == 0 ? acc[c][0] : small;
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(Bf8, a[p]), __builtin_bit_cast(Bf8, b[w]), sum, 0, 0, 0);
+          }
+          if (next_c >= 0) a[p] = read_a(p, next_c);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[c][0][r] += small[r];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+  bool finite[2] = {true, true};
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) finite[order_of(c) % 3 == 0 ? 0 : 1] &= __builtin_isfinite(acc[c][0][r]);
+  x_served = x_inexact == 0;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) redo[g] = w_inexact[g] != 0 || __builtin_amdgcn_ballot_w64(!finite[g]) != 0;
+}
+
+// The accumulators of wave group G's orders on the fp32 matrix cores, operands straight from memory: what the parts do not serve.
+template <int G>
+__device__ __forceinline__ void plain_tile_product(int64_t n_nodes, int64_t n0, int jc, int k_red, int k_cols,
+                                                   const float* __restrict__ X, const float* __restrict__ W,
+                                                   typename Mma<float>::acc_t (&acc)[16][1]) {
+  typedef SplitOrders<G> O;
+  constexpr int NC = 16;
+  const int lane = threadIdx.x & (kLanes - 1), q = lane / 16, i16 = lane & 15;
+  const int64_t na = n0 + i16 < n_nodes ? n0 + i16 : n_nodes - 1;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[O::component(i)][0] = Mma<float>::acc_t{0, 0, 0, 0};
+  for (int k = q; k < k_red; k += 4) {
+    float a[NC], b[2];
+    load_row<float, NC>(X + (static_cast<size_t>(na) * k_red + k) * NC, a);
+#pragma unroll
+    for (int o = 0; o < 2; ++o) b[o] = W[(static_cast<size_t>(o == 0 ? O::lo : O::hi) * k_red + k) * k_cols + jc];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      acc[O::component(i)][0] = Mma<float>::mma(a[O::component(i)], b[i < O::n_lo ? 0 : 1], acc[O::component(i)][0]);
+  }
+}
+
 // Store of a wave's result tile Y[n0 + 4*(lane/16) + r][jc[t]][0..15].  A lane holds whole 64-byte
 // rows; stored directly, every instruction would write a quarter of each row (16-byte pieces 64
 // bytes apart: partial lines, four times the write requests).  Per (t, r) the 16 rows of a

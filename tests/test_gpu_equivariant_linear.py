@@ -146,11 +146,30 @@ def test_batches_on_both_sides_of_the_rule(el, N, k_red):
             assert err <= 1e-5, (what, c, err)
 
 
+# ... and of the rule that gives a row tile a workgroup of its own, two on a compute unit (256 units; the first and the last of its
+# units with 128 channels summed, 96, 64 and 32, one more, and two groups of columns).
+@pytest.mark.parametrize("N,k_red,k_cols", [(4096, 128, 128), (4097, 128, 128), (5120, 128, 128), (5121, 128, 128), (6656, 96, 128), (6657, 96, 128),
+                                            (4111, 64, 128), (6650, 64, 128), (20497, 64, 128), (4105, 32, 128), (8192, 32, 128), (2049, 160, 256)])
+def test_a_workgroup_for_every_row_tile(el, N, k_red, k_cols):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(8870 + k_red)
+    X = torch.randn((N, k_red, 16), generator=gen, device="cuda")
+    W = torch.randn((4, k_red, k_cols), generator=gen, device="cuda") / k_red ** 0.5
+    Y = torch.full((N + 1, k_cols, 16), 7.0, device="cuda")
+    el.el_forward(el.make_config(k_red, k_cols, 3), N, X, W, Y)
+    assert (Y[N] == 7).all()
+    for c in range(16):
+        ref = X[:, :, c].double() @ W[int(c ** 0.5)].double()
+        err = ((Y[:N, :, c].double() - ref).abs().max() / ref.square().mean().sqrt()).item()
+        assert err <= 1e-5, (c, err)
+
+
 # dX of these products reads W as it is: the same sums in the same order as el_forward on W transposed, also in tiles
 # that are computed again.  One chunk of the reduction and several, two groups of columns, a reduction that is no multiple of
 # 32, a ragged last row tile and none.
 @pytest.mark.parametrize("N,k_in,k_out", [(2065, 128, 32), (2049, 128, 160), (1100, 256, 96), (2070, 128, 48),
-                                          (3072, 128, 512), (3073, 128, 512)])
+                                          (3072, 128, 512), (3073, 128, 512),
+                                          (4300, 128, 128), (4150, 128, 96), (5500, 128, 64)])   # (the forward's tiles in workgroups of their own)
 def test_dx_is_the_product_with_w_transposed(el, N, k_in, k_out):
     import torch
     X, W, dY = (torch.tensor(x, dtype=torch.float32, device="cuda:0") for x in workloads.make_linear_inputs(N, k_in, k_out, 3, 8960))
