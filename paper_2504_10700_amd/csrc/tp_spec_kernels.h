@@ -287,13 +287,22 @@ struct Channels {
 // Forward / backward / second-order pass, us, 128 channels, l_h = 1, wave -> workgroup per (atom, block): 250 atoms
 // 21 -> 9 / 53 -> 24 / 78 -> 37, 2000 40 -> 37 / 100 -> 79 / 230 -> 193, 10 000 243 -> 225 / 500 -> 492 / 859 -> 817; l_h = 2
 // (fp64 arithmetic), 3001 atoms 180 -> 165 / 368 -> 361 / 888 -> 817.
-// Waves per SIMD that the forward is held to: with fp64 arithmetic on fp32 rows and 10 to 17 paths it wants 129 registers if
-// left alone, one over the limit for four.
+// Waves per SIMD that the forward is held to.  fp64 arithmetic on fp32 rows: with 10 to 17 paths it wants 129 registers if left alone, one
+// over the limit for four; with 7 paths 91 for 78 (2000 atoms, 20 edges each, 29.5 -> 29.0 us, one edge 6.5 -> 6.1).
 template <typename T, typename TS, typename G>
-constexpr int kForwardWaves = sizeof(T) == 8 && sizeof(TS) == 4 && G::kP >= 10 && G::kP <= 17 ? 4 : 1;
+constexpr int kForwardWaves = sizeof(T) == 8 && sizeof(TS) == 4 ? (G::kP >= 10 && G::kP <= 17 ? 4 : G::kP == 7 ? 6 : 1) : 1;
 
-template <typename T, typename TS, typename G, bool kFull, int kWaves>
-__global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kForwardWaves<T, TS, G>))) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
+// ... where an atom has few edges, so that a wave of the four has one or two and nothing to overlap: the registers that two edges under way
+// take if left alone (fp32, l_h = 1, 105 for 58; fp64, l_max = 2, 116 for 74) are waves missing.  fp32, l_h = 1, us, left alone / held: 2000
+// atoms with one edge each 8.2 / 6.5, four 12.9 / 11.8, eight 20.0 / 18.7, twenty 44.4 / 45.5; 10 000 with four 48.9 / 43.4, eight 96.2 / 94.7, ten
+// 114 / 116, twenty 213 / 222.  fp64, l_max = 2: 2000 atoms with one 8.1 / 7.1, 10 000 with four 77.4 / 74.8, 2000 with eight 30.3 / 31.0.
+template <typename T, typename TS, typename G>
+constexpr int kFewEdgesWaves = sizeof(T) == 4 ? 8 : sizeof(TS) == 8 && G::kP == 7 ? 6 : kForwardWaves<T, TS, G>;
+template <typename T>
+constexpr int kFewEdges = sizeof(T) == 4 ? 9 : 4;     // edges an atom
+
+template <typename T, typename TS, typename G, bool kFull, int kWaves, int kHold>
+__global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kHold))) void forward_kernel(int K, int chblocks, int64_t unit0, int64_t n_units,
                                                            const TS* __restrict__ Y, const TS* __restrict__ h,
                                                            const TS* __restrict__ R,
                                                            const EdgeList el, TS* __restrict__ A) {
@@ -617,7 +626,10 @@ struct Launch {
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int64_t n_units = a.n_out_nodes * chblocks;
     const int waves = waves_per_unit(a.n_edges, a.n_out_nodes, n_units);
-    const auto kernel = waves == 4 ? &forward_kernel<T, TS, G, kFull, 4> : &forward_kernel<T, TS, G, kFull, 2>;
+    constexpr int kUsual = kForwardWaves<T, TS, G>, kFew = kFewEdgesWaves<T, TS, G>;
+    const auto kernel = waves == 2                                         ? &forward_kernel<T, TS, G, kFull, 2, kUsual>
+                        : a.n_edges <= kFewEdges<T> * a.n_out_nodes ? &forward_kernel<T, TS, G, kFull, 4, kFew>
+                                                                    : &forward_kernel<T, TS, G, kFull, 4, kUsual>;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
       hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, chblocks, unit0, n_units,
                          static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h), static_cast<const TS*>(a.R),

@@ -358,7 +358,8 @@ def test_edge_tensors_that_pass_two_to_the_31_elements(tp):
 # The four waves of an atom's workgroup share its edges: fewer edges than waves, one round and a part of the next;
 # one channel block (its share of dY is the result), a ragged one, several.
 @pytest.mark.parametrize("mean_degree", [1, 2, 4, 6, 9])
-@pytest.mark.parametrize("K,l,l_h,dtype", [(64, 3, 1, "f32"), (40, 2, 2, "f32"), (192, 3, 0, "f32"), (64, 3, 2, "f64"), (72, 3, 1, "f64")])
+@pytest.mark.parametrize("K,l,l_h,dtype", [(64, 3, 1, "f32"), (40, 2, 2, "f32"), (192, 3, 0, "f32"), (64, 3, 2, "f64"), (72, 3, 1, "f64"),
+                                             (64, 2, 1, "f64"), (64, 2, 1, "f32")])
 def test_edges_shared_by_the_waves(tp, mean_degree, K, l, l_h, dtype):
     full_parity(tp, wl_of("shared_edges", 37, mean_degree, K, l, l_h, l, dtype, 5400 + mean_degree))
 
