@@ -82,22 +82,39 @@ LaunchShape launch_shape(const sc_plan* plan, int64_t n) {
     // kernels that matter here, and a compute unit with two whole pieces ends when it has done both, so a whole piece
     // should be hardly more than the even share of a slot (work / slots nodes per wave): one round of whole pieces, which
     // the shorter ones next to element boundaries fill up.  One node per wave on top of the share leaves the pieces that
-    // much fewer, so that the short ones find free slots.  Shares above 24 nodes per wave are cut into equal rounds.  (A list
-    // schedule of the pieces on 2 x 256 slots that share the issue of their compute unit reproduces the times below.)
+    // much fewer, so that the short ones find free slots.  Shares above 28 nodes per wave are cut into equal rounds: every round
+    // costs that one node more (24 577 nodes in one round of 26 nodes per wave, two of 14, and the 24 of a fixed length with its
+    // remainders: backward 80, 87, 91 us, second-order pass 162, 169, 166).
     // Measured, us, 128 channels, 89 elements of skewed frequency, against t: step, 3500 nodes 16 -> 35.5, 20 -> 33.8,
     // 24 -> 34.7; 10000 nodes 32 -> 75.8, 40 -> 71.8, 44 -> 70.4, 56 -> 73.4; 15000 nodes 64 -> 101.2, 80 -> 105.1; 40000
     // nodes 84 -> 230.3, 96 -> 233.6; step with the second-order pass, 6000 nodes 24 -> 104.9, 28 -> 101.6, 32 -> 102.7;
-    // 10000 nodes 32 -> 154.9, 44 -> 141.6, 48 -> 146.6, 56 -> 151.4; 15000 nodes 64 -> 197.8, 80 -> 210.4.
+    // 10000 nodes 32 -> 154.9, 44 -> 141.6, 48 -> 146.6, 56 -> 151.4; 15000 nodes 64 -> 197.8, 80 -> 210.4; second-order pass, 29500
+    // nodes 64 -> 194, 96 -> 210, 120 -> 190; 64 channels, 60000 nodes 64 -> 196, 96 -> 237, 124 -> 192.
     const int64_t slots = static_cast<int64_t>(plan->num_cus) * 2 * waves_per_tile;
-    const int64_t rounds = work > 0 ? (work + 24 * slots - 1) / (24 * slots) : 1;
+    const int64_t rounds = work > 0 ? (work + 28 * slots - 1) / (28 * slots) : 1;
     t = ((work + rounds * slots - 1) / (rounds * slots) + 1) * waves_per_tile;
-    if (t < 2 * waves_per_tile) t = 2 * waves_per_tile;
+    const int64_t least = 2 * waves_per_tile;
+    if (t < least) t = least;
+    // Two exceptions for short shares.  fp32 arithmetic of l_max = 3 with three factors (a unit holds just two workgroups of the backward): the
+    // shortest pieces where all of them, a remainder of every element among them, have slots at once; the launch is as long as the longest
+    // (backward / second-order pass, 8 and 12 nodes a piece, 128 channels, 0e+1o, 1030 nodes 14.4 and 15.6 / 19.1 and 22.2, 1330 15.4 and 16.0 / 21.2 and
+    // 22.3; bfloat16 rows 1030 13.3 and 14.8 / 20.6 and 24.3; 0e+1o+2e, 1030, step 32.1 and 34.0).  The others: a second node on top of shares
+    // between 1.75 and 5.5 (step, one and two on top, 128 channels: fp64, 2600 nodes 61.6 and 58.6, 4000 79.4 and 79.0; l_max = 2 3072 27.7 and
+    // 26.6, 4000 30.5 and 29.3; two factors 3072 26.1 and 24.7, 4000 30.9 and 28.8; the first kind not: 0e+1o+2e, 2600 42.4 and 43.8).
+    const bool two_per_unit = plan->cfg.l_max == 3 && plan->cfg.nu_max == 3 && plan->cfg.dtype != SC_F64 && plan->S <= 49;
+    if (two_per_unit) {
+      if ((n / least + plan->cfg.num_elements) * s.chblocks <= 2 * plan->num_cus) t = least;
+    } else if (4 * work >= 7 * slots && 2 * work <= 11 * slots) {
+      t += waves_per_tile;
+    }
     const bool chosen = plan->cfg.tile_nodes > 0;
     s.tile_nodes = chosen ? plan->cfg.tile_nodes : static_cast<int>(t);
     s.max_tiles = static_cast<int>(n / s.tile_nodes) + 1 + plan->cfg.num_elements;
     // t grows in steps, so a smaller batch may have more tiles: a workspace serves all batches up to its own.  n / t is at
-    // most n / 8 and, with t / 4 above work / (rounds * slots), below rounds * slots / (4 * chblocks); both grow with n.
-    int64_t cuts = n / (2 * waves_per_tile);
+    // most n / 8 and, with t / 4 above work / (rounds * slots) (in the first exception as well: work / slots is below 2 there), below
+    // rounds * slots / (4 * chblocks); both grow with n.  (Dimension of the partial dW at 10 000 and 24 577 nodes, 128 channels, 89
+    // elements: 346 tiles of 2 x 29 x 256 bytes.)
+    int64_t cuts = n / least;
     const int64_t full = rounds * slots / (waves_per_tile * s.chblocks);
     if (full < cuts) cuts = full;
     s.tiles_room = chosen ? s.max_tiles : static_cast<int>(cuts) + 1 + plan->cfg.num_elements;
