@@ -320,6 +320,28 @@ def test_values_that_do_not_split_in_several_passes(el, value):
     (2, 128, 64, 3, "f32"), (17, 128, 128, 3, "f32"), (19, 256, 64, 3, "f32"), (1000, 128, 128, 3, "f32"), (1001, 64, 64, 2, "f64"),
     (4097, 128, 128, 3, "f32"), (4499, 128, 128, 3, "f32"), (8171, 128, 128, 3, "f32"), (2070, 64, 64, 1, "f32"), (1030, 192, 64, 0, "f64")])
 def test_ranges_of_dw(el, N, k_in, k_out, l_max, dtype):
+    assert not adds_ranges_in_a_launch_of_its_own(N, k_in, k_out, l_max, dtype)
+    run_case(el, N, k_in, k_out, l_max, dtype, 8990 + N)
+
+
+def adds_ranges_in_a_launch_of_its_own(N, k_in, k_out, l_max, dtype):
+    """The library's choice of kernel for dX (columns: the input channels): on a tiled kernel the sum of the ranges cannot ride."""
+    import torch
+    cus, tiles = torch.cuda.get_device_properties(0).multi_processor_count, -(-N // 16)
+    long_other = dtype == "f64" or (k_in > 64 and k_in % 128 != 0)
+    small = tiles * (k_in // 16) <= (8 if long_other else 4) * cus
+    units = tiles * (k_in // 128)
+    parts = dtype == "f32" and l_max == 3 and k_in % 128 == 0 and k_out % 32 == 0 and (
+        units <= 2 * cus or k_out > 64 or (k_out == 64 and (units > 5 * cus or units % cus == 0 or units % cus > cus // 2)))
+    return not small and not parts
+
+
+# ... whose workgroups take slices of 256 (fp64 128) values of dW in turn: one column group and several, more slices than one range has.
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype", [
+    (8193, 128, 64, 3, "f32"), (4113, 64, 64, 3, "f32"), (2065, 128, 128, 2, "f32"), (4113, 128, 128, 3, "f64"), (8209, 64, 64, 1, "f64"),
+    (4110, 64, 192, 0, "f32")])
+def test_ranges_of_dw_added_in_a_launch_of_their_own(el, N, k_in, k_out, l_max, dtype):
+    assert adds_ranges_in_a_launch_of_its_own(N, k_in, k_out, l_max, dtype)
     run_case(el, N, k_in, k_out, l_max, dtype, 8990 + N)
 
 
