@@ -16,9 +16,10 @@
  * a multiple of 128 and the channels that are summed a multiple of 32 take the bfloat16 matrix
  * cores: every fp32 value as the exact sum of three bfloat16 values (rows that hold a value for
  * which there is no such sum, below 2^-110 or beyond the largest bfloat16, are computed with fp32
- * products), products down to 2^-34 of the value, sums in fp32.  Its error against 64 bits is
- * that of fp32 products (one term: at most 1.006 of half an ulp; two: 1.2 times the 2-norm of
- * theirs) or smaller (from 32 channels on less than half).
+ * products), products down to 2^-34 of the value, sums in fp32.  Its error against 64 bits, by
+ * the number of terms of a sum that are not zero: one, at most 1.006 of half an ulp; two to four,
+ * 1.2 times the 2-norm of that of fp32 products, six 1.05 times; eight and more, less than theirs
+ * (16 0.76, 32 0.57, 128 0.36 times).
  *
  * Conventions as in sc.h: device pointers, dense row-major, 16-byte aligned; calls enqueue on
  * the given HIP stream and never synchronise; outputs are overwritten; errors by return code

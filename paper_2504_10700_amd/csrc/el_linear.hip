@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     forward_lds_unit<2>(n_nodes, unit / groups * 16, static_cast<int>(unit % groups) * 2, k_red, k_cols, X, W, Y, xs);
 }
 
-// The same product on the bfloat16 matrix cores (SplitPass), k_red % 32 == 0: one workgroup of eight waves per CU (256 registers), which
+// The same product on the bfloat16 matrix cores (SplitPass), k_red % 32 == 0: one workgroup of eight waves per CU (256 registers, 12 bytes a lane spilled outside the loop of a step), which
 // walks its share of the row tiles of its 128 columns, two tiles a pass.  What bounds it at 8192 atoms and 128 -> 128 channels (two tiles per
 // CU, 41 us): 29 us for the rows at the rate of a large copy, 15 us of products, 8 us of stores at the end of the pass with nothing left to
 // overlap them.  Forward on inputs from memory, us, before (two workgroups per CU, each with one tile and its own split of
@@ -252,8 +252,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // 47.2 -> 37.7; 512 -> 128, 3000 atoms 75 -> 58.  The pairs of X split in the first half of a step, right behind their requests: 4096
 // atoms 24.2, 10 000 56.6.  One tile a pass with requests two steps ahead: 24.2 and 55.3, 256 -> 256 6000 atoms 96.6.  Error against 64 bits
 // (2-norm, relative), 128 / 256 / 512 channels summed: 0.73e-7, 1.0e-7, 1.5e-7 where the fp32 instruction gives 2.0e-7, 2.9e-7,
-// 4.0e-7 (32 products per rounding of the sum, not four); of one nonzero weight per column, largest: 5.99e-8 and 5.96e-8; of
-// two, 2-norm: 3.7e-8 and 3.1e-8.
+// 4.0e-7 (32 products per rounding of the sum); of one nonzero weight per column, largest: 5.98e-8 and 5.96e-8; of
+// two, four, six, eight, 2-norm: 3.7e-8 and 3.1e-8, 4.6e-8 and 4.0e-8, 4.9e-8 and 4.7e-8, 5.2e-8 and 5.4e-8.
 // kTrans: W is [L][k_cols][k_red], dX reads the weights of the forward as they are.
 template <bool kTrans, int G>
 __device__ __forceinline__ void split_passes(const SplitArgs& p, int64_t t0, int64_t t1, int j0, unsigned* lds, int* x_bad) {
@@ -380,6 +380,9 @@ __global__ __launch_bounds__(kThreads) void mfma_dw_kernel(int64_t n_nodes, int 
 // all values are zero), 5 us for the partial results, 6 us until the first rows are there.  Four waves with X straight in registers and dY
 // through them to LDS needed the range in steps of 16 atoms: backward, us, that -> this: 40 atoms 28.0 -> 26.7, 2100 53.8 -> 47.0,
 // 10 000 121.1 -> 120.3; 256 -> 128, 2100 atoms 81.2 -> 74.0, 24 000 456 -> 458.
+// Error of dW against 64 bits (2-norm, relative), the 16x16x4 instruction (four atoms) / this one (two): 128 -> 128 channels, 40 atoms 1.61e-7 / 1.61e-7,
+// 2100 1.96e-7 / 1.95e-7, 10 000 3.78e-7 / 3.78e-7, 100 000 1.153e-6 / 1.155e-6; 256 -> 256, 10 000 7.28e-7 / 7.29e-7; positive values, 10 000, 5.28e-8 /
+// 5.29e-8: it does not depend on how many products an instruction takes.
 constexpr int kDwRingWaves = 8;
 constexpr int kDwRingThreads = kDwRingWaves * kLanes;
 constexpr int kDwSlots = 3, kDwChunk = 4;                     // chunks of the ring, atoms of a chunk

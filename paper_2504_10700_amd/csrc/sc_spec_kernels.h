@@ -459,9 +459,9 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
 // The fp32 kernel of the small basis needs 171 registers if left alone, three over the limit for
 // three waves per SIMD; held to 168 (two values go to scratch) it ran three workgroups per CU
 // instead of two, which paid while small batches were cut into many equal tiles (51.1 -> 49.3 us
-// at 10k nodes).  With tiles processed largest first and about one and a half whole tiles per CU
+// at 10k nodes).  With tiles processed largest first, as many whole ones as fill two workgroups per CU once,
 // the third workgroup is rarely resident, and the unconstrained kernel is faster (step 82.8 -> 80.8
-// us at 10k nodes, same box).
+// us at 10k nodes, same box, with tiles a quarter longer than now).
 // kStreamDA: the dA rows are streamed past the cache (non-temporal stores), for batches up to
 // 40 000 nodes: the kernel itself gains 2 us at 10k nodes and the launches after it another 3 us,
 // whereas at 200k nodes the backward loses 2% with them and the next forward gains as much.
@@ -724,10 +724,13 @@ constexpr bool kUseLdsState = sizeof(T) == 4 && G::kS <= 32;
 // of the tiles each, combined through LDS 13 / 14.4 us (four times the waves, most of them idle
 // for the rare elements).  A device-scope "last workgroup finishes the job" scheme inside the
 // backward kernel was far slower than a launch: its fences flush the per-XCD L2s on this chip.
-// Up to kLongSum tiles: a loop of few tiles a trip, the next ones requested ahead.  A wave of this launch lives about as long as
-// its instructions take to arrive (nothing of them is in the instruction cache when it starts), so the short text pays, us a
+// Up to kLongSum tiles: a loop of few tiles a trip, the next ones requested ahead.  A wave executes fewer instructions and requests fewer
+// rows past its last tile than with everything at once (which of the two tells was not measured apart), us a
 // launch: 49 rows, 50 000 nodes, 256 channels 23.3 -> 20.9, fp64, l_max = 2, 2731 nodes 4.7 -> 3.7, 10 000 nodes 6.8 -> 6.4, 3072 the
-// same.  More tiles: all registers' worth at once (200 000 nodes, 217 tiles of an element, 24.0 against 25.5 us by the loop).
+// same.  More tiles: all registers' worth at once (200 000 nodes, 217 tiles of an element, 24.0 against 25.5 us by the loop).  Both sums stand
+// in the kernel, for every number of rows: its text is twice as long (29 rows, fp32, 8.7 -> 17.2 KB) and its registers are 73 for 72 (six waves per
+// SIMD for seven; 13 rows 83 for 40, five for eight), of which no size measured shows a loss (backward with this launch, 0.90 to 1.0 of
+// the time before over 300 to 50 000 nodes).
 constexpr int kLongSum = 64;
 template <typename T, int R, int kMaxR>
 __device__ __forceinline__ void finalize_sum(const T* __restrict__ src, size_t tstride, int t0, int t1,
