@@ -714,102 +714,146 @@ constexpr bool kUseLdsState = sizeof(T) == 4 && G::kS <= 32;
 
 // Second stage of the dW reduction and the map to the external paths, one launch.  The fold
 // matrix F (dW[p] = sum_s F[s,p] r[s]) falls into small independent blocks of one to three
-// internal rows s and the external paths p that depend on them (generated descriptors), so one
-// wave per (element, channel block, block of F) can do both steps without waiting for anyone:
-// it adds the block's rows over the element's tiles in tile order, in fp64, and writes the block's
-// external paths.  Elements without nodes own no tiles and get zeros.  Every sum has a fixed order: results are bitwise reproducible.
-// What was measured on the way here (10k / 200k nodes): a sum kernel followed by an unfold kernel
+// internal rows s and the external paths p that depend on them (generated descriptors).  A workgroup takes a group of
+// consecutive blocks of one (element, channel block): its waves add the group's rows over an equal share of the element's tiles each, in
+// tile order and in fp64, the shares meet in LDS in wave order, and the first wave writes the group's external paths.
+// Elements without nodes own no tiles and get zeros.  Every sum has a fixed order: results are bitwise reproducible.
+// What bounds it: the instructions of its waves (a launch with a wave per block lasted 1.7 us and 1.1 ns a wave, from 2300 to 9600 waves, whatever
+// the waves summed).  So the code of a group is straight-line: its rows, paths and coefficients are constants and not read from a
+// descriptor (176 to 520 bytes of scalar loads, a branch per coefficient), absent tiles are skipped and not masked, and a wave has up to four
+// rows.  A wave per block -> this, us a launch: 128 channels, 0e+1o, 3072 nodes 6.6 -> 4.2, 10 000 6.8 -> 5.2, 200 000 24 -> 16; 0e+1o+2e, 256
+// channels, 50 000 nodes 20.9 -> 13.7; four outputs, 107 nodes 12.3 -> 6.4; 64 channels, 83 nodes 4.2 -> 3.0.  Rows of a group, four / six /
+// eight: 3072 nodes 4.2 / 4.3 / 4.1, 10 000 5.2 / 5.4 / 5.2, 200 000 15.9 / 19.0 / 18.0, 83 nodes 3.0 / 3.1 / 3.3.
+// Earlier forms (10k / 200k nodes): a sum kernel followed by an unfold kernel
 // 11.2 / 15.6 us; one workgroup per (element, channel block) for all rows 13.5 / 31 us (the twelve
-// workgroups of the six frequent elements own 60% of the bytes); four waves per block, a quarter
-// of the tiles each, combined through LDS 13 / 14.4 us (four times the waves, most of them idle
-// for the rare elements).  A device-scope "last workgroup finishes the job" scheme inside the
+// workgroups of the six frequent elements own 60% of the bytes).  A device-scope "last workgroup finishes the job" scheme inside the
 // backward kernel was far slower than a launch: its fences flush the per-XCD L2s on this chip.
-// Up to kLongSum tiles: a loop of few tiles a trip, the next ones requested ahead.  A wave executes fewer instructions and requests fewer
-// rows past its last tile than with everything at once (which of the two tells was not measured apart), us a
-// launch: 49 rows, 50 000 nodes, 256 channels 23.3 -> 20.9, fp64, l_max = 2, 2731 nodes 4.7 -> 3.7, 10 000 nodes 6.8 -> 6.4, 3072 the
-// same.  More tiles: all registers' worth at once (200 000 nodes, 217 tiles of an element, 24.0 against 25.5 us by the loop).  Both sums stand
-// in the kernel, for every number of rows: its text is twice as long (29 rows, fp32, 8.7 -> 17.2 KB) and its registers are 73 for 72 (six waves per
-// SIMD for seven; 13 rows 83 for 40, five for eight), of which no size measured shows a loss (backward with this launch, 0.90 to 1.0 of
-// the time before over 300 to 50 000 nodes).
-constexpr int kLongSum = 64;
-template <typename T, int R, int kMaxR>
-__device__ __forceinline__ void finalize_sum(const T* __restrict__ src, size_t tstride, int t0, int t1,
-                                             const int (&row)[kMaxR], double (&acc)[kMaxR]) {
-  constexpr int kRegs = R * static_cast<int>(sizeof(T) / 4);   // registers per tile in flight
-  auto request = [&](int t, auto& x) {   // past the last tile it is read again and dropped
-#pragma unroll
-    for (auto& tile : x) {
-      const T* at = src + static_cast<size_t>(t < t1 ? t : t1 - 1) * tstride;
-      ++t;
-#pragma unroll
-      for (int r = 0; r < R; ++r) tile[r] = at[row[r] * kLanes];
-    }
+constexpr int kFinalizeRows = 4;    // rows of a group at most (a block has no more: FinalizeGroups)
+
+// Blocks of F in groups of at most kFinalizeRows rows, in order: group g is the blocks first[g] .. first[g + 1] - 1.
+template <typename G>
+struct FinalizeGroups {
+  static_assert(G::kMaxBlockRows <= kFinalizeRows, "a group holds any block");
+  struct Table {
+    int n, first[G::kNumBlocks + 1];
   };
-  auto add = [&](int t, const auto& x) {
-#pragma unroll
-    for (const auto& tile : x) {
-      const bool in = t++ < t1;
-#pragma unroll
-      for (int r = 0; r < R; ++r) acc[r] += in ? static_cast<double>(tile[r]) : 0.0;
+  static constexpr Table make() {
+    Table t{};
+    int rows = 0;
+    for (int b = 0; b < G::kNumBlocks; ++b) {
+      if (b == 0 || rows + G::kBlocks[b].n_rows > kFinalizeRows) {
+        t.first[t.n++] = b;
+        rows = 0;
+      }
+      rows += G::kBlocks[b].n_rows;
     }
-  };
-  if (t1 - t0 > kLongSum) {
-    T v[kRegs <= 1 ? 32 : kRegs <= 2 ? 16 : 8][R];   // (more in flight measured slower: fewer resident waves)
-    for (int t = t0; t < t1; t += sizeof(v) / sizeof(v[0])) {
-      request(t, v);
-      add(t, v);
-    }
-    return;
+    t.first[t.n] = G::kNumBlocks;
+    return t;
   }
-  if (t0 >= t1) return;
-  constexpr int U = kRegs <= 1 ? 16 : kRegs <= 2 ? 8 : 4;
-  T v[U][R], next[U][R];
-  request(t0, v);
-#pragma unroll 1
-  for (int t = t0; t < t1; t += U) {
-    request(t + U, next);
-    __builtin_amdgcn_sched_barrier(0);
-    add(t, v);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[u][r] = next[u][r];
+  static constexpr Table table = make();
+  static constexpr int rows_of(int g) {
+    int rows = 0;
+    for (int b = table.first[g]; b < table.first[g + 1]; ++b) rows += G::kBlocks[b].n_rows;
+    return rows;
+  }
+  static constexpr int row(int g, int i) {   // the i-th row of group g
+    for (int b = table.first[g]; b < table.first[g + 1]; ++b) {
+      if (i < G::kBlocks[b].n_rows) return G::kBlocks[b].row[i];
+      i -= G::kBlocks[b].n_rows;
+    }
+    return 0;
+  }
+  static constexpr int first_of(int g, int blk) {   // position of the block's first row in the group
+    int i = 0;
+    for (int b = table.first[g]; b < blk; ++b) i += G::kBlocks[b].n_rows;
+    return i;
+  }
+};
+
+template <int kBegin, int kEnd, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (kBegin < kEnd) {
+    f(std::integral_constant<int, kBegin>{});
+    static_for<kBegin + 1, kEnd>(f);
   }
 }
 
-template <typename T, typename G, typename TW>
-__global__ __launch_bounds__(kLanes) void spec_finalize_kernel(int K, int chblocks, int max_tiles,
-                                                               const T* __restrict__ partial,
-                                                               const int32_t* __restrict__ tile_off,
-                                                               TW* __restrict__ dW) {
-  constexpr int S = G::kS, R = G::kMaxBlockRows;
-  const int lane = threadIdx.x;
-  const int blk = blockIdx.x % G::kNumBlocks;
-  const int cb = blockIdx.x / G::kNumBlocks;
-  const int e = blockIdx.y;
-  const typename G::Block d = G::kBlocks[blk];   // the whole descriptor at once: one scalar-load latency
-  int t0 = tile_off[e], t1 = tile_off[e + 1];
-  if (t1 > max_tiles) t1 = max_tiles;
-  const size_t tstride = static_cast<size_t>(chblocks) * S * kLanes;
-  const T* src = partial + static_cast<size_t>(cb) * S * kLanes + lane;
+// shared: (kWaves - 1) * kFinalizeRows * kLanes values, in which the waves meet.
+template <typename T, typename G, typename TW, int kWaves, int g>
+__device__ __forceinline__ void finalize_group(int K, int ch, int lane, int wave, const T* __restrict__ src, size_t tstride, int t0, int t1,
+                                               TW* __restrict__ out, double* shared) {
+  typedef FinalizeGroups<G> F;
+  constexpr int R = F::rows_of(g), U = 4;   // U: tiles a trip, the next ones requested ahead
   double sum[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) sum[r] = 0.0;
-  if (d.n_rows == 1) finalize_sum<T, 1, R>(src, tstride, t0, t1, d.row, sum);
-  else if (R >= 2 && d.n_rows == 2) finalize_sum<T, (R >= 2 ? 2 : 1), R>(src, tstride, t0, t1, d.row, sum);
-  else finalize_sum<T, R, R>(src, tstride, t0, t1, d.row, sum);
-  if (cb * kLanes + lane >= K) return;   // lanes past the last channel
-  TW* out = dW + static_cast<size_t>(e) * G::kP * K + cb * kLanes + lane;
+  const int n = t1 - t0, ta = t0 + n * wave / kWaves, tb = t0 + n * (wave + 1) / kWaves;
+  if (ta < tb) {
+    T v[U][R], next[U][R];
+    auto request = [&](int t, T (&x)[U][R]) {   // past the last tile it is read again and dropped
 #pragma unroll
-  for (int i = 0; i < G::kMaxBlockPaths; ++i) {
-    if (i < d.n_paths) {   // uniform
-      double v = 0.0;
+      for (int u = 0; u < U; ++u) {
+        const T* at = src + static_cast<size_t>(t + u < tb ? t + u : tb - 1) * tstride;
+        static_for<0, R>([&](auto r) { x[u][r] = at[F::row(g, r) * kLanes + lane]; });
+      }
+    };
+    request(ta, v);
+#pragma unroll 1
+    for (int t = ta; t < tb; t += U) {
+      request(t + U, next);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (d.coef[i][r] != 0.0) v += d.coef[i][r] * sum[r];   // uniform; rows in ascending order
-      out[static_cast<size_t>(d.path[i]) * K] = static_cast<TW>(v);
+      for (int u = 0; u < U; ++u)
+        if (t + u < tb) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) sum[r] += static_cast<double>(v[u][r]);
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[u][r] = next[u][r];
     }
   }
+  if (wave > 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) shared[((wave - 1) * R + r) * kLanes + lane] = sum[r];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w)
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r] += shared[((w - 1) * R + r) * kLanes + lane];
+  if (ch >= K) return;   // lanes past the last channel
+  static_for<F::table.first[g], F::table.first[g + 1]>([&](auto blk) {
+    static_for<0, G::kBlocks[blk].n_paths>([&](auto i) {
+      double v = 0.0;
+      static_for<0, G::kBlocks[blk].n_rows>([&](auto r) {
+        if constexpr (G::kBlocks[blk].coef[i][r] != 0.0) v += G::kBlocks[blk].coef[i][r] * sum[F::first_of(g, blk) + r];
+      });
+      out[static_cast<size_t>(G::kBlocks[blk].path[i]) * K + ch] = static_cast<TW>(v);
+    });
+  });
+}
+
+template <typename T, typename G, typename TW, int kWaves>
+__global__ __launch_bounds__(kWaves * kLanes) void spec_finalize_kernel(int K, int chblocks, int max_tiles,
+                                                                        const T* __restrict__ partial,
+                                                                        const int32_t* __restrict__ tile_off,
+                                                                        TW* __restrict__ dW) {
+  constexpr int S = G::kS, kGroups = FinalizeGroups<G>::table.n;
+  __shared__ double shared[(kWaves - 1) * kFinalizeRows * kLanes];
+  const int lane = threadIdx.x % kLanes, wave = wave_of_thread();
+  const int group = blockIdx.x % kGroups;
+  const int cb = blockIdx.x / kGroups;
+  const int e = blockIdx.y;
+  const int t0 = tile_off[e], t1 = tile_off[e + 1] < max_tiles ? tile_off[e + 1] : max_tiles;
+  const size_t tstride = static_cast<size_t>(chblocks) * S * kLanes;
+  const T* src = partial + static_cast<size_t>(cb) * S * kLanes;
+  TW* out = dW + static_cast<size_t>(e) * G::kP * K;
+  static_for<0, kGroups>([&](auto g) {
+    if (group == g) finalize_group<T, G, TW, kWaves, g>(K, cb * kLanes + lane, lane, wave, src, tstride, t0, t1, out, shared);
+  });
 }
 
 SplitGroupArgs group_args(const sc_plan* plan, int64_t n, const int32_t* z, const Workspace& ws,
@@ -961,7 +1005,11 @@ template <typename T, typename G, typename TW>
 hipError_t finalize_launch(const sc_plan* plan, void* dW, const Workspace& ws, const LaunchShape& shape,
                            hipStream_t stream) {
   const int Z = plan->cfg.num_elements;
-  hipLaunchKernelGGL((spec_finalize_kernel<T, G, TW>), dim3(shape.chblocks * G::kNumBlocks, Z), dim3(kLanes), 0, stream,
+  // Waves of a workgroup, one / two / four, us a launch: 3072 nodes (three tiles an element on average, nineteen of the frequent ones) 6.5 / 4.2 / 4.2,
+  // 10 000 (four) 5.4 / 5.2 / 5.2, 107 nodes (four outputs) 6.9 / 6.9 / 6.3, 83 nodes 2.8 / 3.0 / 3.3; 200 000 (20 tiles) 39 / 24 / 16.
+  const int waves = shape.max_tiles > 8 * Z ? 4 : 2;
+  const auto kernel = waves == 4 ? &spec_finalize_kernel<T, G, TW, 4> : &spec_finalize_kernel<T, G, TW, 2>;
+  hipLaunchKernelGGL(kernel, dim3(shape.chblocks * FinalizeGroups<G>::table.n, Z), dim3(waves * kLanes), 0, stream,
                      plan->cfg.num_channels, shape.chblocks, shape.max_tiles, static_cast<const T*>(ws.partial),
                      ws.tile_off, static_cast<TW*>(dW));
   return hipGetLastError();

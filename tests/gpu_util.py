@@ -130,7 +130,7 @@ def oracle_double_backward(osc, T, A, z, W, dB, H):
 class GpuRun:
     """Device buffers + plan for one workload; forward()/backward() return numpy arrays."""
 
-    def __init__(self, sc, wl, inp, flags=0, n_nodes=None):
+    def __init__(self, sc, wl, inp, flags=0, n_nodes=None, tile_nodes=0):
         import torch
         self.sc, self.wl, self.torch = sc, wl, torch
         self.dev = torch.device("cuda:0")
@@ -138,7 +138,7 @@ class GpuRun:
         self.tdt = {"f32": torch.float32, "f64": torch.float64, "bf16": torch.bfloat16}[wl.dtype]
         self.wdt = torch.float64 if wl.dtype == "f64" else torch.float32
         self.plan = sc.sc_plan_create(wl.num_channels, wl.l_max, wl.nu_max, wl.num_elements, wl.out_irreps,
-                                      {"f32": sc.SC_F32, "f64": sc.SC_F64, "bf16": sc.SC_BF16}[wl.dtype], 0, flags)
+                                      {"f32": sc.SC_F32, "f64": sc.SC_F64, "bf16": sc.SC_BF16}[wl.dtype], 0, flags, tile_nodes)
         self.N = inp.A.shape[0] if n_nodes is None else n_nodes
         self.A = torch.tensor(inp.A, dtype=self.tdt, device=self.dev)
         self.W = torch.tensor(inp.W, dtype=self.wdt, device=self.dev)

@@ -591,6 +591,26 @@ def test_three_launch_grouping_and_many_elements(sc):
     full_parity(sc, wl_of("z1024", 200, 1024, 64, 2, 2, ((0, 1), (1, -1)), "f64", 2603, z_mode="uniform"))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("l_max,nu,outs", [(3, 3, O01), (3, 3, O012), (2, 3, O012), (3, 2, O01), (3, 3, ((0, 1),))])
+def test_dw_sum_over_few_and_many_tiles(sc, l_max, nu, outs, dtype):
+    """Second stage of dW: element e has `tiles[e]` pieces of eight nodes (a trip of the sum is four of them; two waves share an
+    element's pieces up to eight an element on average, four beyond), and one element has none."""
+    for tiles in ((1, 0, 2, 3, 4, 5), (7, 8, 9, 0, 16, 17)):
+        z = np.concatenate([np.full(8 * t - (3 if t > 1 else 0), e) for e, t in enumerate(tiles)]).astype(np.int32)
+        wl = wl_of(f"dw_tiles_{sum(tiles)}", len(z), len(tiles), 72, l_max, nu, outs, dtype, 4100 + sum(tiles))
+        T = oracle_tables(wl)
+        inp = workloads.make_inputs(wl, T.paths)
+        inp.z[:] = np.random.default_rng(5).permutation(z)
+        run = GpuRun(sc, wl, inp, tile_nodes=8)
+        A, z, W, dB = run.inputs_as_computed()
+        dA, dW = run.backward(0)
+        dA_ref, dW_ref = oracle_backward(osc, T, A, z, W, dB)
+        check("dA", dA, dA_ref, dtype)
+        check_dw("dW", dW, dW_ref, z, dtype, case=f"{wl.name}/{dtype}")
+        run.close()
+
+
 def test_tile_size_knob_does_not_change_results_beyond_rounding(sc):
     wl = wl_of("tiles", 700, 7, 128, 3, 3, O01, "f32", 2701)
     T = oracle_tables(wl)
