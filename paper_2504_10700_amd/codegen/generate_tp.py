@@ -103,10 +103,45 @@ def sl(l: int) -> slice:
     return slice(l * l, (l + 1) * (l + 1))
 
 
+def couple_directly(P: Program, C: np.ndarray, x, v, acc: List[Optional[int]]) -> None:
+    """acc[c] += sum_ab C[a,b,c] x[a] v[b] with a fused multiply-add straight into acc for every term of unit magnitude.
+    Terms of another magnitude: v scaled by it once, or the terms of a component summed and then scaled, whichever takes
+    fewer operations.  (More roundings at the size of acc than by sums of equal magnitude: for arithmetic in fp64, whose instructions
+    bound these kernels.  l_h = 2: forward 404 -> 350 operations, 3001 atoms, 128 channels 140 -> 130 us; second-order pass
+    1725 -> 1679, 1500 atoms 316 -> 305 us; l = 2, l_h = 2, 2500 atoms, 64 channels, forward 33.4 -> 32.0.)"""
+    by_mag: Dict[float, Dict[int, List[Tuple[int, int, float]]]] = {}
+    for a, b, c in zip(*np.nonzero(C)):
+        by_mag.setdefault(round(abs(float(C[a, b, c])), 11), {}).setdefault(int(c), []).append((int(a), int(b), float(C[a, b, c])))
+    for mag, targets in sorted(by_mag.items(), key=lambda kv: (abs(kv[0] - 1.0) > 1e-9, kv[0])):
+        factors = {b for lst in targets.values() for _, b, _ in lst}
+        unit = abs(mag - 1.0) < 1e-9
+        if unit or len(factors) <= len(targets):
+            exact = 1.0 if unit else abs(next(iter(targets.values()))[0][2])
+            scaled = {b: P.cmul(v[b], exact) for b in sorted(factors)}
+            for c, lst in targets.items():
+                for a, b, coef in lst:
+                    if acc[c] is None:
+                        acc[c] = P.cmul(P.mul(x[a], scaled[b]), 1.0 if coef > 0 else -1.0)
+                    else:
+                        acc[c] = P.fma(x[a], scaled[b], acc[c]) if coef > 0 else P.fnma(x[a], scaled[b], acc[c])
+            continue
+        for c, lst in targets.items():
+            q = P.mul(x[lst[0][0]], v[lst[0][1]])
+            for a, b, coef in lst[1:]:
+                q = P.fma(x[a], v[b], q) if (coef > 0) == (lst[0][2] > 0) else P.fnma(x[a], v[b], q)
+            acc[c] = P.cfma(q, lst[0][2], acc[c])
+
+
+def in_fp32(tab: TPTables) -> bool:
+    """Shapes whose fp32 rows are computed in fp32."""
+    return tab.n_Y == 16 and tab.n_out == 16 and tab.n_h <= 4
+
+
 def build_programs(tab: TPTables) -> Tuple[Program, Program]:
     scaled = [split_scale(Cp) for Cp in tab.C]
     # forward: acc[c] += sum C[a,b,c] y[a] (kappa r[p] h[b])
     F = Program()
+    couple = couple_into if in_fp32(tab) else couple_directly
     y = [F.inp(f"y[{a}]") for a in range(tab.n_Y)]
     h = [F.inp(f"h[{b}]") for b in range(tab.n_h)]
     acc: List[Optional[int]] = [F.inp(f"acc[{c}]") for c in range(tab.n_out)]
@@ -115,7 +150,7 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
         rk = F.cmul(F.load(f"r[{p}]"), kappa)
         u = [F.mul(rk, hb) for hb in h[sl(l2)]]
         part = acc[sl(l3)]
-        couple_into(F, Cs, y[sl(l1)], u, part)
+        couple(F, Cs, y[sl(l1)], u, part)
         acc[sl(l3)] = part
         if tab.n_h >= 9:   # many paths: without a boundary all of r is converted to fp64 in front of them
             F.fence(part)
@@ -206,6 +241,7 @@ def build_double_backward(tab: TPTables) -> Program:
     (Differentiating the forward program mechanically gives the same sums in an order in which the
     intermediates of all paths are live at once: 6 KB of scratch per lane for l_h = 2 in fp64.)"""
     P = Program()
+    couple = couple_into if in_fp32(tab) else couple_directly
     y = [P.inp(f"y[{a}]") for a in range(tab.n_Y)]
     hy = [P.inp(f"hy[{a}]") for a in range(tab.n_Y)]
     h = [P.inp(f"h[{b}]") for b in range(tab.n_h)]
@@ -220,7 +256,7 @@ def build_double_backward(tab: TPTables) -> Program:
         u = [P.mul(rk, x) for x in h[sl(l2)]]
         v = [P.fma(hrk, x, P.mul(rk, hx)) for x, hx in zip(h[sl(l2)], hh[sl(l2)])]
         part = dda[sl(l3)]
-        couple_into(P, stack_pairs(Cs), y[sl(l1)] + hy[sl(l1)], v + u, part)
+        couple(P, stack_pairs(Cs), y[sl(l1)] + hy[sl(l1)], v + u, part)
         dda[sl(l3)] = part
         terms, _ = scaled_terms(P, tab.C[p], g[sl(l3)])
         d2y[sl(l1)] = couple_terms(P, terms, v, "a", d2y[sl(l1)])
