@@ -246,26 +246,39 @@ __device__ __forceinline__ void load_folded(const T* __restrict__ wf, int z, int
   for (int s = 0; s < G::kS; ++s) w[s] = src[s * kLanes];
 }
 
-// Workgroup `wg` of the fold role: one wave per (element, 64 channels) folds W[element, :, channel] into wf.
-template <typename T, typename G, typename TW>
-__device__ __forceinline__ void fold_role(int wg, int K, int chblocks, int n_pairs, const TW* __restrict__ W, T* __restrict__ wf) {
-  const int lane = threadIdx.x & (kLanes - 1);
-  const int pair = wg * kSpecWaves + wave_of_thread();
-  if (pair >= n_pairs) return;
-  const int z = pair / chblocks, cb = pair % chblocks;
-  const int live = K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes;
-  const int ch = cb * kLanes + (lane < live ? lane : live - 1);   // dead lanes repeat the last channel
+// The internal rows kPart, kPart + kSpecWaves, ... of one (element, 64 channels): what they need is requested before the first
+// value is used (one memory latency, not one per few rows); what belongs to other rows is not computed.
+template <typename T, typename G, typename TW, int kPart>
+__device__ __forceinline__ void fold_part(const TW* __restrict__ src, int K, T* __restrict__ dst) {
   T w[G::kS];
   TW wz[G::kP];
-  // all kP rows are requested before the first is used (one memory latency, not one per few rows)
-  const TW* src = W + static_cast<size_t>(z) * G::kP * K + ch;
 #pragma unroll
   for (int p = 0; p < G::kP; ++p) wz[p] = src[static_cast<size_t>(p) * K];
   asm volatile("" ::: "memory");
   G::fold(wz, 1, w);
-  T* dst = wf + static_cast<size_t>(pair) * G::kS * kLanes + lane;   // pair = element * chblocks + channel block
 #pragma unroll
-  for (int s = 0; s < G::kS; ++s) dst[s * kLanes] = w[s];
+  for (int s = kPart; s < G::kS; s += kSpecWaves) dst[s * kLanes] = w[s];
+}
+
+// A workgroup of the fold role folds W[element, :, 64 channels] into wf, a quarter of the rows per wave: bound by one memory latency and by what one
+// compute unit can request.  A wave for all rows, four pairs a workgroup (45 of the 256 units at 89 elements, 128 channels) -> this, us a
+// launch: 0e+1o, 3072 nodes 4.1 -> 2.9, l_max = 2 in fp64, 2731 nodes 4.1 -> 2.9; 10 000 nodes, whose launch waits for memory that has left
+// the caches, 5.3 either way.
+template <typename T, typename G, typename TW>
+__device__ __forceinline__ void fold_role(int pair, int K, int chblocks, const TW* __restrict__ W, T* __restrict__ wf) {
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int z = pair / chblocks, cb = pair % chblocks;   // pair = element * chblocks + channel block
+  const int live = K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes;
+  const int ch = cb * kLanes + (lane < live ? lane : live - 1);   // dead lanes repeat the last channel
+  const TW* src = W + static_cast<size_t>(z) * G::kP * K + ch;
+  T* dst = wf + static_cast<size_t>(pair) * G::kS * kLanes + lane;
+  static_assert(kSpecWaves == 4, "a part per wave");
+  switch (wave_of_thread()) {
+    case 0: return fold_part<T, G, TW, 0>(src, K, dst);
+    case 1: return fold_part<T, G, TW, 1>(src, K, dst);
+    case 2: return fold_part<T, G, TW, 2>(src, K, dst);
+    default: return fold_part<T, G, TW, 3>(src, K, dst);
+  }
 }
 
 // Launch 1.  Workgroups [0, window_wgs): window role (order of the forward pass); the next
@@ -273,7 +286,7 @@ __device__ __forceinline__ void fold_role(int wg, int K, int chblocks, int n_pai
 template <typename T, typename G, typename TW>
 __global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(const int32_t* __restrict__ z, int n, int Z, int window_wgs,
                                                                     int count_wgs, const TW* __restrict__ W, T* __restrict__ wf,
-                                                                    int K, int chblocks, int n_pairs, SplitGroupArgs ga) {
+                                                                    int K, int chblocks, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
   ga.z = z;
   ga.n = n;
@@ -286,7 +299,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(const int32_
     split_count_role(ga, blockIdx.x - window_wgs, reinterpret_cast<int32_t*>(lds_raw));
     return;
   }
-  fold_role<T, G, TW>(static_cast<int>(blockIdx.x) - window_wgs - count_wgs, K, chblocks, n_pairs, W, wf);
+  fold_role<T, G, TW>(static_cast<int>(blockIdx.x) - window_wgs - count_wgs, K, chblocks, W, wf);
 }
 
 // The grouping alone (a backward pass that cannot reuse a forward's grouping): scatter and table roles.
@@ -317,7 +330,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
       split_count_all(ga, counts);
       ga.counts = counts;
     } else if (block < scatter_wgs + table + fold_wgs) {
-      fold_role<T, G, TW>(block - scatter_wgs - table, K, chblocks, Z * chblocks, W, const_cast<T*>(wf));   // read by nobody in this launch
+      fold_role<T, G, TW>(block - scatter_wgs - table, K, chblocks, W, const_cast<T*>(wf));   // read by nobody in this launch
       return;
     }
   }
@@ -891,13 +904,13 @@ hipError_t prepare_launch(const sc_plan* plan, int64_t n, const int32_t* z, cons
   const bool window = window_order && ws.wnode && ws.wkey;
   const int window_wgs = window ? static_cast<int>((n + kWindowNodes - 1) / kWindowNodes) : 0;
   const int n_pairs = fold ? plan->cfg.num_elements * shape.chblocks : 0;
-  const int grid = window_wgs + count_wgs + (n_pairs + kSpecWaves - 1) / kSpecWaves;
+  const int grid = window_wgs + count_wgs + n_pairs;
   if (grid == 0) return hipSuccess;
   const size_t lds = window ? split_window_lds_bytes(plan->cfg.num_elements)
                             : count ? split_group_lds_bytes(plan->cfg.num_elements) : 0;
   hipLaunchKernelGGL((spec_prepare_kernel<T, G, TW>), dim3(grid), dim3(kSpecThreads), lds, stream,
                      z, static_cast<int>(n), plan->cfg.num_elements, window_wgs, count_wgs, static_cast<const TW*>(W),
-                     static_cast<T*>(ws.wfold), plan->cfg.num_channels, shape.chblocks, n_pairs,
+                     static_cast<T*>(ws.wfold), plan->cfg.num_channels, shape.chblocks,
                      group_args(plan, n, z, ws, shape, window));
   return hipGetLastError();
 }
@@ -943,7 +956,7 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
     const size_t roles = split_group_lds_bytes(plan->cfg.num_elements) + (kDirect ? split_counts_bytes(plan, shape) : 0);
     if (roles > lds) lds = roles;
   }
-  const int fold_wgs = kDirect && fold_table ? (plan->cfg.num_elements * shape.chblocks + kSpecWaves - 1) / kSpecWaves : 0;
+  const int fold_wgs = kDirect && fold_table ? plan->cfg.num_elements * shape.chblocks : 0;
   static const int wgs_per_cu = [] {   // resident workgroups per compute unit of this instance
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, &spec_forward_kernel<T, G, TS, TW, kCM, kDirect>, kSpecThreads, 0) != hipSuccess || nb < 1)
