@@ -164,7 +164,9 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
     g = [Bq.inp(f"g[{c}]") for c in range(tab.n_out)]
     # path by path, so that only the sums over the paths stay live from one path to the next
     dy: List[Optional[int]] = [None] * tab.n_Y
-    dh: List[Optional[int]] = [None] * tab.n_h   # the edge's share of its sender's gradient
+    # the gradient of the sender's features: sums in fp32 take the edge's share at once
+    dh_in = [Bq.inp(f"dh[{b}]") for b in range(tab.n_h)]
+    dh: List[Optional[int]] = [None] * tab.n_h if in_fp32(tab) else list(dh_in)
     for p, (l1, l2, l3) in enumerate(tab.paths):
         terms, kappa = scaled_terms(Bq, tab.C[p], g[sl(l3)])
         rk = Bq.cmul(Bq.load(f"r[{p}]"), kappa)
@@ -176,7 +178,7 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
         out_when_complete(Bq, "dy", dy, tab.paths, p)
         Bq.fence(dy[sl(l1)] + dh[sl(l2)])
     for b in range(tab.n_h):
-        Bq.out(f"dh[{b}]", dh[b])
+        Bq.out(f"dh[{b}]", Bq.add(dh[b], dh_in[b]) if in_fp32(tab) else dh[b])
     return F, Bq
 
 
@@ -338,6 +340,7 @@ def self_check(tab: TPTables, F: Program, Bq: Program, dtype=np.float64) -> Dict
     inputs.update({f"r[{i}]": r[:, i] for i in range(tab.P)})
     inputs.update({f"g[{i}]": g[:, i] for i in range(tab.n_out)})
     inputs.update({f"acc[{i}]": np.zeros(n) for i in range(tab.n_out)})
+    inputs.update({f"dh[{i}]": np.zeros(n) for i in range(tab.n_h)})
 
     def col(v):
         return np.zeros(n) if v is None else v.astype(np.float64)
@@ -380,8 +383,8 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append(F.emit("T", "    "))
     L.append("  }")
     L.append("")
-    L.append("  // g = dA of the receiver; overwritten: dr, dy (this channel's share of the edge's dY) and dh")
-    L.append("  // (the edge's share of the gradient of its sender's features)")
+    L.append("  // g = dA of the receiver; overwritten: dr and dy (this channel's share of the edge's dY); dh += the edge's")
+    L.append("  // share of the gradient of its sender's features")
     L.append("  template <typename T, typename R, typename DR, typename DY>")
     L.append("  static __device__ __forceinline__ void backward(const T (&y)[kNY], const T (&h)[kNh], const R& r,")
     L.append("                                                  const T (&g)[kNout], DR& dr, DY& dy, T (&dh)[kNh]) {")

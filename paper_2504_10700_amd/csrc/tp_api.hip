@@ -271,9 +271,10 @@ sc_status tp_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_out, in
   char* dh_edge = workspace ? static_cast<char*>(workspace) +
                                   align_up(static_cast<size_t>(chblocks_of(plan)) * n_edges * plan->n_Y * elem_size(plan), 256)
                             : nullptr;
-  const bool one_block = chblocks_of(plan) == 1;   // its share of dY is the result: no sum, no copy (5 us)
+  const int dY_parts = plan->specialised ? tp::spec_dY_parts(plan, n_nodes_in) : chblocks_of(plan);
+  const bool one_block = dY_parts == 1;   // its share of dY is the result: no sum, no copy (5 us)
   const tp::BwdArgs a{n_nodes_in, n_nodes_out, n_edges, Y,  h,  R,  sender,
-                      row_ptr,    send_ptr,    send_edge, dA, dY, dh, dR, one_block ? dY : workspace, dh_edge};
+                      row_ptr,    send_ptr,    send_edge, dA, dY, dh, dR, one_block ? dY : workspace, dh_edge, dY_parts};
   hipError_t e = hipSuccess;
   if (plan->specialised) {
     // generated kernels: one pass over the edges grouped by sender writes dR, the dY partials and dh itself
@@ -352,7 +353,7 @@ sc_status tp_double_backward(tp_plan* plan, int64_t n_nodes_in, int64_t n_nodes_
                             : nullptr;
   const bool one_block = chblocks_of(plan) == 1;   // its share of d2Y is the result: no sum, no copy
   const tp::DblArgs a{{n_nodes_in, n_nodes_out, n_edges, Y, h, R, sender, row_ptr, send_ptr, send_edge, dA, d2Y, d2h,
-                       d2R, one_block ? d2Y : workspace, dh_edge},
+                       d2R, one_block ? d2Y : workspace, dh_edge, chblocks_of(plan)},
                       HY, Hh, HR, ddA};
   hipError_t e = hipSuccess;
   if (n_nodes_out > 0) {  // also with no edges: ddA is zeroed

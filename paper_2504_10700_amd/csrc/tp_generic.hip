@@ -283,10 +283,9 @@ hipError_t dh_sum_t(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
 
 template <typename T>
 hipError_t dY_sum_t(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
-  const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
   const int64_t n = a.n_edges * plan->n_Y;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(dY_sum_kernel<T>, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream, n, chblocks,
+  hipLaunchKernelGGL(dY_sum_kernel<T>, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream, n, a.dY_parts,
                      static_cast<const T*>(a.dY_partial), static_cast<T*>(a.dY));
   return hipGetLastError();
 }

@@ -78,8 +78,9 @@ struct BwdArgs {
   const int32_t *sender, *row_ptr, *send_ptr, *send_edge;
   const void* dA;
   void *dY, *dh, *dR;
-  void* dY_partial;  // [chblocks][n_edges][n_Y] of the plan's dtype
+  void* dY_partial;  // [dY_parts][n_edges][n_Y] of the plan's dtype
   void* dh_edge;     // [n_edges][K][n_h]: every edge's share of its sender's dh (table-driven and second-order kernels)
+  int dY_parts;      // shares of dY that are added up: one per 64-channel block or per two (spec_dY_parts)
 };
 
 // Second-order pass: the backward's arguments (dY, dh, dR of BwdArgs receive d2Y, d2h, d2R)
@@ -104,5 +105,7 @@ hipError_t launch_spec_forward(const tp_plan* plan, const FwdArgs& a, hipStream_
 // edges walked by sender: writes dR, the dY partials and dh itself (every atom's row, zero for atoms that send
 // nothing); a.dh_edge receives the edges' receivers (int32), not shares.  Valid for n_in > 0, also without edges.
 hipError_t launch_spec_backward(const tp_plan* plan, const BwdArgs& a, hipStream_t stream);
+// BwdArgs::dY_parts of that launch
+int spec_dY_parts(const tp_plan* plan, int64_t n_in);
 
 }  // namespace tp

@@ -10,6 +10,7 @@ struct SpecEntry {
   hipError_t (*forward)(const tp_plan* plan, const FwdArgs& a, hipStream_t stream);
   hipError_t (*backward)(const tp_plan* plan, const BwdArgs& a, hipStream_t stream);
   hipError_t (*double_backward)(const tp_plan* plan, const DblArgs& a, hipStream_t stream);
+  int (*dY_parts)(const tp_plan* plan, int64_t n_in);   // of the backward
 };
 
 // The shapes with L_max = l_Y = 3 and sender features up to order 0 and 1, 2, 3, and those with

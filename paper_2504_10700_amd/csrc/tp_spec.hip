@@ -55,6 +55,8 @@ int spec_lookup(const tp_plan* plan) {
   return 0;
 }
 
+int spec_dY_parts(const tp_plan* plan, int64_t n_in) { return entry(plan->specialised).dY_parts(plan, n_in); }
+
 void spec_op_counts(int id, int32_t ops[3], int32_t flops[3]) {
   for (int i = 0; i < 3; ++i) {
     ops[i] = id ? entry(id).ops[i] : 0;

@@ -126,15 +126,20 @@ struct PathStore {
   __device__ __forceinline__ Ref operator[](int p) const { return Ref{*this, p}; }
 };
 
-// This channel's share of dY[e][a], into the wave's transpose stage (see lane_sum_store) when it is assigned.
-template <bool kFull, typename T>
+// This channel's share of dY[e][a], into the wave's transpose stage (see lane_sum_store) when it is assigned (kAdd: on top of what
+// another channel of this lane has put there).
+template <bool kFull, bool kAdd, typename T>
 struct StageStore {
   T* lane_column;
   bool live;
   struct Ref {
     const StageStore& s;
     int a;
-    __device__ __forceinline__ void operator=(T v) const { s.lane_column[a * kStageStride] = kFull || s.live ? v : T(0); }
+    __device__ __forceinline__ void operator=(T v) const {
+      T* const to = s.lane_column + a * kStageStride;
+      const T mine = kFull || s.live ? v : T(0);
+      *to = kAdd ? *to + mine : mine;
+    }
   };
   __device__ __forceinline__ Ref operator[](int a) const { return Ref{*this, a}; }
 };
@@ -274,8 +279,8 @@ __device__ __forceinline__ void store_rows_coalesced(TS* __restrict__ block, TS*
 // Channels of block cb: the lane's channel (dead lanes repeat the last one) and the number of live lanes.
 template <bool kFull>
 struct Channels {
-  int live, ch;
-  __device__ __forceinline__ Channels(int K, int cb, int lane) {
+  int live, ch, first;   // first: channel of lane 0
+  __device__ __forceinline__ Channels(int K, int cb, int lane) : first(cb * kLanes) {
     live = kFull ? kLanes : (K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes);
     ch = cb * kLanes + (kFull || lane < live ? lane : live - 1);
   }
@@ -374,17 +379,17 @@ __global__ __launch_bounds__(256) void edge_receiver_kernel(int64_t n_out_nodes,
 template <typename T, typename TS, typename G>
 constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
 
-// The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, 64-channel block).
-// Its waves keep the atom's h row and their dh sums in registers, walk the edges the atom sends
+// The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, kBlocks 64-channel blocks; two_blocks).
+// Its waves keep the atom's h rows and their dh sums in registers, walk the edges the atom sends
 // (every kWaves-th in send_edge order: with the order of the waves, the order of the sum) and gather
 // per edge the dA row of the receiver (rows of
-// one structure, met in the XCD's L2) next to the edge's own R rows; dR and the channel block's
-// partial of dY leave per edge, dh leaves once per atom: no per-edge shares
+// one structure, met in the XCD's L2) next to the edge's own R rows; dR and the blocks'
+// share of dY leave per edge, dh leaves once per atom: no per-edge shares
 // of dh go to memory and come back.  Atoms that send nothing get a zero row.  Every index is
 // clamped where it is used.
-template <typename T, typename TS, typename G, bool kFull, int kWaves>
+template <typename T, typename TS, typename G, bool kFull, int kWaves, int kBlocks>
 __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void backward_by_sender_kernel(
-    int K, int chblocks, int64_t unit0, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
+    int K, int groups, int64_t unit0, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
     const TS* __restrict__ h, const TS* __restrict__ R, const int32_t* __restrict__ send_ptr,
     const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const TS* __restrict__ dA,
     TS* __restrict__ dR, TS* __restrict__ dY_partial, TS* __restrict__ dh) {
@@ -394,10 +399,9 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
   T* stage = stage_all[wave];
   const int64_t unit = unit0 + xcd_contiguous_block();
   if (unit >= n_units) return;   // the whole workgroup: its waves meet at the end
-  const size_t node = unit / chblocks;
-  const int cb = static_cast<int>(unit % chblocks);
-  const Channels<kFull> chan(K, cb, lane);
-  const int ch = chan.ch;
+  const size_t node = unit / groups;
+  const int group = static_cast<int>(unit % groups);
+  const Channels<kFull> chan[2] = {Channels<kFull>(K, group * kBlocks, lane), Channels<kFull>(K, group * kBlocks + kBlocks - 1, lane)};
   auto pos = [&](int v) { return v < 0 ? 0 : (v > n_edges ? n_edges : v); };
   auto edge = [&](int q) {
     const int e = send_edge[q];
@@ -405,51 +409,80 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
   };
   auto atom = [&](int r) { return static_cast<size_t>(r < 0 ? 0 : (r >= n_out_nodes ? n_out_nodes - 1 : r)); };
   const int q0 = uniform(pos(send_ptr[node])) + wave, q1 = uniform(pos(send_ptr[node + 1]));
-  T acc[G::kNh];
+  T acc[kBlocks][G::kNh];
 #pragma unroll
-  for (int c = 0; c < G::kNh; ++c) acc[c] = T(0);
+  for (int b = 0; b < kBlocks; ++b)
+#pragma unroll
+    for (int c = 0; c < G::kNh; ++c) acc[b][c] = T(0);
   if (q0 < q1) {
-    T hh[G::kNh];
-    {
-      TS h_row[G::kNh];
-      load_row<TS, G::kNh>(h + (node * K + ch) * G::kNh, h_row);
-      widen(h_row, hh);
-    }
-    // one set of rows in registers where two do not fit (see the second-order kernel)
-    constexpr bool kOneSet = sizeof(TS) == 8 && G::kP >= 17;
+    TS h_row[kBlocks][G::kNh];
+#pragma unroll
+    for (int b = 0; b < kBlocks; ++b) load_row<TS, G::kNh>(h + (node * K + chan[b].ch) * G::kNh, h_row[b]);
     TS r0[G::kP], g0[G::kNout];
     UniformRow<T, TS, G::kNY> y0;
-    int ea = uniform(edge(q0));
+    auto load_rows = [&](int e, int receiving, int ch, TS (&r_row)[G::kP], TS (&g_row)[G::kNout]) {
+      load_weights<TS, G::kP>(R, e, K, ch, r_row);
+      load_row<TS, G::kNout>(dA + (atom(receiving) * K + ch) * G::kNout, g_row);
+    };
+    int ea = uniform(edge(q0)), ra = uniform(receiver[ea]);
     y0.request(Y, ea, lane);
-    load_weights<TS, G::kP>(R, ea, K, ch, r0);
-    load_row<TS, G::kNout>(dA + (atom(uniform(receiver[ea])) * K + ch) * G::kNout, g0);
+    load_rows(ea, ra, chan[0].ch, r0, g0);
     // edge id and receiver of the edge after the current one, read one step ahead of its rows
-    int en = (q0 + kWaves < q1) ? uniform(edge(q0 + kWaves)) : 0;
+    int en = uniform(edge(q0 + kWaves < q1 ? q0 + kWaves : q0));
     int rn = uniform(receiver[en]);
 
-    // One edge: arithmetic, dR row stores, dY summed over the 64 lanes in a fixed order, dh added up.
-    auto finish_edge = [&](int e, const UniformRow<T, TS, G::kNY>& y_row, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
-      T y[G::kNY], g[G::kNout], dhe[G::kNh];
-      const PathStore<kFull, T, TS> dr{dR + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
-      const StageStore<kFull, T> dy{stage + lane, lane < chan.live};
-      y_row.use(Y, e, y);
+    // One edge and channel block: arithmetic, dR row stores, dh added up; with the last block dY summed over the 64 lanes in a fixed order.
+    auto finish_block = [&](auto block, int e, const T (&y)[G::kNY], const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
+      constexpr int b = decltype(block)::value;
+      T g[G::kNout], hh[G::kNh];
+      const bool live = lane < chan[b].live;
+      const PathStore<kFull, T, TS> dr{dR + static_cast<size_t>(e) * G::kP * K + chan[b].ch, static_cast<size_t>(K), live};
+      const StageStore<kFull, (b > 0), T> dy{stage + lane, live};
       widen(g_row, g);
-      stage_is_free();
-      G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, dhe);
-#pragma unroll
-      for (int c = 0; c < G::kNh; ++c) acc[c] += dhe[c];
-      pin_values(acc);
-      lane_sum_store<G::kNY>(stage, lane, dY_partial + (static_cast<size_t>(cb) * n_edges + e) * G::kNY);
+      widen(h_row[b], hh);
+      if (b == 0) stage_is_free();
+      G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, acc[b]);
+      pin_values(acc[b]);
+      if (b == kBlocks - 1) lane_sum_store<G::kNY>(stage, lane, dY_partial + (static_cast<size_t>(group) * n_edges + e) * G::kNY);
     };
+    auto finish_edge = [&](int e, const UniformRow<T, TS, G::kNY>& y_row, const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
+      T y[G::kNY];
+      y_row.use(Y, e, y);
+      finish_block(std::integral_constant<int, 0>{}, e, y, r_row, g_row);
+    };
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, kBlocks - 1> last{};
 
-    if constexpr (kOneSet) {
+    // one set of rows in registers where two do not fit (see the second-order kernel)
+    constexpr bool kOneSet = sizeof(TS) == 8 && G::kP >= 17;
+    if constexpr (kBlocks == 2) {
+      // The rows of the edge's two blocks in two sets.  No request stands under a condition (see the forward).
+      TS r1[G::kP], g1[G::kNout];
+      for (int q = q0; q < q1; q += kWaves) {
+        load_rows(ea, ra, chan[1].ch, r1, g1);
+        __builtin_amdgcn_sched_barrier(0);
+        T y[G::kNY];
+        y0.use(Y, ea, y);
+        const int q2 = q + 2 * kWaves < q1 ? q + 2 * kWaves : q0;
+        const int e2 = uniform(edge(q2));
+        finish_block(first, ea, y, r0, g0);
+        y0.request(Y, en, lane);
+        load_rows(en, rn, q + kWaves < q1 ? chan[0].ch : chan[0].first, r0, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int r2 = uniform(receiver[e2]);
+        finish_block(last, ea, y, r1, g1);
+        ea = en;
+        ra = rn;
+        en = e2;
+        rn = r2;
+      }
+    } else if constexpr (kOneSet) {
       for (int q = q0; q < q1; q += kWaves) {
         finish_edge(ea, y0, r0, g0);
         if (q + kWaves < q1) {
           ea = en;
           y0.request(Y, ea, lane);
-          load_weights<TS, G::kP>(R, ea, K, ch, r0);
-          load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
+          load_rows(ea, rn, chan[0].ch, r0, g0);
           if (q + 2 * kWaves < q1) {
             en = uniform(edge(q + 2 * kWaves));
             rn = uniform(receiver[en]);
@@ -464,8 +497,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
         if (q + kWaves < q1) {
           eb = en;
           y1.request(Y, eb, lane);
-          load_weights<TS, G::kP>(R, eb, K, ch, r1);
-          load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g1);
+          load_rows(eb, rn, chan[0].ch, r1, g1);
           if (q + 2 * kWaves < q1) {
             en = uniform(edge(q + 2 * kWaves));
             rn = uniform(receiver[en]);
@@ -476,8 +508,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
           if (q + 2 * kWaves < q1) {
             ea = en;
             y0.request(Y, ea, lane);
-            load_weights<TS, G::kP>(R, ea, K, ch, r0);
-            load_row<TS, G::kNout>(dA + (atom(rn) * K + ch) * G::kNout, g0);
+            load_rows(ea, rn, chan[0].ch, r0, g0);
             if (q + 3 * kWaves < q1) {
               en = uniform(edge(q + 3 * kWaves));
               rn = uniform(receiver[en]);
@@ -488,8 +519,12 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       }
     }
   }
-  if (!add_waves<kWaves, G::kNY * kStageStride>(wave, lane, acc, stage_all[0])) return;
-  if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(dh + (node * K + ch) * G::kNh, acc);
+#pragma unroll
+  for (int b = 0; b < kBlocks; ++b) {
+    if (b > 0) __syncthreads();   // the first block's sums have been read
+    if (add_waves<kWaves, G::kNY * kStageStride>(wave, lane, acc[b], stage_all[0]) && (kFull || lane < chan[b].live))
+      store_row<TS, T, G::kNh>(dh + (node * K + chan[b].ch) * G::kNh, acc[b]);
+  }
 }
 
 // Second-order pass: the backward's walk with the cotangents HR (per edge and path), Hh (at the
@@ -544,7 +579,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
                            const UniformRow<T, TS, G::kNY>& hy_row) {
       T y[G::kNY], hy[G::kNY], hh[G::kNh], hx[G::kNh], d2h[G::kNh];
       const PathStore<kFull, T, TS> d2r{d2R + static_cast<size_t>(e) * G::kP * K + ch, static_cast<size_t>(K), lane < chan.live};
-      const StageStore<kFull, T> d2y{stage + lane, lane < chan.live};
+      const StageStore<kFull, false, T> d2y{stage + lane, lane < chan.live};
       pin_values(g);
       y_row.use(Y, e, y);
       hy_row.use(HY, e, hy);
@@ -612,6 +647,22 @@ int waves_per_unit(int64_t n_edges, int64_t n_atoms, int64_t n_units) {
   return n_edges <= 3 * n_atoms && n_units >= 8192 ? 2 : 4;
 }
 
+// Channel blocks of an atom that a workgroup of the backward walks together (2: their shares of dY are added in the lanes, one sum over the lanes
+// serves both, and with two blocks in all it is dY: no shares through memory, no launch that adds them), and up to how many workgroups eight waves share the edges, so
+// that a small graph has as many waves as with a workgroup per block.  Backward with the sum of the shares, us, a workgroup per block / for two, four waves / eight, 128
+// channels: fp32 arithmetic, l_h = 1, 60 atoms 16.8 / 20.6 / 14.0, 250 24.4 / 26.9 / 19.5, 1000 43.5 / 45.5 / 41.6, 2000 78.6 / 80.0 / 76.0, 10 000 458.7 / 451.5
+// / 465.9; l_h = 0, 250 16.8 / 15.5 / 10.4; fp64 arithmetic, l = 2, l_h = 1, 250 21.5 / 20.2 / 16.6, 1000 39.9 / 33.2 / 32.9, 4000 140.7 / 127.3 / 134.7; l_h = 2, 250 27.1 / 27.2 /
+// 23.7, 1000 63.1 / 56.4 / 64.1; fp64 rows, l_h = 1, 200 34.5 / 30.1 / 30.6, 1000 87.6 / 87.2 / 94.5, 2500 271.7 / 263.2 / 298; 96 channels, l_h = 1, 250 30.0 / 31.8 / 25.7, 2000
+// 124.3 / 102.2 / 130.7.  17 paths: fp32 rows (255 registers) 250 40.2 / 47.5 / 42.9, 1000 104.9 / 106.2 / 113.5, 3001 311.7 / 299.8; fp64 rows (which then spill) 1000 169
+// / 237 / 253.
+template <typename T, typename TS, typename G>
+bool two_blocks(int chblocks, int64_t n_in) {
+  if (chblocks % 2 != 0 || (sizeof(TS) == 8 && G::kP >= 17)) return false;
+  return sizeof(T) == 4 || G::kP < 17 || n_in * (chblocks / 2) >= 2048;
+}
+template <typename T>
+constexpr int64_t kEightWaves = sizeof(T) == 4 ? 2048 : 512;
+
 EdgeList edge_list(const FwdArgs& a) {
   return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
 }
@@ -646,18 +697,22 @@ struct Launch {
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    const int64_t n_units = a.n_in * chblocks;
-    const int waves = waves_per_unit(a.n_edges, a.n_in, n_units);
-    const auto kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4> : &backward_by_sender_kernel<T, TS, G, kFull, 2>;
+    const int groups = a.dY_parts, blocks = chblocks / groups;
+    const int64_t n_units = a.n_in * groups;
+    const int waves = blocks == 2 && n_units <= kEightWaves<T> && a.n_edges > 4 * a.n_in ? 8 : waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
+    const auto kernel = blocks == 2 ? (waves == 8 ? &backward_by_sender_kernel<T, TS, G, kFull, 8, 2> : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2>)
+                                    : (waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1>);
     // without receivers or edges no list is walked: every atom gets its zero row
     const int n_edges = a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
-      hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, chblocks, unit0,
+      hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, groups, unit0,
                          n_units, a.n_out_nodes, n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
                          static_cast<const TS*>(a.R), a.send_ptr, a.send_edge, receiver, static_cast<const TS*>(a.dA),
                          static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
     });
   }
+
+  static int dY_parts(int chblocks, int64_t n_in) { return two_blocks<T, TS, G>(chblocks, n_in) ? chblocks / 2 : chblocks; }
 
   static hipError_t double_backward(const tp_plan* plan, const DblArgs& d, hipStream_t stream) {
     const BwdArgs& a = d.b;
@@ -678,7 +733,7 @@ struct Launch {
 
 // Calls fn.template operator()<Launch<...>>() for the instance that serves the plan.
 template <typename G, typename F>
-hipError_t with_instance(const tp_plan* plan, F&& fn) {
+auto with_instance(const tp_plan* plan, F&& fn) {
   constexpr bool kSingle = G::kLY == 3 && G::kLout == 3 && G::kLh <= 1;   // fp32 arithmetic on full blocks (see the top)
   typedef typename std::conditional<kSingle, float, double>::type F32Full;
   const bool full = plan->cfg.num_channels % kLanes == 0;
@@ -695,6 +750,10 @@ struct BackwardFn {
   const tp_plan* plan; const BwdArgs& a; hipStream_t stream;
   template <typename L> hipError_t operator()() const { return L::backward(plan, a, stream); }
 };
+struct PartsFn {
+  int chblocks; int64_t n_in;
+  template <typename L> int operator()() const { return L::dY_parts(chblocks, n_in); }
+};
 struct DoubleBackwardFn {
   const tp_plan* plan; const DblArgs& a; hipStream_t stream;
   template <typename L> hipError_t operator()() const { return L::double_backward(plan, a, stream); }
@@ -708,9 +767,12 @@ struct GeneratedShape {
   static hipError_t double_backward(const tp_plan* p, const DblArgs& a, hipStream_t s) {
     return with_instance<G>(p, DoubleBackwardFn{p, a, s});
   }
+  static int dY_parts(const tp_plan* p, int64_t n_in) {
+    return with_instance<G>(p, PartsFn{(p->cfg.num_channels + kLanes - 1) / kLanes, n_in});
+  }
   static SpecEntry entry() {
     return SpecEntry{G::kLY, G::kLh, G::kLout, G::kP, {G::kOps[0], G::kOps[1], G::kOps[2]},
-                     {G::kFlops[0], G::kFlops[1], G::kFlops[2]}, &forward, &backward, &double_backward};
+                     {G::kFlops[0], G::kFlops[1], G::kFlops[2]}, &forward, &backward, &double_backward, &dY_parts};
   }
 };
 
