@@ -22,7 +22,8 @@
 // lane.  The atoms are cut into ranges, every range writes a partial dW (mfma_dw_lds_kernel:
 // both operands through a ring in LDS; mfma_dw_kernel: every other shape), a
 // second kernel adds the partials in a fixed order (no atomics).
-// Channel counts outside these tilings: split_forward_kernel and split_dw_kernel (fp64 products and sums).
+// Channel counts outside these tilings: split_forward_kernel and split_dw_kernel (fp64 products and sums); both in one launch
+// for the backward of small batches of any channel count (split_backward_kernel).
 #include <algorithm>
 #include <atomic>
 #include <string>
@@ -520,9 +521,9 @@ struct SplitRow {   // elements per row of a partial tile in LDS: the four rows 
 // blockIdx -> logical block such that an XCD's blocks are one contiguous range (the column tiles of a row tile read
 // the same rows of X: they meet in one L2).  blocks is a multiple of kXcds.
 constexpr int kXcds = 8;
-__device__ __forceinline__ int64_t xcd_contiguous_block(unsigned blocks) {
+__device__ __forceinline__ int64_t xcd_contiguous_block(unsigned block, unsigned blocks) {
   const int64_t per = blocks / kXcds;
-  return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+  return (block % kXcds) * per + block / kXcds;
 }
 
 // Calls launch(first tile, workgroups) until all tiles (a workgroup of so many threads each) are served: a grid holds
@@ -539,21 +540,108 @@ hipError_t for_all_tiles(int64_t n_tiles, int threads, F&& launch) {
   return hipSuccess;
 }
 
-// kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).  kSum: workgroups from `blocks` on add
-// partial dW.
+// The tile at atom n0 and column j0.  kTrans: W is [L][k_cols][k_red] (the dX product reads the weights of the forward as they are).
+template <typename TS, typename TA, int LMAX, bool kTrans>
+struct SplitTile {
+  static constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
+  static constexpr int CG = NC < 4 ? NC : 4;                 // components per round through LDS
+  static constexpr int RS = SplitRow<TA>::stride;
+  typedef typename Mma<TA>::acc_t acc_t;
+  // in LDS, as two arrays (as one structure the reads of the sums wait for the writes of the result): the partial tiles, the tile
+  typedef TA Partial[kWaves][CG][16 * RS];
+  typedef TS Out[16][16 * NC];
+  static __device__ __forceinline__ void run(int64_t n0, int j0, int64_t n_nodes, int k_red, int k_cols, const TS* X, const TS* W, TS* Y,
+                                             Partial& red, Out& out) {
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    const int kq = lane / 16, i16 = lane & 15;
+    const int64_t na = n0 + i16 < n_nodes ? n0 + i16 : n_nodes - 1;
+    const int j = j0 + i16 < k_cols ? j0 + i16 : k_cols - 1;
+    const int steps = (k_red + 3) / 4;
+    const TS* xrow = X + static_cast<size_t>(na) * k_red * NC;
+    acc_t acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = acc_t{0, 0, 0, 0};
+
+    auto load = [&](int s, TS (&a)[NC], TS (&b)[L]) {
+      const int k = s * 4 + kq, kc = k < k_red ? k : k_red - 1;
+      load_unaligned<TS, NC>(xrow + static_cast<size_t>(kc) * NC, a);
+#pragma unroll
+      for (int l = 0; l < L; ++l)
+        b[l] = kTrans ? W[(static_cast<size_t>(l) * k_cols + j) * k_red + kc] : W[(static_cast<size_t>(l) * k_red + kc) * k_cols + j];
+    };
+    auto multiply = [&](int s, const TS (&a)[NC], const TS (&b)[L]) {
+      const bool live = s * 4 + kq < k_red;                    // both operands are zeroed: the row re-read may hold a NaN
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        acc[c] = Mma<TA>::mma(live ? static_cast<TA>(a[c]) : TA(0), live ? static_cast<TA>(b[order_of(c)]) : TA(0), acc[c]);
+    };
+    if (wave < steps) {
+      TS a[2][NC], b[2][L];
+      load(wave, a[0], b[0]);
+      // Requests stand before the products that they overlap and under no condition; left alone, the compiler moves them behind the
+      // products, and every step of a small batch lasts one memory latency more (how much depends on how the waves fall: 13% between kernel
+      // arguments from memory and in registers).  Forward, us, left alone / so: 128 -> 128 channels, 40 atoms 9.5 / 7.1, 300
+      // 10.0 / 7.5, 2000 22.9 / 22.0; 256 -> 256, 100 17.1 / 11.5; l_max = 2, 300 8.0 / 6.4; fp64, 300 17.3 / 15.5.  Not the fp64 dX, W strided: backward of 300 35.6 for 35.1.
+      constexpr bool kPin = sizeof(TA) == 4 || !kTrans;
+      for (int s = wave; s < steps; s += 2 * kWaves) {
+        const int s1 = s + kWaves, s2 = s + 2 * kWaves;
+        load(s1 < steps ? s1 : s, a[1], b[1]);
+        if constexpr (kPin) {
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(s, a[0], b[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          load(s2 < steps ? s2 : s, a[0], b[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(s1, a[1], b[1]);                          // (zeros past the end; under a condition its requests of W would move there)
+        } else {
+          multiply(s, a[0], b[0]);
+          if (s1 < steps) {
+            load(s2 < steps ? s2 : s1, a[0], b[0]);
+            multiply(s1, a[1], b[1]);
+          }
+        }
+      }
+    }
+    const int er = threadIdx.x / 16, ec = threadIdx.x % 16;    // the entry that this thread sums
+#pragma unroll
+    for (int c0 = 0; c0 < NC; c0 += CG) {
+      if (c0 > 0) __syncthreads();                             // the previous round has been read
+#pragma unroll
+      for (int c = c0; c < c0 + CG && c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][c - c0][Mma<TA>::row(lane, r) * RS + i16] = acc[c][r];
+      __syncthreads();
+#pragma unroll
+      for (int c = c0; c < c0 + CG && c < NC; ++c) {
+        TA y = red[0][c - c0][er * RS + ec];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) y += red[w][c - c0][er * RS + ec];
+        out[er][ec * NC + c] = static_cast<TS>(y);
+      }
+    }
+    __syncthreads();
+    constexpr int V = NC % 4 == 0 ? 16 / sizeof(TS) : 1;       // rows of X and Y are whole 16-byte pieces, or not
+    typedef TS Vec __attribute__((ext_vector_type(V)));
+    constexpr int kPieces = 16 * NC / V;                       // per atom
+    const int live = (k_cols - j0 < 16 ? k_cols - j0 : 16) * NC / V;
+    for (int q = threadIdx.x; q < 16 * kPieces; q += kThreads) {
+      const int r = q / kPieces, p = q % kPieces;
+      if (n0 + r < n_nodes && p < live)
+        *reinterpret_cast<Vec*>(Y + (static_cast<size_t>(n0 + r) * k_cols + j0) * NC + p * V) =
+            *reinterpret_cast<const Vec*>(&out[r][p * V]);
+    }
+  }
+};
+
+// kSum: workgroups from `blocks` on add partial dW.
 template <typename TS, typename TA, int LMAX, bool kTrans, bool kSum>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void split_forward_kernel(
     int64_t tile0, unsigned blocks, int64_t n_nodes, int k_red, int k_cols, const TS* __restrict__ X, const TS* __restrict__ W,
     TS* __restrict__ Y, RangeSum<TS> sum) {
-  constexpr int NC = (LMAX + 1) * (LMAX + 1), L = LMAX + 1;
-  constexpr int CG = NC < 4 ? NC : 4;                        // components per round through LDS
-  constexpr int RS = SplitRow<TA>::stride;
-  typedef typename Mma<TA>::acc_t acc_t;
-  __shared__ __attribute__((aligned(16))) TA red[kWaves][CG][16 * RS];
-  __shared__ __attribute__((aligned(16))) TS out[16][16 * NC];
-  const int lane = threadIdx.x & (kLanes - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-  const int kq = lane / 16, i16 = lane & 15;
+  typedef SplitTile<TS, TA, LMAX, kTrans> Tile;
+  __shared__ __attribute__((aligned(16))) typename Tile::Partial red;
+  __shared__ __attribute__((aligned(16))) typename Tile::Out out;
   const int col_tiles = (k_cols + 15) / 16;
   if constexpr (kSum) {
     if (blockIdx.x >= blocks) {
@@ -561,86 +649,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       return add_ranges(sum, blockIdx.x - blocks, gridDim.x - blocks, reinterpret_cast<TS*>(red));
     }
   }
-  const int64_t tile = tile0 + xcd_contiguous_block(blocks);
+  const int64_t tile = tile0 + xcd_contiguous_block(blockIdx.x, blocks);
   if (tile >= (n_nodes + 15) / 16 * col_tiles) return;       // the same for the whole workgroup
-  const int64_t n0 = tile / col_tiles * 16;
-  const int j0 = static_cast<int>(tile % col_tiles) * 16;
-  const int64_t na = n0 + i16 < n_nodes ? n0 + i16 : n_nodes - 1;
-  const int j = j0 + i16 < k_cols ? j0 + i16 : k_cols - 1;
-  const int steps = (k_red + 3) / 4;
-  const TS* xrow = X + static_cast<size_t>(na) * k_red * NC;
-  acc_t acc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = acc_t{0, 0, 0, 0};
-
-  auto load = [&](int s, TS (&a)[NC], TS (&b)[L]) {
-    const int k = s * 4 + kq, kc = k < k_red ? k : k_red - 1;
-    load_unaligned<TS, NC>(xrow + static_cast<size_t>(kc) * NC, a);
-#pragma unroll
-    for (int l = 0; l < L; ++l)
-      b[l] = kTrans ? W[(static_cast<size_t>(l) * k_cols + j) * k_red + kc] : W[(static_cast<size_t>(l) * k_red + kc) * k_cols + j];
-  };
-  auto multiply = [&](int s, const TS (&a)[NC], const TS (&b)[L]) {
-    const bool live = s * 4 + kq < k_red;                    // both operands are zeroed: the row re-read may hold a NaN
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      acc[c] = Mma<TA>::mma(live ? static_cast<TA>(a[c]) : TA(0), live ? static_cast<TA>(b[order_of(c)]) : TA(0), acc[c]);
-  };
-  if (wave < steps) {
-    TS a[2][NC], b[2][L];
-    load(wave, a[0], b[0]);
-    // Requests stand before the products that they overlap and under no condition; left alone, the compiler moves them behind the
-    // products, and every step of a small batch lasts one memory latency more (how much depends on how the waves fall: 13% between kernel
-    // arguments from memory and in registers).  Forward, us, left alone / so: 128 -> 128 channels, 40 atoms 9.5 / 7.1, 300
-    // 10.0 / 7.5, 2000 22.9 / 22.0; 256 -> 256, 100 17.1 / 11.5; l_max = 2, 300 8.0 / 6.4; fp64, 300 17.3 / 15.5.  Not the fp64 dX, W strided: backward of 300 35.6 for 35.1.
-    constexpr bool kPin = sizeof(TA) == 4 || !kTrans;
-    for (int s = wave; s < steps; s += 2 * kWaves) {
-      const int s1 = s + kWaves, s2 = s + 2 * kWaves;
-      load(s1 < steps ? s1 : s, a[1], b[1]);
-      if constexpr (kPin) {
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(s, a[0], b[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        load(s2 < steps ? s2 : s, a[0], b[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s1 < steps) multiply(s1, a[1], b[1]);
-      } else {
-        multiply(s, a[0], b[0]);
-        if (s1 < steps) {
-          load(s2 < steps ? s2 : s1, a[0], b[0]);
-          multiply(s1, a[1], b[1]);
-        }
-      }
-    }
-  }
-  const int er = threadIdx.x / 16, ec = threadIdx.x % 16;    // the entry that this thread sums
-#pragma unroll
-  for (int c0 = 0; c0 < NC; c0 += CG) {
-    if (c0 > 0) __syncthreads();                             // the previous round has been read
-#pragma unroll
-    for (int c = c0; c < c0 + CG && c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][c - c0][Mma<TA>::row(lane, r) * RS + i16] = acc[c][r];
-    __syncthreads();
-#pragma unroll
-    for (int c = c0; c < c0 + CG && c < NC; ++c) {
-      TA y = red[0][c - c0][er * RS + ec];
-#pragma unroll
-      for (int w = 1; w < kWaves; ++w) y += red[w][c - c0][er * RS + ec];
-      out[er][ec * NC + c] = static_cast<TS>(y);
-    }
-  }
-  __syncthreads();
-  constexpr int V = NC % 4 == 0 ? 16 / sizeof(TS) : 1;       // rows of X and Y are whole 16-byte pieces, or not
-  typedef TS Vec __attribute__((ext_vector_type(V)));
-  constexpr int kPieces = 16 * NC / V;                       // per atom
-  const int live = (k_cols - j0 < 16 ? k_cols - j0 : 16) * NC / V;
-  for (int q = threadIdx.x; q < 16 * kPieces; q += kThreads) {
-    const int r = q / kPieces, p = q % kPieces;
-    if (n0 + r < n_nodes && p < live)
-      *reinterpret_cast<Vec*>(Y + (static_cast<size_t>(n0 + r) * k_cols + j0) * NC + p * V) =
-          *reinterpret_cast<const Vec*>(&out[r][p * V]);
-  }
+  Tile::run(tile / col_tiles * 16, static_cast<int>(tile % col_tiles) * 16, n_nodes, k_red, k_cols, X, W, Y, red, out);
 }
 
 // The same product where the tiles would be mostly padding (few_channels): one thread per (atom, column), fp64 products
@@ -678,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void few_channels_kernel(int64_t block0, 
 // atoms 143 -> 7, 4000 3980 -> 120; 96 -> 96, 3000 atoms 2962 -> 75.
 constexpr int kDwWaves = 16;
 
-template <typename TS, int ORDER>
+template <typename TS, int ORDER, int kDwWaves>
 __device__ __forceinline__ void split_dw_order(int64_t n_nodes, int nc, int k_in, int k_out, const TS* __restrict__ X,
                                                const TS* __restrict__ dY, TS* __restrict__ dW, int k0, int j0,
                                                double (*red)[256]) {
@@ -707,13 +718,25 @@ __device__ __forceinline__ void split_dw_order(int64_t n_nodes, int nc, int k_in
   if (wave < steps) {
     TS a[2][M], b[2][M];
     load(wave, a[0], b[0]);
+    // Requests before the products that they overlap, as in SplitTile, where the steps of a wave are few (split_backward_kernel; 40 atoms, 256 -> 256
+    // channels 35 -> 22 us); sixteen waves of long sums are better left alone (fp64, 96 -> 96, 300 atoms 21 against 24).
+    constexpr bool kPin = kDwWaves == kWaves;
     for (int64_t s = wave; s < steps; s += 2 * kDwWaves) {
       const int64_t s1 = s + kDwWaves, s2 = s + 2 * kDwWaves;
       load(s1 < steps ? s1 : s, a[1], b[1]);
-      multiply(s, a[0], b[0]);
-      if (s1 < steps) {
-        load(s2 < steps ? s2 : s1, a[0], b[0]);
+      if constexpr (kPin) {
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(s, a[0], b[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(s2 < steps ? s2 : s, a[0], b[0]);
+        __builtin_amdgcn_sched_barrier(0);
         multiply(s1, a[1], b[1]);
+      } else {
+        multiply(s, a[0], b[0]);
+        if (s1 < steps) {
+          load(s2 < steps ? s2 : s1, a[0], b[0]);
+          multiply(s1, a[1], b[1]);
+        }
       }
     }
   }
@@ -728,21 +751,50 @@ __device__ __forceinline__ void split_dw_order(int64_t n_nodes, int nc, int k_in
   dW[(static_cast<size_t>(ORDER) * k_in + ko) * k_out + jo] = static_cast<TS>(y);
 }
 
+// Tile `tile` of order l_max - `rank`.  red: kW partial tiles of LDS.
+template <typename TS, int kW>
+__device__ __forceinline__ void split_dw_tile(int64_t tile, int rank, int64_t n_nodes, int l_max, int k_in, int k_out, const TS* __restrict__ X,
+                                              const TS* __restrict__ dY, TS* __restrict__ dW, double (*red)[256]) {
+  const int jtiles = (k_out + 15) / 16, nc = (l_max + 1) * (l_max + 1);
+  if (tile >= static_cast<int64_t>((k_in + 15) / 16) * jtiles) return;   // the grid is rounded up; the whole workgroup
+  const int j0 = static_cast<int>(tile % jtiles) * 16, k0 = static_cast<int>(tile / jtiles) * 16;
+  switch (l_max - rank) {
+    case 0: return split_dw_order<TS, 0, kW>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    case 1: return split_dw_order<TS, 1, kW>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    case 2: return split_dw_order<TS, 2, kW>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+    default: return split_dw_order<TS, 3, kW>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+  }
+}
+
 template <typename TS>
 __global__ __launch_bounds__(kDwWaves * kLanes) void split_dw_kernel(int64_t tile0, int64_t n_nodes, int l_max, int k_in,
                                                                      int k_out, const TS* __restrict__ X, const TS* __restrict__ dY,
                                                                      TS* __restrict__ dW) {
   __shared__ double red[kDwWaves][256];
-  const int jtiles = (k_out + 15) / 16, nc = (l_max + 1) * (l_max + 1);
-  const int64_t tile = tile0 + blockIdx.x;
-  if (tile >= static_cast<int64_t>((k_in + 15) / 16) * jtiles) return;   // the grid is rounded up; the whole workgroup
-  const int j0 = static_cast<int>(tile % jtiles) * 16, k0 = static_cast<int>(tile / jtiles) * 16;
-  switch (l_max - static_cast<int>(blockIdx.y)) {
-    case 0: return split_dw_order<TS, 0>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
-    case 1: return split_dw_order<TS, 1>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
-    case 2: return split_dw_order<TS, 2>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
-    default: return split_dw_order<TS, 3>(n_nodes, nc, k_in, k_out, X, dY, dW, k0, j0, red);
+  split_dw_tile<TS, kDwWaves>(tile0 + blockIdx.x, static_cast<int>(blockIdx.y), n_nodes, l_max, k_in, k_out, X, dY, dW, red);
+}
+
+// The backward of a small batch as one launch (backward_together): workgroups [0, dx_tiles) own tiles of dX, the others tiles of dW, dw_tiles per
+// order, the highest first (both numbers are multiples of kXcds).  dW with four waves a tile for sixteen: both kinds last as long as the chain of
+// one wave, and run beside each other.
+template <typename TS, typename TA, int LMAX>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void split_backward_kernel(
+    unsigned dx_tiles, unsigned dw_tiles, int64_t n_nodes, int k_in, int k_out, const TS* __restrict__ X, const TS* __restrict__ W,
+    const TS* __restrict__ dY, TS* __restrict__ dX, TS* __restrict__ dW) {
+  typedef SplitTile<TS, TA, LMAX, true> Tile;
+  typedef double DwPartial[kWaves][256];
+  __shared__ __attribute__((aligned(16))) unsigned char partial[std::max(sizeof(typename Tile::Partial), sizeof(DwPartial))];
+  __shared__ __attribute__((aligned(16))) typename Tile::Out out;
+  if (blockIdx.x >= dx_tiles) {
+    const unsigned block = blockIdx.x - dx_tiles;
+    return split_dw_tile<TS, kWaves>(xcd_contiguous_block(block % dw_tiles, dw_tiles), static_cast<int>(block / dw_tiles), n_nodes, LMAX, k_in, k_out,
+                                     X, dY, dW, *reinterpret_cast<DwPartial*>(partial));
   }
+  const int col_tiles = (k_in + 15) / 16;
+  const int64_t tile = xcd_contiguous_block(blockIdx.x, dx_tiles);
+  if (tile >= (n_nodes + 15) / 16 * col_tiles) return;       // the same for the whole workgroup
+  Tile::run(tile / col_tiles * 16, static_cast<int>(tile % col_tiles) * 16, n_nodes, k_out, k_in, dY, W, dX,
+            *reinterpret_cast<typename Tile::Partial*>(partial), out);
 }
 
 __global__ void zero_kernel(unsigned int* p, size_t n_words) {
@@ -976,6 +1028,46 @@ hipError_t partial_dw(const el_config* cfg, int64_t n, const void* X, const void
   }
 }
 
+// Is the backward one launch of split_backward_kernel?  Its workgroups all have a place at once and each lasts as long as its chain: the
+// atoms in the four waves of a tile of dW, k_out in those of a tile of dX.  Of two launches (the tiled partial dW with 13 us for its first rows alone, or
+// split_dw_kernel; then dX) each would have its own chain.  Backward, us, two launches / one: fp32, 128 -> 128 channels, 40 atoms 24.0 / 13.5, 300
+// 26.2 / 17.4, 500 28.0 / 21.8, 800 32 / 36; 64 -> 64, 300 18.0 / 10.2; 256 -> 256, 40 31.7 / 20.6, 160 35.9 / 26.2, 250 40.6 / 39.4, 300 40 / 49; 192 -> 128, 400 26.2 /
+// 24.9, 500 27.1 / 28.9; l_max = 1, 300 10.6 / 7.8, 500 11.2 / 11.1; fp64, 128 -> 128, 160 34.2 / 19.5, 300 35.3 / 28.6, 400 36.7 / 38.8.  Channel counts whose
+// dW is not tiled: 96 -> 96, 300 20.7 / 14.0, 800 36.6 / 27.2, 2000 71 / 101; 100 -> 128, l_max = 2, 800 30.4 / 22.2, 2000 61 / 62; fp64, 96 -> 96, 800 84.6 / 56.3.
+bool backward_together(const el_config* cfg, int64_t n) {
+  if (few_channels(cfg->l_max, cfg->k_out, cfg->k_in)) return false;
+  const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);
+  if (!mfma_dw_ok(cfg)) return n <= 1024 && n * tiles <= 60000;
+  return cfg->dtype == SC_F64 ? n <= 320 && n * tiles <= 24000 : n <= 448 && n * tiles <= 48000;
+}
+
+template <typename T, typename TA, int LMAX>
+hipError_t launch_together(const el_config* cfg, int64_t n, const T* X, const T* W, const T* dY, T* dX, T* dW, hipStream_t stream) {
+  const unsigned dw_tiles = static_cast<unsigned>(((cfg->k_in + 15) / 16 * ((cfg->k_out + 15) / 16) + kXcds - 1) / kXcds * kXcds);
+  const unsigned dx_tiles = static_cast<unsigned>(((n + 15) / 16 * ((cfg->k_in + 15) / 16) + kXcds - 1) / kXcds * kXcds);
+  hipLaunchKernelGGL((split_backward_kernel<T, TA, LMAX>), dim3(dx_tiles + (LMAX + 1) * dw_tiles), dim3(kThreads), 0, stream, dx_tiles,
+                     dw_tiles, n, cfg->k_in, cfg->k_out, X, W, dY, dX, dW);
+  return hipGetLastError();
+}
+
+template <typename T, int LMAX>
+hipError_t together_l(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, void* dX, void* dW, hipStream_t stream) {
+  const T *x = static_cast<const T*>(X), *w = static_cast<const T*>(W), *dy = static_cast<const T*>(dY);
+  T *dx = static_cast<T*>(dX), *dw = static_cast<T*>(dW);
+  if (mfma_forward_ok(cfg->k_out, cfg->k_in)) return launch_together<T, T, LMAX>(cfg, n, x, w, dy, dx, dw, stream);
+  return launch_together<T, double, LMAX>(cfg, n, x, w, dy, dx, dw, stream);
+}
+
+template <typename T>
+hipError_t together_t(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, void* dX, void* dW, hipStream_t stream) {
+  switch (cfg->l_max) {
+    case 0: return together_l<T, 0>(cfg, n, X, W, dY, dX, dW, stream);
+    case 1: return together_l<T, 1>(cfg, n, X, W, dY, dX, dW, stream);
+    case 2: return together_l<T, 2>(cfg, n, X, W, dY, dX, dW, stream);
+    default: return together_l<T, 3>(cfg, n, X, W, dY, dX, dW, stream);
+  }
+}
+
 // Workspace: [ W transposed, rounded up to 256 bytes ][ partial dW per range of atoms ].
 size_t wt_bytes(const el_config* cfg) {
   if (!mfma_forward_ok(cfg->k_out, cfg->k_in)) return 0;   // split_forward_kernel reads W as it is
@@ -1003,6 +1095,7 @@ size_t workspace_bytes(const el_config* cfg, int64_t n) {
 template <typename T>
 hipError_t backward_t(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, void* dX, void* dW, void* ws,
                       hipStream_t stream) {
+  if (backward_together(cfg, n)) return together_t<T>(cfg, n, X, W, dY, dX, dW, stream);
   const bool transposed = mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n, cfg->k_in) && !dx_parts_read_w_as_is(cfg, n);
   Transpose<T> tr{static_cast<const T*>(W), static_cast<T*>(ws), cfg->l_max + 1, cfg->k_in, cfg->k_out, 0};
   if (transposed) {                            // about a thousand elements a workgroup

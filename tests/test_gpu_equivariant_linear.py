@@ -345,6 +345,15 @@ def test_ranges_of_dw_added_in_a_launch_of_their_own(el, N, k_in, k_out, l_max, 
     run_case(el, N, k_in, k_out, l_max, dtype, 8990 + N)
 
 
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype", [
+    (1, 128, 128, 3, "f32"), (17, 64, 64, 0, "f32"), (63, 128, 64, 1, "f32"), (448, 128, 128, 3, "f32"), (449, 128, 128, 3, "f32"),
+    (187, 256, 256, 3, "f32"), (188, 256, 256, 3, "f32"), (320, 64, 128, 2, "f64"), (321, 64, 128, 2, "f64"), (93, 256, 256, 1, "f64"),
+    (5, 100, 128, 2, "f32"), (1024, 96, 96, 3, "f32"), (1025, 96, 96, 3, "f32"), (66, 7, 9, 3, "f64"), (34, 64, 96, 3, "f32"),
+    (130, 300, 300, 0, "f32"), (16, 6, 20, 1, "f64"), (3, 33, 1, 3, "f32")])
+def test_backward_of_small_batches_in_one_launch(el, N, k_in, k_out, l_max, dtype):
+    run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N + k_in)
+
+
 def test_infinite_row_at_the_end_of_a_range(el):
     import torch
     N, K = 5, 128
