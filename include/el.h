@@ -70,8 +70,10 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
  *   B [n_nodes][K][n_LM]  (overwritten)
  * For fp32 plans served by the generated 0e+1o kernel with K a multiple of 128 and k_in a multiple
  * of 16, one kernel computes the tile of A on the matrix cores and evaluates the contraction from
- * the accumulators: A is never written (el_sc_is_fused returns 1).  Every other plan runs
- * el_forward into the workspace and then sc_forward, with the same result up to rounding.
+ * the accumulators: A is never written (el_sc_is_fused returns 1).  Every other plan, and those batches
+ * of these plans for which it is faster and the workspace has the room (up to 2048 atoms; 256 input
+ * channels and more), run el_forward into the workspace and then the contraction, with the same result
+ * up to rounding.  The size that el_sc_workspace_bytes() gives for 0 atoms always serves these plans.
  * workspace: device memory, 256-byte aligned, at least el_sc_workspace_bytes().  Same conventions
  * as sc_forward (stream, no synchronisation); z is not validated: an index outside 0..Z-1 gives an
  * undefined B row for that atom, never an access outside the buffers.  n_nodes == 0 does nothing. */

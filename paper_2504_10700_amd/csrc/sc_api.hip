@@ -474,10 +474,11 @@ static sc_status check_layout_flag(const char* fn, const sc_plan* plan, uint32_t
 // Checks of the tensor arguments and the launches of the forward pass, shared by sc_forward and
 // sc_forward_noalloc; the plan's device is current.  direct (generated kernels):
 // one launch whose waves fold their weights themselves; without a grouping ws is not used.  fold_table: that launch also
-// writes the folded table and, if wanted, the grouping, for the backward of the step.
+// writes the folded table and, if wanted, the grouping, for the backward of the step.  clamp (generated kernels, with
+// SC_REUSE_GROUPING): an element index outside the range takes the nearest element's weights.
 static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z,
                                   const void* W, void* B, const sc::Workspace& ws, const sc::LaunchShape& shape,
-                                  uint32_t flags, bool direct, bool fold_table, hipStream_t stream) {
+                                  uint32_t flags, bool direct, bool fold_table, hipStream_t stream, bool clamp = false) {
   if (!A || !z || !W || !B) return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": NULL tensor argument");
   if (misaligned(A, 16) || misaligned(W, 16) || misaligned(B, 16) || misaligned(z, 4))
     return fail(SC_ERR_INVALID_ARG, std::string(fn) + ": tensor pointer not 16-byte aligned");
@@ -487,7 +488,7 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
   const bool group = !(flags & SC_REUSE_GROUPING);
   // the prepare launch also orders windows of the batch by element for the forward kernel (not for a
   // batch that is ordered already, nor for small ones, where that costs more than it saves)
-  const bool window_order = plan->specialised && !direct && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
+  const bool window_order = plan->specialised && !direct && !clamp && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
                             (n_nodes >= SC_WINDOW_ORDER_MIN_NODES || (plan->cfg.flags & SC_PLAN_WINDOW_ORDER));
   if (plan->specialised && direct) {
     // nothing to prepare
@@ -501,7 +502,7 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
   }
   if (plan->profile) (void)hipEventRecord(plan->ev[0], stream);
   e = plan->specialised ? sc::launch_spec_forward(plan, n_nodes, A, z, W, B, ws, shape,
-                                                  !group ? 0 : (flags & SC_Z_GROUPED) ? 2 : 1, window_order,
+                                                  !group ? (clamp ? 3 : 0) : (flags & SC_Z_GROUPED) ? 2 : 1, window_order,
                                                   (flags & SC_COMPONENT_MAJOR) != 0, direct, fold_table, stream)
                         : sc::launch_generic_forward(plan, n_nodes, A, W, B, ws, shape, stream);
   if (e != hipSuccess) return fail_hip(e, (std::string(fn) + ": kernel launch").c_str());
@@ -652,3 +653,18 @@ sc_status sc_double_backward(sc_plan* plan, int64_t n_nodes, const void* A, cons
 }
 
 }  // extern "C"
+
+// sc_forward for a caller that runs no backward pass on this workspace: generated kernels group nothing, so more batches take
+// the one launch.  clamp: see forward_launches.
+sc_status sc::forward_alone(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B,
+                            void* workspace, size_t workspace_bytes, bool clamp, hipStream_t stream) {
+  sc::LaunchShape shape;
+  sc::Workspace ws;
+  sc_status st = check_common("el_sc_forward", plan, n_nodes, workspace, workspace_bytes, &shape, &ws);
+  if (st != SC_OK) return st;
+  DeviceGuard guard(plan->cfg.device);
+  if (!guard.ok) return fail(SC_ERR_HIP, "el_sc_forward: cannot make the plan's device current");
+  const bool direct = plan->specialised && !(plan->cfg.flags & SC_PLAN_WINDOW_ORDER) && sc::spec_direct_pays(plan, n_nodes, shape, false);
+  return forward_launches("el_sc_forward", plan, n_nodes, A, z, W, B, ws, shape, plan->specialised ? SC_REUSE_GROUPING : 0u,
+                          direct, false, stream, clamp && plan->specialised);
+}

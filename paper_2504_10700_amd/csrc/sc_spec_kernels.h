@@ -319,7 +319,7 @@ template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDire
 __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_t* __restrict__ wnode,
                                                                     const int32_t* __restrict__ elements, int scatter_wgs,
                                                                     int table, int chblocks, int tile, int n, int Z, int K,
-                                                                    int fold_wgs, const TS* __restrict__ A,
+                                                                    int fold_wgs, int clamp, const TS* __restrict__ A,
                                                                     const T* __restrict__ wf, const TW* __restrict__ W,
                                                                     TS* __restrict__ B, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
   // their element indices inside the wave - so that a run of nodes of one element reads the
   // folded weights once (they are re-read per node otherwise: 61 of 432 us at 200k nodes).  The
   // indices are read at once, which also takes them off the per-node chain of dependent loads.
-  // Nodes with an element index outside [0, Z) sort last and are skipped.  (A third row buffer, i.e.
+  // Nodes with an element index outside [0, Z) sort last and are skipped (clamp: take the nearest element's weights).  (A third row buffer, i.e.
   // the rows of node p+2 requested while node p is evaluated, measured the same at 10k nodes and 3%
   // slower at 200k.)
   // With the window order of the prepare launch (ga.wnode) the wave's positions hold nodes of a
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
       mine = wnode[j0 + lane];
       mine = mine < 0 ? 0 : (mine >= n ? n - 1 : mine);
     }
-    key = (e >= 0 && e < Z) ? e : Z;
+    key = (e >= 0 && e < Z) ? e : !clamp ? Z : e < 0 ? 0 : Z - 1;
   }
   int rank = lane;   // lanes past the last node keep their own slot
   if (lane < cnt) rank = 0;
@@ -947,9 +947,9 @@ template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDire
 hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                       const Workspace& ws, const LaunchShape& shape, int group, bool window_order, bool fold_table,
                       hipStream_t stream) {
-  // group: 0 no grouping roles, 1 scatter + table, 2 table only (the batch is already grouped)
+  // group: 0 no grouping roles, 1 scatter + table, 2 table only (the batch is already grouped), 3 no roles and clamped indices
   const bool scatter = group == 1;
-  const int table = group != 0;
+  const int table = group == 1 || group == 2;
   const int scatter_wgs = scatter ? shape.split_waves / kGroupWavesPerWG : 0;
   size_t lds = (G::kNLM * sizeof(TS) != 16) ? sizeof(T) * kSpecWaves * G::kNLM * kLanes : 0;
   if (table) {
@@ -970,8 +970,8 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
   const int grid = scatter_wgs + table + fold_wgs + tiles * shape.chblocks;
   hipLaunchKernelGGL((spec_forward_kernel<T, G, TS, TW, kCM, kDirect>), dim3(grid), dim3(kSpecThreads), lds, stream,
                      window_order ? ws.wnode : nullptr, window_order ? ws.wkey : z, scatter_wgs, table, shape.chblocks, tile,
-                     static_cast<int>(n), plan->cfg.num_elements, plan->cfg.num_channels, fold_wgs, static_cast<const TS*>(A),
-                     static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B),
+                     static_cast<int>(n), plan->cfg.num_elements, plan->cfg.num_channels, fold_wgs, group == 3,
+                     static_cast<const TS*>(A), static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B),
                      group_args(plan, n, z, ws, shape, window_order));
   return hipGetLastError();
 }

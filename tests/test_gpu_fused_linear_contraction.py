@@ -50,7 +50,9 @@ def mods():
     return binding, el_binding
 
 
-def run_case(mods, N, k_in, K, Z, l_max, nu_max, out, dtype, seed, expect_fused, z_mode="skewed"):
+def run_case(mods, N, k_in, K, Z, l_max, nu_max, out, dtype, seed, expect_fused, z_mode="skewed",
+             ws_nodes=None):
+    """ws_nodes: the workspace is the one for so many atoms (0: without room for A, the single kernel whatever N)."""
     import torch
     sc, el = mods
     print(f"case N={N} k_in={k_in} K={K} Z={Z} l_max={l_max} nu={nu_max} out={out} {dtype}", flush=True)
@@ -67,7 +69,7 @@ def run_case(mods, N, k_in, K, Z, l_max, nu_max, out, dtype, seed, expect_fused,
     plan = sc.sc_plan_create(K, l_max, nu_max, Z, out, sc.SC_F32 if dtype == "f32" else sc.SC_F64, 0)
     try:
         assert el.el_sc_is_fused(plan, k_in) == expect_fused
-        nbytes = el.el_sc_workspace_bytes(plan, k_in, N)
+        nbytes = el.el_sc_workspace_bytes(plan, k_in, N if ws_nodes is None else ws_nodes)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         B = torch.full((N, K, wl.n_LM), float("nan"), dtype=tdt, device=dev)
         el.el_sc_forward(plan, k_in, N, Xd, Wl, z, W, B, ws, nbytes)
@@ -94,6 +96,17 @@ def run_case(mods, N, k_in, K, Z, l_max, nu_max, out, dtype, seed, expect_fused,
         err = rel_err_f32(two_calls, ref)
         print(f"two separate calls (N={N}, {k_in}->{K}): error {err:.3e}", flush=True)
     check(f"B (N={N}, {k_in}->{K}, {dtype})", got, ref, dtype, WIDER.get((N, k_in, K, dtype), 1.0))
+
+
+# Batches at the edges of the rule that takes the two steps, each with the workspace of its size, of 0 atoms (the single
+# kernel) and of a larger batch.  The bar is the one of the other cases of these sizes: the maximum over the outputs grows with
+# their number (WIDER: 10 000 atoms), and with the length of the sum.
+@pytest.mark.parametrize("ws_nodes", [None, 0, 5000])
+@pytest.mark.parametrize("N,k_in,K", [(17, 128, 128), (333, 128, 128), (2048, 16, 128), (2049, 16, 128), (1366, 16, 384),
+                                      (100, 256, 128), (2500, 256, 128)])
+def test_either_way_at_the_edges_of_the_rule(mods, N, k_in, K, ws_nodes):
+    WIDER.setdefault((N, k_in, K, "f32"), 3.0 if N > 1000 else 1.0)
+    run_case(mods, N, k_in, K, 5, 3, 3, O01, "f32", 9700 + N, True, z_mode="uniform", ws_nodes=ws_nodes)
 
 
 def test_single_kernel_path_small(mods):
