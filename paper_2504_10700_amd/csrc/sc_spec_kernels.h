@@ -246,9 +246,9 @@ __device__ __forceinline__ void load_folded(const T* __restrict__ wf, int z, int
   for (int s = 0; s < G::kS; ++s) w[s] = src[s * kLanes];
 }
 
-// The internal rows kPart, kPart + kSpecWaves, ... of one (element, 64 channels): what they need is requested before the first
+// The internal rows kPart, kPart + kParts, ... of one (element, 64 channels): what they need is requested before the first
 // value is used (one memory latency, not one per few rows); what belongs to other rows is not computed.
-template <typename T, typename G, typename TW, int kPart>
+template <typename T, typename G, typename TW, int kPart, int kParts>
 __device__ __forceinline__ void fold_part(const TW* __restrict__ src, int K, T* __restrict__ dst) {
   T w[G::kS];
   TW wz[G::kP];
@@ -257,27 +257,36 @@ __device__ __forceinline__ void fold_part(const TW* __restrict__ src, int K, T* 
   asm volatile("" ::: "memory");
   G::fold(wz, 1, w);
 #pragma unroll
-  for (int s = kPart; s < G::kS; s += kSpecWaves) dst[s * kLanes] = w[s];
+  for (int s = kPart; s < G::kS; s += kParts) dst[s * kLanes] = w[s];
 }
 
-// A workgroup of the fold role folds W[element, :, 64 channels] into wf, a quarter of the rows per wave: bound by one memory latency and by what one
-// compute unit can request.  A wave for all rows, four pairs a workgroup (45 of the 256 units at 89 elements, 128 channels) -> this, us a
-// launch: 0e+1o, 3072 nodes 4.1 -> 2.9, l_max = 2 in fp64, 2731 nodes 4.1 -> 2.9; 10 000 nodes, whose launch waits for memory that has left
-// the caches, 5.3 either way.
-template <typename T, typename G, typename TW>
-__device__ __forceinline__ void fold_role(int pair, int K, int chblocks, const TW* __restrict__ W, T* __restrict__ wf) {
-  const int lane = threadIdx.x & (kLanes - 1);
+// The fold role folds W[element, :, 64 channels] into wf, a workgroup per such pair and a quarter of the rows per wave: bound by one memory latency
+// and by what one compute unit can request.  A wave for all rows, four pairs a workgroup (45 of the 256 units at 89 elements, 128
+// channels) -> this, us a launch: 0e+1o, 3072 nodes 4.1 -> 2.9, l_max = 2 in fp64, 2731 nodes 4.1 -> 2.9; 10 000 nodes, whose launch waits for
+// memory that has left the caches, 5.3 either way.
+// kWaves = 1: a wave for all rows, for the launches that also evaluate, with the few rows of a small basis: there the workgroups of this role
+// stand before those of the nodes, and fewer of them hold those up less (l_max = 2 in fp64, us, four waves / one: 1398 nodes 7.7 /
+// 7.3, 2000 8.1 / 7.8; l_max = 3, nu = 2, 0e in fp32 2000 7.7 / 7.5; the 86 rows of 0e+1o 2000 9.1 / 9.2, 0e+1o+2e 9.8 / 10.8).
+template <typename G>
+constexpr int direct_fold_waves() { return G::kP > 64 ? kSpecWaves : 1; }
+
+template <typename T, typename G, typename TW, int kWaves>
+__device__ __forceinline__ void fold_role(int wg, int Z, int K, int chblocks, const TW* __restrict__ W, T* __restrict__ wf) {
+  static_assert(kSpecWaves == 4 && (kWaves == 1 || kWaves == 4), "a part per wave");
+  const int lane = threadIdx.x & (kLanes - 1), wave = wave_of_thread();
+  const int pair = kWaves == 1 ? wg * kSpecWaves + wave : wg;
+  if (pair >= Z * chblocks) return;
   const int z = pair / chblocks, cb = pair % chblocks;   // pair = element * chblocks + channel block
   const int live = K - cb * kLanes < kLanes ? K - cb * kLanes : kLanes;
   const int ch = cb * kLanes + (lane < live ? lane : live - 1);   // dead lanes repeat the last channel
   const TW* src = W + static_cast<size_t>(z) * G::kP * K + ch;
   T* dst = wf + static_cast<size_t>(pair) * G::kS * kLanes + lane;
-  static_assert(kSpecWaves == 4, "a part per wave");
-  switch (wave_of_thread()) {
-    case 0: return fold_part<T, G, TW, 0>(src, K, dst);
-    case 1: return fold_part<T, G, TW, 1>(src, K, dst);
-    case 2: return fold_part<T, G, TW, 2>(src, K, dst);
-    default: return fold_part<T, G, TW, 3>(src, K, dst);
+  if constexpr (kWaves == 1) return fold_part<T, G, TW, 0, 1>(src, K, dst);
+  switch (wave) {
+    case 0: return fold_part<T, G, TW, 0, kSpecWaves>(src, K, dst);
+    case 1: return fold_part<T, G, TW, 1, kSpecWaves>(src, K, dst);
+    case 2: return fold_part<T, G, TW, 2, kSpecWaves>(src, K, dst);
+    default: return fold_part<T, G, TW, 3, kSpecWaves>(src, K, dst);
   }
 }
 
@@ -299,7 +308,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_prepare_kernel(const int32_
     split_count_role(ga, blockIdx.x - window_wgs, reinterpret_cast<int32_t*>(lds_raw));
     return;
   }
-  fold_role<T, G, TW>(static_cast<int>(blockIdx.x) - window_wgs - count_wgs, K, chblocks, W, wf);
+  fold_role<T, G, TW, kSpecWaves>(static_cast<int>(blockIdx.x) - window_wgs - count_wgs, Z, K, chblocks, W, wf);
 }
 
 // The grouping alone (a backward pass that cannot reuse a forward's grouping): scatter and table roles.
@@ -330,7 +339,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
       split_count_all(ga, counts);
       ga.counts = counts;
     } else if (block < scatter_wgs + table + fold_wgs) {
-      fold_role<T, G, TW>(block - scatter_wgs - table, K, chblocks, W, const_cast<T*>(wf));   // read by nobody in this launch
+      fold_role<T, G, TW, direct_fold_waves<G>()>(block - scatter_wgs - table, Z, K, chblocks, W, const_cast<T*>(wf));   // read by nobody in this launch
       return;
     }
   }
@@ -956,7 +965,8 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
     const size_t roles = split_group_lds_bytes(plan->cfg.num_elements) + (kDirect ? split_counts_bytes(plan, shape) : 0);
     if (roles > lds) lds = roles;
   }
-  const int fold_wgs = kDirect && fold_table ? plan->cfg.num_elements * shape.chblocks : 0;
+  constexpr int kPairs = kSpecWaves / direct_fold_waves<G>();   // a workgroup of the fold role
+  const int fold_wgs = kDirect && fold_table ? (plan->cfg.num_elements * shape.chblocks + kPairs - 1) / kPairs : 0;
   static const int wgs_per_cu = [] {   // resident workgroups per compute unit of this instance
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, &spec_forward_kernel<T, G, TS, TW, kCM, kDirect>, kSpecThreads, 0) != hipSuccess || nb < 1)
