@@ -652,16 +652,25 @@ int waves_per_unit(int64_t n_edges, int64_t n_atoms, int64_t n_units) {
 // that a small graph has as many waves as with a workgroup per block.  Backward with the sum of the shares, us, a workgroup per block / for two, four waves / eight, 128
 // channels: fp32 arithmetic, l_h = 1, 60 atoms 16.8 / 20.6 / 14.0, 250 24.4 / 26.9 / 19.5, 1000 43.5 / 45.5 / 41.6, 2000 78.6 / 80.0 / 76.0, 10 000 458.7 / 451.5
 // / 465.9; l_h = 0, 250 16.8 / 15.5 / 10.4; fp64 arithmetic, l = 2, l_h = 1, 250 21.5 / 20.2 / 16.6, 1000 39.9 / 33.2 / 32.9, 4000 140.7 / 127.3 / 134.7; l_h = 2, 250 27.1 / 27.2 /
-// 23.7, 1000 63.1 / 56.4 / 64.1; fp64 rows, l_h = 1, 200 34.5 / 30.1 / 30.6, 1000 87.6 / 87.2 / 94.5, 2500 271.7 / 263.2 / 298; 96 channels, l_h = 1, 250 30.0 / 31.8 / 25.7, 2000
+// 23.7, 1000 63.1 / 56.4 / 64.1; 96 channels, l_h = 1, 250 30.0 / 31.8 / 25.7, 2000
 // 124.3 / 102.2 / 130.7.  17 paths: fp32 rows (255 registers) 250 40.2 / 47.5 / 42.9, 1000 104.9 / 106.2 / 113.5, 3001 311.7 / 299.8; fp64 rows (which then spill) 1000 169
 // / 237 / 253.
-template <typename T, typename TS, typename G>
+// fp64 rows are bound by what a compute unit takes in (12 KB per edge and block): half the workgroups leave units idle or make a
+// last round longer.  Four waves, us, a workgroup per block / for two: l_h = 0, 42 atoms 15.7 / 19.2, 250 25.2 / 26.0, 500 39.2 / 34.4, 700 47.9 / 48.9, 3000 188.5 /
+// 190.3; l_h = 1, 42 20.7 / 25.2, 250 36.1 / 35.3, 330 45.6 / 50.8, 1000 88.9 / 87.1, 1500 171.2 / 171.1, 3000 319 / 311, 6000 623 / 599; 96 channels, whose second
+// block moves half the bytes, 250 26.3 / 25.5, 400 34.0 / 29.6, 1500 81.4 / 71.6, 6000 358 / 312.
+// With more than two blocks the shares are added up all the same.  256 channels, us: fp32 arithmetic, l_h = 1, 127 atoms 22.5 / 22.1, 500 46.2 / 47.2,
+// 1000 80.6 / 84.4, 3000 286.7 / 286.2; l_h = 0, 330 24.2 / 26.3, 1500 56.7 / 58.1; fp64 arithmetic, l_h = 1, 330 31.2 / 33.1, 1500 98.3 / 89.6, 3000 212.5 /
+// 200.9; fp64 rows, l_h = 1, 330 76.4 / 82.6, 1500 316.7 / 316.3.
+template <typename T, typename TS, typename G, bool kFull>
 bool two_blocks(int chblocks, int64_t n_in) {
-  if (chblocks % 2 != 0 || (sizeof(TS) == 8 && G::kP >= 17)) return false;
-  return sizeof(T) == 4 || G::kP < 17 || n_in * (chblocks / 2) >= 2048;
+  if (chblocks % 2 != 0) return false;
+  if (sizeof(TS) == 8) return chblocks == 2 && G::kP < 17 && (kFull ? G::kNh > 1 && n_in >= 1024 : n_in >= 384);
+  if (chblocks > 2) return sizeof(T) == 8 && n_in * (chblocks / 2) > 2048;
+  return sizeof(T) == 4 || G::kP < 17 || n_in >= 2048;
 }
-template <typename T>
-constexpr int64_t kEightWaves = sizeof(T) == 4 ? 2048 : 512;
+template <typename T, typename TS>
+constexpr int64_t kEightWaves = sizeof(TS) == 8 ? 0 : sizeof(T) == 4 ? 2048 : 512;
 
 EdgeList edge_list(const FwdArgs& a) {
   return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
@@ -699,9 +708,17 @@ struct Launch {
     }
     const int groups = a.dY_parts, blocks = chblocks / groups;
     const int64_t n_units = a.n_in * groups;
-    const int waves = blocks == 2 && n_units <= kEightWaves<T> && a.n_edges > 4 * a.n_in ? 8 : waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
-    const auto kernel = blocks == 2 ? (waves == 8 ? &backward_by_sender_kernel<T, TS, G, kFull, 8, 2> : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2>)
-                                    : (waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1>);
+    int waves = waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
+    auto kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1>;
+    if (blocks == 2) {
+      kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2>;
+      if constexpr (kEightWaves<T, TS> > 0) {
+        if (n_units <= kEightWaves<T, TS> && a.n_edges > 4 * a.n_in) {
+          waves = 8;
+          kernel = &backward_by_sender_kernel<T, TS, G, kFull, 8, 2>;
+        }
+      }
+    }
     // without receivers or edges no list is walked: every atom gets its zero row
     const int n_edges = a.n_out_nodes > 0 ? static_cast<int>(a.n_edges) : 0;
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
@@ -712,7 +729,7 @@ struct Launch {
     });
   }
 
-  static int dY_parts(int chblocks, int64_t n_in) { return two_blocks<T, TS, G>(chblocks, n_in) ? chblocks / 2 : chblocks; }
+  static int dY_parts(int chblocks, int64_t n_in) { return two_blocks<T, TS, G, kFull>(chblocks, n_in) ? chblocks / 2 : chblocks; }
 
   static hipError_t double_backward(const tp_plan* plan, const DblArgs& d, hipStream_t stream) {
     const BwdArgs& a = d.b;
