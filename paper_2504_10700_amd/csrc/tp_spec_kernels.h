@@ -379,6 +379,10 @@ __global__ __launch_bounds__(256) void edge_receiver_kernel(int64_t n_out_nodes,
 template <typename T, typename TS, typename G>
 constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
 
+// Receiving atoms up to which the workgroups of the backward find the receivers of their edges themselves (receivers_by_search): 64 edges of a
+// wave at a time, by bisection of the receivers' offsets in LDS.
+constexpr int kSearchNodes = 1024;
+
 // The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, kBlocks 64-channel blocks; two_blocks).
 // Its waves keep the atom's h rows and their dh sums in registers, walk the edges the atom sends
 // (every kWaves-th in send_edge order: with the order of the waves, the order of the sum) and gather
@@ -387,13 +391,14 @@ constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
 // share of dY leave per edge, dh leaves once per atom: no per-edge shares
 // of dh go to memory and come back.  Atoms that send nothing get a zero row.  Every index is
 // clamped where it is used.
-template <typename T, typename TS, typename G, bool kFull, int kWaves, int kBlocks>
+template <typename T, typename TS, typename G, bool kFull, int kWaves, int kBlocks, bool kSearch>
 __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu(kMinWaves<T, TS, G>))) void backward_by_sender_kernel(
     int K, int groups, int64_t unit0, int64_t n_units, int64_t n_out_nodes, int n_edges, const TS* __restrict__ Y,
     const TS* __restrict__ h, const TS* __restrict__ R, const int32_t* __restrict__ send_ptr,
-    const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const TS* __restrict__ dA,
-    TS* __restrict__ dR, TS* __restrict__ dY_partial, TS* __restrict__ dh) {
+    const int32_t* __restrict__ send_edge, const int32_t* __restrict__ receiver, const int32_t* __restrict__ row_ptr,
+    const TS* __restrict__ dA, TS* __restrict__ dR, TS* __restrict__ dY_partial, TS* __restrict__ dh) {
   __shared__ T stage_all[kWaves][G::kNY * kStageStride];
+  __shared__ int32_t rows[kSearch ? kSearchNodes : 1];   // first edge of every receiving atom
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = uniform(threadIdx.x / kLanes);
   T* stage = stage_all[wave];
@@ -409,6 +414,32 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
   };
   auto atom = [&](int r) { return static_cast<size_t>(r < 0 ? 0 : (r >= n_out_nodes ? n_out_nodes - 1 : r)); };
   const int q0 = uniform(pos(send_ptr[node])) + wave, q1 = uniform(pos(send_ptr[node + 1]));
+  // The i-th edge of this wave and its receiver, asked for in order (past the last edge: that one again).  kSearch: 64 of
+  // them at a time, one a lane, the receiver by bisection of the rows in LDS.
+  int my_e = 0, my_r = 0;
+  auto next_edge = [&](int i, int& e, int& r) {
+    const int last = (q1 - 1 - q0) / kWaves;
+    if constexpr (kSearch) {
+      if ((i & (kLanes - 1)) == 0) {
+        my_e = edge(q0 + (i + lane < last ? i + lane : last) * kWaves);
+        my_r = 0;
+#pragma unroll
+        for (int step = kSearchNodes / 2; step > 0; step /= 2) {
+          const int at = my_r + step;
+          if (at < n_out_nodes && rows[at < kSearchNodes ? at : 0] <= my_e) my_r = at;
+        }
+      }
+      e = __builtin_amdgcn_readlane(my_e, i & (kLanes - 1));
+      r = __builtin_amdgcn_readlane(my_r, i & (kLanes - 1));
+    } else {
+      e = uniform(edge(q0 + (i < last ? i : last) * kWaves));
+      r = uniform(receiver[e]);
+    }
+  };
+  if constexpr (kSearch) {
+    for (int v = threadIdx.x; v < n_out_nodes; v += kWaves * kLanes) rows[v] = pos(row_ptr[v]);   // at most kSearchNodes
+    __syncthreads();
+  }
   T acc[kBlocks][G::kNh];
 #pragma unroll
   for (int b = 0; b < kBlocks; ++b)
@@ -424,12 +455,13 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       load_weights<TS, G::kP>(R, e, K, ch, r_row);
       load_row<TS, G::kNout>(dA + (atom(receiving) * K + ch) * G::kNout, g_row);
     };
-    int ea = uniform(edge(q0)), ra = uniform(receiver[ea]);
+    int ea, ra;
+    next_edge(0, ea, ra);
     y0.request(Y, ea, lane);
     load_rows(ea, ra, chan[0].ch, r0, g0);
     // edge id and receiver of the edge after the current one, read one step ahead of its rows
-    int en = uniform(edge(q0 + kWaves < q1 ? q0 + kWaves : q0));
-    int rn = uniform(receiver[en]);
+    int i = 1, en, rn;
+    next_edge(i, en, rn);
 
     // One edge and channel block: arithmetic, dR row stores, dh added up; with the last block dY summed over the 64 lanes in a fixed order.
     auto finish_block = [&](auto block, int e, const T (&y)[G::kNY], const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
@@ -463,13 +495,14 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
         __builtin_amdgcn_sched_barrier(0);
         T y[G::kNY];
         y0.use(Y, ea, y);
-        const int q2 = q + 2 * kWaves < q1 ? q + 2 * kWaves : q0;
-        const int e2 = uniform(edge(q2));
+        int e2, r2;
+        if constexpr (!kSearch) e2 = uniform(edge(q + 2 * kWaves < q1 ? q + 2 * kWaves : q0));
         finish_block(first, ea, y, r0, g0);
         y0.request(Y, en, lane);
         load_rows(en, rn, q + kWaves < q1 ? chan[0].ch : chan[0].first, r0, g0);
         __builtin_amdgcn_sched_barrier(0);
-        const int r2 = uniform(receiver[e2]);
+        if constexpr (kSearch) next_edge(++i, e2, r2);
+        else r2 = uniform(receiver[e2]);
         finish_block(last, ea, y, r1, g1);
         ea = en;
         ra = rn;
@@ -483,10 +516,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
           ea = en;
           y0.request(Y, ea, lane);
           load_rows(ea, rn, chan[0].ch, r0, g0);
-          if (q + 2 * kWaves < q1) {
-            en = uniform(edge(q + 2 * kWaves));
-            rn = uniform(receiver[en]);
-          }
+          if (q + 2 * kWaves < q1) next_edge(++i, en, rn);
         }
       }
     } else {
@@ -498,10 +528,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
           eb = en;
           y1.request(Y, eb, lane);
           load_rows(eb, rn, chan[0].ch, r1, g1);
-          if (q + 2 * kWaves < q1) {
-            en = uniform(edge(q + 2 * kWaves));
-            rn = uniform(receiver[en]);
-          }
+          if (q + 2 * kWaves < q1) next_edge(++i, en, rn);
         }
         finish_edge(ea, y0, r0, g0);
         if (q + kWaves < q1) {
@@ -509,10 +536,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
             ea = en;
             y0.request(Y, ea, lane);
             load_rows(ea, rn, chan[0].ch, r0, g0);
-            if (q + 3 * kWaves < q1) {
-              en = uniform(edge(q + 3 * kWaves));
-              rn = uniform(receiver[en]);
-            }
+            if (q + 3 * kWaves < q1) next_edge(++i, en, rn);
           }
           finish_edge(eb, y1, r1, g1);
         }
@@ -672,6 +696,13 @@ bool two_blocks(int chblocks, int64_t n_in) {
 template <typename T, typename TS>
 constexpr int64_t kEightWaves = sizeof(TS) == 8 ? 0 : sizeof(T) == 4 ? 2048 : 512;
 
+// Do the workgroups of the backward search for receivers?  It saves the launch that writes every edge's receiver and costs each workgroup the rows
+// in LDS and about ten reads there per 64 edges of a wave, so it pays up to a number of workgroups.  Receivers and backward, us, with the launch /
+// searched: 128 channels, fp32, l_h = 0, 42 atoms 9.6 / 8.3, 330 19.2 / 14.9, 1000 27.5 / 25.1; l_h = 1, 127 19.9 / 15.6, 330 28.5 / 23.4, 1000 46.0 / 42.4; l = 2,
+// l_h = 2, 250 28.8 / 24.5; 256 channels, l_h = 1, 330 (1320 workgroups) 39.0 / 36.2, 700 (2800) 60.5 / 60.1, l = 2 700 52.2 / 53.7; 17 paths, 250
+// (500) 41.3 / 37.0, 1000 (2000) 106.1 / 107.3; fp64 rows, l_h = 1, 330 46.3 / 44.6, 1000 89.8 / 89.7.
+inline bool receivers_by_search(int64_t n_out_nodes, int64_t n_units) { return n_out_nodes <= kSearchNodes && n_units <= 1536; }
+
 EdgeList edge_list(const FwdArgs& a) {
   return EdgeList{a.sender, a.row_ptr, static_cast<int>(a.n_in), static_cast<int>(a.n_edges)};
 }
@@ -699,23 +730,26 @@ struct Launch {
 
   static hipError_t backward(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
+    const int groups = a.dY_parts, blocks = chblocks / groups;
+    const int64_t n_units = a.n_in * groups;
+    const bool search = receivers_by_search(a.n_out_nodes, n_units);
     int32_t* receiver = static_cast<int32_t*>(a.dh_edge);   // the shares' part of the workspace is free on this path
-    if (a.n_edges > 0 && a.n_out_nodes > 0) {
+    if (a.n_edges > 0 && a.n_out_nodes > 0 && !search) {
       hipLaunchKernelGGL(edge_receiver_kernel, dim3(static_cast<unsigned>((a.n_out_nodes + 255) / 256)), dim3(256), 0,
                          stream, a.n_out_nodes, edge_list(a), receiver);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    const int groups = a.dY_parts, blocks = chblocks / groups;
-    const int64_t n_units = a.n_in * groups;
-    int waves = waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
-    auto kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1>;
+    int waves = search ? 4 : waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
+    auto kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1, true>
+                : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1, false> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1, false>;
     if (blocks == 2) {
-      kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2>;
+      kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, true>
+             : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, false> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2, false>;
       if constexpr (kEightWaves<T, TS> > 0) {
         if (n_units <= kEightWaves<T, TS> && a.n_edges > 4 * a.n_in) {
           waves = 8;
-          kernel = &backward_by_sender_kernel<T, TS, G, kFull, 8, 2>;
+          kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, true> : &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, false>;
         }
       }
     }
@@ -724,8 +758,8 @@ struct Launch {
     return for_all_units(n_units, [&](int64_t unit0, dim3 grid) {
       hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), 0, stream, K, groups, unit0,
                          n_units, a.n_out_nodes, n_edges, static_cast<const TS*>(a.Y), static_cast<const TS*>(a.h),
-                         static_cast<const TS*>(a.R), a.send_ptr, a.send_edge, receiver, static_cast<const TS*>(a.dA),
-                         static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
+                         static_cast<const TS*>(a.R), a.send_ptr, a.send_edge, receiver, a.row_ptr,
+                         static_cast<const TS*>(a.dA), static_cast<TS*>(a.dR), static_cast<TS*>(a.dY_partial), static_cast<TS*>(a.dh));
     });
   }
 

@@ -382,6 +382,14 @@ def test_backward_of_two_channel_blocks(tp, N, mean_degree, K, l, l_h, dtype):
     full_parity(tp, wl_of(f"tp_blocks_{N}_{K}", N, mean_degree, K, l, l_h, l, dtype, 9300 + N + K))
 
 
+# Receivers found by the workgroups: more than 64 edges a wave (with eight waves and with four), the most atoms and workgroups of the rule and one more.
+@pytest.mark.parametrize("N,mean_degree,K,l,l_h,dtype", [
+    (12, 560, 128, 3, 1, "f32"), (10, 300, 64, 3, 1, "f64"), (1024, 2, 64, 3, 0, "f32"), (1025, 2, 64, 3, 0, "f32"),
+    (768, 3, 128, 3, 2, "f64"), (769, 3, 128, 3, 2, "f64"), (1, 70, 40, 2, 2, "f32")])
+def test_receivers_found_by_the_backward(tp, N, mean_degree, K, l, l_h, dtype):
+    full_parity(tp, wl_of(f"tp_search_{N}_{K}", N, mean_degree, K, l, l_h, l, dtype, 9400 + N + K))
+
+
 @pytest.mark.parametrize("flags", [0, 2])
 def test_wrong_index_arrays_stay_inside_the_buffers(tp, flags):
     """The index arrays are not validated, but every index is clamped where it is read: a list with
