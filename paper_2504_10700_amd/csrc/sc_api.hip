@@ -447,9 +447,11 @@ static hipError_t grouped_pass_prologue(const char* fn, sc_plan* plan, int64_t n
                                         bool uses_folded_table, hipStream_t stream) {
   const bool group = !(flags & SC_REUSE_GROUPING);
   hipError_t e = hipSuccess;
-  if (plan->specialised) {
-    e = sc::launch_spec_prepare(plan, n_nodes, z, W, ws, shape, group, uses_folded_table && !(flags & SC_REUSE_WEIGHTS),
-                                false, stream);
+  const bool fold = uses_folded_table && !(flags & SC_REUSE_WEIGHTS);
+  if (plan->specialised && group && sc::spec_group_direct_pays(plan, n_nodes, shape)) {
+    e = sc::launch_spec_group(plan, n_nodes, z, W, ws, shape, (flags & SC_Z_GROUPED) != 0, fold, stream);
+  } else if (plan->specialised) {
+    e = sc::launch_spec_prepare(plan, n_nodes, z, W, ws, shape, group, fold, false, stream);
     if (e == hipSuccess && group) e = sc::launch_spec_scatter(plan, n_nodes, z, ws, shape, (flags & SC_Z_GROUPED) != 0, stream);
   } else if (group) {
     e = sc::launch_grouping(plan, n_nodes, z, ws, shape, stream);

@@ -1,7 +1,8 @@
 // Channel-mixing linear fused into the forward of the symmetric contraction (see include/el.h,
 // el_sc_forward): B = contraction(A, z, W) with A[i,k',(l,m)] = sum_k W_lin[l,k,k'] X[i,k,(l,m)]
 // (Section 4.1 of arXiv 2504.10700: the linear combination of the channels of each order and
-// Algorithm 2 are consecutive steps on the receiving atom).  A never goes through memory.
+// Algorithm 2 are consecutive steps on the receiving atom).  In the fused kernel A never goes through memory; small batches and
+// long reductions take the two steps through it (two_step_nodes).
 //
 // The MFMA 16x16x4 result layout puts, for one output channel (column lane%16 of the tile) and
 // four atoms (rows 4*(lane/16)+r), every component (l,m) of A into the registers of one lane:

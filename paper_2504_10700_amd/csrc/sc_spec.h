@@ -64,6 +64,10 @@ hipError_t launch_spec_prepare(const sc_plan* plan, int64_t n, const int32_t* z,
 // table_only: offsets and tile table without the permutation (the batch is already grouped).
 hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z, const Workspace& ws,
                                const LaunchShape& shape, bool table_only, hipStream_t stream);
+// Grouping and, if wanted, the folded table by one launch: the roles of a direct forward without the forward.
+bool spec_group_direct_pays(const sc_plan* plan, int64_t n, const LaunchShape& shape);
+hipError_t launch_spec_group(const sc_plan* plan, int64_t n, const int32_t* z, const void* W, const Workspace& ws,
+                             const LaunchShape& shape, bool table_only, bool fold, hipStream_t stream);
 // Forward over the nodes in natural order from ws.wfold, or (direct) with weights that every wave
 // folds from W by itself; group: the second half of the grouping
 // rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only, 3 no, and an element index outside the

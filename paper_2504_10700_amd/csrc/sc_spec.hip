@@ -102,6 +102,18 @@ bool spec_direct_pays(const sc_plan* plan, int64_t n, const LaunchShape& shape, 
   return n <= 10000 && bytes <= 2.8e6;
 }
 
+// For a backward or second-order pass that finds no grouping: one launch instead of prepare and scatter, whose workgroups then count
+// the whole batch each.  us, two launches (and the gap between them) / one, 89 elements: fp32, 128 channels, 0e+1o 60 nodes 8.0 / 6.5, 500 8.9 / 6.5,
+// 2000 10.2 / 7.6; 0e+1o+2e 1000 9.8 / 7.1; fp64 60 10.3 / 7.4, 2000 10.8 / 8.7.
+bool spec_group_direct_pays(const sc_plan* plan, int64_t n, const LaunchShape& shape) {
+  return n <= 2048 && split_counts_bytes(plan, shape) <= 16 * 1024;
+}
+
+hipError_t launch_spec_group(const sc_plan* plan, int64_t n, const int32_t* z, const void* W, const Workspace& ws,
+                             const LaunchShape& shape, bool table_only, bool fold, hipStream_t stream) {
+  return launch_spec_forward(plan, n, nullptr, z, W, nullptr, ws, shape, table_only ? 2 : 1, false, false, true, fold, stream);
+}
+
 hipError_t launch_spec_prepare(const sc_plan* plan, int64_t n, const int32_t* z, const void* W, const Workspace& ws,
                                const LaunchShape& shape, bool count, bool fold, bool window_order, hipStream_t stream) {
   return entry_of(plan->specialised)->prepare(plan, n, z, W, ws, shape, count, fold, window_order, stream);

@@ -976,7 +976,7 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
   const int tile = shape.fwd_tile_nodes > 0 ? shape.fwd_tile_nodes
                                             : forward_tile_nodes(n, shape.chblocks, static_cast<int64_t>(wgs_per_cu) * plan->num_cus,
                                                                  G::kS > 32 ? 64 : 32);
-  const int tiles = static_cast<int>((n + tile - 1) / tile);
+  const int tiles = B ? static_cast<int>((n + tile - 1) / tile) : 0;   // (launch_spec_group: the roles alone)
   const int grid = scatter_wgs + table + fold_wgs + tiles * shape.chblocks;
   hipLaunchKernelGGL((spec_forward_kernel<T, G, TS, TW, kCM, kDirect>), dim3(grid), dim3(kSpecThreads), lds, stream,
                      window_order ? ws.wnode : nullptr, window_order ? ws.wkey : z, scatter_wgs, table, shape.chblocks, tile,

@@ -761,6 +761,29 @@ def test_component_major_layout(sc, case):
             sc.sc_plan_destroy(plan)
 
 
+# A backward and a second-order pass that group for themselves, by one launch up to 2048 nodes and by two beyond: the bits of those that reuse
+# the forward's grouping.
+@pytest.mark.parametrize("N,K,out,dtype,ordered", [(1, 128, O01, "f32", False), (70, 72, O012, "f64", False), (2048, 128, O01, "f32", False),
+                                                   (2048, 128, O01, "f32", True), (2049, 64, O01, "f32", False), (500, 128, O01, "bf16", False)])
+def test_passes_that_group_for_themselves(sc, N, K, out, dtype, ordered):
+    wl = wl_of(f"own_grouping_{N}", N, 17, K, 3, 3, out, dtype, 8800 + N)
+    inp = workloads.make_inputs(wl, oracle_tables(wl).paths)
+    if ordered:
+        inp.z[:] = np.sort(inp.z)
+    run = GpuRun(sc, wl, inp)
+    H = workloads.make_cotangent(wl)
+    run.forward()
+    ref = run.backward(sc.SC_REUSE_GROUPING | sc.SC_REUSE_WEIGHTS)
+    ref2 = run.double_backward(H, sc.SC_REUSE_GROUPING)[:3]
+    grouped = sc.SC_Z_GROUPED if ordered else 0
+    run.ws.zero_()
+    assert all(np.array_equal(x, y) for x, y in zip(run.backward(grouped), ref))
+    assert all(np.array_equal(x, y) for x, y in zip(run.backward(grouped | sc.SC_REUSE_WEIGHTS), ref))
+    run.ws.zero_()
+    assert all(np.array_equal(x, y) for x, y in zip(run.double_backward(H, grouped)[:3], ref2))
+    run.close()
+
+
 def test_out_of_range_elements_are_skipped_not_fatal(sc):
     import torch
     wl = wl_of("badz", 50, 4, 128, 3, 3, O01, "f32", 2801, z_mode="uniform")
