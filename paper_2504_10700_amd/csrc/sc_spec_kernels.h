@@ -328,11 +328,12 @@ template <typename T, typename G, typename TS, typename TW, bool kCM, bool kDire
 __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_t* __restrict__ wnode,
                                                                     const int32_t* __restrict__ elements, int scatter_wgs,
                                                                     int table, int chblocks, int tile, int n, int Z, int K,
-                                                                    int fold_wgs, int clamp, const TS* __restrict__ A,
+                                                                    int fold_wgs, const TS* __restrict__ A,
                                                                     const T* __restrict__ wf, const TW* __restrict__ W,
                                                                     TS* __restrict__ B, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
   int block = blockIdx.x;
+  const bool clamp = fold_wgs < 0;   // (a word of its own would be one of the first 14 too many)
   if constexpr (kDirect) {   // no launch came before: the roles count for themselves, the fold role is here
     if (block < scatter_wgs + table) {
       int32_t* counts = reinterpret_cast<int32_t*>(lds_raw) + split_group_lds_bytes(Z) / sizeof(int32_t);
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
     return;
   }
   block -= scatter_wgs + table;
-  if constexpr (kDirect) block -= fold_wgs;
+  if constexpr (kDirect) block -= clamp ? 0 : fold_wgs;
   const int lane = threadIdx.x & (kLanes - 1);
   const int wave = wave_of_thread();
   T* stage = reinterpret_cast<T*>(lds_raw) + wave * kLanes * G::kNLM;  // [64][kNLM] per wave (if used)
@@ -966,7 +967,8 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
     if (roles > lds) lds = roles;
   }
   constexpr int kPairs = kSpecWaves / direct_fold_waves<G>();   // a workgroup of the fold role
-  const int fold_wgs = kDirect && fold_table ? (plan->cfg.num_elements * shape.chblocks + kPairs - 1) / kPairs : 0;
+  const bool clamp = group == 3;   // given as fold_wgs = -1: no such workgroups then
+  const int fold_wgs = kDirect && fold_table && !clamp ? (plan->cfg.num_elements * shape.chblocks + kPairs - 1) / kPairs : 0;
   static const int wgs_per_cu = [] {   // resident workgroups per compute unit of this instance
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, &spec_forward_kernel<T, G, TS, TW, kCM, kDirect>, kSpecThreads, 0) != hipSuccess || nb < 1)
@@ -980,7 +982,7 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
   const int grid = scatter_wgs + table + fold_wgs + tiles * shape.chblocks;
   hipLaunchKernelGGL((spec_forward_kernel<T, G, TS, TW, kCM, kDirect>), dim3(grid), dim3(kSpecThreads), lds, stream,
                      window_order ? ws.wnode : nullptr, window_order ? ws.wkey : z, scatter_wgs, table, shape.chblocks, tile,
-                     static_cast<int>(n), plan->cfg.num_elements, plan->cfg.num_channels, fold_wgs, group == 3,
+                     static_cast<int>(n), plan->cfg.num_elements, plan->cfg.num_channels, clamp ? -1 : fold_wgs,
                      static_cast<const TS*>(A), static_cast<const T*>(ws.wfold), static_cast<const TW*>(W), static_cast<TS*>(B),
                      group_args(plan, n, z, ws, shape, window_order));
   return hipGetLastError();
