@@ -106,9 +106,13 @@ def sl(l: int) -> slice:
 def couple_directly(P: Program, C: np.ndarray, x, v, acc: List[Optional[int]]) -> None:
     """acc[c] += sum_ab C[a,b,c] x[a] v[b] with a fused multiply-add straight into acc for every term of unit magnitude.
     Terms of another magnitude: v scaled by it once, or the terms of a component summed and then scaled, whichever takes
-    fewer operations.  (More roundings at the size of acc than by sums of equal magnitude: for arithmetic in fp64, whose instructions
-    bound these kernels.  l_h = 2: forward 404 -> 350 operations, 3001 atoms, 128 channels 140 -> 130 us; second-order pass
-    1725 -> 1679, 1500 atoms 316 -> 305 us; l = 2, l_h = 2, 2500 atoms, 64 channels, forward 33.4 -> 32.0.)"""
+    fewer operations.
+
+    More roundings at the size of acc than by sums of equal magnitude (couple_into): in fp64, twenty edges, l_h = 2, the error of the
+    sum is 5.5e-16 for 4.3e-16 of its 2-norm, 6.8e-16 for 4.3e-16 in the second-order pass.  So for fp32 rows in fp64 arithmetic, whose results
+    are rounded to 6e-8 and whose kernels are bound by the instructions: l_h = 2, forward 404 -> 350 operations, 3001 atoms,
+    128 channels 140 -> 130 us; second-order pass 1725 -> 1679, 1500 atoms 316 -> 305 us; l = 2, l_h = 2, 2500 atoms, 64 channels,
+    forward 33.4 -> 32.0."""
     by_mag: Dict[float, Dict[int, List[Tuple[int, int, float]]]] = {}
     for a, b, c in zip(*np.nonzero(C)):
         by_mag.setdefault(round(abs(float(C[a, b, c])), 11), {}).setdefault(int(c), []).append((int(a), int(b), float(C[a, b, c])))
@@ -137,11 +141,10 @@ def in_fp32(tab: TPTables) -> bool:
     return tab.n_Y == 16 and tab.n_out == 16 and tab.n_h <= 4
 
 
-def build_programs(tab: TPTables) -> Tuple[Program, Program]:
+def build_forward(tab: TPTables, couple) -> Program:
+    """acc[c] += sum C[a,b,c] y[a] (kappa r[p] h[b]), by couple_into or couple_directly."""
     scaled = [split_scale(Cp) for Cp in tab.C]
-    # forward: acc[c] += sum C[a,b,c] y[a] (kappa r[p] h[b])
     F = Program()
-    couple = couple_into if in_fp32(tab) else couple_directly
     y = [F.inp(f"y[{a}]") for a in range(tab.n_Y)]
     h = [F.inp(f"h[{b}]") for b in range(tab.n_h)]
     acc: List[Optional[int]] = [F.inp(f"acc[{c}]") for c in range(tab.n_out)]
@@ -156,15 +159,19 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
             F.fence(part)
     for c in range(tab.n_out):
         F.out(f"acc[{c}]", acc[c])
+    return F
 
-    # backward of one edge
+
+def build_backward(tab: TPTables) -> Program:
+    """Backward of one edge."""
     Bq = Program()
     y = [Bq.inp(f"y[{a}]") for a in range(tab.n_Y)]
     h = [Bq.inp(f"h[{b}]") for b in range(tab.n_h)]
     g = [Bq.inp(f"g[{c}]") for c in range(tab.n_out)]
     # path by path, so that only the sums over the paths stay live from one path to the next
     dy: List[Optional[int]] = [None] * tab.n_Y
-    # the gradient of the sender's features: sums in fp32 take the edge's share at once
+    # the gradient of the sender's features: sums in fp32 take the edge's share at once, the others term by term (or from
+    # zero, where the kernel adds the share: see the header of the function)
     dh_in = [Bq.inp(f"dh[{b}]") for b in range(tab.n_h)]
     dh: List[Optional[int]] = [None] * tab.n_h if in_fp32(tab) else list(dh_in)
     for p, (l1, l2, l3) in enumerate(tab.paths):
@@ -179,7 +186,7 @@ def build_programs(tab: TPTables) -> Tuple[Program, Program]:
         Bq.fence(dy[sl(l1)] + dh[sl(l2)])
     for b in range(tab.n_h):
         Bq.out(f"dh[{b}]", Bq.add(dh[b], dh_in[b]) if in_fp32(tab) else dh[b])
-    return F, Bq
+    return Bq
 
 
 def out_when_complete(P: Program, name: str, v, paths, p: int) -> None:
@@ -231,7 +238,7 @@ def add_scaled(P: Program, f: int, v, acc: List[Optional[int]], l: int) -> None:
             acc[l * l + i] = P.fma(f, vi, acc[l * l + i])
 
 
-def build_double_backward(tab: TPTables) -> Program:
+def build_double_backward(tab: TPTables, couple) -> Program:
     """psi = sum_c g[c] * (derivative of the edge's message along (hy, hh, hr)):
     dda += that derivative; d2y, d2h, d2r = d psi / d (y, h, r) (overwritten).
 
@@ -243,7 +250,6 @@ def build_double_backward(tab: TPTables) -> Program:
     (Differentiating the forward program mechanically gives the same sums in an order in which the
     intermediates of all paths are live at once: 6 KB of scratch per lane for l_h = 2 in fp64.)"""
     P = Program()
-    couple = couple_into if in_fp32(tab) else couple_directly
     y = [P.inp(f"y[{a}]") for a in range(tab.n_Y)]
     hy = [P.inp(f"hy[{a}]") for a in range(tab.n_Y)]
     h = [P.inp(f"h[{b}]") for b in range(tab.n_h)]
@@ -360,9 +366,23 @@ def flops(c: Dict[str, int]) -> int:
     return 2 * (c.get("fma", 0) + c.get("fnma", 0) + c.get("cfma", 0)) + sum(c.get(k, 0) for k in ("mul", "add", "sub", "cmul"))
 
 
-def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program) -> str:
+def emit_either(L: List[str], direct: Program, by_magnitude: Program) -> None:
+    """The body of a function whose first template parameter is kDirect (one program where both are the same)."""
+    if direct is by_magnitude:
+        L.append(direct.emit("T", "    "))
+        return
+    L.append("    if constexpr (kDirect) {")
+    L.append(direct.emit("T", "      "))
+    L.append("    } else {")
+    L.append(by_magnitude.emit("T", "      "))
+    L.append("    }")
+
+
+def emit_inc(tag: str, spec, tab: TPTables, F, Bq: Program, D) -> str:
+    """F, D: (term by term, by magnitude)."""
     l_Y, l_h, L_max = spec
-    cs = [F.count(), Bq.count(), D.count()]
+    cs = [F[0].count(), Bq.count(), D[0].count()]
+    cs_by_magnitude = [F[1].count(), Bq.count(), D[1].count()]
     L = []
     L.append(f"// GENERATED by paper_2504_10700_amd/codegen/generate_tp.py for l_Y={l_Y}, l_h={l_h}, L_max={L_max}.  Do not edit.")
     L.append("//")
@@ -372,15 +392,21 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append(f"  static constexpr int kLY = {l_Y}, kLh = {l_h}, kLout = {L_max};")
     L.append(f"  static constexpr int kNY = {tab.n_Y}, kNh = {tab.n_h}, kNout = {tab.n_out}, kP = {tab.P};")
     L.append("  // vector instructions / flops (a fused multiply-add counts twice) per (edge, channel):")
-    L.append("  // forward, backward, second-order pass")
-    L.append("  static constexpr int kOps[3] = {" + ", ".join(str(c["total"]) for c in cs) + "};")
-    L.append("  static constexpr int kFlops[3] = {" + ", ".join(str(flops(c)) for c in cs) + "};")
+    L.append("  // forward, backward, second-order pass; of the programs without and with kDirect")
+    L.append("  static constexpr int kOps[2][3] = {" + ", ".join(
+        "{" + ", ".join(str(c["total"]) for c in x) + "}" for x in (cs_by_magnitude, cs)) + "};")
+    L.append("  static constexpr int kFlops[2][3] = {" + ", ".join(
+        "{" + ", ".join(str(flops(c)) for c in x) + "}" for x in (cs_by_magnitude, cs)) + "};")
+    L.append("  // does backward add the terms of dh to the sum one by one (or the edge's share at once)?")
+    L.append(f"  static constexpr bool kDhByTerms = {'false' if in_fp32(tab) else 'true'};")
     L.append("")
+    L.append("  // kDirect: the terms of a coupling go into the sum over the edges one by one, and not as sums of equal magnitude: fewer")
+    L.append("  // operations, more roundings at the size of that sum." + ("  (Not for this shape.)" if in_fp32(tab) else ""))
     L.append("  // R: r[p] as T.  DR, DY: element p or a is assigned once, where the last path that contributes ends.")
     L.append("  // acc += message of one edge")
-    L.append("  template <typename T, typename R>")
+    L.append("  template <bool kDirect, typename T, typename R>")
     L.append("  static __device__ __forceinline__ void forward(const T (&y)[kNY], const T (&h)[kNh], const R& r, T (&acc)[kNout]) {")
-    L.append(F.emit("T", "    "))
+    emit_either(L, *F)
     L.append("  }")
     L.append("")
     L.append("  // g = dA of the receiver; overwritten: dr and dy (this channel's share of the edge's dY); dh += the edge's")
@@ -395,12 +421,12 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
     L.append("  // dda += derivative of the edge's message along (hy, hh, hr); with psi = sum(g * that derivative):")
     L.append("  // d2r = d psi / d r, d2y = this channel's share of d psi / d y, d2h = the edge's share of d psi / d h")
     L.append("  // (all three overwritten).")
-    L.append("  template <typename T, typename R, typename DR, typename DY>")
+    L.append("  template <bool kDirect, typename T, typename R, typename DR, typename DY>")
     L.append("  static __device__ __forceinline__ void double_backward(const T (&y)[kNY], const T (&hy)[kNY], const T (&h)[kNh],")
     L.append("                                                         const T (&hh)[kNh], const R& r, const R& hr,")
     L.append("                                                         const T (&g)[kNout], T (&dda)[kNout], DR& d2r, DY& d2y,")
     L.append("                                                         T (&d2h)[kNh]) {")
-    L.append(D.emit("T", "    "))
+    emit_either(L, *D)
     L.append("  }")
     L.append("};")
     return "\n".join(L) + "\n"
@@ -409,20 +435,23 @@ def emit_inc(tag: str, spec, tab: TPTables, F: Program, Bq: Program, D: Program)
 def generate(tag: str, lib_path: str = HOST_LIB, verbose: bool = True) -> str:
     spec = SPECS[tag]
     tab = TPTables(lib_path, *spec)
-    F, Bq = build_programs(tab)
-    D = build_double_backward(tab)
-    e64 = self_check(tab, F, Bq, np.float64)
-    assert max(e64.values()) < 1e-12, e64
-    d64 = self_check_double(tab, D, np.float64)
-    assert max(d64.values()) < 1e-12, d64
-    if verbose:
-        e32 = self_check(tab, F, Bq, np.float32)
-        d32 = self_check_double(tab, D, np.float32)
-        print(f"[tp {tag}] P={tab.P} terms={len(tab.terms[4])} ops fwd={F.count()['total']} bwd={Bq.count()['total']} "
-              f"second-order={D.count()['total']}")
-        print(f"[tp {tag}] fp64 self-check max|err|/rms: {e64} {d64}")
-        print(f"[tp {tag}] fp32 emulation  max|err|/rms: {e32} {d32}")
-    return emit_inc(tag, spec, tab, F, Bq, D)
+    Bq = build_backward(tab)
+    F, D = [], []
+    for couple in (couple_into,) if in_fp32(tab) else (couple_directly, couple_into):
+        F.append(build_forward(tab, couple))
+        D.append(build_double_backward(tab, couple))
+        e64 = self_check(tab, F[-1], Bq, np.float64)
+        assert max(e64.values()) < 1e-12, e64
+        d64 = self_check_double(tab, D[-1], np.float64)
+        assert max(d64.values()) < 1e-12, d64
+        if verbose:
+            e32 = self_check(tab, F[-1], Bq, np.float32)
+            d32 = self_check_double(tab, D[-1], np.float32)
+            print(f"[tp {tag}] {couple.__name__}: P={tab.P} terms={len(tab.terms[4])} ops fwd={F[-1].count()['total']} "
+                  f"bwd={Bq.count()['total']} second-order={D[-1].count()['total']}")
+            print(f"[tp {tag}] fp64 self-check max|err|/rms: {e64} {d64}")
+            print(f"[tp {tag}] fp32 emulation  max|err|/rms: {e32} {d32}")
+    return emit_inc(tag, spec, tab, (F[0], F[-1]), Bq, (D[0], D[-1]))
 
 
 def main(argv=None) -> int:

@@ -139,7 +139,7 @@ sc_status tp_plan_info(const tp_plan* plan, tp_info* out) {
   out->n_out = plan->n_out;
   out->num_paths = static_cast<int32_t>(plan->paths.size());
   out->specialised = plan->specialised ? 1 : 0;
-  tp::spec_op_counts(plan->specialised, out->ops, out->flops);
+  tp::spec_op_counts(plan, out->ops, out->flops);
   return SC_OK;
 }
 

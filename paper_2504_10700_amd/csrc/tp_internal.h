@@ -100,7 +100,7 @@ hipError_t launch_dh_sum(const tp_plan* plan, const BwdArgs& a, hipStream_t stre
 
 // generated kernels (tp_spec.hip)
 int spec_lookup(const tp_plan* plan);
-void spec_op_counts(int id, int32_t ops[3], int32_t flops[3]);
+void spec_op_counts(const tp_plan* plan, int32_t ops[3], int32_t flops[3]);
 hipError_t launch_spec_forward(const tp_plan* plan, const FwdArgs& a, hipStream_t stream);
 // edges walked by sender: writes dR, the dY partials and dh itself (every atom's row, zero for atoms that send
 // nothing); a.dh_edge receives the edges' receivers (int32), not shares.  Valid for n_in > 0, also without edges.

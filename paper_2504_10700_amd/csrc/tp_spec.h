@@ -6,7 +6,7 @@ namespace tp {
 
 struct SpecEntry {
   int l_Y, l_h, L_max, num_paths;
-  int ops[3], flops[3];   // per (edge, channel): forward, backward, second-order pass
+  const int (*ops)[3], (*flops)[3];   // per (edge, channel): forward, backward, second-order pass; of fp64 rows, of fp32 rows
   hipError_t (*forward)(const tp_plan* plan, const FwdArgs& a, hipStream_t stream);
   hipError_t (*backward)(const tp_plan* plan, const BwdArgs& a, hipStream_t stream);
   hipError_t (*double_backward)(const tp_plan* plan, const DblArgs& a, hipStream_t stream);

@@ -57,10 +57,11 @@ int spec_lookup(const tp_plan* plan) {
 
 int spec_dY_parts(const tp_plan* plan, int64_t n_in) { return entry(plan->specialised).dY_parts(plan, n_in); }
 
-void spec_op_counts(int id, int32_t ops[3], int32_t flops[3]) {
+void spec_op_counts(const tp_plan* plan, int32_t ops[3], int32_t flops[3]) {
+  const int id = plan->specialised, f32 = plan->cfg.dtype == SC_F32;
   for (int i = 0; i < 3; ++i) {
-    ops[i] = id ? entry(id).ops[i] : 0;
-    flops[i] = id ? entry(id).flops[i] : 0;
+    ops[i] = id ? entry(id).ops[f32][i] : 0;
+    flops[i] = id ? entry(id).flops[f32][i] : 0;
   }
 }
 

@@ -34,6 +34,12 @@ __device__ __forceinline__ void end_of_part(const V&... v) {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Do the terms of an edge go into the sums over the edges one by one?  Not for fp64 rows, whose results keep the roundings that this costs: an
+// edge's terms of equal magnitude, and its share of dh, are formed first there.  (Error of fp64 rows, one by one / so, twenty edges,
+// 2-norm, l = 3, l_h = 2: A 5.5e-16 / 4.3e-16, ddA 6.8e-16 / 4.3e-16, dh 3.7e-16 / 2.0e-16.)
+template <typename TS>
+constexpr bool kDirect = sizeof(TS) == 4;
+
 constexpr int kStageStride = kLanes + 1;  // LDS row stride of the dY transpose (odd: two-way conflicts at most)
 
 // A row of N elements at p: 16-byte accesses and a scalar tail.  p is aligned to 16 B if the row size is
@@ -331,7 +337,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       T y[G::kNY], hh[G::kNh];
       y_row.use(Y, e, y);
       widen(h_row, hh);
-      G::forward(y, hh, PathRow<T, TS, G::kP>{r_row}, acc);
+      G::template forward<kDirect<TS>>(y, hh, PathRow<T, TS, G::kP>{r_row}, acc);
     };
     // No request stands under a condition: behind one the compiler waits for all of them, the one just made included, before
     // the arithmetic that is meant to overlap it.  Past the last edge a request repeats its last one, all lanes the same line.
@@ -473,7 +479,16 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       widen(g_row, g);
       widen(h_row[b], hh);
       if (b == 0) stage_is_free();
-      G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, acc[b]);
+      if constexpr (!kDirect<TS> && G::kDhByTerms) {
+        T share[G::kNh];
+#pragma unroll
+        for (int c = 0; c < G::kNh; ++c) share[c] = T(0);
+        G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, share);
+#pragma unroll
+        for (int c = 0; c < G::kNh; ++c) acc[b][c] += share[c];
+      } else {
+        G::backward(y, hh, PathRow<T, TS, G::kP>{r_row}, g, dr, dy, acc[b]);
+      }
       pin_values(acc[b]);
       if (b == kBlocks - 1) lane_sum_store<G::kNY>(stage, lane, dY_partial + (static_cast<size_t>(group) * n_edges + e) * G::kNY);
     };
@@ -610,7 +625,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       widen(h_row, hh);
       widen(hx_row, hx);
       stage_is_free();
-      G::double_backward(y, hy, hh, hx, PathRow<T, TS, G::kP>{r_row}, PathRow<T, TS, G::kP>{hr_row}, g, dda, d2r, d2y, d2h);
+      G::template double_backward<kDirect<TS>>(y, hy, hh, hx, PathRow<T, TS, G::kP>{r_row}, PathRow<T, TS, G::kP>{hr_row}, g, dda, d2r, d2y, d2h);
       pin_values(dda);
       pin_values(d2h);
       if (kFull || lane < chan.live) store_row<TS, T, G::kNh>(d2h_edge + (static_cast<size_t>(e) * K + ch) * G::kNh, d2h);
@@ -822,8 +837,7 @@ struct GeneratedShape {
     return with_instance<G>(p, PartsFn{(p->cfg.num_channels + kLanes - 1) / kLanes, n_in});
   }
   static SpecEntry entry() {
-    return SpecEntry{G::kLY, G::kLh, G::kLout, G::kP, {G::kOps[0], G::kOps[1], G::kOps[2]},
-                     {G::kFlops[0], G::kFlops[1], G::kFlops[2]}, &forward, &backward, &double_backward, &dY_parts};
+    return SpecEntry{G::kLY, G::kLh, G::kLout, G::kP, G::kOps, G::kFlops, &forward, &backward, &double_backward, &dY_parts};
   }
 };
 

@@ -163,6 +163,38 @@ def test_every_generated_shape(tp, l, l_h, dtype, K):
     assert info.specialised == 1
 
 
+# Relative 2-norm error of A, dh and ddA against 80 bits.  A wave of the four has about five edges of an atom; the terms of an edge
+# that have one magnitude, and its share of dh, are summed before they meet the sum over the edges.  Bars: halfway between what that
+# gives on MI355X and the terms one by one (1e-16: 3, 2 2.59 and 3.10, 1.92 and 2.42, 2.78 and 3.86; 2, 2 2.29 and 2.76, 1.90 and 2.15, 2.45
+# and 3.55; 2, 1 2.01 and 2.18, 1.85 and 2.13, 2.14 and 2.73; 3, 3 3.07 and 3.83, 1.95 and 2.44, 3.23 and 4.54).  No rounding depends
+# on anything but the inputs.
+@pytest.mark.parametrize("l,l_h,bars", [(3, 2, (2.84e-16, 2.17e-16, 3.32e-16)), (2, 2, (2.52e-16, 2.02e-16, 3.00e-16)),
+                                        (2, 1, (2.09e-16, 1.99e-16, 2.43e-16)), (3, 3, (3.45e-16, 2.19e-16, 3.88e-16))])
+def test_error_of_the_sums_of_fp64_rows(tp, l, l_h, bars):
+    wl = wl_of("fp64_sums", 40, 20, 64, l, l_h, l, "f64", 5280)
+    inp = workloads.make_tp_inputs(wl, otp.enumerate_paths(oracle_cfg(wl)))
+    run = TPRun(tp, wl, inp)
+    A, dh = run.forward(), run.backward()[1]
+    HY, Hh, HR = workloads.make_tp_cotangents(wl, inp)
+    ddA = run.double_backward(HY, Hh, HR)[0][0]
+    terms = list(zip(*tp.tp_plan_terms(run.plan)))
+    run.close()
+    Y, R, g, HY, HR, h, Hh = (x.astype(np.longdouble) for x in (inp.Y[:, None, :], inp.R.transpose(0, 2, 1), inp.dA[inp.receiver],
+                                                             HY[:, None, :], HR.transpose(0, 2, 1), inp.h[inp.sender], Hh[inp.sender]))
+    message, share, along = (np.zeros(inp.sender.shape + x.shape[1:], np.longdouble) for x in (A, dh, ddA))
+    for p, a, b, c, coef in terms:
+        r, y, x = R[..., p] * np.longdouble(coef), Y[..., a], h[..., b]
+        message[..., c] += r * y * x
+        share[..., b] += r * y * g[..., c]
+        along[..., c] += np.longdouble(coef) * HR[..., p] * y * x + r * (HY[..., a] * x + y * Hh[..., b])
+    for i, (name, got, per_edge, index) in enumerate((("A", A, message, inp.receiver), ("dh", dh, share, inp.sender), ("ddA", ddA, along, inp.receiver))):
+        ref = np.zeros(got.shape, np.longdouble)
+        np.add.at(ref, index, per_edge)
+        err = float(np.sqrt(((got - ref) ** 2).sum() / (ref ** 2).sum()))
+        say(f"l={l} l_h={l_h} {name}: {err:.3e}")
+        assert err <= bars[i]
+
+
 def test_degenerate_graphs(tp):
     # one node without edges; a star (every edge into node 0); a high-degree tail
     full_parity(tp, wl_of("one_node", 1, 3, 128, 3, 1, 3, "f32", 5301))
