@@ -69,12 +69,15 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
  *   X [n_nodes][k_in][(l_max+1)^2]   W_lin [l_max+1][k_in][K]   z [n_nodes] int32   W [Z][num_paths][K]
  *   B [n_nodes][K][n_LM]  (overwritten)
  * For fp32 plans served by the generated 0e+1o kernel with K a multiple of 128 and k_in a multiple
- * of 16, one kernel computes the tile of A on the matrix cores and evaluates the contraction from
- * the accumulators: A is never written (el_sc_is_fused returns 1).  Every other plan, and those batches
- * of these plans for which it is faster and the workspace has the room (up to 2048 atoms; 256 input
- * channels and more), run el_forward into the workspace and then the contraction, with the same result
- * up to rounding.  The size that el_sc_workspace_bytes() gives for 0 atoms always serves these plans.
- * workspace: device memory, 256-byte aligned, at least el_sc_workspace_bytes().  Same conventions
+ * of 16 (el_sc_is_fused returns 1), one kernel computes the tile of A on the matrix cores, by fp32 products, and evaluates
+ * the contraction from the accumulators: A is never written.  Small batches of these plans, where two launches are faster, and
+ * every batch of every other plan run el_forward into the workspace and then the contraction, with the same result up to
+ * rounding.  Small: on 256 compute units n_nodes * K up to 2^18, with fewer than 64 input channels up to 2^17, with a multiple
+ * of 32 from 256 on up to 2^19; up to 2^18 by fp32 products as well, beyond by the bfloat16 parts of el_forward, whose error for
+ * sums of that many channels is the smaller one.
+ * workspace: device memory, 256-byte aligned, at least el_sc_workspace_bytes(): for plans with el_sc_is_fused the same for
+ * every n_nodes (the folded weights, 128 bytes per element and channel, or A of a small batch, at most 32 MB), otherwise room
+ * for A and the contraction's own workspace.  Same conventions
  * as sc_forward (stream, no synchronisation); z is not validated: an index outside 0..Z-1 gives an
  * undefined B row for that atom, never an access outside the buffers.  n_nodes == 0 does nothing. */
 int32_t el_sc_is_fused(const sc_plan* plan, int32_t k_in);

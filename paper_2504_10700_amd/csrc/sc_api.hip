@@ -476,7 +476,7 @@ static sc_status check_layout_flag(const char* fn, const sc_plan* plan, uint32_t
 // Checks of the tensor arguments and the launches of the forward pass, shared by sc_forward and
 // sc_forward_noalloc; the plan's device is current.  direct (generated kernels):
 // one launch whose waves fold their weights themselves; without a grouping ws is not used.  fold_table: that launch also
-// writes the folded table and, if wanted, the grouping, for the backward of the step.  clamp (generated kernels, with
+// writes the folded table and, if wanted, the grouping, for the backward of the step.  clamp (direct, with
 // SC_REUSE_GROUPING): an element index outside the range takes the nearest element's weights.
 static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z,
                                   const void* W, void* B, const sc::Workspace& ws, const sc::LaunchShape& shape,
@@ -490,7 +490,7 @@ static sc_status forward_launches(const char* fn, sc_plan* plan, int64_t n_nodes
   const bool group = !(flags & SC_REUSE_GROUPING);
   // the prepare launch also orders windows of the batch by element for the forward kernel (not for a
   // batch that is ordered already, nor for small ones, where that costs more than it saves)
-  const bool window_order = plan->specialised && !direct && !clamp && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
+  const bool window_order = plan->specialised && !direct && !(flags & SC_Z_GROUPED) && ws.wnode != nullptr &&
                             (n_nodes >= SC_WINDOW_ORDER_MIN_NODES || (plan->cfg.flags & SC_PLAN_WINDOW_ORDER));
   if (plan->specialised && direct) {
     // nothing to prepare
@@ -656,10 +656,10 @@ sc_status sc_double_backward(sc_plan* plan, int64_t n_nodes, const void* A, cons
 
 }  // extern "C"
 
-// sc_forward for a caller that runs no backward pass on this workspace: generated kernels group nothing, so more batches take
-// the one launch.  clamp: see forward_launches.
+// Forward of el_sc_forward, whose caller runs no backward pass on this workspace: generated kernels group nothing, so more batches
+// take the one launch.
 sc_status sc::forward_alone(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B,
-                            void* workspace, size_t workspace_bytes, bool clamp, hipStream_t stream) {
+                            void* workspace, size_t workspace_bytes, hipStream_t stream) {
   sc::LaunchShape shape;
   sc::Workspace ws;
   sc_status st = check_common("el_sc_forward", plan, n_nodes, workspace, workspace_bytes, &shape, &ws);
@@ -668,5 +668,14 @@ sc_status sc::forward_alone(sc_plan* plan, int64_t n_nodes, const void* A, const
   if (!guard.ok) return fail(SC_ERR_HIP, "el_sc_forward: cannot make the plan's device current");
   const bool direct = plan->specialised && !(plan->cfg.flags & SC_PLAN_WINDOW_ORDER) && sc::spec_direct_pays(plan, n_nodes, shape, false);
   return forward_launches("el_sc_forward", plan, n_nodes, A, z, W, B, ws, shape, plan->specialised ? SC_REUSE_GROUPING : 0u,
-                          direct, false, stream, clamp && plan->specialised);
+                          direct, false, stream);
+}
+
+// ... of a plan with generated kernels and a small batch: the one launch, without a workspace, in which an element index outside the
+// range takes the nearest element's weights.
+sc_status sc::forward_clamped(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B, hipStream_t stream) {
+  DeviceGuard guard(plan->cfg.device);
+  if (!guard.ok) return fail(SC_ERR_HIP, "el_sc_forward: cannot make the plan's device current");
+  return forward_launches("el_sc_forward", plan, n_nodes, A, z, W, B, sc::Workspace{}, sc::launch_shape(plan, n_nodes), SC_REUSE_GROUPING,
+                          true, false, stream, true);
 }

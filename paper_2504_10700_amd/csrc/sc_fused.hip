@@ -1,8 +1,8 @@
 // Channel-mixing linear fused into the forward of the symmetric contraction (see include/el.h,
 // el_sc_forward): B = contraction(A, z, W) with A[i,k',(l,m)] = sum_k W_lin[l,k,k'] X[i,k,(l,m)]
 // (Section 4.1 of arXiv 2504.10700: the linear combination of the channels of each order and
-// Algorithm 2 are consecutive steps on the receiving atom).  In the fused kernel A never goes through memory; small batches and
-// long reductions take the two steps through it (two_step_nodes).
+// Algorithm 2 are consecutive steps on the receiving atom).  In the fused kernel A never goes through memory; small batches take
+// the two steps through it (two_step_nodes).
 //
 // The MFMA 16x16x4 result layout puts, for one output channel (column lane%16 of the tile) and
 // four atoms (rows 4*(lane/16)+r), every component (l,m) of A into the registers of one lane:
@@ -145,24 +145,26 @@ sc_status check(const char* fn, const sc_plan* plan, int32_t k_in, int64_t n) {
   return SC_OK;
 }
 
-// The plain product has kernels cut along the reduction (small batches) and ones on the bfloat16 matrix cores (long
-// reductions) that the tile with the contraction behind it has not: the fused kernel takes a lane through all of its eight
-// pairs behind the whole product, 18 to 100 us however small the batch.  So where the fused call is served, the two steps through A
-// are taken as well, for up to 2048 atoms (half of that per 128 channels beyond 256), and from 256 input channels on while
-// A stays within 512 MB.  Forward, us, fused / two steps: 16 -> 128 channels, 1500 atoms 19.4 / 16.8, 2500 19.8 / 20.6; 64 -> 128,
-// 200 26.1 / 10.4, 2000 27.4 / 23.8, 2500 27.6 / 27.8, 3500 28.1 / 32.2; 128 -> 128, 200 35.9 / 12.0, 2000 38.2 / 29.6, 2500
-// 38.0 / 32.8, 4000 39.4 / 41.6, 10 000 74.1 / 85.8, 20 000 144 / 148; 64 -> 256, 1500 37.6 / 28.4, 2500 40.7 / 40.6; 256 -> 256, 200
-// 60.7 / 17, 2500 89.6 / 74.8, 7000 152 / 159, 10 000 234 / 206, 50 000 1080 / 965; 256 -> 128, 5000 90 / 76, 10 000 120 / 122; 512 -> 128,
-// 2500 102 / 66, 20 000 435 / 333.
-int64_t two_step_nodes(const sc_plan* plan, int32_t k_in) {   // up to so many atoms
-  const int64_t K = plan->cfg.num_channels;
-  return k_in >= 256 ? (int64_t(1) << 23) / K : std::min<int64_t>(2048, (int64_t(1) << 19) / K);
+// Up to how many atoms are the two steps through A taken where the fused kernel serves the plan?  The fused kernel takes a lane through all of its
+// eight pairs behind the whole product, 17 us and more however small the batch.
+// Up to four workgroups (16 atoms x 16 columns) per CU the plain product has a kernel cut along the reduction, with fp32 products like the fused
+// one's; it and one launch of the contraction are faster that far from 64 input channels on, with fewer, where the fused kernel's product is
+// short, half as far.  From 256 input channels on the kernels on bfloat16 parts make it twice as far; beyond that the contraction
+// would want the folded weights in a launch of their own and A more memory than the gain is worth.
+//
+// Forward, us, fused / two steps:
+//    64 -> 128 channels, 2048 atoms 36.5 / 25.8     128 -> 128, 2048 52.0 / 31.7     64 -> 384, 672 30.3 / 27.4     64 -> 2048, 128 46.0 / 29.0
+//    16 -> 128, 1024 24.6 / 15.1, 1300 18.1 / 18.1, 1800 18.3 / 22.9     32 -> 128, 1800 20.6 / 22.4     16 -> 384, 336 20.3 / 15.1, 672 21.9 / 23.9
+//    256 -> 128, 2500 59.3 / 43.8, 4096 87.8 / 53.1     512 -> 128, 2304 152 / 65     256 -> 256, 1500 88.0 / 45.2, 2048 91.6 / 52.8
+int64_t two_step_nodes(const sc_plan* plan, int32_t k_in) {
+  const int64_t columns = plan->cfg.num_channels / 16;
+  const int per_cu = k_in >= 256 && k_in % 32 == 0 ? 8 : k_in >= 64 ? 4 : 2;
+  return per_cu * static_cast<int64_t>(plan->num_cus) / columns * 16;
 }
-sc_status two_step_bytes(const sc_plan* plan, int64_t n, size_t* bytes) {
-  size_t inner = 0;
-  const sc_status st = sc_workspace_bytes(plan, n, &inner);
-  if (st == SC_OK) *bytes = a_bytes(plan, n) + round256(inner) + 256;
-  return st;
+// Workspace of the plans that the fused kernel serves: its table or A of the two steps.  The same for every batch, so that neither the
+// way of a batch nor the bits of B depend on the batch that the workspace was asked for (A: 32 MB at most).
+size_t fused_bytes(const sc_plan* plan, int32_t k_in) {
+  return std::max(fold_table_bytes(plan), a_bytes(plan, two_step_nodes(plan, k_in))) + 256;
 }
 
 el_config linear_config(const sc_plan* plan, int32_t k_in) {
@@ -190,11 +192,15 @@ sc_status el_sc_workspace_bytes(const sc_plan* plan, int32_t k_in, int64_t n_nod
   sc_status st = check("el_sc_workspace_bytes", plan, k_in, n_nodes);
   if (st != SC_OK) return st;
   if (!bytes) return set_error(SC_ERR_INVALID_ARG, "el_sc_workspace_bytes: bytes is NULL");
-  if (!fused_ok(plan, k_in)) return two_step_bytes(plan, n_nodes, bytes);
-  // room for either way, for this batch and smaller ones
-  st = two_step_bytes(plan, std::min<int64_t>(n_nodes, two_step_nodes(plan, k_in)), bytes);
-  *bytes = std::max(*bytes, fold_table_bytes(plan) + 256);
-  return st;
+  if (fused_ok(plan, k_in)) {
+    *bytes = fused_bytes(plan, k_in);
+    return SC_OK;
+  }
+  size_t inner = 0;
+  st = sc_workspace_bytes(plan, n_nodes, &inner);
+  if (st != SC_OK) return st;
+  *bytes = a_bytes(plan, n_nodes) + round256(inner) + 256;
+  return SC_OK;
 }
 
 sc_status el_sc_forward(sc_plan* plan, int32_t k_in, int64_t n_nodes, const void* X, const void* W_lin,
@@ -207,28 +213,23 @@ sc_status el_sc_forward(sc_plan* plan, int32_t k_in, int64_t n_nodes, const void
   if (!X || !W_lin || !z || !W || !B) return set_error(SC_ERR_INVALID_ARG, "el_sc_forward: NULL tensor argument");
   if (misaligned(X, 16) || misaligned(W_lin, 16) || misaligned(W, 16) || misaligned(B, 16) || misaligned(z, 4))
     return set_error(SC_ERR_INVALID_ARG, "el_sc_forward: tensor pointer not aligned (16 bytes, z: 4)");
-  const bool fused = fused_ok(plan, k_in);
-  bool two_steps = !fused || n_nodes <= two_step_nodes(plan, k_in);
-  size_t need = fold_table_bytes(plan) + 256;
-  if (two_steps) {
-    size_t two = 0;
-    st = two_step_bytes(plan, n_nodes, &two);
-    if (st != SC_OK) return st;
-    if (!fused) need = two;
-    else two_steps = workspace_bytes >= two;   // one without room for A, as for larger batches: the fused kernel
-  }
+  size_t need = 0;
+  st = el_sc_workspace_bytes(plan, k_in, n_nodes, &need);
+  if (st != SC_OK) return st;
   if (!workspace || workspace_bytes < need)
     return set_error(SC_ERR_WORKSPACE, "el_sc_forward: workspace missing or smaller than el_sc_workspace_bytes()");
   if (misaligned(workspace, 256)) return set_error(SC_ERR_WORKSPACE, "el_sc_forward: workspace not 256-byte aligned");
 
-  if (two_steps) {
+  const bool fused = fused_ok(plan, k_in);
+  if (!fused || n_nodes <= two_step_nodes(plan, k_in)) {
     // Two steps through A in the workspace: the linear, then the contraction.
     const el_config lc = linear_config(plan, k_in);
     st = el_forward(&lc, n_nodes, X, W_lin, workspace, hip_stream);
     if (st != SC_OK) return st;
+    if (fused) return forward_clamped(plan, n_nodes, workspace, z, W, B, static_cast<hipStream_t>(hip_stream));
     const size_t off = a_bytes(plan, n_nodes);
     return forward_alone(plan, n_nodes, workspace, z, W, B, static_cast<char*>(workspace) + off, workspace_bytes - off,
-                         fused /* whose kernel clamps the indices */, static_cast<hipStream_t>(hip_stream));
+                         static_cast<hipStream_t>(hip_stream));
   }
 
   DeviceGuard guard(plan->cfg.device);

@@ -108,7 +108,8 @@ sc_status set_error(sc_status code, const std::string& msg);
 
 LaunchShape launch_shape(const sc_plan* plan, int64_t n_nodes);
 sc_status forward_alone(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B,
-                        void* workspace, size_t workspace_bytes, bool clamp, hipStream_t stream);
+                        void* workspace, size_t workspace_bytes, hipStream_t stream);
+sc_status forward_clamped(sc_plan* plan, int64_t n_nodes, const void* A, const int32_t* z, const void* W, void* B, hipStream_t stream);
 // forward_only: the part the forward pass alone uses: no weight-gradient rows and, for the generated kernels, whose forward
 // needs no grouping, no tiles.
 Workspace carve_workspace(const sc_plan* plan, int64_t n_nodes, const LaunchShape& shape, void* base,

@@ -70,8 +70,8 @@ hipError_t launch_spec_group(const sc_plan* plan, int64_t n, const int32_t* z, c
                              const LaunchShape& shape, bool table_only, bool fold, hipStream_t stream);
 // Forward over the nodes in natural order from ws.wfold, or (direct) with weights that every wave
 // folds from W by itself; group: the second half of the grouping
-// rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only, 3 no, and an element index outside the
-// range takes the nearest element's weights instead of leaving its row of B; without window_order); with direct its
+// rides in the same launch (0 no, 1 permutation + tile table, 2 tile table only; with direct also 3: no, and an element index
+// outside the range takes the nearest element's weights instead of leaving its row of B); with direct its
 // roles need no prepare launch, and fold_table: the launch also writes ws.wfold.
 // component_major: the per-node tensors are laid out [node][component][channel]
 // (SC_COMPONENT_MAJOR; plans whose rows are stored in the arithmetic type only).

@@ -131,7 +131,7 @@ hipError_t launch_spec_scatter(const sc_plan* plan, int64_t n, const int32_t* z,
 hipError_t launch_spec_forward(const sc_plan* plan, int64_t n, const void* A, const int32_t* z, const void* W, void* B,
                                const Workspace& ws, const LaunchShape& shape, int group, bool window_order,
                                bool component_major, bool direct, bool fold_table, hipStream_t stream) {
-  if ((group == 1 || group == 2) && !ws.tiles) return hipErrorInvalidValue;
+  if (((group == 1 || group == 2) && !ws.tiles) || (group == 3 && !direct)) return hipErrorInvalidValue;
   return entry_of(plan->specialised)->forward(plan, n, A, z, W, B, ws, shape, group, window_order && ws.wnode && ws.wkey,
                                               component_major, direct, fold_table, stream);
 }

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kSpecThreads) void spec_forward_kernel(const int32_
                                                                     TS* __restrict__ B, SplitGroupArgs ga) {
   extern __shared__ unsigned char lds_raw[];
   int block = blockIdx.x;
-  const bool clamp = fold_wgs < 0;   // (a word of its own would be one of the first 14 too many)
+  const bool clamp = kDirect && fold_wgs < 0;   // (a word of its own would be one of the first 14 too many)
   if constexpr (kDirect) {   // no launch came before: the roles count for themselves, the fold role is here
     if (block < scatter_wgs + table) {
       int32_t* counts = reinterpret_cast<int32_t*>(lds_raw) + split_group_lds_bytes(Z) / sizeof(int32_t);
@@ -967,7 +967,7 @@ hipError_t fwd_launch(const sc_plan* plan, int64_t n, const void* A, const int32
     if (roles > lds) lds = roles;
   }
   constexpr int kPairs = kSpecWaves / direct_fold_waves<G>();   // a workgroup of the fold role
-  const bool clamp = group == 3;   // given as fold_wgs = -1: no such workgroups then
+  const bool clamp = kDirect && group == 3;   // given as fold_wgs = -1: no such workgroups then
   const int fold_wgs = kDirect && fold_table && !clamp ? (plan->cfg.num_elements * shape.chblocks + kPairs - 1) / kPairs : 0;
   static const int wgs_per_cu = [] {   // resident workgroups per compute unit of this instance
     int nb = 0;
