@@ -55,6 +55,8 @@ sc_status el_workspace_bytes(const el_config* cfg, int64_t n_nodes, size_t* byte
  *   dW [l_max+1][K_in][K_out]       = sum over atoms and m of X[.,k,.] dY[.,k',.]   (overwritten)
  * workspace: device memory, 256-byte aligned, at least el_workspace_bytes().  dW is summed in a
  * fixed order (per range of atoms, then over the ranges): bitwise reproducible.
+ * dX may be the buffer of X itself if K_in and K_out are multiples of 64 (dW is then summed before dX is written); apart from
+ * that the outputs share no memory with the inputs.
  * n_nodes == 0 zeroes dW. */
 sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, const void* W, const void* dY, void* dX,
                       void* dW, void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -1068,6 +1068,18 @@ hipError_t together_t(const el_config* cfg, int64_t n, const void* X, const void
   }
 }
 
+// Does an output lie on an input?  With two launches dX may take X's place (tiled channel counts: dW has been summed over X by then), and dW that
+// of W where the launch of dX reads W transposed; in one launch the workgroups that write either run beside those that still read.
+bool written_in_place(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, const void* dX, const void* dW) {
+  const size_t row = static_cast<size_t>(n) * (cfg->l_max + 1) * (cfg->l_max + 1) * elem_size(cfg);
+  const size_t x = row * cfg->k_in, y = row * cfg->k_out, w = static_cast<size_t>(cfg->l_max + 1) * cfg->k_in * cfg->k_out * elem_size(cfg);
+  auto overlap = [](const void* p, size_t p_bytes, const void* q, size_t q_bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + q_bytes && b < a + p_bytes;
+  };
+  return overlap(dX, x, X, x) || overlap(dX, x, W, w) || overlap(dX, x, dY, y) || overlap(dW, w, X, x) || overlap(dW, w, W, w) || overlap(dW, w, dY, y);
+}
+
 // Workspace: [ W transposed, rounded up to 256 bytes ][ partial dW per range of atoms ].
 size_t wt_bytes(const el_config* cfg) {
   if (!mfma_forward_ok(cfg->k_out, cfg->k_in)) return 0;   // split_forward_kernel reads W as it is
@@ -1095,7 +1107,7 @@ size_t workspace_bytes(const el_config* cfg, int64_t n) {
 template <typename T>
 hipError_t backward_t(const el_config* cfg, int64_t n, const void* X, const void* W, const void* dY, void* dX, void* dW, void* ws,
                       hipStream_t stream) {
-  if (backward_together(cfg, n)) return together_t<T>(cfg, n, X, W, dY, dX, dW, stream);
+  if (backward_together(cfg, n) && !written_in_place(cfg, n, X, W, dY, dX, dW)) return together_t<T>(cfg, n, X, W, dY, dX, dW, stream);
   const bool transposed = mfma_forward_ok(cfg->k_out, cfg->k_in) && !dx_reads_w_as_is(n, cfg->k_in) && !dx_parts_read_w_as_is(cfg, n);
   Transpose<T> tr{static_cast<const T*>(W), static_cast<T*>(ws), cfg->l_max + 1, cfg->k_in, cfg->k_out, 0};
   if (transposed) {                            // about a thousand elements a workgroup

@@ -354,6 +354,27 @@ def test_backward_of_small_batches_in_one_launch(el, N, k_in, k_out, l_max, dtyp
     run_case(el, N, k_in, k_out, l_max, dtype, 8700 + N + k_in)
 
 
+# dX in the buffer of X, around the batches that have dX and dW in one launch otherwise; W's buffer as that of dW where the launch of
+# dX reads W transposed (more than a workgroup of 16 atoms x 16 columns per compute unit).
+@pytest.mark.parametrize("N,k_in,k_out,l_max,dtype,over_w", [
+    (1, 64, 64, 3, "f32", False), (40, 128, 128, 3, "f32", False), (333, 128, 64, 3, "f32", False), (449, 128, 128, 3, "f32", False),
+    (300, 64, 128, 1, "f64", False), (440, 256, 64, 3, "f32", True), (310, 256, 64, 2, "f64", True)])
+def test_backward_in_place(el, N, k_in, k_out, l_max, dtype, over_w):
+    import torch
+    print(f"case N={N} k_in={k_in} k_out={k_out} l_max={l_max} {dtype} in place", flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    X, W, dY = (torch.tensor(x, dtype=tdt, device="cuda:0") for x in workloads.make_linear_inputs(N, k_in, k_out, l_max, 8990 + N))
+    dX_ref, dW_ref = oel.backward(*(x.double().cpu().numpy() for x in (X, W, dY)))
+    cfg = el.make_config(k_in, k_out, l_max, el.SC_F32 if dtype == "f32" else el.SC_F64)
+    nbytes = el.el_workspace_bytes(cfg, N)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+    dW = W if over_w else torch.full_like(W, float("nan"))
+    el.el_backward(cfg, N, X, W, dY, X, dW, ws, nbytes)
+    torch.cuda.synchronize()
+    check("dX", X.cpu().numpy(), dX_ref, dtype)
+    check("dW", dW.cpu().numpy(), dW_ref, dtype)
+
+
 def test_infinite_row_at_the_end_of_a_range(el):
     import torch
     N, K = 5, 128
