@@ -420,12 +420,12 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
   };
   auto atom = [&](int r) { return static_cast<size_t>(r < 0 ? 0 : (r >= n_out_nodes ? n_out_nodes - 1 : r)); };
   const int q0 = uniform(pos(send_ptr[node])) + wave, q1 = uniform(pos(send_ptr[node + 1]));
-  // The i-th edge of this wave and its receiver, asked for in order (past the last edge: that one again).  kSearch: 64 of
-  // them at a time, one a lane, the receiver by bisection of the rows in LDS.
+  // The edge at position q of this wave's (q0, q0 + kWaves, ...) and its receiver; past the last one any edge of the list.  kSearch: asked for
+  // in order, 64 of them at a time, one a lane, the receiver by bisection of the rows in LDS.
   int my_e = 0, my_r = 0;
-  auto next_edge = [&](int i, int& e, int& r) {
-    const int last = (q1 - 1 - q0) / kWaves;
+  auto next_edge = [&](int q, int& e, int& r) {
     if constexpr (kSearch) {
+      const int i = static_cast<int>(static_cast<unsigned>(q - q0) / kWaves), last = (q1 - 1 - q0) / kWaves;
       if ((i & (kLanes - 1)) == 0) {
         my_e = edge(q0 + (i + lane < last ? i + lane : last) * kWaves);
         my_r = 0;
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       e = __builtin_amdgcn_readlane(my_e, i & (kLanes - 1));
       r = __builtin_amdgcn_readlane(my_r, i & (kLanes - 1));
     } else {
-      e = uniform(edge(q0 + (i < last ? i : last) * kWaves));
+      e = uniform(edge(q < q1 ? q : q0));
       r = uniform(receiver[e]);
     }
   };
@@ -455,6 +455,10 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
     TS h_row[kBlocks][G::kNh];
 #pragma unroll
     for (int b = 0; b < kBlocks; ++b) load_row<TS, G::kNh>(h + (node * K + chan[b].ch) * G::kNh, h_row[b]);
+    // One block: the row widened once.  (As with two, per edge, it takes registers: l = 3, l_h = 1 in fp32 130 for 126, of the 128 that four waves
+    // per SIMD have.  us, per edge / once, 64 channels, 8000 atoms 192.3 / 189.7; fp64 rows, l_h = 0, 128 channels, 5000 atoms 327.6 / 319.8.)
+    T h_one[G::kNh];
+    if constexpr (kBlocks == 1) widen(h_row[0], h_one);
     TS r0[G::kP], g0[G::kNout];
     UniformRow<T, TS, G::kNY> y0;
     auto load_rows = [&](int e, int receiving, int ch, TS (&r_row)[G::kP], TS (&g_row)[G::kNout]) {
@@ -462,12 +466,12 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       load_row<TS, G::kNout>(dA + (atom(receiving) * K + ch) * G::kNout, g_row);
     };
     int ea, ra;
-    next_edge(0, ea, ra);
+    next_edge(q0, ea, ra);
     y0.request(Y, ea, lane);
     load_rows(ea, ra, chan[0].ch, r0, g0);
     // edge id and receiver of the edge after the current one, read one step ahead of its rows
-    int i = 1, en, rn;
-    next_edge(i, en, rn);
+    int en, rn;
+    next_edge(q0 + kWaves, en, rn);
 
     // One edge and channel block: arithmetic, dR row stores, dh added up; with the last block dY summed over the 64 lanes in a fixed order.
     auto finish_block = [&](auto block, int e, const T (&y)[G::kNY], const TS (&r_row)[G::kP], const TS (&g_row)[G::kNout]) {
@@ -477,9 +481,16 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
       const PathStore<kFull, T, TS> dr{dR + static_cast<size_t>(e) * G::kP * K + chan[b].ch, static_cast<size_t>(K), live};
       const StageStore<kFull, (b > 0), T> dy{stage + lane, live};
       widen(g_row, g);
-      widen(h_row[b], hh);
+      if constexpr (kBlocks == 1) {
+#pragma unroll
+        for (int c = 0; c < G::kNh; ++c) hh[c] = h_one[c];
+      } else {
+        widen(h_row[b], hh);
+      }
       if (b == 0) stage_is_free();
-      if constexpr (!kDirect<TS> && G::kDhByTerms) {
+      // (fp32 rows, one ragged block, 17 paths and more: term by term 1 to 3% slower; 96 channels, l_h = 2, 900 atoms 111.4 / 108.2 us.  Full blocks the
+      // other way: 64 channels, l = 2, l_h = 2, 3000 atoms 93 / 105.)
+      if constexpr ((!kDirect<TS> || (kBlocks == 1 && !kFull && G::kP >= 17)) && G::kDhByTerms) {
         T share[G::kNh];
 #pragma unroll
         for (int c = 0; c < G::kNh; ++c) share[c] = T(0);
@@ -516,7 +527,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
         y0.request(Y, en, lane);
         load_rows(en, rn, q + kWaves < q1 ? chan[0].ch : chan[0].first, r0, g0);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kSearch) next_edge(++i, e2, r2);
+        if constexpr (kSearch) next_edge(q + 2 * kWaves, e2, r2);
         else r2 = uniform(receiver[e2]);
         finish_block(last, ea, y, r1, g1);
         ea = en;
@@ -531,7 +542,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
           ea = en;
           y0.request(Y, ea, lane);
           load_rows(ea, rn, chan[0].ch, r0, g0);
-          if (q + 2 * kWaves < q1) next_edge(++i, en, rn);
+          if (q + 2 * kWaves < q1) next_edge(q + 2 * kWaves, en, rn);
         }
       }
     } else {
@@ -543,7 +554,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
           eb = en;
           y1.request(Y, eb, lane);
           load_rows(eb, rn, chan[0].ch, r1, g1);
-          if (q + 2 * kWaves < q1) next_edge(++i, en, rn);
+          if (q + 2 * kWaves < q1) next_edge(q + 2 * kWaves, en, rn);
         }
         finish_edge(ea, y0, r0, g0);
         if (q + kWaves < q1) {
@@ -551,7 +562,7 @@ __global__ __launch_bounds__(kWaves * kLanes) __attribute__((amdgpu_waves_per_eu
             ea = en;
             y0.request(Y, ea, lane);
             load_rows(ea, rn, chan[0].ch, r0, g0);
-            if (q + 3 * kWaves < q1) next_edge(++i, en, rn);
+            if (q + 3 * kWaves < q1) next_edge(q + 3 * kWaves, en, rn);
           }
           finish_edge(eb, y1, r1, g1);
         }
