@@ -697,30 +697,45 @@ int waves_per_unit(int64_t n_edges, int64_t n_atoms, int64_t n_units) {
   return n_edges <= 3 * n_atoms && n_units >= 8192 ? 2 : 4;
 }
 
-// Channel blocks of an atom that a workgroup of the backward walks together (2: their shares of dY are added in the lanes, one sum over the lanes
-// serves both, and with two blocks in all it is dY: no shares through memory, no launch that adds them), and up to how many workgroups eight waves share the edges, so
-// that a small graph has as many waves as with a workgroup per block.  Backward with the sum of the shares, us, a workgroup per block / for two, four waves / eight, 128
-// channels: fp32 arithmetic, l_h = 1, 60 atoms 16.8 / 20.6 / 14.0, 250 24.4 / 26.9 / 19.5, 1000 43.5 / 45.5 / 41.6, 2000 78.6 / 80.0 / 76.0, 10 000 458.7 / 451.5
-// / 465.9; l_h = 0, 250 16.8 / 15.5 / 10.4; fp64 arithmetic, l = 2, l_h = 1, 250 21.5 / 20.2 / 16.6, 1000 39.9 / 33.2 / 32.9, 4000 140.7 / 127.3 / 134.7; l_h = 2, 250 27.1 / 27.2 /
-// 23.7, 1000 63.1 / 56.4 / 64.1; 96 channels, l_h = 1, 250 30.0 / 31.8 / 25.7, 2000
-// 124.3 / 102.2 / 130.7.  17 paths: fp32 rows (255 registers) 250 40.2 / 47.5 / 42.9, 1000 104.9 / 106.2 / 113.5, 3001 311.7 / 299.8; fp64 rows (which then spill) 1000 169
-// / 237 / 253.
-// fp64 rows are bound by what a compute unit takes in (12 KB per edge and block): half the workgroups leave units idle or make a
-// last round longer.  Four waves, us, a workgroup per block / for two: l_h = 0, 42 atoms 15.7 / 19.2, 250 25.2 / 26.0, 500 39.2 / 34.4, 700 47.9 / 48.9, 3000 188.5 /
-// 190.3; l_h = 1, 42 20.7 / 25.2, 250 36.1 / 35.3, 330 45.6 / 50.8, 1000 88.9 / 87.1, 1500 171.2 / 171.1, 3000 319 / 311, 6000 623 / 599; 96 channels, whose second
-// block moves half the bytes, 250 26.3 / 25.5, 400 34.0 / 29.6, 1500 81.4 / 71.6, 6000 358 / 312.
-// With more than two blocks the shares are added up all the same.  256 channels, us: fp32 arithmetic, l_h = 1, 127 atoms 22.5 / 22.1, 500 46.2 / 47.2,
-// 1000 80.6 / 84.4, 3000 286.7 / 286.2; l_h = 0, 330 24.2 / 26.3, 1500 56.7 / 58.1; fp64 arithmetic, l_h = 1, 330 31.2 / 33.1, 1500 98.3 / 89.6, 3000 212.5 /
-// 200.9; fp64 rows, l_h = 1, 330 76.4 / 82.6, 1500 316.7 / 316.3.
+// Channel blocks of an atom that a workgroup of the backward walks together.  Two: their shares of dY are added in the lanes, one sum over the
+// lanes serves both, and with two blocks in all it is dY (no shares through memory, no launch that adds them).  But half the workgroups, so small
+// graphs have eight waves share the edges, and a second row in registers.  Backward with the sum of the shares, us; 128 channels, one / two
+// / two and eight waves:
+//   l = 3, l_h = 1, fp32      60 atoms 16.8 / 20.6 / 14.0   250 24.4 / 26.9 / 19.5   1000 43.5 / 45.5 / 41.6   2000 78.6 / 80.0 / 76.0
+//                             2060 109.1 / 111.6   2700 138.6 / 140.6   4500 221.4 / 221.4   5000 243.3 / 241.8   10 000 466 / 460 / 473
+//   l = 3, l_h = 0, fp32      250 16.8 / 15.5 / 10.4   2700 83.1 / 82.3   4000 114.5 / 115.3   9000 240 / 237
+//   fp32 rows in fp64 arithmetic (their shares of dY as fp64 are summed once):
+//   l = 2, l_h = 1            250 21.5 / 20.2 / 16.6   1000 39.9 / 33.2 / 32.9   4000 140.7 / 127.3 / 134.7
+//   l = 2, l_h = 2            250 27.1 / 27.2 / 23.7   1000 63.1 / 56.4 / 64.1   3000 191 / 175
+//   96 channels, l_h = 1      250 30.0 / 31.8 / 25.7   2000 124.3 / 102.2 / 130.7
+//   17 paths (255 registers)  250 40.2 / 47.5 / 42.9   1000 104.9 / 106.2 / 113.5   3001 315 / 305   23 paths 2100 421 / 390   3001 579 / 546
+//   96 channels, 17 paths     900 108 / 113   1300 150 / 147   1755 196 / 186   23 paths 1000 224 / 229   1700 371 / 366
+// fp64 rows are bound by what a compute unit takes in (12 KB per edge and block), and 17 paths spill: two only where the second block is half empty
+// or the shares of dY are long:
+//   l = 3, l_h = 1            330 45.6 / 50.8   1100 132.8 / 137   1800 206.5 / 205   3000 327.9 / 323.1   4500 482 / 466
+//   l = 3, l_h = 0            42 15.7 / 19.2   250 25.2 / 26.0   700 47.9 / 48.9   3000 188.5 / 190.3
+//   l = 2, l_h = 1, 1500      109.4 / 113.3   2500 172.5 / 174.9   4000 268.8 / 269.7     l = 2, l_h = 2, 2000 210.4 / 214.0   3500 357.2 / 356.8
+//   96 channels, l_h = 1      250 26.3 / 25.5   400 34.0 / 29.6   1500 81.4 / 71.6   3000 315 / 272
+// With more than two blocks the shares are added up all the same; 256 channels:
+//   l_h = 1, fp32             127 22.5 / 22.1   500 46.2 / 47.2   1000 80.6 / 84.4   3000 286.7 / 286.2
+//   l = 2, l_h = 1            330 31.2 / 33.1   1500 98.3 / 89.6   3000 212.5 / 200.9      17 paths 1100 236 / 232   1500 316 / 306   23 paths 1100 416 / 402
+//   fp64 rows, l_h = 1        330 76.4 / 82.6   1500 316.7 / 316.3
 template <typename T, typename TS, typename G, bool kFull>
-bool two_blocks(int chblocks, int64_t n_in) {
-  if (chblocks % 2 != 0) return false;
-  if (sizeof(TS) == 8) return chblocks == 2 && G::kP < 17 && (kFull ? G::kNh > 1 && n_in >= 1024 : n_in >= 384);
-  if (chblocks > 2) return sizeof(T) == 8 && n_in * (chblocks / 2) > 2048;
-  return sizeof(T) == 4 || G::kP < 17 || n_in >= 2048;
-}
-template <typename T, typename TS>
-constexpr int64_t kEightWaves = sizeof(TS) == 8 ? 0 : sizeof(T) == 4 ? 2048 : 512;
+struct BackwardBlocks {
+  static constexpr bool kSingle = sizeof(T) == 4, kRows64 = sizeof(TS) == 8, kManyPaths = G::kP >= 17;
+  // Are there workgroups of two blocks, some whose edges find their receivers themselves (receivers_by_search: small graphs), and some of eight
+  // waves, up to how many workgroups?
+  static constexpr bool kTwo = !kRows64 || (!kManyPaths && (!kFull || (G::kNY == 16 && G::kNh > 1)));
+  static constexpr bool kTwoSearch = kTwo && (kRows64 ? !kFull : !kManyPaths);
+  static constexpr int64_t kEightWaves = kRows64 || kManyPaths ? 0 : kSingle ? 2048 : 512;
+  static bool two(int chblocks, int64_t n_in) {
+    if (!kTwo || chblocks % 2 != 0) return false;
+    if (kRows64) return chblocks == 2 && n_in >= (kFull ? 1792 : 384);
+    if (chblocks > 2) return !kSingle && n_in * (chblocks / 2) > 2048;
+    if (kSingle) return G::kNh == 1 || n_in <= kEightWaves || n_in > 4608;
+    return !kManyPaths || n_in >= (kFull ? 2048 : 1280);
+  }
+};
 
 // Do the workgroups of the backward search for receivers?  It saves the launch that writes every edge's receiver and costs each workgroup the rows
 // in LDS and about ten reads there per 64 edges of a wave, so it pays up to a number of workgroups.  Receivers and backward, us, with the launch /
@@ -754,11 +769,12 @@ struct Launch {
     });
   }
 
+  typedef BackwardBlocks<T, TS, G, kFull> Blocks;
   static hipError_t backward(const tp_plan* plan, const BwdArgs& a, hipStream_t stream) {
     const int K = plan->cfg.num_channels, chblocks = (K + kLanes - 1) / kLanes;
     const int groups = a.dY_parts, blocks = chblocks / groups;
     const int64_t n_units = a.n_in * groups;
-    const bool search = receivers_by_search(a.n_out_nodes, n_units);
+    const bool search = receivers_by_search(a.n_out_nodes, n_units) && (blocks == 1 || Blocks::kTwoSearch);
     int32_t* receiver = static_cast<int32_t*>(a.dh_edge);   // the shares' part of the workspace is free on this path
     if (a.n_edges > 0 && a.n_out_nodes > 0 && !search) {
       hipLaunchKernelGGL(edge_receiver_kernel, dim3(static_cast<unsigned>((a.n_out_nodes + 255) / 256)), dim3(256), 0,
@@ -769,13 +785,17 @@ struct Launch {
     int waves = search ? 4 : waves_per_unit(a.n_edges, a.n_in, a.n_in * chblocks);
     auto kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1, true>
                 : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 1, false> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 1, false>;
-    if (blocks == 2) {
-      kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, true>
-             : waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, false> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2, false>;
-      if constexpr (kEightWaves<T, TS> > 0) {
-        if (n_units <= kEightWaves<T, TS> && a.n_edges > 4 * a.n_in) {
-          waves = 8;
-          kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, true> : &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, false>;
+    if constexpr (Blocks::kTwo) {
+      if (blocks == 2) {
+        kernel = waves == 4 ? &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, false> : &backward_by_sender_kernel<T, TS, G, kFull, 2, 2, false>;
+        if constexpr (Blocks::kTwoSearch) {
+          if (search) kernel = &backward_by_sender_kernel<T, TS, G, kFull, 4, 2, true>;
+        }
+        if constexpr (Blocks::kEightWaves > 0) {
+          if (n_units <= Blocks::kEightWaves && a.n_edges > 4 * a.n_in) {
+            waves = 8;
+            kernel = search ? &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, true> : &backward_by_sender_kernel<T, TS, G, kFull, 8, 2, false>;
+          }
         }
       }
     }
@@ -789,7 +809,7 @@ struct Launch {
     });
   }
 
-  static int dY_parts(int chblocks, int64_t n_in) { return two_blocks<T, TS, G, kFull>(chblocks, n_in) ? chblocks / 2 : chblocks; }
+  static int dY_parts(int chblocks, int64_t n_in) { return Blocks::two(chblocks, n_in) ? chblocks / 2 : chblocks; }
 
   static hipError_t double_backward(const tp_plan* plan, const DblArgs& d, hipStream_t stream) {
     const BwdArgs& a = d.b;

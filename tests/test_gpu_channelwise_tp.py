@@ -405,11 +405,15 @@ def test_edges_shared_by_two_waves(tp, N, mean_degree, K, l, l_h, dtype):
 
 
 @pytest.mark.parametrize("N,mean_degree,K,l,l_h,dtype", [
-    (300, 8, 128, 3, 1, "f32"), (300, 3, 128, 3, 1, "f32"), (2100, 5, 128, 3, 1, "f32"),   # eight waves, four of few edges, four
+    (300, 8, 128, 3, 1, "f32"), (300, 3, 128, 3, 1, "f32"), (2100, 5, 128, 3, 1, "f32"),   # eight waves, four of few edges, a block
     (150, 7, 96, 3, 1, "f32"), (60, 6, 256, 3, 0, "f32"), (30, 9, 224, 2, 1, "f32"),       # a ragged block; two shares of dY; both
-    (520, 5, 128, 2, 2, "f64"), (200, 6, 128, 3, 1, "f64"),
-    (1030, 4, 128, 2, 1, "f64"), (390, 5, 96, 3, 0, "f64"), (1030, 3, 256, 2, 1, "f32"),   # from 1024 atoms on; 384; 2048 workgroups
-    (2100, 2, 128, 3, 2, "f32"), (300, 6, 128, 3, 2, "f32"), (100, 6, 128, 3, 2, "f64")])  # 17 paths: large graphs of fp32 rows only
+    (520, 5, 128, 2, 2, "f64"), (200, 6, 128, 3, 1, "f64"), (1030, 4, 128, 2, 1, "f64"),   # a block of fp64 rows
+    (390, 5, 96, 3, 0, "f64"), (1030, 3, 256, 2, 1, "f32"),                                # from 384 atoms on; 2048 workgroups
+    (2100, 2, 128, 3, 2, "f32"), (300, 6, 128, 3, 2, "f32"), (100, 6, 128, 3, 2, "f64"),   # 17 paths: large graphs of fp32 rows only
+    (1030, 3, 96, 2, 2, "f64"), (1791, 3, 128, 3, 1, "f64"), (1792, 3, 128, 3, 1, "f64"),  # fp64 rows beyond the searched receivers
+    (4608, 2, 128, 3, 1, "f32"), (4609, 4, 128, 3, 1, "f32"),                              # fp32 arithmetic beyond eight waves
+    (2100, 2, 128, 3, 3, "f32"), (1279, 2, 96, 3, 2, "f32"), (1280, 2, 96, 3, 2, "f32"),   # 23 paths, ragged blocks of 17 and of 23,
+    (1280, 2, 96, 3, 3, "f32"), (1030, 2, 256, 3, 2, "f32"), (1030, 2, 224, 3, 3, "f32")]) # two shares of dY
 def test_backward_of_two_channel_blocks(tp, N, mean_degree, K, l, l_h, dtype):
     full_parity(tp, wl_of(f"tp_blocks_{N}_{K}", N, mean_degree, K, l, l_h, l, dtype, 9300 + N + K))
 
