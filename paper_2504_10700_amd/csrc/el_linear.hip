@@ -579,28 +579,24 @@ struct SplitTile {
     if (wave < steps) {
       TS a[2][NC], b[2][L];
       load(wave, a[0], b[0]);
-      // Requests stand before the products that they overlap and under no condition; left alone, the compiler moves them behind the
-      // products, and every step of a small batch lasts one memory latency more (how much depends on how the waves fall: 13% between kernel
-      // arguments from memory and in registers).  Forward, us, left alone / so: 128 -> 128 channels, 40 atoms 9.5 / 7.1, 300
-      // 10.0 / 7.5, 2000 22.9 / 22.0; 256 -> 256, 100 17.1 / 11.5; l_max = 2, 300 8.0 / 6.4; fp64, 300 17.3 / 15.5.  Not the fp64 dX, W strided: backward of 300 35.6 for 35.1.
-      constexpr bool kPin = sizeof(TA) == 4 || !kTrans;
+      // No request stands under a condition, and steps past the end multiply zeros: behind a condition the compiler puts the requests of W, and
+      // every step of a small batch lasts one memory latency more.  Left alone it also moves the requests behind the products that they are to overlap;
+      // only the fp64 forward it orders better by itself.  Forward, us, left alone / pinned: 128 -> 128 channels, 40 atoms 9.5 / 7.1, 300 10.0 / 7.5,
+      // 2000 22.9 / 22.0; 256 -> 256, 100 17.1 / 11.5; l_max = 2, 300 8.0 / 6.4; 100 -> 128, 1500 23.7 / 21.5; fp64, 128 -> 128, 350 14.8 / 15.4, 3000 67.5 /
+      // 68.9, 192 -> 128, 2500 79.0 / 83.9.  Backward in fp64, whose dX reads W strided: 256 -> 128, 199 39.0 / 37.8, 256 -> 256, 150 61.0 / 59.5.
+      constexpr bool kPin = sizeof(TS) == 4 || kTrans;
+      auto pin = [] {
+        if constexpr (kPin) __builtin_amdgcn_sched_barrier(0);
+      };
       for (int s = wave; s < steps; s += 2 * kWaves) {
         const int s1 = s + kWaves, s2 = s + 2 * kWaves;
         load(s1 < steps ? s1 : s, a[1], b[1]);
-        if constexpr (kPin) {
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(s, a[0], b[0]);
-          __builtin_amdgcn_sched_barrier(0);
-          load(s2 < steps ? s2 : s, a[0], b[0]);
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(s1, a[1], b[1]);                          // (zeros past the end; under a condition its requests of W would move there)
-        } else {
-          multiply(s, a[0], b[0]);
-          if (s1 < steps) {
-            load(s2 < steps ? s2 : s1, a[0], b[0]);
-            multiply(s1, a[1], b[1]);
-          }
-        }
+        pin();
+        multiply(s, a[0], b[0]);
+        pin();
+        load(s2 < steps ? s2 : s, a[0], b[0]);
+        pin();
+        multiply(s1, a[1], b[1]);
       }
     }
     const int er = threadIdx.x / 16, ec = threadIdx.x % 16;    // the entry that this thread sums
