@@ -113,7 +113,8 @@ sc_status tp_workspace_bytes(const tp_plan* plan, int64_t n_edges, size_t* bytes
  * tp_workspace_bytes(plan, n_edges).  All sums have a fixed order: results are bitwise
  * reproducible for identical inputs.  Generated kernels: one launch walks the edges grouped by
  * sender, in the order of send_edge (dR and the partial dY of every edge; dh of an atom is summed
- * in registers and written once, zero for an atom that sends nothing), one sums the dY partials.
+ * in registers and written once, zero for an atom that sends nothing), and one sums the dY partials
+ * where the channels of an edge are shared by several workgroups.
  * dR and dY of an edge are written by the walk of the sender under which send_edge lists it: an
  * edge that send_edge omits keeps whatever dR and dY held.  Table-driven kernels walk by receiver,
  * write every edge's share of dh into the workspace and sum the shares per sender in a third launch. */

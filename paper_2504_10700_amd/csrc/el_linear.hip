@@ -1025,11 +1025,17 @@ hipError_t partial_dw(const el_config* cfg, int64_t n, const void* X, const void
 }
 
 // Is the backward one launch of split_backward_kernel?  Its workgroups all have a place at once and each lasts as long as its chain: the
-// atoms in the four waves of a tile of dW, k_out in those of a tile of dX.  Of two launches (the tiled partial dW with 13 us for its first rows alone, or
-// split_dw_kernel; then dX) each would have its own chain.  Backward, us, two launches / one: fp32, 128 -> 128 channels, 40 atoms 24.0 / 13.5, 300
-// 26.2 / 17.4, 500 28.0 / 21.8, 800 32 / 36; 64 -> 64, 300 18.0 / 10.2; 256 -> 256, 40 31.7 / 20.6, 160 35.9 / 26.2, 250 40.6 / 39.4, 300 40 / 49; 192 -> 128, 400 26.2 /
-// 24.9, 500 27.1 / 28.9; l_max = 1, 300 10.6 / 7.8, 500 11.2 / 11.1; fp64, 128 -> 128, 160 34.2 / 19.5, 300 35.3 / 28.6, 400 36.7 / 38.8.  Channel counts whose
-// dW is not tiled: 96 -> 96, 300 20.7 / 14.0, 800 36.6 / 27.2, 2000 71 / 101; 100 -> 128, l_max = 2, 800 30.4 / 22.2, 2000 61 / 62; fp64, 96 -> 96, 800 84.6 / 56.3.
+// atoms in the four waves of a tile of dW, k_out in those of a tile of dX.  Of two launches (the tiled partial dW with 13 us for its first rows
+// alone, or split_dw_kernel; then dX) each would have its own chain.  So the atoms are limited by the chain, atoms x tiles of dW by the places.
+// Backward, us, two launches / one:
+//   fp32   128 -> 128    40 atoms 24.0 / 13.5   300 26.2 / 17.4   500 28.0 / 21.8   800 32 / 36
+//          192 -> 128    400 26.2 / 24.9        500 27.1 / 28.9 (the limit of atoms)
+//          256 -> 256    40 31.7 / 20.6         160 35.9 / 26.2   250 40.6 / 39.4   300 40 / 49 (beyond the limit of places)
+//          64 -> 64      300 18.0 / 10.2        l_max = 1, 128 -> 128  300 10.6 / 7.8   500 11.2 / 11.1
+//   fp64   128 -> 128    160 34.2 / 19.5        300 35.3 / 28.6   400 36.7 / 38.8
+// and for channel counts whose dW is not tiled:
+//   fp32   96 -> 96      300 20.7 / 14.0        800 36.6 / 27.2   2000 71 / 101
+//          100 -> 128    l_max = 2  800 30.4 / 22.2   2000 61 / 62        fp64, 96 -> 96  800 84.6 / 56.3
 bool backward_together(const el_config* cfg, int64_t n) {
   if (few_channels(cfg->l_max, cfg->k_out, cfg->k_in)) return false;
   const int64_t tiles = static_cast<int64_t>((cfg->k_in + 15) / 16) * ((cfg->k_out + 15) / 16);

@@ -260,13 +260,13 @@ __device__ __forceinline__ void fold_part(const TW* __restrict__ src, int K, T* 
   for (int s = kPart; s < G::kS; s += kParts) dst[s * kLanes] = w[s];
 }
 
-// The fold role folds W[element, :, 64 channels] into wf, a workgroup per such pair and a quarter of the rows per wave: bound by one memory latency
-// and by what one compute unit can request.  A wave for all rows, four pairs a workgroup (45 of the 256 units at 89 elements, 128
-// channels) -> this, us a launch: 0e+1o, 3072 nodes 4.1 -> 2.9, l_max = 2 in fp64, 2731 nodes 4.1 -> 2.9; 10 000 nodes, whose launch waits for
+// The fold role folds W[element, :, 64 channels] into wf, a workgroup per such pair and a quarter of the rows per wave: bound by one memory
+// latency and by what one compute unit can request.  A wave for all rows, four pairs a workgroup (45 of the 256 units at 89 elements, 128
+// channels) -> this, us a launch: 0e+1o, 3072 nodes 4.1 -> 2.9; l_max = 2 in fp64, 2731 nodes 4.1 -> 2.9; 10 000 nodes, whose launch waits for
 // memory that has left the caches, 5.3 either way.
-// kWaves = 1: a wave for all rows, for the launches that also evaluate, with the few rows of a small basis: there the workgroups of this role
-// stand before those of the nodes, and fewer of them hold those up less (l_max = 2 in fp64, us, four waves / one: 1398 nodes 7.7 /
-// 7.3, 2000 8.1 / 7.8; l_max = 3, nu = 2, 0e in fp32 2000 7.7 / 7.5; the 86 rows of 0e+1o 2000 9.1 / 9.2, 0e+1o+2e 9.8 / 10.8).
+// kWaves = 1: a wave for all rows, for the launches that also evaluate, with the few rows of a small basis: there the workgroups of this
+// role stand before those of the nodes, and fewer of them hold those up less.  us, four waves / one: l_max = 2 in fp64 1398 nodes 7.7 / 7.3, 2000
+// 8.1 / 7.8; l_max = 3, nu = 2, 0e in fp32 2000 7.7 / 7.5; the 86 rows of 0e+1o 2000 9.1 / 9.2, 0e+1o+2e 9.8 / 10.8.
 template <typename G>
 constexpr int direct_fold_waves() { return G::kP > 64 ? kSpecWaves : 1; }
 
@@ -741,12 +741,13 @@ constexpr bool kUseLdsState = sizeof(T) == 4 && G::kS <= 32;
 // consecutive blocks of one (element, channel block): its waves add the group's rows over an equal share of the element's tiles each, in
 // tile order and in fp64, the shares meet in LDS in wave order, and the first wave writes the group's external paths.
 // Elements without nodes own no tiles and get zeros.  Every sum has a fixed order: results are bitwise reproducible.
-// What bounds it: the instructions of its waves (a launch with a wave per block lasted 1.7 us and 1.1 ns a wave, from 2300 to 9600 waves, whatever
-// the waves summed).  So the code of a group is straight-line: its rows, paths and coefficients are constants and not read from a
+// What bounds it: the instructions of its waves (a launch with a wave per block lasted 1.7 us and 1.1 ns a wave, from 2300 to 9600 waves,
+// whatever the waves summed).  So the code of a group is straight-line: its rows, paths and coefficients are constants and not read from a
 // descriptor (176 to 520 bytes of scalar loads, a branch per coefficient), absent tiles are skipped and not masked, and a wave has up to four
-// rows.  A wave per block -> this, us a launch: 128 channels, 0e+1o, 3072 nodes 6.6 -> 4.2, 10 000 6.8 -> 5.2, 200 000 24 -> 16; 0e+1o+2e, 256
-// channels, 50 000 nodes 20.9 -> 13.7; four outputs, 107 nodes 12.3 -> 6.4; 64 channels, 83 nodes 4.2 -> 3.0.  Rows of a group, four / six /
-// eight: 3072 nodes 4.2 / 4.3 / 4.1, 10 000 5.2 / 5.4 / 5.2, 200 000 15.9 / 19.0 / 18.0, 83 nodes 3.0 / 3.1 / 3.3.
+// rows.  us a launch, a wave per block -> this:
+//   128 channels, 0e+1o       3072 nodes 6.6 -> 4.2    10 000 6.8 -> 5.2    200 000 24 -> 16
+//   256 channels, 0e+1o+2e    50 000 nodes 20.9 -> 13.7        four outputs, 107 nodes 12.3 -> 6.4        64 channels, 83 nodes 4.2 -> 3.0
+// and with four / six / eight rows a group: 3072 nodes 4.2 / 4.3 / 4.1, 10 000 5.2 / 5.4 / 5.2, 200 000 15.9 / 19.0 / 18.0, 83 nodes 3.0 / 3.1 / 3.3.
 // Earlier forms (10k / 200k nodes): a sum kernel followed by an unfold kernel
 // 11.2 / 15.6 us; one workgroup per (element, channel block) for all rows 13.5 / 31 us (the twelve
 // workgroups of the six frequent elements own 60% of the bytes).  A device-scope "last workgroup finishes the job" scheme inside the
@@ -1030,8 +1031,8 @@ template <typename T, typename G, typename TW>
 hipError_t finalize_launch(const sc_plan* plan, void* dW, const Workspace& ws, const LaunchShape& shape,
                            hipStream_t stream) {
   const int Z = plan->cfg.num_elements;
-  // Waves of a workgroup, one / two / four, us a launch: 3072 nodes (three tiles an element on average, nineteen of the frequent ones) 6.5 / 4.2 / 4.2,
-  // 10 000 (four) 5.4 / 5.2 / 5.2, 107 nodes (four outputs) 6.9 / 6.9 / 6.3, 83 nodes 2.8 / 3.0 / 3.3; 200 000 (20 tiles) 39 / 24 / 16.
+  // Waves that share an element's tiles, one / two / four, us a launch: 3072 nodes (three tiles an element on average, nineteen of the frequent
+  // ones) 6.5 / 4.2 / 4.2, 10 000 (four) 5.4 / 5.2 / 5.2, 200 000 (20) 39 / 24 / 16; 107 nodes, four outputs, 6.9 / 6.9 / 6.3, 83 nodes 2.8 / 3.0 / 3.3.
   const int waves = shape.max_tiles > 8 * Z ? 4 : 2;
   const auto kernel = waves == 4 ? &spec_finalize_kernel<T, G, TW, 4> : &spec_finalize_kernel<T, G, TW, 2>;
   hipLaunchKernelGGL(kernel, dim3(shape.chblocks * FinalizeGroups<G>::table.n, Z), dim3(waves * kLanes), 0, stream,

@@ -8,7 +8,7 @@
 //               contiguous 256 B row per wave, the sender's features h[j][k][:] 16 B per lane
 //   workgroup = forward: one (receiving atom, 64-channel block); each of its four waves (two,
 //               waves_per_unit) walks every fourth edge the atom receives and keeps its sum in registers.  Backward: one (sending
-//               atom, one or two 64-channel blocks: two_blocks); a wave walks every fourth (eighth) edge the atom sends, keeps the
+//               atom, one or two 64-channel blocks: BackwardBlocks); a wave walks every fourth (eighth) edge the atom sends, keeps the
 //               atom's h rows and its dh sums in registers and gathers the receivers' dA rows; per edge
 //               it writes dR and its blocks' share of dY, which is dY where the workgroup has all blocks.  Either way the waves' sums meet in
 //               LDS: no atomics, a fixed summation order, one store per atom.  The second-order pass

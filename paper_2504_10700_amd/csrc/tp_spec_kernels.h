@@ -389,7 +389,7 @@ constexpr int kMinWaves = sizeof(T) == 8 && G::kP >= 10 && G::kP <= 17 ? 2 : 1;
 // wave at a time, by bisection of the receivers' offsets in LDS.
 constexpr int kSearchNodes = 1024;
 
-// The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, kBlocks 64-channel blocks; two_blocks).
+// The backward walks the edges grouped by SENDER: one workgroup = one (sending atom, kBlocks 64-channel blocks; BackwardBlocks).
 // Its waves keep the atom's h rows and their dh sums in registers, walk the edges the atom sends
 // (every kWaves-th in send_edge order: with the order of the waves, the order of the sum) and gather
 // per edge the dA row of the receiver (rows of
@@ -737,11 +737,15 @@ struct BackwardBlocks {
   }
 };
 
-// Do the workgroups of the backward search for receivers?  It saves the launch that writes every edge's receiver and costs each workgroup the rows
-// in LDS and about ten reads there per 64 edges of a wave, so it pays up to a number of workgroups.  Receivers and backward, us, with the launch /
-// searched: 128 channels, fp32, l_h = 0, 42 atoms 9.6 / 8.3, 330 19.2 / 14.9, 1000 27.5 / 25.1; l_h = 1, 127 19.9 / 15.6, 330 28.5 / 23.4, 1000 46.0 / 42.4; l = 2,
-// l_h = 2, 250 28.8 / 24.5; 256 channels, l_h = 1, 330 (1320 workgroups) 39.0 / 36.2, 700 (2800) 60.5 / 60.1, l = 2 700 52.2 / 53.7; 17 paths, 250
-// (500) 41.3 / 37.0, 1000 (2000) 106.1 / 107.3; fp64 rows, l_h = 1, 330 46.3 / 44.6, 1000 89.8 / 89.7.
+// Do the workgroups of the backward search for the receivers of their edges?  It saves the launch that writes every edge's receiver and costs
+// each workgroup the rows in LDS and about ten reads there per 64 edges of a wave: it pays up to some number of workgroups (six per compute
+// unit), and the rows are kSearchNodes at most.  Receivers and backward, us, with the launch / searched, by workgroups:
+//   128 channels, fp32      l_h = 0    42 9.6 / 8.3     330 19.2 / 14.9    1000 27.5 / 25.1
+//                           l_h = 1    127 19.9 / 15.6  330 28.5 / 23.4    1000 46.0 / 42.4
+//   l = 2, l_h = 2          250 28.8 / 24.5
+//   256 channels, l_h = 1   1320 39.0 / 36.2    2800 60.5 / 60.1    l = 2 1400 52.2 / 53.7
+//   17 paths                500 41.3 / 37.0     2000 106.1 / 107.3
+//   fp64 rows, l_h = 1      660 46.3 / 44.6     2000 89.8 / 89.7
 inline bool receivers_by_search(int64_t n_out_nodes, int64_t n_units) { return n_out_nodes <= kSearchNodes && n_units <= 1536; }
 
 EdgeList edge_list(const FwdArgs& a) {
