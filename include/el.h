@@ -75,8 +75,8 @@ sc_status el_backward(const el_config* cfg, int64_t n_nodes, const void* X, cons
  * the contraction from the accumulators: A is never written.  Small batches of these plans, where two launches are faster, and
  * every batch of every other plan run el_forward into the workspace and then the contraction, with the same result up to
  * rounding.  Small: on 256 compute units n_nodes * K up to 2^18, with fewer than 64 input channels up to 2^17, with a multiple
- * of 32 from 256 on up to 2^19; up to 2^18 by fp32 products as well, beyond by the bfloat16 parts of el_forward, whose error for
- * sums of that many channels is the smaller one.
+ * of 32 from 256 on up to 2^19; up to 2^18 by fp32 products as well, beyond by the bfloat16 parts of el_forward (error by the
+ * number of nonzero terms of a sum: see the top; for dense sums the smaller one).
  * workspace: device memory, 256-byte aligned, at least el_sc_workspace_bytes(): for plans with el_sc_is_fused the same for
  * every n_nodes (the folded weights, 128 bytes per element and channel, or A of a small batch, at most 32 MB), otherwise room
  * for A and the contraction's own workspace.  Same conventions
